@@ -12,6 +12,7 @@ namespace tj {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMaxCountingWgs = 1024;     // workgroups of a kernel that ends with an addition to one counter
 
 struct F8 { float v[8]; };
 
@@ -114,24 +115,36 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
     if (threadIdx.x == 0) wg_count = 0;
     __syncthreads();
     unsigned int mine = 0;
-    // a workgroup walks over several chunks per thread: one atomic per workgroup at the end, and few workgroups
+    // Two chunks per thread and iteration, all their loads in flight together.  The counter is one address for the whole
+    // chip, and additions to it are executed one after the other at about 10 ns each: with a workgroup per 256 chunks
+    // (4096 additions on 8192 x 1024) the kernel took 50 us for 134 MB; at most 1024 workgroups, one addition each: 24 us.
     const int64_t stride = (int64_t)gridDim.x * kThreads;      // a multiple of 16: rows of 16 lanes stay whole
-    for (int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x; c < nchunks; c += stride) {
-        const int64_t e = c * 8;
-        F8 w = load8(W + e);
-        const F8 dm = load8(dist_m + e), dq = load8(dist_q + e);
-        const F8 q = quant_dequant8(w, inv_tab);
-        unsigned int here = 0;
+    for (int64_t c0 = (int64_t)blockIdx.x * kThreads + threadIdx.x; c0 < nchunks; c0 += 2 * stride) {
+        F8 w[2], dm[2], dq[2];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float risk = dq.v[i] / dm.v[i];          // IEEE quotient; 0 / 0 is NaN and compares false
-            if (risk >= tau) {
-                w.v[i] = q.v[i];
-                ++here;
-            }
+        for (int u = 0; u < 2; ++u) {
+            const int64_t e = (u == 0 || c0 + stride < nchunks ? c0 + u * stride : c0) * 8;    // past the end: chunk c0 again, not used
+            w[u] = load8(W + e);
+            dm[u] = load8(dist_m + e);
+            dq[u] = load8(dist_q + e);
         }
-        if (here) store8(W + e, w);
-        mine += here;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t c = c0 + u * stride;
+            if (c >= nchunks) break;
+            const F8 q = quant_dequant8(w[u], inv_tab);
+            unsigned int here = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float risk = dq[u].v[i] / dm[u].v[i];    // IEEE quotient; 0 / 0 is NaN and compares false
+                if (risk >= tau) {
+                    w[u].v[i] = q.v[i];
+                    ++here;
+                }
+            }
+            if (here) store8(W + c * 8, w[u]);
+            mine += here;
+        }
     }
     if (n_reset) {
         for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
@@ -144,76 +157,147 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
 // ---- Appendix Alg. 3: selection of the k largest sensitivity scores (equal scores in ascending index order) ----------
 //
 // Scores are non-negative binary32 values, so they order like their bit patterns.  The k-th largest pattern is found by
-// a three-digit radix search (11 + 11 + 10 bits: a histogram pass over the tensor and a pick per digit); the tensor is
-// then compacted in index order: a count of (greater, equal) per 2048-element tile, an exclusive scan over the tiles,
-// and a pass that ranks every selected element and writes its index and the states of the tracked subset.  Every pass
-// recomputes Q(W) (the scores are never stored: the point of the algorithm is to keep no per-element state).
+// narrowing an interval [lo, lo + span) that holds it: a histogram pass over the tensor counts the patterns of the
+// interval in 2048 bins, and the workgroup that finishes last picks the bin.  The first pass splits the patterns where
+// scores live (|x - Q(x)| / binwidth is at most 1, and all but a few lie above 2^-8) into 256 bins per octave, with one
+// open bin below and one above: 15 bits are left after it, 4 after the second pass, none after the third.  (An equal
+// split of all patterns put the scores of normal weights into a dozen bins, and their LDS counters became the bound: 76
+// us for the first pass on 8192 x 1024, 19 us now.)  Only a threshold in an open bin needs the fourth pass; otherwise it
+// ends at once.  The tensor is then compacted in index order: a count of (greater, equal) per 2048-element tile, whose
+// last workgroup turns the counts into exclusive sums, and a pass that ranks every selected element and writes its index
+// and the states of the tracked subset.  Every pass recomputes Q(W) (the scores are never stored: the point of the
+// algorithm is to keep no per-element state).
+//
+// What workgroups leave for the last one travels by device-scope atomics (additions, stores, loads): they meet in
+// memory, not in one of the eight L2 caches.
+//
+// Additions to one address are executed one after the other (about 8 ns each), so the passes that end with additions to
+// shared counters run as at most kPassWgs workgroups of 1024 threads: 256 of them cost 2 us, 1024 of 256 threads 8 us.
 constexpr int kTile = kThreads * 8;
+constexpr int kPassThreads = 1024, kPassWgs = 256, kPassWaves = kPassThreads / 64;
+constexpr int kBins = 2048;
+constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kBins - 2);   // pattern >> 15 of bin 0; 1.0 falls into bin 2046
 
 struct SelState {
-    uint32_t prefix;      // the digits of the threshold found so far
-    uint32_t kneed;       // how many elements are still to be taken among those that match the prefix
-    uint32_t thr;         // after the third digit: the k-th largest score (bit pattern)
+    uint32_t lo, span;    // the interval [lo, lo + span) of patterns that holds the threshold
+    uint32_t width;       // bits still open: span <= 2^width
+    uint32_t kneed;       // how many elements are still to be taken among those of the interval
+    uint32_t thr;         // width 0: the k-th largest score (bit pattern)
     uint32_t ties;        // elements equal to thr that belong to the selection (the first ones in index order)
+    uint32_t done[5];     // workgroups that have finished, per pass
 };
 
-__global__ __launch_bounds__(kThreads) void osci_zero_kernel(uint32_t *p, int n)
+__device__ __forceinline__ uint32_t load_dev(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_dev(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// true in every thread of the workgroup that arrives last; what the others sent by device-scope atomics before has landed
+__device__ __forceinline__ bool last_to_arrive(uint32_t *counter, uint32_t *flag)
 {
-    for (int i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) p[i] = 0;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");   // this wave's atomics have been executed
+    __syncthreads();
+    if (threadIdx.x == 0) *flag = atomicAdd(counter, 1u) == gridDim.x - 1 ? 1u : 0u;
+    __syncthreads();
+    return *flag != 0;
 }
 
+__global__ __launch_bounds__(kThreads) void osci_zero_kernel(SelState *st, uint32_t *hist)
+{
+    const int i = blockIdx.x * kThreads + threadIdx.x;
+    if (i < kBins) hist[i] = 0;
+    if (i < 5) st->done[i] = 0;
+}
+
+// exclusive prefix sum of v over the workgroup's threads (thread order) and their total; red: one word of LDS per wave
+template <int WAVES>
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *red, uint32_t &total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+    }
+    __syncthreads();                                       // the previous use of red is over
+    if (lane == 63) red[wave] = incl;
+    __syncthreads();
+    uint32_t base = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const uint32_t r = red[w];
+        base += w < wave ? r : 0u;
+        total += r;
+    }
+    return base + incl - v;
+}
+
+// PASS 0: the whole range; later passes: the interval of the state
 template <int PASS>
-__global__ __launch_bounds__(kThreads) void osci_hist_kernel(const float *W, int64_t nchunks, const SelState *st, uint32_t *hist)
+__global__ __launch_bounds__(kPassThreads) void osci_hist_kernel(const float *W, int64_t nchunks, SelState *st, uint32_t *hist, uint32_t k_total)
 {
     __shared__ float inv_tab[128];
-    __shared__ uint32_t bins[2048];
+    __shared__ uint32_t bins[kBins];
+    __shared__ uint32_t red[kPassWaves], flag;
+    const uint32_t lo = PASS == 0 ? 0u : st->lo, span = PASS == 0 ? 0u : st->span, width = PASS == 0 ? 31u : st->width;
+    if (PASS > 0 && width == 0) return;                    // uniform: the threshold is known
+    const uint32_t shift = width > 11 ? width - 11 : 0;
     fill_inv_table(inv_tab);
-    for (int b = threadIdx.x; b < 2048; b += kThreads) bins[b] = 0;
+    for (int b = threadIdx.x; b < kBins; b += kPassThreads) bins[b] = 0;
     __syncthreads();
-    const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (c < nchunks) {                                    // whole rows of 16 lanes (nchunks is a multiple of 16)
-        const F8 w = load8(W + c * 8);
+    const int64_t stride = (int64_t)gridDim.x * kPassThreads;      // a multiple of 16: rows of 16 lanes stay whole
+    int64_t c = (int64_t)blockIdx.x * kPassThreads + threadIdx.x;
+    F8 next{};
+    if (c < nchunks) next = load8(W + c * 8);
+    for (; c < nchunks; c += stride) {
+        const F8 w = next;
+        next = load8(W + (c + stride < nchunks ? c + stride : c) * 8);   // in flight while this chunk is counted
         F8 sc;
         quant_dequant8_t<true>(w, inv_tab, &sc);
-        const uint32_t prefix = PASS == 0 ? 0u : st->prefix;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const uint32_t b = f2u(sc.v[i]);
-            if (PASS == 0) atomicAdd(&bins[b >> 21], 1u);
-            else if (PASS == 1) { if ((b >> 21) == prefix) atomicAdd(&bins[(b >> 10) & 2047u], 1u); }
-            else { if ((b >> 10) == prefix) atomicAdd(&bins[b & 1023u], 1u); }
+            if (PASS == 0) {
+                const int d = (int)(b >> 15) - (int)kFirstBin;
+                atomicAdd(&bins[d < 0 ? 0 : d > kBins - 1 ? kBins - 1 : d], 1u);
+            } else if (b - lo < span) {                    // unsigned: patterns below lo wrap around
+                atomicAdd(&bins[(b - lo) >> shift], 1u);
+            }
         }
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < 2048; b += kThreads)
+    for (int b = threadIdx.x; b < kBins; b += kPassThreads)
         if (bins[b]) atomicAdd(&hist[b], bins[b]);
-}
-
-// one workgroup: the digit whose bin holds the kneed-th largest element; clears the histogram for the next pass
-template <int PASS>
-__global__ __launch_bounds__(kThreads) void osci_pick_kernel(SelState *st, uint32_t *hist, uint32_t k_total)
-{
-    __shared__ uint32_t bins[2048];
-    for (int b = threadIdx.x; b < 2048; b += kThreads) {
-        bins[b] = hist[b];
-        hist[b] = 0;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t kneed = PASS == 0 ? k_total : st->kneed;
-        uint32_t above = 0;
-        int digit = 0;
-        for (int b = (PASS == 2 ? 1023 : 2047); b >= 0; --b) {
-            if (above + bins[b] >= kneed) { digit = b; break; }
-            above += bins[b];
+    if (!last_to_arrive(&st->done[PASS], &flag)) return;
+    // the last workgroup: thread t holds bins 2047 - 2 t and 2046 - 2 t, so that the sums run from the top
+    const uint32_t kneed = PASS == 0 ? k_total : st->kneed;
+    const int b0 = kBins - 1 - 2 * (int)threadIdx.x;
+    const uint32_t n0 = load_dev(&hist[b0]), n1 = load_dev(&hist[b0 - 1]);
+    store_dev(&hist[b0], 0u);                              // for the next pass
+    store_dev(&hist[b0 - 1], 0u);
+    uint32_t total;
+    uint32_t above = block_exclusive_scan<kPassWaves>(n0 + n1, red, total);
+    if (above < kneed && kneed <= above + n0 + n1) {       // exactly one thread
+        const bool first = kneed <= above + n0;
+        const uint32_t digit = (uint32_t)(first ? b0 : b0 - 1);
+        if (!first) above += n0;
+        uint32_t nlo, nspan, nwidth;
+        if (PASS == 0) {
+            const bool bottom = digit == 0, top = digit == kBins - 1;       // the open bins
+            nlo = bottom ? 0u : (kFirstBin + digit) << 15;
+            nspan = bottom ? (kFirstBin + 1) << 15 : top ? 1u << 30 : 1u << 15;
+            nwidth = bottom || top ? 30u : 15u;
+        } else {
+            const uint32_t left = span - (digit << shift);
+            nlo = lo + (digit << shift);
+            nspan = left < (1u << shift) ? left : 1u << shift;
+            nwidth = shift;
         }
-        const uint32_t prefix = PASS == 0 ? (uint32_t)digit : (st->prefix << (PASS == 1 ? 11 : 10)) | (uint32_t)digit;
-        st->prefix = prefix;
+        st->lo = nlo;
+        st->span = nspan;
+        st->width = nwidth;
         st->kneed = kneed - above;
-        if (PASS == 2) {
-            st->thr = prefix;
-            st->ties = kneed - above;
-        }
+        st->thr = nlo;
+        st->ties = kneed - above;
     }
 }
 
@@ -229,86 +313,71 @@ __device__ __forceinline__ void score_flags(const F8 &sc, uint32_t thr, uint32_t
     }
 }
 
-__global__ __launch_bounds__(kThreads) void osci_count_kernel(const float *W, int64_t nchunks, const SelState *st, uint32_t *counts)
+// (greater, equal) counts per tile; the last workgroup replaces them by their exclusive prefix sums.  A workgroup takes
+// four tiles at a time, four waves each.
+__global__ __launch_bounds__(kPassThreads) void osci_count_kernel(const float *W, int64_t nchunks, SelState *st, uint32_t *counts, int64_t ntiles)
 {
     __shared__ float inv_tab[128];
-    __shared__ uint32_t tot[2];
+    __shared__ uint32_t red[2][kPassWaves], flag;
     fill_inv_table(inv_tab);
-    if (threadIdx.x < 2) tot[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    uint32_t ngt = 0, neq = 0;
-    if (c < nchunks) {
-        F8 sc;
-        quant_dequant8_t<true>(load8(W + c * 8), inv_tab, &sc);
-        uint32_t gt, eq;
-        score_flags(sc, st->thr, gt, eq);
-        ngt = __builtin_popcount(gt);
-        neq = __builtin_popcount(eq);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        ngt += __shfl_xor(ngt, o, 64);
-        neq += __shfl_xor(neq, o, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&tot[0], ngt);
-        atomicAdd(&tot[1], neq);
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) counts[2 * blockIdx.x + threadIdx.x] = tot[threadIdx.x];
-}
-
-// exclusive prefix sums of the per-tile (greater, equal) counts, in place; one workgroup
-__global__ __launch_bounds__(kThreads) void osci_scan_kernel(uint32_t *counts, int64_t ntiles)
-{
-    __shared__ uint32_t part[kThreads][2];
-    const int64_t per = (ntiles + kThreads - 1) / kThreads;
-    const int64_t lo = per * threadIdx.x, hi = lo + per < ntiles ? lo + per : ntiles;
-    uint32_t a = 0, b = 0;
-    for (int64_t t = lo; t < hi; ++t) {
-        a += counts[2 * t];
-        b += counts[2 * t + 1];
-    }
-    part[threadIdx.x][0] = a;
-    part[threadIdx.x][1] = b;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t ra = 0, rb = 0;
-        for (int t = 0; t < kThreads; ++t) {
-            const uint32_t va = part[t][0], vb = part[t][1];
-            part[t][0] = ra;
-            part[t][1] = rb;
-            ra += va;
-            rb += vb;
+    const uint32_t thr = st->thr;
+    const int64_t stride = (int64_t)gridDim.x * kPassThreads;
+    const int64_t c0 = (int64_t)blockIdx.x * kPassThreads;
+    F8 next{};
+    if (c0 + threadIdx.x < nchunks) next = load8(W + (c0 + threadIdx.x) * 8);
+    int set = 0;
+    for (int64_t cb = c0; cb < nchunks; cb += stride, set ^= 1) {          // uniform over the workgroup
+        const int64_t c = cb + threadIdx.x;
+        const F8 w = next;
+        if (c + stride < nchunks) next = load8(W + (c + stride) * 8);
+        uint32_t gt = 0, eq = 0;
+        if (c < nchunks) {
+            F8 sc;
+            quant_dequant8_t<true>(w, inv_tab, &sc);
+            score_flags(sc, thr, gt, eq);
+        }
+        // both counts fit 16 bits (2048 elements per tile)
+        uint32_t n = (uint32_t)__builtin_popcount(gt) | ((uint32_t)__builtin_popcount(eq) << 16);
+        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+        uint32_t *r = red[set];                            // two sets: one barrier per round
+        if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = n;
+        __syncthreads();
+        const int64_t t = cb / kThreads + threadIdx.x;
+        if (threadIdx.x < kPassThreads / kThreads && t < ntiles) {
+            const uint32_t *q = r + 4 * threadIdx.x;
+            const uint32_t sum = q[0] + q[1] + q[2] + q[3];
+            store_dev(&counts[2 * t], sum & 0xFFFFu);
+            store_dev(&counts[2 * t + 1], sum >> 16);
         }
     }
-    __syncthreads();
-    a = part[threadIdx.x][0];
-    b = part[threadIdx.x][1];
-    for (int64_t t = lo; t < hi; ++t) {
-        const uint32_t va = counts[2 * t], vb = counts[2 * t + 1];
-        counts[2 * t] = a;
-        counts[2 * t + 1] = b;
-        a += va;
-        b += vb;
+    if (!last_to_arrive(&st->done[4], &flag)) return;
+    constexpr int kPer = 4;                                // tiles per thread and round
+    uint32_t base_g = 0, base_e = 0;
+    for (int64_t t0 = 0; t0 < ntiles; t0 += kPer * kPassThreads) {
+        uint32_t vg[kPer], ve[kPer], sg = 0, se = 0, tot_g, tot_e;
+        const int64_t t = t0 + (int64_t)threadIdx.x * kPer;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            vg[i] = t + i < ntiles ? load_dev(&counts[2 * (t + i)]) : 0u;
+            ve[i] = t + i < ntiles ? load_dev(&counts[2 * (t + i) + 1]) : 0u;
+            sg += vg[i];
+            se += ve[i];
+        }
+        uint32_t pg = base_g + block_exclusive_scan<kPassWaves>(sg, red[0], tot_g);
+        uint32_t pe = base_e + block_exclusive_scan<kPassWaves>(se, red[0], tot_e);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (t + i < ntiles) {
+                counts[2 * (t + i)] = pg;
+                counts[2 * (t + i) + 1] = pe;
+            }
+            pg += vg[i];
+            pe += ve[i];
+        }
+        base_g += tot_g;
+        base_e += tot_e;
     }
-}
-
-// exclusive prefix sum of v over the workgroup's 256 threads (thread order); red: 4 words of LDS
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *red)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
-    __syncthreads();                                       // the previous use of red is over
-    if (lane == 63) red[wave] = incl;
-    __syncthreads();
-    uint32_t base = 0;
-    for (int w = 0; w < wave; ++w) base += red[w];
-    return base + incl - v;
 }
 
 __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int64_t nchunks, const SelState *st, const uint32_t *offs,
@@ -330,7 +399,8 @@ __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int
     }
     // equal elements are ranked in index order over the whole tensor; the first `ties` of them are selected
     const uint32_t eq_tiles = offs[2 * blockIdx.x + 1], gt_tiles = offs[2 * blockIdx.x];
-    const uint32_t eq_before = eq_tiles + block_exclusive_scan(__builtin_popcount(eq), red);
+    uint32_t total;
+    const uint32_t eq_before = eq_tiles + block_exclusive_scan<4>(__builtin_popcount(eq), red, total);
     uint32_t sel = gt, rank = eq_before;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
@@ -339,7 +409,7 @@ __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int
             ++rank;
         }
     const uint32_t taken_eq_tiles = eq_tiles < ties ? eq_tiles : ties;       // selected equal elements of earlier tiles
-    uint32_t pos = gt_tiles + taken_eq_tiles + block_exclusive_scan(__builtin_popcount(sel), red);
+    uint32_t pos = gt_tiles + taken_eq_tiles + block_exclusive_scan<4>(__builtin_popcount(sel), red, total);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
         if ((sel >> i) & 1u) {
@@ -352,47 +422,68 @@ __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int
         }
 }
 
-// first position j in the ascending list idx[0..k) with idx[j] >= e
-__device__ __forceinline__ int64_t lower_bound_u32(const uint32_t *idx, int64_t k, int64_t e)
+// First position j in the ascending list idx[0..k) with idx[j] >= e, by one whole wave: 64 probes per step, so that a
+// list of 400 000 entries takes four dependent loads instead of nineteen.
+__device__ __forceinline__ int64_t wave_lower_bound(const uint32_t *idx, int64_t k, int64_t e)
 {
-    int64_t lo = 0, hi = k;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)idx[mid] < e) lo = mid + 1;
-        else hi = mid;
+    const int lane = threadIdx.x & 63;
+    int64_t lo = 0, n = k;                                 // the answer is in [lo, lo + n]
+    while (n > 0) {
+        const int64_t step = (n + 63) / 64;
+        const int64_t j = lo + step * (lane + 1) - 1;      // the last entry of the lane's piece
+        const bool below = j < lo + n && (int64_t)idx[j] < e;
+        const int pieces = __builtin_popcountll(__ballot(below));
+        const int64_t left = n - step * pieces;
+        lo += step * pieces;
+        // every piece that ends below e is behind us; the answer lies in the next one (its last entry is not below e, or
+        // it is the unfinished piece at the end)
+        n = left <= 0 ? 0 : (step - 1 < left ? step - 1 : left);
+        if (step == 1) break;
     }
     return lo;
 }
 
-// Alg. 3 at a later step (SUPPRESS = false) and Alg. 1 on the tracked subset (SUPPRESS = true).  A workgroup takes a
-// tile of 2048 consecutive weights: Q of the tile goes to LDS, then the tile's entries of the (ascending) index list -
-// found by binary search - are updated from it.  Tiles without a tracked element stop after the search.
-template <bool SUPPRESS>
+// Alg. 3 at a later step (SUPPRESS = false) and Alg. 1 on the tracked subset (SUPPRESS = true).  A workgroup takes T tiles
+// of 2048 consecutive weights: Q of the tiles goes to LDS, then their entries of the (ascending) index list are updated
+// from it.  The call is bound by its chain of dependent loads (search, entries, weights), so the weights are fetched
+// before the search (`dense`: lists in which nearly every tile has entries; otherwise tiles without a tracked weight stop
+// after the search and read nothing else), and a long tensor takes four tiles per search: 8192 x 1024 with 5 % tracked
+// took 21 us with one tile and a one-thread search, 14 us like this.
+template <bool SUPPRESS, int T>
 __global__ __launch_bounds__(kThreads) void osci_sparse_kernel(float *W, int64_t nchunks, const uint32_t *idx, int64_t k, float *wp,
                                                                float *qp, float *dm, float *dq, float tau,
-                                                               unsigned long long *n_reset)
+                                                               unsigned long long *n_reset, int dense)
 {
     __shared__ float inv_tab[128];
-    __shared__ float qt[kTile];
+    __shared__ __attribute__((aligned(16))) float qt[T * kTile];
     __shared__ int64_t range[2];
     __shared__ unsigned int wg_count;
-    const int64_t tile0 = (int64_t)blockIdx.x * kTile;
+    const int64_t tile0 = (int64_t)blockIdx.x * (T * kTile);
+    const int64_t c0 = (int64_t)blockIdx.x * (T * kThreads) + threadIdx.x;
+    F8 w[T];
+    auto fetch = [&]() {
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int64_t c = c0 + t * kThreads;
+            w[t] = load8(W + (c < nchunks ? c : nchunks - 1 - ((nchunks - 1 - c) & 15)) * 8);   // past the end: some valid chunk, not used
+        }
+    };
+    if (dense) fetch();
     fill_inv_table(inv_tab);
-    if (threadIdx.x == 0) {
-        range[0] = lower_bound_u32(idx, k, tile0);
-        range[1] = lower_bound_u32(idx, k, tile0 + kTile);
-        wg_count = 0;
+    const int wave = threadIdx.x >> 6;
+    if (wave < 2) {
+        const int64_t j = wave_lower_bound(idx, k, tile0 + wave * (T * kTile));
+        if ((threadIdx.x & 63) == 0) range[wave] = j;
     }
+    if (threadIdx.x == 0) wg_count = 0;
     __syncthreads();
     const int64_t j0 = range[0], j1 = range[1];
     if (j0 == j1) return;                                  // uniform
-    const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (c < nchunks) {
-        const F8 q = quant_dequant8(load8(W + c * 8), inv_tab);
+    if (!dense) fetch();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) qt[threadIdx.x * 8 + i] = q.v[i];
-    }
-    __syncthreads();                                       // every weight of the tile has been read: resets may follow
+    for (int t = 0; t < T; ++t)
+        if (c0 + t * kThreads < nchunks) store8(qt + (t * kThreads + threadIdx.x) * 8, quant_dequant8(w[t], inv_tab));
+    __syncthreads();                                       // every weight of the tiles has been read: resets may follow
     unsigned int mine = 0;
     for (int64_t j = j0 + threadIdx.x; j < j1; j += kThreads) {
         const int64_t e = idx[j];
@@ -404,10 +495,10 @@ __global__ __launch_bounds__(kThreads) void osci_sparse_kernel(float *W, int64_t
                 ++mine;
             }
         } else {
-            const float w = W[e];
-            dm[j] = dm[j] + fabsf(w - wp[j]);
+            const float wv = W[e];
+            dm[j] = dm[j] + fabsf(wv - wp[j]);
             dq[j] = dq[j] + fabsf(q - qp[j]);
-            wp[j] = w;
+            wp[j] = wv;
             qp[j] = q;
         }
     }
@@ -417,6 +508,24 @@ __global__ __launch_bounds__(kThreads) void osci_sparse_kernel(float *W, int64_t
         __syncthreads();
         if (threadIdx.x == 0 && wg_count) atomicAdd(n_reset, (unsigned long long)wg_count);
     }
+}
+
+template <bool SUPPRESS>
+hipError_t launch_sparse(float *W, int64_t n, const uint32_t *idx, int64_t k, float *wp, float *qp, float *dm, float *dq, float tau,
+                         unsigned long long *n_reset, hipStream_t st)
+{
+    const int64_t nchunks = n / 8;
+    if (nchunks == 0 || k == 0) return hipSuccess;
+    const int64_t ntiles = (nchunks + kThreads - 1) / kThreads;
+    const int dense = k >= ntiles;                         // on average at least one entry per tile
+    // four tiles per workgroup once that still leaves two workgroups per CU
+    if (ntiles >= 2048)
+        hipLaunchKernelGGL((osci_sparse_kernel<SUPPRESS, 4>), dim3((unsigned)((ntiles + 3) / 4)), dim3(kThreads), 0, st, W, nchunks, idx, k, wp,
+                           qp, dm, dq, tau, n_reset, dense);
+    else
+        hipLaunchKernelGGL((osci_sparse_kernel<SUPPRESS, 1>), dim3((unsigned)ntiles), dim3(kThreads), 0, st, W, nchunks, idx, k, wp, qp, dm, dq,
+                           tau, n_reset, dense);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -435,40 +544,29 @@ hipError_t launch_osci_select(const float *W, int64_t n, int64_t k, uint32_t *id
     SelState *state = static_cast<SelState *>(ws);
     uint32_t *hist = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(ws) + 256);
     uint32_t *counts = hist + 2048;
-    const unsigned grid = (unsigned)((nchunks + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(osci_zero_kernel, dim3(8), dim3(kThreads), 0, st, hist, 2048);
-    hipLaunchKernelGGL(osci_hist_kernel<0>, dim3(grid), dim3(kThreads), 0, st, W, nchunks, state, hist);
-    hipLaunchKernelGGL(osci_pick_kernel<0>, dim3(1), dim3(kThreads), 0, st, state, hist, (uint32_t)k);
-    hipLaunchKernelGGL(osci_hist_kernel<1>, dim3(grid), dim3(kThreads), 0, st, W, nchunks, state, hist);
-    hipLaunchKernelGGL(osci_pick_kernel<1>, dim3(1), dim3(kThreads), 0, st, state, hist, (uint32_t)k);
-    hipLaunchKernelGGL(osci_hist_kernel<2>, dim3(grid), dim3(kThreads), 0, st, W, nchunks, state, hist);
-    hipLaunchKernelGGL(osci_pick_kernel<2>, dim3(1), dim3(kThreads), 0, st, state, hist, (uint32_t)k);
-    hipLaunchKernelGGL(osci_count_kernel, dim3(grid), dim3(kThreads), 0, st, W, nchunks, state, counts);
-    hipLaunchKernelGGL(osci_scan_kernel, dim3(1), dim3(kThreads), 0, st, counts, (int64_t)grid);
-    hipLaunchKernelGGL(osci_emit_kernel, dim3(grid), dim3(kThreads), 0, st, W, nchunks, state, counts, idx, wp, qp, dm, dq);
+    const int64_t ntiles = (nchunks + kThreads - 1) / kThreads;
+    const int64_t want = (nchunks + kPassThreads - 1) / kPassThreads;
+    const dim3 grid((unsigned)(want < kPassWgs ? want : kPassWgs)), block(kPassThreads);
+    hipLaunchKernelGGL(osci_zero_kernel, dim3(kBins / kThreads), dim3(kThreads), 0, st, state, hist);
+    hipLaunchKernelGGL(osci_hist_kernel<0>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
+    hipLaunchKernelGGL(osci_hist_kernel<1>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
+    hipLaunchKernelGGL(osci_hist_kernel<2>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
+    hipLaunchKernelGGL(osci_hist_kernel<3>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
+    hipLaunchKernelGGL(osci_count_kernel, grid, block, 0, st, W, nchunks, state, counts, ntiles);
+    hipLaunchKernelGGL(osci_emit_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, st, W, nchunks, state, counts, idx, wp, qp, dm, dq);
     return hipGetLastError();
 }
 
 hipError_t launch_osci_update_sparse(const float *W, int64_t n, const uint32_t *idx, int64_t k, float *wp, float *qp, float *dm,
                                      float *dq, hipStream_t st)
 {
-    const int64_t nchunks = n / 8;
-    if (nchunks == 0 || k == 0) return hipSuccess;
-    const unsigned grid = (unsigned)((nchunks + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(osci_sparse_kernel<false>, dim3(grid), dim3(kThreads), 0, st, const_cast<float *>(W), nchunks, idx, k, wp, qp,
-                       dm, dq, 0.0f, static_cast<unsigned long long *>(nullptr));
-    return hipGetLastError();
+    return launch_sparse<false>(const_cast<float *>(W), n, idx, k, wp, qp, dm, dq, 0.0f, nullptr, st);
 }
 
 hipError_t launch_osci_suppress_sparse(float *W, int64_t n, const uint32_t *idx, int64_t k, const float *dm, const float *dq,
                                        float tau, unsigned long long *n_reset, hipStream_t st)
 {
-    const int64_t nchunks = n / 8;
-    if (nchunks == 0 || k == 0) return hipSuccess;
-    const unsigned grid = (unsigned)((nchunks + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(osci_sparse_kernel<true>, dim3(grid), dim3(kThreads), 0, st, W, nchunks, idx, k, static_cast<float *>(nullptr),
-                       static_cast<float *>(nullptr), const_cast<float *>(dm), const_cast<float *>(dq), tau, n_reset);
-    return hipGetLastError();
+    return launch_sparse<true>(W, n, idx, k, nullptr, nullptr, const_cast<float *>(dm), const_cast<float *>(dq), tau, n_reset, st);
 }
 
 hipError_t launch_osci_update(const float *W, float *W_prev, float *dist_m, float *dist_q, int64_t n, int first, hipStream_t st)
@@ -486,7 +584,7 @@ hipError_t launch_osci_suppress(float *W, const float *dist_m, const float *dist
     const int64_t nchunks = n / 8;
     if (nchunks == 0) return hipSuccess;
     const int64_t want = (nchunks + kThreads - 1) / kThreads;
-    const unsigned grid = (unsigned)(want < 4096 ? want : 4096);
+    const unsigned grid = (unsigned)(want < kMaxCountingWgs ? want : kMaxCountingWgs);
     hipLaunchKernelGGL(osci_suppress_kernel, dim3(grid), dim3(kThreads), 0, st, W, dist_m, dist_q, tau, nchunks, n_reset);
     return hipGetLastError();
 }

@@ -160,3 +160,37 @@ def test_subset_calls_empty_and_bad_arguments():
     with pytest.raises(B.NVFP4Error) as e:
         tj.osci_suppress_sparse(w, st[0], st[3], st[4], 0.0)
     assert e.value.code == -3
+
+
+@pytest.mark.parametrize("shape,frac", [((4104, 1024), 0.05), ((4097, 1024), 0.9), ((4099, 1024), 1.0 / 16384)])
+def test_tensors_of_many_tiles(shape, frac):
+    """more than 2048 tiles of 2048 weights, the last workgroup's share ragged: four tiles per workgroup on the subset
+    (with and without an entry in nearly every tile), two chunks per thread in the reset, several rounds per workgroup in
+    the selection's passes, a threshold far below and close to the largest score"""
+    import paper_2510_27527_amd as tj
+    rng = np.random.default_rng(5)
+    W0 = (rng.standard_normal(shape) * 0.02).astype(np.float32)
+    W0[7, 128:640] = 0.0
+    W1 = (W0 + rng.standard_normal(shape).astype(np.float32) * 2e-4).astype(np.float32)
+    k = int(np.ceil(frac * W0.size))
+    o = list(oracle.osci_select(W0, k))
+    g = list(tj.osci_select(torch.from_numpy(W0).cuda(), k))
+    oracle.osci_update_sparse(W1, *o)
+    tj.osci_update_sparse(torch.from_numpy(W1).cuda(), *g)
+    assert np.array_equal(u32(g[0]), o[0])
+    for a, b in zip(g[1:], o[1:]):
+        assert np.array_equal(bits(a.cpu().numpy()), bits(b))
+    oW, gW = W1.copy(), torch.from_numpy(W1).cuda()
+    n = torch.zeros(1, dtype=torch.int64, device="cuda")
+    want = oracle.osci_suppress_sparse(oW, o[0], o[3], o[4], 2.0)
+    tj.osci_suppress_sparse(gW, g[0], g[3], g[4], 2.0, n)
+    assert int(n.item()) == want > 0
+    assert np.array_equal(bits(gW.cpu().numpy()), bits(oW))
+    # every weight tracked
+    dm, dq = rng.random(shape, dtype=np.float32), rng.random(shape, dtype=np.float32)
+    oW, gW = W1.copy(), torch.from_numpy(W1).cuda()
+    n.zero_()
+    want = oracle.osci_suppress(oW, dm, dq, 4.0)
+    tj.osci_suppress(gW, torch.from_numpy(dm).cuda(), torch.from_numpy(dq).cuda(), 4.0, n)
+    assert int(n.item()) == want > 0
+    assert np.array_equal(bits(gW.cpu().numpy()), bits(oW))
