@@ -196,7 +196,8 @@ int run_quantize(const void *src, const QuantPlan &pl, const nvfp4_qcfg *cfg, nv
                 }
             }
         }
-        if (!zeroed) launch_zero_scalar(o.amax_deq, st);
+        // the row-wise kernel clears it itself with 1 x 128 outer blocks
+        if (!zeroed && !(pl.axis == 0 && pl.outer == NVFP4_OUTER_BLOCK128)) launch_zero_scalar(o.amax_deq, st);
         e = pl.axis == 0 ? launch_quant_row_bf16(src, pl.R, pl.C, p, o, st)
                          : launch_quant_col_bf16(src, pl.R, pl.C, p, o, st);
     } else {
@@ -253,11 +254,6 @@ int run_quantize_row_pair(const void *src0, const QuantPlan &pl0, nvfp4_tensor *
                                   o1.amax_deq, &p1.npart, st);
         p0.amax_partials = partials0;
         p1.amax_partials = partials1;
-    } else {
-        // 1 x 128 outer blocks: no maximum pass; the dequantized maximum (an atomic maximum over the workgroups) is
-        // only wanted by a later tensor-mode re-quantization and starts from zero
-        if (o0.amax_deq) launch_zero_scalar(o0.amax_deq, st);
-        if (o1.amax_deq) launch_zero_scalar(o1.amax_deq, st);
     }
     const hipError_t e = launch_quant_row_bf16_pair(src0, pl0.R, pl0.C, p0, o0, src1, pl1.R, pl1.C, p1, o1, st);
     return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;

@@ -192,7 +192,9 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
     // Largest dequantized magnitude.  In tensor mode the group holding the tensor maximum always gets
     // the scale 448 and its largest element the code 6, so the maximum is 6 * 448 * S_g in closed form;
     // only a floored S_g (maximum below 2688 * 2^-100) needs the reduction over all groups.
-    bool reduce_deq = DEQ && OUTER == 1 && a.amax_deq != nullptr;
+    // With 1 x 128 outer blocks the kernel only clears the result: deq_max_kernel takes it from the outer scales afterwards.
+    bool reduce_deq = false;
+    if (OUTER == 1 && DEQ && a.amax_deq && bid == 0 && tid == 0) a.amax_deq[0] = 0.0f;
     if (OUTER == 0) {
         const float amax = block_tensor_amax(a, red);
         os = outer_scale(amax);
@@ -280,17 +282,59 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
             if (DEQ && reduce_deq) {
                 // the group's largest element gets the group's largest code (rounding is monotone)
                 const uint32_t mm = e2m1_rtn(amax_b * r) & 7u;
-                float val = e2m1_value(mm) * e4m3_value(sc);
-                if (OUTER == 1) val = val * os.S_g;
-                deq = fmaxf(deq, val);
+                deq = fmaxf(deq, e2m1_value(mm) * e4m3_value(sc));
             }
         }
     };
     if (full) run(std::false_type{});
     else run(std::true_type{});
     if (DEQ && reduce_deq) {
-        if (OUTER == 0) deq = deq * os.S_g;
-        publish_deq_max(deq, a.amax_deq, red);
+        publish_deq_max(deq * os.S_g, a.amax_deq, red);
+    }
+}
+
+// Largest dequantized magnitude of an operand with 1 x 128 outer blocks.  The group that holds a block's maximum gets the
+// scale 448 and its largest element the code 6, so the block's maximum is RN(2688 * S_g); only a block whose S_g is the
+// floor 2^-100 or exactly 1 (which an all-zero block also has) is looked into.  A tensor has one outer scale per 128
+// elements, so this reads 1/64 of the bytes the quantizer wrote; leaving the maximum to the quantizer's own workgroups
+// (one atomic each, executed one after the other on a single address) cost 20 us on 9000 x 3072 (and 12 us of 54 on 8192 x 8192); this kernel costs 2.
+struct DeqJob {
+    const float *gscale;
+    const uint8_t *scales;
+    const uint32_t *codes;
+    float *amax_deq;       // cleared by the quantizer
+    int64_t nblocks;
+    unsigned nwg;
+};
+constexpr int kDeqWgs = 64;
+
+__global__ __launch_bounds__(kThreads) void deq_max_kernel(DeqJob j0, DeqJob j1)
+{
+    __shared__ float red[4];
+    const bool second = blockIdx.x >= j0.nwg;
+    const DeqJob j = second ? j1 : j0;
+    const int64_t stride = (int64_t)j.nwg * kThreads;
+    float m = 0.0f;
+    for (int64_t b = (int64_t)(second ? blockIdx.x - j0.nwg : blockIdx.x) * kThreads + threadIdx.x; b < j.nblocks; b += stride) {
+        const float sg = j.gscale[b];
+        if (sg != 0x1p-100f && sg != 1.0f) {
+            m = fmaxf(m, 2688.0f * sg);
+            continue;
+        }
+        for (int grp = 0; grp < 8; ++grp) {
+            const float sb = e4m3_value(j.scales[b * 8 + grp]);
+            for (int w = 0; w < 2; ++w) {
+                const uint32_t q = j.codes[(b * 8 + grp) * 2 + w];
+                for (int e = 0; e < 8; ++e) m = fmaxf(m, (e2m1_value((q >> (4 * e)) & 7u) * sb) * sg);
+            }
+        }
+    }
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+        if (m > 0.0f) atomicMax(reinterpret_cast<unsigned int *>(j.amax_deq), f2u(m));
     }
 }
 
@@ -460,24 +504,32 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
 // ------------------------------------------------------------- column-wise, one strip per wave ----
 //
 // Groups of 16 run down the columns of the source [R x C]; the output is the transposed operand [C x R].  A wave
-// owns a strip of 128 source columns x 128 source rows (8 slabs of 16 rows): lane l holds columns 2 l, 2 l + 1 of a
+// owns a strip of 128 source columns x SLABS slabs of 16 rows: lane l holds columns 2 l, 2 l + 1 of a
 // slab as 16 registers (one dword of two bf16 per row - a wave load is 256 contiguous bytes of a row; or one byte of
 // two codes per row for a packed source), i.e. two complete groups, with no exchange between lanes and no barrier
 // while it quantizes.  The four waves of a workgroup take four strips below each other, so for each of the 128
-// output rows the workgroup produces 256 contiguous bytes of codes and 32 of scales; these are gathered in LDS and
-// written after the workgroup's only barrier, whole runs per store instruction (measured on this chip: 16-byte
-// pieces scattered over rows 2.3 TB/s, 64-byte runs 4.2, 256-byte runs 4.6; 8-byte scale pieces cost as much as all
-// the codes).  With a 1 x 128 outer block (OUTER = 1) a strip's 128 rows are exactly one outer block of each of its
-// output rows: a first pass over the strip takes the column maxima, the second pass (the same addresses again, now
-// from cache) quantizes.
-constexpr int kStripC = 128, kStripR = 128, kSlabs = kStripR / 16;
+// output rows the workgroup produces one contiguous run of codes and one of scales; these are gathered in LDS and
+// written after the barrier, whole runs per store instruction (measured on this chip: 16-byte pieces scattered over rows
+// 2.3 TB/s, 64-byte runs 4.2, 256-byte runs 4.6; 8-byte scale pieces cost as much as all the codes).
+//
+// SLABS: a wave's slabs are a serial chain of load, decode, quantize, so short strips (more waves) hide it better and long
+// ones write longer runs.  Two slabs (64-byte runs) measured best everywhere for a packed source - 8192 x 8192 29.6 us,
+// with four 31.4, with eight 32.3; 16384 x 1024 10.6 / 11.9 / 14.6 - and for a bf16 source up to about 32 M elements; above,
+// four (8192 x 8192: 33.5 us with four, 41.7 with two, 36.8 with eight; 8192 x 4096: 19.4 / 19.9 / 19.6).
+//
+// With 1 x 128 outer blocks (OUTER = 1, two slabs per wave) the workgroup's 128 rows are exactly one outer block of each
+// of its output rows: the waves decode their slabs into registers, exchange the column maxima through LDS and quantize
+// from the registers, so the source is read and decoded once.
+constexpr int kStripC = 128;
 
 // RHT (with OUTER = 1): a lane's 16 values of a column are one block of the random Hadamard transform (Sec. 4.1), all
 // in its own registers; the signs depend on the source row only, so they are wave-uniform masks.
-template <int ROUND, bool SUP, bool PACKED, int OUTER, bool RHT = false>
+template <int ROUND, bool SUP, bool PACKED, int OUTER, bool RHT, int SLABS>
 __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArgs a1, unsigned first_second)
 {
     static_assert(!RHT || OUTER == 1, "the transform is provided with 1 x 128 outer blocks");
+    static_assert(OUTER == 0 || SLABS == 2, "a workgroup's rows are one outer block");
+    constexpr int kSlabs = SLABS, kStripR = 16 * SLABS;
     __shared__ float inv_tab[128];
     __shared__ float red[4];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -509,8 +561,10 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     const uint32_t tc = __builtin_amdgcn_readfirstlane(wg % tiles_c), trg = __builtin_amdgcn_readfirstlane(wg / tiles_c);
     const uint32_t tr = trg * kWaves + wave;
     const bool have = tr < tiles_r;                                // this wave has a strip (all of them reach the barrier)
-    // strips of this workgroup that are whole and whose output runs are 16-byte aligned: these go out through LDS
-    const int nwide = (R & 127) == 0 ? (int)min((uint32_t)kWaves, tiles_r - trg * kWaves) : 0;
+    // strips of this workgroup that are whole and whose output runs are aligned (16 bytes of codes, 4 of scales): these go
+    // out through LDS
+    const int whole = (int)min((int64_t)kWaves, R / kStripR - (int64_t)trg * kWaves);
+    const int nwide = (R & 63) == 0 && whole > 0 ? whole : 0;
     const int64_t R0 = (int64_t)tr * kStripR, c0 = (int64_t)tc * kStripC + 2 * lane;
     const bool colok = c0 < C;                                     // C is even: both columns or none
     const int nslab = have ? (int)min((int64_t)kSlabs, (R - R0) >> 4) : 0;    // R is a multiple of 16
@@ -536,9 +590,9 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
         const bool src_blocks = a.src_outer != 0;
         const int64_t nbc = C >> 7;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < (kStripR + 63) / 64; ++h) {
             const int64_t row = R0 + lane + 64 * h;
-            row_sg[lane + 64 * h] = !src_blocks ? src_sg_tensor : row < R ? a.src_gscale[row * nbc + tc] : 0.0f;
+            if (lane + 64 * h < kStripR) row_sg[lane + 64 * h] = !src_blocks ? src_sg_tensor : row < R ? a.src_gscale[row * nbc + tc] : 0.0f;
         }
         // same wave writes and reads: the compiler's wait on the LDS counter orders them
     }
@@ -609,55 +663,55 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     };
 
     Raw raw[2];                                                    // slab s lives in raw[s % 2] (s is a constant after unrolling)
-    if (OUTER == 1 && have) {
-        // first pass: the maximum of each column over the strip's 128 rows = one outer block of the output row
-        float cm0 = 0.0f, cm1 = 0.0f;
-        fetch(std::false_type{}, 0, raw[0]);
+    // OUTER: both slabs, decoded once
+    float xb0[OUTER ? 2 : 1][16], xb1[OUTER ? 2 : 1][16], mb[OUTER ? 2 : 1][2];
+    __shared__ __attribute__((aligned(16))) float2 col_max[OUTER ? kWaves : 1][OUTER ? 64 : 1];
+    if constexpr (OUTER == 1) {
+        // R is a multiple of 128: every wave has its two slabs
+        fetch(std::true_type{}, 0, raw[0]);
+        fetch(std::true_type{}, 1, raw[1]);
 #pragma unroll
-        for (int s = 0; s < kSlabs; ++s) {
-            if (s >= nslab) break;
-            const Raw &cur = raw[s & 1];
-            if (s + 1 < nslab) fetch(std::false_type{}, s + 1, raw[(s + 1) & 1]);
-            if constexpr (!PACKED && !RHT) {
-                ushort2_t m2 = {0, 0};
+        for (int s = 0; s < 2; ++s) decode(raw[s], s, xb0[s], xb1[s], mb[s][0], mb[s][1]);
+        col_max[wave][lane] = make_float2(fmaxf(mb[0][0], mb[1][0]), fmaxf(mb[0][1], mb[1][1]));
+        __syncthreads();
+        float2 m = col_max[0][lane];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) m2 = __builtin_elementwise_max(m2, as_us2(cur.w[i] & 0x7FFF7FFFu));
-                cm0 = fmaxf(cm0, u2f((uint32_t)m2.x << 16));
-                cm1 = fmaxf(cm1, u2f((uint32_t)m2.y << 16));
-            } else {
-                float x0[16], x1[16], m0, m1;
-                decode(cur, s, x0, x1, m0, m1);
-                cm0 = fmaxf(cm0, m0);
-                cm1 = fmaxf(cm1, m1);
-            }
+        for (int w = 1; w < kWaves; ++w) {
+            const float2 t = col_max[w][lane];
+            m = make_float2(fmaxf(m.x, t.x), fmaxf(m.y, t.y));
         }
-        os[0] = outer_scale(cm0);
-        os[1] = outer_scale(cm1);
-        if (colok) {
+        os[0] = outer_scale(m.x);
+        os[1] = outer_scale(m.y);
+        if (colok && wave == 0) {
             const int64_t nb = R >> 7;
-            a.k.gscale[c0 * nb + tr] = os[0].S_g;
-            a.k.gscale[(c0 + 1) * nb + tr] = os[1].S_g;
+            a.k.gscale[c0 * nb + trg] = os[0].S_g;
+            a.k.gscale[(c0 + 1) * nb + trg] = os[1].S_g;
         }
     }
 
-    // Codes and scale bytes of the workgroup's whole strips are gathered in LDS: [output row][wave][64 + 8 bytes].
-    // Code row pitch 264 bytes (256 + 8) spreads the lanes' 8-byte writes over the banks.
-    constexpr int kPitch = kWaves * 64 + 8, kScPitch = kWaves * 8;
+    // Codes and scale bytes of the workgroup's whole strips are gathered in LDS: [output row][wave][8 SLABS + SLABS bytes].
+    // Code row pitch: 8 bytes more than the row spread the lanes' 8-byte writes over the banks.
+    constexpr int kRun = kWaves * 8 * SLABS, kPitch = kRun + 8, kScPitch = kWaves * SLABS;
     __shared__ __attribute__((aligned(16))) uint8_t stage[kStripC * kPitch];
     __shared__ __attribute__((aligned(16))) uint8_t sc_stage[kStripC * kScPitch];
-    uint32_t scb[2][2] = {{0, 0}, {0, 0}};                          // scale bytes of slabs 0..3 and 4..7, per column
+    uint32_t scb[2] = {0, 0};                                       // the slabs' scale bytes, per column
     const bool wide = (int)wave < nwide;
-    if (have) fetch(std::true_type{}, 0, raw[0]);
+    if (OUTER == 0 && have) fetch(std::true_type{}, 0, raw[0]);
 #pragma unroll
     for (int s = 0; s < kSlabs; ++s) {
         if (s >= nslab) break;
-        const Raw &cur = raw[s & 1];
-        if (s + 1 < nslab) fetch(std::true_type{}, s + 1, raw[(s + 1) & 1]);
         float x0[16], x1[16], mx[2];
-        decode(cur, s, x0, x1, mx[0], mx[1]);
+        if constexpr (OUTER == 0) {
+            const Raw &cur = raw[s & 1];
+            if (s + 1 < nslab) fetch(std::true_type{}, s + 1, raw[(s + 1) & 1]);
+            decode(cur, s, x0, x1, mx[0], mx[1]);
+        } else {
+            mx[0] = mb[s][0];
+            mx[1] = mb[s][1];
+        }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const float (&x)[16] = j == 0 ? x0 : x1;
+            const float (&x)[16] = OUTER ? (j == 0 ? xb0[OUTER ? s : 0] : xb1[OUTER ? s : 0]) : (j == 0 ? x0 : x1);
             const uint32_t sc = e4m3_round<SUP>(mx[j] * os[j].inv_cg);
             const float r = os[j].inv_sg * inv_tab[sc];
             const int64_t e = (c0 + j) * R + R0 + 16 * s;           // index in the output's [C x R] view
@@ -667,9 +721,9 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
             uint2 q;
             q.x = quant8<ROUND, SUP>(xa, r, quad0, a.k.k0, a.k.k1);
             q.y = quant8<ROUND, SUP>(xb, r, quad0 + 2, a.k.k0, a.k.k1);
-            scb[j][s >> 2] |= sc << (8 * (s & 3));
+            scb[j] |= sc << (8 * s);
             if (wide) {
-                *reinterpret_cast<uint2 *>(stage + (2 * lane + j) * kPitch + wave * 64 + 8 * s) = q;
+                *reinterpret_cast<uint2 *>(stage + (2 * lane + j) * kPitch + wave * (8 * SLABS) + 8 * s) = q;
             } else if (colok) {
                 *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(a.k.codes) + (e >> 1)) = q;
                 a.k.scales[e >> 4] = (uint8_t)sc;
@@ -679,42 +733,51 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     if (nwide == 0) return;                                         // uniform over the workgroup
     if (wide) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            *reinterpret_cast<uint2 *>(sc_stage + (2 * lane + j) * kScPitch + wave * 8) = make_uint2(scb[j][0], scb[j][1]);
+        for (int j = 0; j < 2; ++j) {
+            uint8_t *p = sc_stage + (2 * lane + j) * kScPitch + wave * SLABS;
+            if constexpr (SLABS == 4) *reinterpret_cast<uint32_t *>(p) = scb[j];
+            else *reinterpret_cast<uint16_t *>(p) = (uint16_t)scb[j];
+        }
     }
     __syncthreads();
     {
-        // codes: 16 lanes x 16 bytes cover one output row's 256-byte run; 16 rows per pass
+        // codes: kPieces lanes x 16 bytes cover one output row's run
+        constexpr int kPieces = kRun / 16, kRowsPass = kThreads / kPieces;
         const int64_t Rg = (int64_t)trg * kWaves * kStripR;        // first source row of the workgroup
-        const int piece = tid & 15;
+        const int piece = tid % kPieces;
         uint8_t *out_codes = reinterpret_cast<uint8_t *>(a.k.codes);
-        if (piece < 4 * nwide) {
+        if (piece * 16 < 8 * SLABS * nwide) {
 #pragma unroll
-            for (int it = 0; it < kStripC / 16; ++it) {
-                const int row = it * 16 + (tid >> 4);
+            for (int it = 0; it < kStripC / kRowsPass; ++it) {
+                const int row = it * kRowsPass + tid / kPieces;
                 const uint2 lo = *reinterpret_cast<const uint2 *>(stage + row * kPitch + piece * 16);
                 const uint2 hi = *reinterpret_cast<const uint2 *>(stage + row * kPitch + piece * 16 + 8);
                 const int64_t c = strip0 + row;
                 if (c < C) *reinterpret_cast<uint4 *>(out_codes + ((c * R + Rg) >> 1) + piece * 16) = make_uint4(lo.x, lo.y, hi.x, hi.y);
             }
         }
-        // scales: 4 lanes x 8 bytes cover one output row's 32-byte run; 64 rows per pass
-        const int sp = tid & 3;
-        if (sp < nwide) {
+        // scales: 4-byte pieces (the row offset c * R / 16 is a multiple of 4 only); an odd number of two-slab strips leaves
+        // two bytes over
+        constexpr int kScPieces = kScPitch / 4, kScRows = kThreads / kScPieces;
+        const int sp = tid % kScPieces, have_sc = SLABS * nwide;
 #pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                const int row = it * 64 + (tid >> 2);
-                const uint2 v = *reinterpret_cast<const uint2 *>(sc_stage + row * kScPitch + sp * 8);
-                const int64_t c = strip0 + row;
-                if (c < C) *reinterpret_cast<uint2 *>(a.k.scales + ((c * R + Rg) >> 4) + sp * 8) = v;
+        for (int it = 0; it < (kStripC + kScRows - 1) / kScRows; ++it) {
+            const int row = it * kScRows + tid / kScPieces;
+            const int64_t c = strip0 + row;
+            if (row < kStripC && c < C) {
+                uint8_t *dst = a.k.scales + ((c * R + Rg) >> 4) + sp * 4;
+                const uint32_t v = *reinterpret_cast<const uint32_t *>(sc_stage + row * kScPitch + sp * 4);
+                if (sp * 4 + 4 <= have_sc) *reinterpret_cast<uint32_t *>(dst) = v;
+                else if (SLABS == 2 && sp * 4 + 2 <= have_sc) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)v;
             }
         }
     }
 }
 
-inline unsigned colw_grid(const ColArgs &a)
+inline unsigned colw_grid(const ColArgs &a, int slabs)
 {
-    const int64_t tiles_c = (a.C + kStripC - 1) / kStripC, tiles_r = (a.R + kStripR - 1) / kStripR;
+    const int64_t strip_r = 16 * slabs;
+    const int64_t tiles_c = (a.C + kStripC - 1) / kStripC, tiles_r = (a.R + strip_r - 1) / strip_r;
     return (unsigned)(tiles_c * ((tiles_r + kThreads / 64 - 1) / (kThreads / 64)));
 }
 
@@ -767,19 +830,29 @@ void launch_row_t(const RowJob &j0, const RowJob &j1, bool deq, bool rht, hipStr
                            first_second);
 }
 
-template <bool PACKED, int OUTER, bool RHT>
-void launch_colw_t(const ColArgs &a0, const ColArgs &a1, bool pair, int rounding, int scale_up, hipStream_t st)
+template <bool PACKED, int OUTER, bool RHT, int SLABS>
+void launch_colw_s(const ColArgs &a0, const ColArgs &a1, bool pair, int rounding, int scale_up, hipStream_t st)
 {
-    const unsigned g0 = colw_grid(a0), g1 = pair ? colw_grid(a1) : 0;
+    const unsigned g0 = colw_grid(a0, SLABS), g1 = pair ? colw_grid(a1, SLABS) : 0;
     const unsigned first_second = pair ? g0 : 0xFFFFFFFFu;
     const dim3 grid(g0 + g1);
     if (rounding == 0) {
-        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<0, true, PACKED, OUTER, RHT>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
-        else          hipLaunchKernelGGL((quant_colw_kernel<0, false, PACKED, OUTER, RHT>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
+        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<0, true, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
+        else          hipLaunchKernelGGL((quant_colw_kernel<0, false, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
     } else {
-        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<1, true, PACKED, OUTER, RHT>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
-        else          hipLaunchKernelGGL((quant_colw_kernel<1, false, PACKED, OUTER, RHT>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
+        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<1, true, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
+        else          hipLaunchKernelGGL((quant_colw_kernel<1, false, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
     }
+}
+
+template <bool PACKED, int OUTER, bool RHT>
+void launch_colw_t(const ColArgs &a0, const ColArgs &a1, bool pair, int rounding, int scale_up, hipStream_t st)
+{
+    // bf16 sources above 32 M elements: four slabs per strip (the figures are at the kernel)
+    if constexpr (OUTER == 0 && !PACKED) {
+        if (a0.R * a0.C > ((int64_t)1 << 25)) return launch_colw_s<PACKED, OUTER, RHT, 4>(a0, a1, pair, rounding, scale_up, st);
+    }
+    launch_colw_s<PACKED, OUTER, RHT, 2>(a0, a1, pair, rounding, scale_up, st);
 }
 
 template <bool PACKED>
@@ -827,6 +900,19 @@ void launch_zero_scalar(float *p, hipStream_t st)
     hipLaunchKernelGGL(zero_scalar_kernel, dim3(1), dim3(1), 0, st, p);
 }
 
+// the dequantized maxima of one or two operands with 1 x 128 outer blocks, after their row-wise quantization
+static void launch_deq_max(const RowJob &j0, const RowJob &j1, hipStream_t st)
+{
+    auto job = [](const RowJob &r) {
+        DeqJob d{r.a.gscale, r.a.scales, r.a.codes, r.a.amax_deq, r.nchunks / 16, 0};
+        const int64_t want = (d.nblocks + kThreads - 1) / kThreads;
+        d.nwg = r.a.amax_deq ? (unsigned)(want < kDeqWgs ? want : kDeqWgs) : 0u;
+        return d;
+    };
+    const DeqJob d0 = job(j0), d1 = job(j1);
+    if (d0.nwg + d1.nwg) hipLaunchKernelGGL(deq_max_kernel, dim3(d0.nwg + d1.nwg), dim3(kThreads), 0, st, d0, d1);
+}
+
 static void launch_row_sel(const RowJob &j0, const RowJob &j1, const QuantParams &p, bool deq, hipStream_t st)
 {
     const int sel = (p.rounding << 2) | (p.scale_up << 1) | p.outer;
@@ -849,7 +935,9 @@ hipError_t launch_quant_row_bf16(const void *src, int64_t rows, int64_t K, const
     const int64_t nchunks = rows * K / 8;
     if (nchunks == 0) return hipSuccess;
     RowJob j0{reinterpret_cast<const uint4 *>(src), nchunks, make_kargs(p, o), (uint32_t)(K / 128)}, j1{};
-    launch_row_sel(j0, j1, p, o.amax_deq != nullptr && p.rounding == 0 && !p.rht, st);
+    const bool deq = o.amax_deq != nullptr && p.rounding == 0 && !p.rht;
+    launch_row_sel(j0, j1, p, deq, st);
+    if (deq && p.outer) launch_deq_max(j0, j1, st);
     return hipGetLastError();
 }
 
@@ -861,7 +949,9 @@ hipError_t launch_quant_row_bf16_pair(const void *src0, int64_t rows0, int64_t K
     if (rows1 * K1 == 0) return launch_quant_row_bf16(src0, rows0, K0, p0, o0, st);
     RowJob j0{reinterpret_cast<const uint4 *>(src0), rows0 * K0 / 8, make_kargs(p0, o0), (uint32_t)(K0 / 128)};
     RowJob j1{reinterpret_cast<const uint4 *>(src1), rows1 * K1 / 8, make_kargs(p1, o1), (uint32_t)(K1 / 128)};
-    launch_row_sel(j0, j1, p0, (o0.amax_deq != nullptr || o1.amax_deq != nullptr) && p0.rounding == 0, st);
+    const bool deq = (o0.amax_deq != nullptr || o1.amax_deq != nullptr) && p0.rounding == 0;
+    launch_row_sel(j0, j1, p0, deq, st);
+    if (deq && p0.outer) launch_deq_max(j0, j1, st);
     return hipGetLastError();
 }
 

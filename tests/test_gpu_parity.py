@@ -181,6 +181,52 @@ def test_quant_col(shape, rounding):
     assert_same(got, ref, "col %s r%d" % (shape, rounding))
 
 
+# strips of 32 rows (64 for a bf16 source above 2^25 elements), four per workgroup: rows that end inside a slab's worth of a
+# strip, inside a workgroup, on and off the 64-row alignment of the staged stores; columns that end inside a strip
+STRIP_SHAPES = [(32, 8), (48, 136), (64, 128), (96, 264), (112, 120), (192, 136), (208, 16), (320, 392)]
+
+
+@pytest.mark.parametrize("shape", STRIP_SHAPES + [(4160, 8208), (4112, 8208)])
+def test_quant_col_strip_edges(shape):
+    bits = wl.normal_bf16(shape, 1e-3, 470 + shape[0], 1e-2, 30.0)
+    got = tj.quantize(dev_bf16(bits), 1, 1, seed=8, tensor_id=5)
+    assert_same(got, oracle.quantize_bf16(bits, 1, 1, seed=8, tensor_id=5), "col %s" % (shape,))
+
+
+@pytest.mark.parametrize("shape", [(r, (c + 15) // 16 * 16) for r, c in STRIP_SHAPES])
+@pytest.mark.parametrize("rounding", [0, 1])
+def test_requant_col_strip_edges(shape, rounding):
+    bits = wl.normal_bf16(shape, 1.0, 480 + shape[0], 1e-2, 50.0)
+    src = tj.quantize(dev_bf16(bits), 0, 0)
+    got = tj.quantize(src, 1, rounding, seed=17, tensor_id=6)
+    assert_same(got, oracle.requantize(oracle.quantize_bf16(bits, 0, 0), 1, rounding, seed=17, tensor_id=6), "requant %s" % (shape,))
+
+
+@pytest.mark.parametrize("case", ["ordinary", "many blocks", "zero", "floored", "scale one"])
+def test_dequantized_maximum_block128(case):
+    """the maximum of an operand with 1 x 128 outer blocks is taken from its outer scales, except for blocks whose scale is
+    the floor 2^-100 or exactly 1 (as that of an all-zero block is)"""
+    shape = (300, 8192) if case == "many blocks" else (6, 384)
+    x = wl.bf16_to_f32(wl.normal_bf16(shape, 1.0, 490)).copy()
+    if case == "zero":
+        x[:] = 0
+    elif case == "floored":
+        x = x * np.float32(2.0 ** -115)
+        x[0] = 0
+    elif case == "scale one":
+        x[0, :128] = 0
+        x[2, 130] = 2688.0                              # S_g = 1 and the largest value of the tensor
+        x[2, 128:256:2] = 1000.0
+    elif case == "many blocks":
+        x[299, 8100] = 77.0
+    bits = wl.f32_to_bf16(x)
+    ref = oracle.quantize_bf16(bits, 0, 0, outer=oracle.OUTER_BLOCK128)
+    got = tj.alloc_nvfp4(shape[0], shape[1], tj.binding.OUTER_BLOCK128)
+    got.amax_deq.fill_(123.0)                            # stale value: the call must overwrite it
+    tj.quantize(dev_bf16(bits), 0, 0, got, outer=tj.binding.OUTER_BLOCK128)
+    assert_same(got, ref, case, check_amax=True)
+
+
 @pytest.mark.parametrize("shape", [(128, 8), (256, 512), (384, 136), (1152, 1040), (2048, 72)])
 @pytest.mark.parametrize("rounding", [0, 1])
 def test_quant_col_block128_mode(shape, rounding):
