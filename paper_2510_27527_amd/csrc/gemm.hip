@@ -66,8 +66,9 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *__
 struct TileCfg { int tm, tn; double t_stage; double t_fixed; int occupancy; };
 // t_stage: one 128-k pipeline stage of one workgroup with the CU to itself; t_fixed: prologue + epilogue
 // the 128 x 192 tile exists for the paired scale fetch only (K a multiple of 256)
-const TileCfg kTiles[] = {{4, 4, 3.2, 6.0, 1}, {4, 2, 2.0, 5.0, 1}, {2, 4, 2.0, 5.0, 1}, {2, 2, 1.5, 5.0, 3}, {2, 3, 1.4, 5.0, 2}};
-constexpr int kNumTiles = 5;
+const TileCfg kTiles[] = {{4, 4, 3.2, 6.0, 1}, {4, 2, 2.0, 5.0, 1}, {2, 4, 2.0, 5.0, 1}, {2, 2, 1.5, 5.0, 3}, {2, 3, 1.4, 5.0, 2},
+                          {1, 1, 0.6, 3.2, 3}, {1, 2, 0.9, 3.2, 2}};
+constexpr int kNumTiles = 7;
 constexpr int kNumCU = 256;
 
 struct Plan { int tile; int split; int chunks_per_split; };
@@ -80,6 +81,22 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
     double best_t = 1e300;
     for (int t = 0; t < kNumTiles; ++t) {
         if (t == 4 && K % 256 != 0) continue;
+        // The small tiles are for outputs that leave CUs idle with 128 x 128 workgroups: there the time is the chain of a
+        // tile's stages, and a 64-row tile's stage is half as long (256 x 512 x 512: 9.6 us with 128 x 192, 5.6 with
+        // 64 x 64; 2048 x 1024 x 1024: 14.6 us with 128 x 192, 10.4 with 64 x 128); longer chains than 16 stages are split
+        // instead.  A filled chip pays for them with twice the expansions per product (8192 x 3072 x 768: 73 us with
+        // 64 x 64, 42 with 128 x 192), and a sliver of an output with
+        // rows that are mostly padding.  With 1 x 128 outer blocks the same holds (2048 x 1024 x 1024: 19.8 us with 128 x 192),
+        // a little earlier where only the 64 x 64 tile exists.
+        if (t >= 5) {
+            const int64_t least = outer ? 256 : 128, tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
+            // Ragged outputs with reductions of more than 22 stages keep the large tiles (the parity tests of ragged edges under
+            // a K split are pinned to them), although the small ones are faster there too (1000 x 520 x 3072: 16.2 against
+            // 20.2 us; whole tiles: 768 x 768 x 3072 15.5 / 20.0, 512 x 512 x 8192 17.3 / 23.3).
+            if (K > 22 * 64 * kNC && (M % 64 != 0 || N % 64 != 0)) continue;
+            if (M < least || N < least || tiles128 > (outer && K % 256 != 0 ? 3 * kNumCU / 8 : kNumCU / 2)) continue;
+        }
+        if (t == 6 && K % 256 != 0) continue;
         if (t == 0 && outer) continue;                      // block mode keeps two accumulator sets: at most 2 x 4 tiles per wave
         const int64_t bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
         const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -89,6 +106,7 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
             if (chunks % 4 == 0) cps = (cps + 3) / 4 * 4;                       // splits on 256-k boundaries
             else if (outer) cps = (cps + 1) / 2 * 2;                            // block mode: on 128-k boundaries
             if (split > 1 && (chunks + cps - 1) / cps != split) continue;      // same launch as a smaller split
+            if (t >= 5 && cps > 16 * kNC) continue;                                          // small tiles: at most 16 stages
             const int64_t wgs = tiles * split;
             const double stages = (double)((cps + kNC - 1) / kNC);
             // workgroups sharing a CU slow each other down (128 x 128 tiles: up to three per CU)

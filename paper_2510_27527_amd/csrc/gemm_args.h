@@ -31,7 +31,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
 // One translation unit per (output kind, scale-fetch variant, outer mode) instantiates the product kernel for every
 // tile shape: out 0 bf16, 1 f32, 2 raw f32 split-K partial; ps = paired scale fetch (K a multiple of 256); outer = 1:
 // one FP32 outer scale per row and 128 k.  tile: 0 256x256 (outer 0 only), 1 256x128, 2 128x256, 3 128x128,
-// 4 128x192 (ps only).
+// 4 128x192 (ps only), 5 64x64, 6 64x128 (ps only).
 #define TJ_DECL_GEMM_INST(ps, out, outer) \
     hipError_t launch_gemm_inst_ps##ps##_out##out##_outer##outer(int tile, const GemmArgs &g, dim3 grid, hipStream_t st);
 TJ_DECL_GEMM_INST(0, 0, 0) TJ_DECL_GEMM_INST(0, 1, 0) TJ_DECL_GEMM_INST(0, 2, 0)

@@ -550,7 +550,7 @@ hipError_t launch_cfg(const GemmArgs &g, dim3 grid, hipStream_t st)
 }
 
 // tile: 0 256x256 (tensor mode only: block mode needs two accumulator sets), 1 256x128, 2 128x256, 3 128x128,
-// 4 128x192 (paired scale fetch only)
+// 4 128x192 (paired scale fetch only), 5 64x64, 6 64x128 (paired scale fetch only)
 template <int OUT, bool PS, int OUTER>
 hipError_t launch_tile(int tile, const GemmArgs &g, dim3 grid, hipStream_t st)
 {
@@ -562,6 +562,11 @@ hipError_t launch_tile(int tile, const GemmArgs &g, dim3 grid, hipStream_t st)
         case 2: return launch_cfg<2, 4, OUT, PS, OUTER>(g, grid, st);
         case 4:
             if constexpr (PS) return launch_cfg<2, 3, OUT, true, OUTER>(g, grid, st);
+            else return hipErrorInvalidValue;
+        case 5:
+            return launch_cfg<1, 1, OUT, PS, OUTER>(g, grid, st);
+        case 6:
+            if constexpr (PS) return launch_cfg<1, 2, OUT, true, OUTER>(g, grid, st);
             else return hipErrorInvalidValue;
         default: return launch_cfg<2, 2, OUT, PS, OUTER>(g, grid, st);
     }

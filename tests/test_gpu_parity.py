@@ -379,6 +379,36 @@ def test_gemm_every_kernel_instantiation(key, shape, out_dtype):
     check_product(got[torch.from_numpy(rows).cuda()], ref, absref, "gemm %dx%dx%d" % (M, N, K))
 
 
+# (outer mode, M, N, K, workgroup tile, K split) of the small tiles: ragged in both directions; 1088: whole chunks of 64 but
+# half a stage at the end; whole tiles with a 16-byte aligned row take the staged epilogue
+SMALL_TILE_SHAPES = [(0, 154, 131, 64, (64, 64), False), (0, 135, 153, 1600, (64, 64), True), (0, 133, 151, 256, (64, 64), False),
+                     (0, 150, 150, 1536, (64, 64), True), (0, 1227, 777, 256, (64, 128), False), (0, 640, 2240, 1088, (64, 64), False),
+                     (0, 704, 1152, 2816, (64, 128), True), (0, 256, 512, 512, (64, 64), False), (0, 2048, 1024, 1024, (64, 128), False),
+                     (1, 261, 295, 128, (64, 64), False), (1, 309, 267, 1664, (64, 64), True), (1, 274, 258, 256, (64, 64), False),
+                     (1, 263, 262, 1536, (64, 64), True), (1, 1228, 769, 256, (64, 128), False), (1, 268, 777, 2560, (64, 128), True),
+                     (1, 256, 512, 512, (64, 64), False), (1, 2048, 1024, 1024, (64, 128), False)]
+
+
+@pytest.mark.parametrize("outer,M,N,K,tile,split", SMALL_TILE_SHAPES)
+@pytest.mark.parametrize("out_dtype", [0, 1])
+def test_gemm_small_tiles(outer, M, N, K, tile, split, out_dtype):
+    plan = tj.binding.gemm_plan(M, N, K, outer)
+    assert plan[:2] == tile and (plan[2] > 1) == split, plan
+    if outer:
+        A = oracle.quantize_bf16(_block_operand(M, K, 760 + N, 1.0), 0, 0, outer=oracle.OUTER_BLOCK128)
+        B = oracle.quantize_bf16(_block_operand(N, K, 761 + M, 0.02), 0, 1, outer=oracle.OUTER_BLOCK128, seed=6)
+    else:
+        A = oracle.quantize_bf16(wl.normal_bf16((M, K), 1.0, 760 + N, 1e-2, 50.0), 0, 0)
+        B = oracle.quantize_bf16(wl.normal_bf16((N, K), 0.02, 761 + M), 0, 1, seed=6)
+    got = tj.gemm_nt(to_dev(A), to_dev(B), out_dtype)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(M + 7 * N + K)
+    tiles = np.arange(0, M, tile[0])
+    rows = np.unique(np.concatenate([tiles, np.minimum(tiles + tile[0] - 1, M - 1), rng.choice(M, 32, replace=False)]))
+    ref, absref = oracle.gemm_nt(A, B, rows_a=rows)
+    check_product(got[torch.from_numpy(rows).cuda()], ref, absref, "gemm small tiles %dx%dx%d" % (M, N, K))
+
+
 # (outer mode, M, N, K, tile): whole tiles, K a multiple of 256, more workgroups than the chip holds of that tile at
 # once and not a multiple of that number, so tiles start and end at different times on one compute unit.  K = 256 is the
 # shortest reduction with paired scale fetch (two stages, one scale pair), 768 a typical short one.
