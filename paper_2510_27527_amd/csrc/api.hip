@@ -259,15 +259,17 @@ int run_quantize_row_pair(const void *src0, const QuantPlan &pl0, nvfp4_tensor *
     return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
-// Two column-wise re-quantizations of packed tensors (Q4 and Q6 of one backward call) in one launch.
+// Two column-wise re-quantizations of packed tensors (Q4 and Q6 of one backward call) in one launch; with `bf16`, the
+// partial maxima of that array of n elements come from the same launch.
 int run_requant_pair(const nvfp4_tensor *s0, const QuantPlan &pl0, const nvfp4_qcfg *c0, nvfp4_tensor *out0,
                      const nvfp4_tensor *s1, const QuantPlan &pl1, const nvfp4_qcfg *c1, nvfp4_tensor *out1,
-                     hipStream_t st)
+                     hipStream_t st, const void *bf16 = nullptr, int64_t n = 0, float *partials = nullptr, int *npart = nullptr)
 {
     QuantParams p0 = params_of(pl0, c0), p1 = params_of(pl1, c1);
     p0.amax_scalar = pl0.outer == NVFP4_OUTER_TENSOR ? (c0->amax_in ? c0->amax_in : s0->amax_deq) : nullptr;
     p1.amax_scalar = pl1.outer == NVFP4_OUTER_TENSOR ? (c1->amax_in ? c1->amax_in : s1->amax_deq) : nullptr;
     if (p0.rounding != p1.rounding || p0.scale_up != p1.scale_up || p0.outer != p1.outer || p0.rht != p1.rht) {
+        if (bf16) *npart = launch_amax_partials(bf16, n, partials, nullptr, st);
         const int rc = run_quantize(s0, pl0, c0, out0, nullptr, st);
         return rc ? rc : run_quantize(s1, pl1, c1, out1, nullptr, st);
     }
@@ -275,7 +277,8 @@ int run_requant_pair(const nvfp4_tensor *s0, const QuantPlan &pl0, const nvfp4_q
     stamp(out1, pl1);
     QuantOut o0{out0->codes, out0->scales, out0->gscale, nullptr}, o1{out1->codes, out1->scales, out1->gscale, nullptr};
     PackedSrc ps0{s0->codes, s0->scales, s0->gscale, s0->outer_mode}, ps1{s1->codes, s1->scales, s1->gscale, s1->outer_mode};
-    const hipError_t e = launch_requant_col_pair(ps0, pl0.R, pl0.C, p0, o0, ps1, pl1.R, pl1.C, p1, o1, st);
+    const hipError_t e = bf16 ? launch_requant_col_pair_amax(ps0, pl0.R, pl0.C, p0, o0, ps1, pl1.R, pl1.C, p1, o1, bf16, n, partials, npart, st)
+                              : launch_requant_col_pair(ps0, pl0.R, pl0.C, p0, o0, ps1, pl1.R, pl1.C, p1, o1, st);
     return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
@@ -842,8 +845,11 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (outer == NVFP4_OUTER_TENSOR) {
         if (N > 0 && C > 0) {
-            // every workgroup of the quantizer reduces the partial maxima itself: no launch in between
-            const int npart = launch_amax_partials(dY, N * C, part, nullptr, st);
+            // one launch for the maximum of dY and the re-quantizations Q4, Q6 (which do not need it); every workgroup of
+            // the quantizer after it reduces the partial maxima itself
+            int npart = 0;
+            rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st, dY, N * C, part, &npart);
+            if (rc) return rc;
             QuantParams pr{}, pc{};
             pr.rounding = pc.rounding = 1;
             pr.scale_up = pc.scale_up = 1;
@@ -854,6 +860,9 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
             pc.k0 = (uint32_t)k5; pc.k1 = (uint32_t)(k5 >> 32);
             QuantOut orow{q3.codes, q3.scales, q3.gscale, nullptr}, ocol{q5.codes, q5.scales, q5.gscale, nullptr};
             if (launch_quant_dual_bf16(dY, N, C, pr, orow, pc, ocol, st) != hipSuccess) return NVFP4_ERR_HIP;
+        } else {
+            rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st);
+            if (rc) return rc;
         }
         q3.rows = N; q3.K = C; q5.rows = C; q5.K = N;
     } else {
@@ -862,9 +871,9 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
         if (rc) return rc;
         rc = run_quantize(dY, p5, &c[2], &q5, nullptr, st);
         if (rc) return rc;
+        rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st);
+        if (rc) return rc;
     }
-    rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st);
-    if (rc) return rc;
     rc = run_gemm(&q3, &q4, dX, out_dtype, gws, gbytes, st);
     if (rc) return rc;
     return run_gemm(&q5, &q6, dW, out_dtype, gws, gbytes, st);

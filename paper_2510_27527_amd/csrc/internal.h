@@ -71,6 +71,12 @@ hipError_t launch_requant_col_pair(const PackedSrc &src0, int64_t R0, int64_t C0
                                    const QuantOut &o0, const PackedSrc &src1, int64_t R1, int64_t C1,
                                    const QuantParams &p1, const QuantOut &o1, hipStream_t st);
 
+// the same together with the partial maxima of |x| over a bf16 array of n elements (n % 8 == 0) in one launch; *npart is
+// the number of partials
+hipError_t launch_requant_col_pair_amax(const PackedSrc &src0, int64_t R0, int64_t C0, const QuantParams &p0, const QuantOut &o0,
+                                        const PackedSrc &src1, int64_t R1, int64_t C1, const QuantParams &p1, const QuantOut &o1,
+                                        const void *bf16, int64_t n, float *partials, int *npart, hipStream_t st);
+
 struct GemmOperand {
     const uint8_t *codes;
     const uint8_t *scales;

@@ -100,18 +100,14 @@ struct AmaxJob {
     unsigned nblocks;
 };
 
-__global__ __launch_bounds__(kThreads) void amax_partials_kernel(AmaxJob j0, AmaxJob j1)
+// workgroup `bid` of the job's nblocks
+__device__ __forceinline__ void amax_partials(const AmaxJob &j, unsigned bid, float *red)
 {
-    __shared__ float red[4];
-    const bool second = blockIdx.x >= j0.nblocks;
-    const uint4 *__restrict__ src = second ? j1.src : j0.src;
-    const int64_t nchunks = second ? j1.nchunks : j0.nchunks;
-    float *partials = second ? j1.partials : j0.partials;
-    float *zero_me = second ? j1.zero_me : j0.zero_me;
-    const unsigned bid = second ? blockIdx.x - j0.nblocks : blockIdx.x, nb = second ? j1.nblocks : j0.nblocks;
-    if (zero_me && bid == 0 && threadIdx.x == 0) zero_me[0] = 0.0f;
+    const uint4 *__restrict__ src = j.src;
+    const int64_t nchunks = j.nchunks;
+    if (j.zero_me && bid == 0 && threadIdx.x == 0) j.zero_me[0] = 0.0f;
     uint32_t m = 0;
-    const int64_t stride = (int64_t)nb * kThreads;
+    const int64_t stride = (int64_t)j.nblocks * kThreads;
     int64_t c = (int64_t)bid * kThreads + threadIdx.x;
     for (; c + 3 * stride < nchunks; c += 4 * stride) {
         // streaming loads: measured 2 % on a whole layer step against ordinary loads
@@ -129,7 +125,14 @@ __global__ __launch_bounds__(kThreads) void amax_partials_kernel(AmaxJob j0, Ama
     float f = wave_max(u2f(m << 16));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = f;
     __syncthreads();
-    if (threadIdx.x == 0) partials[bid] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    if (threadIdx.x == 0) j.partials[bid] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+__global__ __launch_bounds__(kThreads) void amax_partials_kernel(AmaxJob j0, AmaxJob j1)
+{
+    __shared__ float red[4];
+    if (blockIdx.x >= j0.nblocks) amax_partials(j1, blockIdx.x - j0.nblocks, red);
+    else amax_partials(j0, blockIdx.x, red);
 }
 
 // out may alias partials: it is written after every partial has been read
@@ -524,8 +527,11 @@ constexpr int kStripC = 128;
 
 // RHT (with OUTER = 1): a lane's 16 values of a column are one block of the random Hadamard transform (Sec. 4.1), all
 // in its own registers; the signs depend on the source row only, so they are wave-uniform masks.
-template <int ROUND, bool SUP, bool PACKED, int OUTER, bool RHT, int SLABS>
-__global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArgs a1, unsigned first_second)
+//
+// AMAX: the launch's first workgroups take the maximum of an unrelated bf16 tensor (a backward call's dY, whose maximum the
+// quantizers that follow need): a pass that waits for memory beside one that is bound by the vector ALU.
+template <int ROUND, bool SUP, bool PACKED, int OUTER, bool RHT, int SLABS, bool AMAX = false>
+__global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArgs a1, unsigned first_second, AmaxJob am)
 {
     static_assert(!RHT || OUTER == 1, "the transform is provided with 1 x 128 outer blocks");
     static_assert(OUTER == 0 || SLABS == 2, "a workgroup's rows are one outer block");
@@ -533,16 +539,21 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     __shared__ float inv_tab[128];
     __shared__ float red[4];
     const int tid = threadIdx.x, lane = tid & 63;
-    const bool second = blockIdx.x >= first_second;
+    if (AMAX && blockIdx.x < am.nblocks) {
+        amax_partials(am, blockIdx.x, red);
+        return;
+    }
+    const unsigned bid = AMAX ? blockIdx.x - am.nblocks : blockIdx.x, nbid = AMAX ? gridDim.x - am.nblocks : gridDim.x;
+    const bool second = bid >= first_second;
     const ColArgs a = second ? a1 : a0;
-    const uint32_t wg0 = second ? blockIdx.x - first_second : blockIdx.x;
+    const uint32_t wg0 = second ? bid - first_second : bid;
     // Workgroup ids are dealt round-robin over the 8 XCDs.  Each XCD gets a contiguous run of this job's strips (column
     // index fastest, so whole bands of strip rows): its strips then cover every column offset - all of the cache's
     // channels, where a strided walk down one column offset would keep hitting the same few - and neighbouring strips,
     // which share cache lines of a packed source, meet in one L2.  Measured on 8192 x 8192 bf16: 6.1 TB/s against 4.0.
     uint32_t wg = wg0;
     {
-        const uint32_t nwg = second ? gridDim.x - first_second : (first_second < gridDim.x ? first_second : gridDim.x);
+        const uint32_t nwg = second ? nbid - first_second : (first_second < nbid ? first_second : nbid);
         const uint32_t per_xcd = nwg / 8;
         if (wg < per_xcd * 8) wg = (wg & 7) * per_xcd + (wg >> 3);
     }
@@ -837,11 +848,11 @@ void launch_colw_s(const ColArgs &a0, const ColArgs &a1, bool pair, int rounding
     const unsigned first_second = pair ? g0 : 0xFFFFFFFFu;
     const dim3 grid(g0 + g1);
     if (rounding == 0) {
-        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<0, true, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
-        else          hipLaunchKernelGGL((quant_colw_kernel<0, false, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
+        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<0, true, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second, AmaxJob{});
+        else          hipLaunchKernelGGL((quant_colw_kernel<0, false, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second, AmaxJob{});
     } else {
-        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<1, true, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
-        else          hipLaunchKernelGGL((quant_colw_kernel<1, false, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second);
+        if (scale_up) hipLaunchKernelGGL((quant_colw_kernel<1, true, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second, AmaxJob{});
+        else          hipLaunchKernelGGL((quant_colw_kernel<1, false, PACKED, OUTER, RHT, SLABS>), grid, dim3(kThreads), 0, st, a0, a1, first_second, AmaxJob{});
     }
 }
 
@@ -1020,6 +1031,23 @@ hipError_t launch_requant_col_pair(const PackedSrc &src0, int64_t R0, int64_t C0
     if (R1 == 0 || C1 == 0) return launch_requant_col(src0, R0, C0, p0, o0, st);
     ColArgs a0 = packed_args(src0, R0, C0, p0, o0), a1 = packed_args(src1, R1, C1, p1, o1);
     launch_colw<true>(a0, a1, true, p0, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_requant_col_pair_amax(const PackedSrc &src0, int64_t R0, int64_t C0, const QuantParams &p0, const QuantOut &o0,
+                                        const PackedSrc &src1, int64_t R1, int64_t C1, const QuantParams &p1, const QuantOut &o1,
+                                        const void *bf16, int64_t n, float *partials, int *npart, hipStream_t st)
+{
+    if (R0 * C0 == 0 || R1 * C1 == 0 || p0.rounding != 1 || !p0.scale_up || p0.outer != 0) {
+        *npart = launch_amax_partials(bf16, n, partials, nullptr, st);
+        return launch_requant_col_pair(src0, R0, C0, p0, o0, src1, R1, C1, p1, o1, st);
+    }
+    const ColArgs a0 = packed_args(src0, R0, C0, p0, o0), a1 = packed_args(src1, R1, C1, p1, o1);
+    const AmaxJob am{reinterpret_cast<const uint4 *>(bf16), n / 8, partials, nullptr, (unsigned)amax_grid(n / 8)};
+    const unsigned g0 = colw_grid(a0, 2), g1 = colw_grid(a1, 2);
+    hipLaunchKernelGGL((quant_colw_kernel<1, true, true, 0, false, 2, true>), dim3(am.nblocks + g0 + g1), dim3(kThreads), 0, st, a0, a1,
+                       g0, am);
+    *npart = (int)am.nblocks;
     return hipGetLastError();
 }
 
