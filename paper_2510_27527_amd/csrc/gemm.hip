@@ -121,7 +121,7 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
             const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU;
             const TileCfg &cfg = fit ? kTilesBlock[t] : kTiles[t];
             const int64_t conc = per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
-            const double slow = conc == 1 ? 1.0 : conc == 2 ? (fit && t < 5 ? 1.55 : 1.75) : 2.35;
+            const double slow = conc == 1 ? 1.0 : conc == 2 ? (fit && t < 5 ? 1.55 : t == 4 ? 1.9 : 1.75) : 2.35;
             const int64_t waves = (wgs + kNumCU * conc - 1) / (kNumCU * conc);
             // block mode, short reductions: the per-block rescale of the accumulators makes a stage about a third longer
             double time = fit ? (double)waves * (stages * cfg.t_stage + cfg.t_fixed) * slow
