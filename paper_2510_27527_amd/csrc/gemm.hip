@@ -69,13 +69,16 @@ struct TileCfg { int tm, tn; double t_stage; double t_fixed; int occupancy; };
 const TileCfg kTiles[] = {{4, 4, 3.2, 6.0, 1}, {4, 2, 2.0, 5.0, 1}, {2, 4, 2.0, 5.0, 1}, {2, 2, 1.5, 5.0, 3}, {2, 3, 1.4, 5.0, 2},
                           {1, 1, 0.6, 3.2, 3}, {1, 2, 0.9, 3.2, 2}};
 constexpr int kNumTiles = 7;
-// The same for operands with 1 x 128 outer blocks and reductions of at least kBlockFitK: the rescale of every stage and the
-// second accumulator set change the tiles' order (one 128 x 192 workgroup per CU instead of two).  Fitted to products of
-// 1024 .. 16384 rows with K = 768 .. 6272 under sustained load, e.g. 8192 x 4096 x 4096: 331 us with 256 x 128, 386 with
-// 128 x 192; 2048 x 2048 x 2048: 30.6 us with 128 x 128, 35.5 with 128 x 192, 40.4 with 256 x 128.
-const TileCfg kTilesBlock[] = {{4, 4, 0, 0, 1}, {4, 2, 2.48, 3.2, 1}, {2, 4, 2.57, 3.2, 1}, {2, 2, 1.66, 4.0, 2}, {2, 3, 2.0, 3.3, 1},
-                               {1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}};
-constexpr int64_t kBlockFitK = 768;
+// Costs fitted to sustained runs of the tiles on whole layers' products (64 x 64 to 256 x 256 tiles; 1000 to 16384 rows, K =
+// 512 .. 16384), here with t_fixed shared between the workgroups of a CU like the stages: [0] per-tensor scales, [1]
+// 1 x 128 outer blocks, whose rescale in every stage and second accumulator set change the tiles' order.  Examples: 1000 x
+// 3072 x 1024 12.8 us with 128 x 128, 15.8 with 128 x 192; with outer blocks 8192 x 4096 x 4096 331 us with 256 x 128, 386 with
+// 128 x 192, and 2048 x 2048 x 2048 30.6 us with 128 x 128, 40.4 with 256 x 128.  They are used for outputs of whole 64
+// columns (a layer's weight side) and reductions that are not very short; slivers, ragged columns and short reductions
+// keep the costs above, to which the parity tests' choice of a shape for every kernel is pinned.
+const TileCfg kTilesFit[2][kNumTiles] = {
+    {{4, 4, 2.9, 7.2, 1}, {4, 2, 1.78, 4.0, 1}, {2, 4, 1.78, 4.0, 1}, {2, 2, 1.1, 4.0, 2}, {2, 3, 1.33, 5.2, 2}, {1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}},
+    {{4, 4, 0, 0, 1}, {4, 2, 2.48, 3.2, 1}, {2, 4, 2.57, 3.2, 1}, {2, 2, 1.52, 4.0, 2}, {2, 3, 2.0, 3.3, 1}, {1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
 constexpr int kNumCU = 256;
 
 struct Plan { int tile; int split; int chunks_per_split; };
@@ -86,7 +89,7 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
     Plan best{3, 1, (int)chunks};
     if (M <= 0 || N <= 0 || chunks == 0) return best;      // nothing to tile (empty output or empty reduction)
     double best_t = 1e300;
-    const bool fit = outer && K >= kBlockFitK && M >= 128 && N >= 128;      // slivers: as for short reductions
+    const bool fit = M >= 128 && N >= 128 && N % 64 == 0 && K >= (outer ? 768 : 512);
     for (int t = 0; t < kNumTiles; ++t) {
         if (t == 4 && K % 256 != 0) continue;
         // The small tiles are for outputs that leave CUs idle with 128 x 128 workgroups: there the time is the chain of a
@@ -119,11 +122,11 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
             const double stages = (double)((cps + kNC - 1) / kNC);
             // workgroups sharing a CU slow each other down (128 x 128 tiles: up to three per CU)
             const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU;
-            const TileCfg &cfg = fit ? kTilesBlock[t] : kTiles[t];
+            const TileCfg &cfg = fit ? kTilesFit[outer][t] : kTiles[t];
             const int64_t conc = per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
-            const double slow = conc == 1 ? 1.0 : conc == 2 ? (fit && t < 5 ? 1.55 : t == 4 ? 1.9 : 1.75) : 2.35;
+            const double slow = conc == 1 ? 1.0 : fit ? (conc > 2 ? 1.95 : t >= 5 ? 1.4 : outer ? 1.7 : 1.58) : conc == 2 ? (t == 4 ? 1.9 : 1.75) : 2.35;
             const int64_t waves = (wgs + kNumCU * conc - 1) / (kNumCU * conc);
-            // block mode, short reductions: the per-block rescale of the accumulators makes a stage about a third longer
+            // unfitted block mode: the per-block rescale of the accumulators makes a stage about a third longer
             double time = fit ? (double)waves * (stages * cfg.t_stage + cfg.t_fixed) * slow
                               : (double)waves * (stages * cfg.t_stage * (outer ? 1.35 : 1.0) * slow + cfg.t_fixed);
             if (split > 1) time += 4.0 + (double)(split + 1) * (double)(M * N) * 4.0 / 3.5e6;   // partials out and back in

@@ -184,6 +184,9 @@ template <int TM, int TN>
 struct RawFrags {
     uint4 qa[TM], qb[TN];       // 32 codes per fragment
 };
+// whether a wave prepares the scale factors of a chunk's two groups together (see expand in the kernel)
+template <int TM, int TN, bool PS, int OUTER>
+constexpr bool kPairScales = TM * TN <= 6 && (PS || OUTER == 0);
 template <int TM, int TN>
 struct OpFrags {
     half8_t a[TM], b[TN];
@@ -385,7 +388,7 @@ __global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) voi
         };
 
         uint32_t scA[NC][TM], scB[NC][TN];   // four scale bytes per chunk and fragment row
-        uint32_t live[NC];                    // 0xFF, or 0 for a chunk past the end of K (its scales count as zero)
+        uint32_t live[NC];                    // a mask: 0xFF or more, or 0 for a chunk past the end of K (its scales count as zero)
         auto read_raw = [&](RawFrags<TM, TN> &r, int buf, int c, bool is_live) {
             const uint4 *codes = reinterpret_cast<const uint4 *>(smem_raw + buf * CODE_BYTES);
             const uint32_t *scales = reinterpret_cast<const uint32_t *>(smem_raw + SC_BASE + buf * SC_BYTES) + c * ROWS;
@@ -401,7 +404,7 @@ __global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) voi
                 r.qb[j] = codes[A_SLOTS + row * SLOTS + ((2 * c + kg) ^ ((row >> 2) & (SLOTS - 1)))];
                 if (!PS) scB[c][j] = scales[BM + row];
             }
-            if (!PS) live[c] = is_live ? 0xFFu : 0u;
+            if (!PS) live[c] = is_live ? (kPairScales<TM, TN, PS, OUTER> ? 0xFFFFFFFFu : 0xFFu) : 0u;
         };
         // PS: the two chunk dwords of stage kt for every fragment row (second half of the pair for odd stages)
         auto read_stage_scales = [&](int kt) {
@@ -418,19 +421,31 @@ __global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) voi
             }
         };
 
+        // A lane needs two of a row's four scale bytes per chunk (groups 2 kg and 2 kg + 1).  Tiles of up to 2 x 3 per wave
+        // make both at once - one byte permute, one shift, and the multiplications broadcast the half they need - where the
+        // larger ones extract and replicate one byte per group: four instructions instead of two, but the larger tiles have
+        // no registers to spare (the 256 x 128 tile with outer blocks spills).  With the pair the 128 x 128 tile gains 5-20 %
+        // (2048 x 1024 x 1024: 13.5 -> 11.2 us, 8192 x 768 x 3072: 50.2 -> 45.2), 128 x 192 1-3 %; the larger ones lost 1 %.
+        // (With outer blocks and scale bytes fetched chunk by chunk the 128 x 128 tile lost 10 %.)
+        constexpr bool PAIR = kPairScales<TM, TN, PS, OUTER>;
+        const uint32_t sc_sel = kg ? 0x0C030C02u : 0x0C010C00u;
         half2_t fA[TM], fB[TN];
+        auto factor = [&](uint32_t sc, int c, int ks) {
+            if (PAIR) return __builtin_bit_cast(half2_t, (__builtin_amdgcn_perm(0u, sc, sc_sel) & (PS ? 0xFFFFFFFFu : live[c])) << 7);
+            return scale_pair((sc >> (16 * kg + 4 * ks)) & (PS ? 0xFFu : live[c]));
+        };
+        auto half_of = [&](half2_t f, int ks) { return !PAIR ? f : ks < 2 ? (half2_t){f.x, f.x} : (half2_t){f.y, f.y}; };
         auto expand = [&](OpFrags<TM, TN> &o, const RawFrags<TM, TN> &r, int c, int ks) {
-            if ((ks & 1) == 0) {
-                const uint32_t mask = PS ? 0xFFu : live[c];
+            if (ks == 0 || (!PAIR && ks == 2)) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i) fA[i] = scale_pair((scA[c][i] >> (16 * kg + 4 * ks)) & mask);
+                for (int i = 0; i < TM; ++i) fA[i] = factor(scA[c][i], c, ks);
 #pragma unroll
-                for (int j = 0; j < TN; ++j) fB[j] = scale_pair((scB[c][j] >> (16 * kg + 4 * ks)) & mask);
+                for (int j = 0; j < TN; ++j) fB[j] = factor(scB[c][j], c, ks);
             }
 #pragma unroll
-            for (int i = 0; i < TM; ++i) o.a[i] = expand8(pick(r.qa[i], ks), fA[i]);
+            for (int i = 0; i < TM; ++i) o.a[i] = expand8(pick(r.qa[i], ks), half_of(fA[i], ks));
 #pragma unroll
-            for (int j = 0; j < TN; ++j) o.b[j] = expand8(pick(r.qb[j], ks), fB[j]);
+            for (int j = 0; j < TN; ++j) o.b[j] = expand8(pick(r.qb[j], ks), half_of(fB[j], ks));
         };
 
         RawFrags<TM, TN> raw[2];
