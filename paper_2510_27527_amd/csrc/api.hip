@@ -530,7 +530,7 @@ int nvfp4_outctl_fwd(const void *X_lo, const void *W_lo, const void *X_hp, const
                                             : reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + fwd_ws);
     rc = nvfp4_linear_fwd(X_lo, W_lo, N, D_lo, C, y32, NVFP4_OUT_F32, Xq_ctx, Wq_ctx, outer_mode, ws, fwd_ws, stream);
     if (rc) return rc;
-    return launch_hp_gemm_nt(X_hp, W_hp, N, C, D_hp, y32, Y, out_dtype == NVFP4_OUT_F32, static_cast<hipStream_t>(stream)) ==
+    return launch_hp_gemm_nt(X_hp, W_hp, N, C, D_hp, y32, Y, out_dtype == NVFP4_OUT_F32, nullptr, 0, static_cast<hipStream_t>(stream)) ==
                    hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
@@ -595,7 +595,8 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     if (D_hp > 0 && C > 0) {
         if (launch_transpose_bf16(dY, dYT, N, C, st) != hipSuccess) return NVFP4_ERR_HIP;
         if (launch_transpose_bf16(X_hp, XhT, N, D_hp, st) != hipSuccess) return NVFP4_ERR_HIP;
-        if (launch_hp_gemm_nt(dYT, XhT, C, D_hp, N, nullptr, dW_hp, out_dtype == NVFP4_OUT_F32, st) != hipSuccess)
+        // the quantized products are done with their scratch: it is free for the partial sums of this one
+        if (launch_hp_gemm_nt(dYT, XhT, C, D_hp, N, nullptr, dW_hp, out_dtype == NVFP4_OUT_F32, gws, gbytes, st) != hipSuccess)
             return NVFP4_ERR_HIP;
     }
     return NVFP4_OK;

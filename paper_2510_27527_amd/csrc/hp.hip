@@ -29,6 +29,7 @@ struct HpArgs {
     int64_t M, N, K;
     int out_f32;
     int tiles_n;
+    int stages;                // 32-k stages per K split (blockIdx.z); more than one split: out is f32 partials [split][M x N]
 };
 
 // global -> LDS copy that bypasses registers (16 bytes per lane, the wave's data lands at lds_addr + lane * 16); inline
@@ -52,7 +53,8 @@ __global__ __launch_bounds__(kThreads, (TM * TN >= 16 ? 1 : 2)) void hp_gemm_nt_
     const int wm = wave >> 1, wn = wave & 1, lr = lane & 31, kg = lane >> 5;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)hp_smem;
     const int64_t m0 = (int64_t)(blockIdx.x / g.tiles_n) * BM, n0 = (int64_t)(blockIdx.x % g.tiles_n) * BN;
-    const int nk = (int)(g.K / 32);
+    const int64_t stage0 = (int64_t)blockIdx.z * g.stages;
+    const int nk = (int)(g.K / 32 - stage0 < g.stages ? g.K / 32 - stage0 : g.stages);
 
     float16_t acc[TM][TN];
 #pragma unroll
@@ -76,8 +78,8 @@ __global__ __launch_bounds__(kThreads, (TM * TN >= 16 ? 1 : 2)) void hp_gemm_nt_
             const int64_t r = row < last ? row : last;
             off[u] = (uint32_t)(r * g.K * 2) + (uint32_t)piece * 16u;
         }
-        const uint8_t *a_base = reinterpret_cast<const uint8_t *>(g.A + m0 * g.K);
-        const uint8_t *b_base = reinterpret_cast<const uint8_t *>(g.B + n0 * g.K);
+        const uint8_t *a_base = reinterpret_cast<const uint8_t *>(g.A + m0 * g.K + stage0 * 32);
+        const uint8_t *b_base = reinterpret_cast<const uint8_t *>(g.B + n0 * g.K + stage0 * 32);
         // every call issues exactly L copies (the waits below count them); stages past the end repeat the last one
         auto issue = [&](int kt, int buf) {
             const int64_t ko = (int64_t)(kt < nk ? kt : nk - 1) * 64;
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(kThreads, (TM * TN >= 16 ? 1 : 2)) void hp_gemm_nt_
                         float v;
                         asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[i][j][e]));
                         if (ADD) v = ad[e] + v;
-                        if (F32) (reinterpret_cast<float *>(g.out) + base)[lane_off] = v;
+                        if (F32) (reinterpret_cast<float *>(g.out) + (int64_t)blockIdx.z * g.M * g.N + base)[lane_off] = v;
                         else (reinterpret_cast<uint16_t *>(g.out) + base)[lane_off] = (uint16_t)f32_to_bf16_bits(v);
                     }
                 }
@@ -185,6 +187,21 @@ __global__ __launch_bounds__(kThreads, (TM * TN >= 16 ? 1 : 2)) void hp_gemm_nt_
         if (g.out_f32) emit2(std::false_type{}, std::true_type{});
         else emit2(std::false_type{}, std::false_type{});
     }
+}
+
+// sum of the K splits' partials in split order, converted; mn = M * N is a multiple of 4
+__global__ __launch_bounds__(kThreads) void hp_reduce_kernel(const float *__restrict__ part, int split, int64_t mn, void *out, int out_f32)
+{
+    const int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+    if (i >= mn) return;
+    float4_t s = __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(part + i));
+    for (int z = 1; z < split; ++z) {
+        const float4_t t = __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(part + z * mn + i));
+        s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    }
+    if (out_f32) *reinterpret_cast<float4_t *>(reinterpret_cast<float *>(out) + i) = s;
+    else *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(out) + i) =
+             make_uint2(f32_to_bf16_bits(s.x) | (f32_to_bf16_bits(s.y) << 16), f32_to_bf16_bits(s.z) | (f32_to_bf16_bits(s.w) << 16));
 }
 
 // 64 x 64 tile through LDS (one padding element per row); R and C arbitrary
@@ -237,7 +254,7 @@ __global__ __launch_bounds__(kThreads) void transpose_bf16_pairs_kernel(const ui
 }  // namespace
 
 template <int TM, int TN>
-static hipError_t launch_hp_t(HpArgs g, hipStream_t st)
+static hipError_t launch_hp_t(HpArgs g, int split, hipStream_t st)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
     constexpr int lds = 3 * (BM + BN) * 64;
@@ -247,12 +264,12 @@ static hipError_t launch_hp_t(HpArgs g, hipStream_t st)
     if (attr != hipSuccess) return attr;
     g.tiles_n = (int)((g.N + BN - 1) / BN);
     const int64_t tiles = ((g.M + BM - 1) / BM) * g.tiles_n;
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(kThreads), lds, st, g);
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles, 1, (unsigned)split), dim3(kThreads), lds, st, g);
     return hipGetLastError();
 }
 
 hipError_t launch_hp_gemm_nt(const void *A, const void *B, int64_t M, int64_t N, int64_t K, const float *addend, void *out,
-                             int out_f32, hipStream_t st)
+                             int out_f32, void *scratch, size_t scratch_bytes, hipStream_t st)
 {
     if (M == 0 || N == 0) return hipSuccess;
     // 32-bit byte offsets inside a tile's operand rows and element offsets inside four output rows
@@ -265,9 +282,28 @@ hipError_t launch_hp_gemm_nt(const void *A, const void *B, int64_t M, int64_t N,
     g.M = M; g.N = N; g.K = K;
     g.out_f32 = out_f32;
     g.tiles_n = 0;
+    g.stages = (int)(K / 32);
     // 256 x 256 tiles when they fill the chip, else 128 x 128
     const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-    return big >= 192 ? launch_hp_t<4, 4>(g, st) : launch_hp_t<2, 2>(g, st);
+    if (big >= 192) return launch_hp_t<4, 4>(g, 1, st);
+    // Few tiles and a long reduction (the weight gradient of a few hundred channels): the time is the chain of a tile's
+    // stages, so the reduction is split over FP32 partials, as far as the caller's scratch goes, until every CU has two
+    // workgroups or a split has 16 stages left.  4096 x 384 x 4096: 37 us in one piece, 28 + 5 for the sum with four.
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), mn = M * N;
+    int64_t split = addend || mn % 4 != 0 || !scratch ? 1 : 512 / tiles;
+    if (split > g.stages / 16) split = g.stages / 16;
+    if (split > 16) split = 16;
+    if (split > 1 && split * mn * 4 > (int64_t)scratch_bytes) split = (int64_t)scratch_bytes / (mn * 4);
+    if (split < 2) return launch_hp_t<2, 2>(g, 1, st);
+    g.stages = (int)((g.stages + split - 1) / split);
+    split = (K / 32 + g.stages - 1) / g.stages;             // no empty split
+    g.out = scratch;
+    g.out_f32 = 1;
+    hipError_t e = launch_hp_t<2, 2>(g, (int)split, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(hp_reduce_kernel, dim3((unsigned)((mn / 4 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                       static_cast<const float *>(scratch), (int)split, mn, out, out_f32);
+    return hipGetLastError();
 }
 
 hipError_t launch_transpose_bf16(const void *src, void *dst, int64_t R, int64_t C, hipStream_t st)

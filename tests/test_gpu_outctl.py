@@ -109,3 +109,22 @@ def test_high_precision_product_with_256x256_tiles(N, D_lo, D_hp, C, out_dtype):
     torch.cuda.synchronize()
     for name, g in zip(("dX_lo", "dX_hp", "dW_lo", "dW_hp"), got):
         check(g, *ref[name], name)
+
+
+@pytest.mark.parametrize("N,D_lo,D_hp,C", [(2048, 256, 96, 320), (1088, 512, 32, 192), (4160, 128, 160, 136)])
+@pytest.mark.parametrize("out_dtype", [1, 0])
+def test_weight_gradient_of_few_outlier_channels(N, D_lo, D_hp, C, out_dtype):
+    """few output tiles and a long reduction over tokens: the bf16 weight-gradient product is split over partial sums in the
+    scratch of the quantized products (as far as it goes), ragged tiles, a last split that is shorter than the others"""
+    import paper_2510_27527_amd as tj
+    C = (C + 63) // 64 * 64
+    Xl, Wl, Xh, Wh, dYb = inputs(N, D_lo, D_hp, C, 21 + N)
+    args = [dev_bf16(a) for a in (Xl, Wl, Xh, Wh)]
+    _, Xq, Wq = tj.outctl_fwd(*args, out_dtype)
+    got = tj.outctl_bwd(dev_bf16(dYb), Xq, Wq, args[2], args[3], 4, 1, out_dtype)
+    again = tj.outctl_bwd(dev_bf16(dYb), Xq, Wq, args[2], args[3], 4, 1, out_dtype)
+    ref = oracle.outctl_bwd(dYb, *oracle.linear_fwd(Xl, Wl), Xh, Wh, 4, 1)
+    torch.cuda.synchronize()
+    for name, g, a in zip(("dX_lo", "dX_hp", "dW_lo", "dW_hp"), got, again):
+        check(g, *ref[name], name)
+        assert torch.equal(g, a), name                   # fixed summation order
