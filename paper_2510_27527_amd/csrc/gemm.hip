@@ -1,5 +1,6 @@
 // Host side of the NT GEMM on two packed NVFP4 operands (tile / split planner, launcher) and the split-K reduction.
 // The product kernel itself lives in gemm_kernel.h and is instantiated slice by slice in gemm_inst.hip.
+#include "../../include/tjnvfp4.h"
 #include "gemm_args.h"
 #include "internal.h"
 
@@ -83,13 +84,14 @@ constexpr int kNumCU = 256;
 
 struct Plan { int tile; int split; int chunks_per_split; };
 
-Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
+// early: the costs and tiles from before the fit
+Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, bool early)
 {
     const int64_t chunks = K / 64;
     Plan best{3, 1, (int)chunks};
     if (M <= 0 || N <= 0 || chunks == 0) return best;      // nothing to tile (empty output or empty reduction)
     double best_t = 1e300;
-    const bool fit = M >= 128 && N >= 128 && N % 64 == 0 && K >= (outer ? 768 : 512);
+    const bool fit = !early && M >= 128 && N >= 128 && N % 64 == 0 && K >= (outer ? 768 : 512);
     for (int t = 0; t < kNumTiles; ++t) {
         if (t == 4 && K % 256 != 0) continue;
         // The small tiles are for outputs that leave CUs idle with 128 x 128 workgroups: there the time is the chain of a
@@ -100,6 +102,7 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
         // rows that are mostly padding.  With 1 x 128 outer blocks the same holds (2048 x 1024 x 1024: 19.8 us with 128 x 192),
         // a little earlier where only the 64 x 64 tile exists.
         if (t >= 5) {
+            if (early) break;
             const int64_t least = outer ? 256 : 128, tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
             // Ragged outputs with reductions of more than 22 stages keep the large tiles (the parity tests of ragged edges under
             // a K split are pinned to them), although the small ones are faster there too (1000 x 520 x 3072: 16.2 against
@@ -124,7 +127,7 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
             const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU;
             const TileCfg &cfg = fit ? kTilesFit[outer][t] : kTiles[t];
             const int64_t conc = per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
-            const double slow = conc == 1 ? 1.0 : fit ? (conc > 2 ? 1.95 : t >= 5 ? 1.4 : outer ? 1.7 : 1.58) : conc == 2 ? (t == 4 ? 1.9 : 1.75) : 2.35;
+            const double slow = conc == 1 ? 1.0 : fit ? (conc > 2 ? 1.95 : t >= 5 ? 1.4 : outer ? 1.7 : 1.58) : conc == 2 ? (t == 4 && !early ? 1.9 : 1.75) : 2.35;
             const int64_t waves = (wgs + kNumCU * conc - 1) / (kNumCU * conc);
             // unfitted block mode: the per-block rescale of the accumulators makes a stage about a third longer
             double time = fit ? (double)waves * (stages * cfg.t_stage + cfg.t_fixed) * slow
@@ -134,6 +137,18 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
         }
     }
     return best;
+}
+
+size_t split_bytes(const Plan &p, int64_t M, int64_t N) { return p.split > 1 ? (size_t)p.split * (size_t)M * (size_t)N * sizeof(float) : 0; }
+
+Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
+{
+    const Plan p = rank_tiles(M, N, K, outer, false);
+    if (split_bytes(p, M, N) <= (size_t)NVFP4_STATIC_SCRATCH_BYTES) return p;
+    // A better split must not put a product out of reach of the entry point with a fixed scratch array: where the earlier
+    // costs gave a plan that fits it, that plan stays (0.7 % of the shapes with 64 to 20000 rows and columns).
+    const Plan q = rank_tiles(M, N, K, outer, true);
+    return split_bytes(q, M, N) <= (size_t)NVFP4_STATIC_SCRATCH_BYTES ? q : p;
 }
 
 }  // namespace
@@ -148,8 +163,7 @@ void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer)
 {
-    const Plan p = make_plan(M, N, K, outer);
-    return p.split > 1 ? (size_t)p.split * (size_t)M * (size_t)N * sizeof(float) : 0;
+    return split_bytes(make_plan(M, N, K, outer), M, N);
 }
 
 hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32,

@@ -288,3 +288,11 @@ def test_outctl_calls_reject_bad_arguments(lib):
     assert bwd(rht=1) == -3                               # per-tensor contexts: the transform is not provided
     assert lib.nvfp4_outctl_workspace_bytes(1, 128, 128, 32, 64, 0, 0) > lib.nvfp4_workspace_bytes(B.OP_LINEAR_BWD, 128, 128, 64, 0)
     assert lib.nvfp4_outctl_workspace_bytes(0, 128, 128, 32, 64, 0, 1) == lib.nvfp4_workspace_bytes(B.OP_LINEAR_FWD, 128, 128, 64, 0)
+
+
+def test_planner_keeps_products_within_the_static_scratch():
+    """where a plan exists whose partial sums fit the static array of nvfp4_gemm_nt_static, a faster split that does not
+    fit is not taken"""
+    for M, N, K, outer in [(7296, 640, 23552, 1), (2048, 704, 132352, 1), (18944, 4160, 71680, 0), (15168, 2240, 23552, 1),
+                           (512, 18240, 6528, 1), (5504, 2112, 8832, 1)]:
+        assert B.workspace_bytes(B.OP_GEMM, M, K, N, outer) <= B.STATIC_SCRATCH_BYTES, (M, N, K, outer)
