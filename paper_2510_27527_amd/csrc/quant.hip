@@ -4,7 +4,7 @@
 //   quant_row       groups of 16 along the contiguous axis; 8 elements (one 128-bit load) per
 //                   lane, two lanes per group, group maximum exchanged by DPP
 //   quant_colw      groups of 16 down the columns, bf16 or packed NVFP4 source (Q5; Q4 / Q6): a wave owns a
-//                   128 x 128 strip, a lane two columns; the output is the transposed operand
+//                   strip of 128 columns, a lane two columns; the output is the transposed operand
 //   quant_dual      row-wise and column-wise operand of one bf16 tensor from one read (Q3 + Q5)
 #include <type_traits>
 
