@@ -14,7 +14,7 @@ SOURCES = [("api.hip", "api.o", []), ("quant.hip", "quant.o", []), ("osci.hip", 
     ("gemm_inst.hip", "gemm_inst_ps%d_out%d_outer%d.o" % (ps, out, outer),
      ["-DTJ_GEMM_PS=%d" % ps, "-DTJ_GEMM_OUT=%d" % out, "-DTJ_GEMM_OUTER=%d" % outer])
     for outer in (0, 1) for ps in (1, 0) for out in (0, 2, 1)]
-HEADERS = ["device_fmt.h", "internal.h", "gemm_args.h", "gemm_kernel.h", os.path.join("..", "..", "include", "tjnvfp4.h")]
+HEADERS = ["device_fmt.h", "internal.h", "gemm_args.h", "gemm_kernel.h", "osci_search.h", os.path.join("..", "..", "include", "tjnvfp4.h")]
 
 # -ffp-contract=off: the quantizer arithmetic is one IEEE rounding per written operation.
 # packed-fp32-ops is switched off: hipcc then never forms v_pk_{add,mul,fma}_f32 on its own.

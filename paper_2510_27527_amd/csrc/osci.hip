@@ -6,6 +6,7 @@
 // loads per array), two lanes a group of 16, sixteen lanes an outer block; maxima travel by DPP.
 #include "device_fmt.h"
 #include "internal.h"
+#include "osci_search.h"
 
 namespace tj {
 
@@ -156,7 +157,8 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
 
 // ---- Appendix Alg. 3: selection of the k largest sensitivity scores (equal scores in ascending index order) ----------
 //
-// Scores are non-negative binary32 values, so they order like their bit patterns.  The k-th largest pattern is found by
+// Scores are non-negative binary32 values, so they order like their bit patterns (a NaN counts as one value above
+// infinity).  The k-th largest pattern is found by
 // narrowing an interval [lo, lo + span) that holds it: a histogram pass over the tensor counts the patterns of the
 // interval in 2048 bins, and the workgroup that finishes last picks the bin.  The first pass splits the patterns where
 // scores live (|x - Q(x)| / binwidth is at most 1, and all but a few lie above 2^-8) into 256 bins per octave, with one
@@ -175,14 +177,11 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
 // shared counters run as at most kPassWgs workgroups of 1024 threads: 256 of them cost 2 us, 1024 of 256 threads 8 us.
 constexpr int kTile = kThreads * 8;
 constexpr int kPassThreads = 1024, kPassWgs = 256, kPassWaves = kPassThreads / 64;
-constexpr int kBins = 2048;
-constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kBins - 2);   // pattern >> 15 of bin 0; 1.0 falls into bin 2046
 
 struct SelState {
-    uint32_t lo, span;    // the interval [lo, lo + span) of patterns that holds the threshold
-    uint32_t width;       // bits still open: span <= 2^width
+    SelInterval iv;       // the keys that hold the threshold
     uint32_t kneed;       // how many elements are still to be taken among those of the interval
-    uint32_t thr;         // width 0: the k-th largest score (bit pattern)
+    uint32_t thr;         // width 0: the key of the k-th largest score
     uint32_t ties;        // elements equal to thr that belong to the selection (the first ones in index order)
     uint32_t done[5];     // workgroups that have finished, per pass
 };
@@ -238,9 +237,8 @@ __global__ __launch_bounds__(kPassThreads) void osci_hist_kernel(const float *W,
     __shared__ float inv_tab[128];
     __shared__ uint32_t bins[kBins];
     __shared__ uint32_t red[kPassWaves], flag;
-    const uint32_t lo = PASS == 0 ? 0u : st->lo, span = PASS == 0 ? 0u : st->span, width = PASS == 0 ? 31u : st->width;
-    if (PASS > 0 && width == 0) return;                    // uniform: the threshold is known
-    const uint32_t shift = width > 11 ? width - 11 : 0;
+    const SelInterval iv = PASS == 0 ? SelInterval{0, 0, 0} : st->iv;
+    if (PASS > 0 && iv.width == 0) return;                 // uniform: the threshold is known
     fill_inv_table(inv_tab);
     for (int b = threadIdx.x; b < kBins; b += kPassThreads) bins[b] = 0;
     __syncthreads();
@@ -255,13 +253,9 @@ __global__ __launch_bounds__(kPassThreads) void osci_hist_kernel(const float *W,
         quant_dequant8_t<true>(w, inv_tab, &sc);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const uint32_t b = f2u(sc.v[i]);
-            if (PASS == 0) {
-                const int d = (int)(b >> 15) - (int)kFirstBin;
-                atomicAdd(&bins[d < 0 ? 0 : d > kBins - 1 ? kBins - 1 : d], 1u);
-            } else if (b - lo < span) {                    // unsigned: patterns below lo wrap around
-                atomicAdd(&bins[(b - lo) >> shift], 1u);
-            }
+            const uint32_t key = score_key(f2u(sc.v[i]));
+            if (PASS == 0) atomicAdd(&bins[first_bin(key)], 1u);
+            else if (in_interval(iv, key)) atomicAdd(&bins[later_bin(iv, key)], 1u);
         }
     }
     __syncthreads();
@@ -280,23 +274,10 @@ __global__ __launch_bounds__(kPassThreads) void osci_hist_kernel(const float *W,
         const bool first = kneed <= above + n0;
         const uint32_t digit = (uint32_t)(first ? b0 : b0 - 1);
         if (!first) above += n0;
-        uint32_t nlo, nspan, nwidth;
-        if (PASS == 0) {
-            const bool bottom = digit == 0, top = digit == kBins - 1;       // the open bins
-            nlo = bottom ? 0u : (kFirstBin + digit) << 15;
-            nspan = bottom ? (kFirstBin + 1) << 15 : top ? 1u << 30 : 1u << 15;
-            nwidth = bottom || top ? 30u : 15u;
-        } else {
-            const uint32_t left = span - (digit << shift);
-            nlo = lo + (digit << shift);
-            nspan = left < (1u << shift) ? left : 1u << shift;
-            nwidth = shift;
-        }
-        st->lo = nlo;
-        st->span = nspan;
-        st->width = nwidth;
+        const SelInterval next = PASS == 0 ? first_interval(digit) : next_interval(iv, digit);
+        st->iv = next;
+        st->thr = next.lo;
         st->kneed = kneed - above;
-        st->thr = nlo;
         st->ties = kneed - above;
     }
 }
@@ -307,9 +288,9 @@ __device__ __forceinline__ void score_flags(const F8 &sc, uint32_t thr, uint32_t
     gt = eq = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const uint32_t b = f2u(sc.v[i]);
-        gt |= (b > thr ? 1u : 0u) << i;
-        eq |= (b == thr ? 1u : 0u) << i;
+        const uint32_t key = score_key(f2u(sc.v[i]));
+        gt |= (key > thr ? 1u : 0u) << i;
+        eq |= (key == thr ? 1u : 0u) << i;
     }
 }
 
@@ -381,7 +362,7 @@ __global__ __launch_bounds__(kPassThreads) void osci_count_kernel(const float *W
 }
 
 __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int64_t nchunks, const SelState *st, const uint32_t *offs,
-                                                             uint32_t *idx, float *wp, float *qp, float *dm, float *dq)
+                                                             uint32_t *idx, float *wp, float *qp, float *dm, float *dq, uint32_t k)
 {
     __shared__ float inv_tab[128];
     __shared__ uint32_t red[4];
@@ -412,7 +393,7 @@ __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int
     uint32_t pos = gt_tiles + taken_eq_tiles + block_exclusive_scan<4>(__builtin_popcount(sel), red, total);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        if ((sel >> i) & 1u) {
+        if (((sel >> i) & 1u) && pos < k) {                // k are selected: the bound only keeps stores inside the arrays
             idx[pos] = (uint32_t)(c * 8 + i);
             wp[pos] = w.v[i];
             qp[pos] = q.v[i];
@@ -553,7 +534,8 @@ hipError_t launch_osci_select(const float *W, int64_t n, int64_t k, uint32_t *id
     hipLaunchKernelGGL(osci_hist_kernel<2>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
     hipLaunchKernelGGL(osci_hist_kernel<3>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
     hipLaunchKernelGGL(osci_count_kernel, grid, block, 0, st, W, nchunks, state, counts, ntiles);
-    hipLaunchKernelGGL(osci_emit_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, st, W, nchunks, state, counts, idx, wp, qp, dm, dq);
+    hipLaunchKernelGGL(osci_emit_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, st, W, nchunks, state, counts, idx, wp, qp, dm, dq,
+                       (uint32_t)k);
     return hipGetLastError();
 }
 

@@ -1,0 +1,49 @@
+// Search for the k-th largest sensitivity score (osci.hip): how a score becomes a key, and how each histogram pass narrows
+// the interval of keys that holds the threshold.  Plain constexpr functions, so that the kernels and a host program run the
+// same code.
+#pragma once
+#include <stdint.h>
+
+namespace tj {
+
+// Scores are non-negative, so they order like their binary32 patterns.  A NaN (the score of a NaN weight, and of the whole
+// outer block of an infinite one) ranks above infinity: all of its patterns, of either sign, get one key, so that every pass
+// counts exactly the elements that the passes before it counted.
+constexpr uint32_t kNaNKey = 0x7F800001u;
+constexpr uint32_t score_key(uint32_t pattern) { return pattern < kNaNKey ? pattern : kNaNKey; }
+
+constexpr int kBins = 2048;
+// The first pass: 256 bins per octave in [2^-8, 1] (the last of them holds 1 itself), an open bin below and one above.
+constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kBins - 2);   // key >> 15 of bin 0; 1.0 falls into bin 2046
+constexpr int first_bin(uint32_t key)
+{
+    const int d = (int)(key >> 15) - (int)kFirstBin;
+    return d < 0 ? 0 : d > kBins - 1 ? kBins - 1 : d;
+}
+
+struct SelInterval {
+    uint32_t lo, span;    // [lo, lo + span) holds the threshold; every key of the bin it came from lies inside
+    uint32_t width;       // bits still open: span <= 2^width
+};
+constexpr SelInterval first_interval(uint32_t bin)
+{
+    if (bin == 0) return {0u, (kFirstBin + 1) << 15, 30u};
+    const uint32_t lo = (kFirstBin + bin) << 15;
+    if (bin == kBins - 1) return {lo, 1u << 30, 30u};
+    return {lo, 1u << 15, 15u};
+}
+static_assert(first_interval(kBins - 1).lo + (1u << 30) > kNaNKey, "the open top bin ends above the largest key");
+static_assert((((kFirstBin + 1) << 15) >> 30) == 0, "the open bottom bin fits its width");
+
+// a later pass: 2048 bins of 2^shift keys (30 -> 19 -> 8 -> 0 open bits; 15 -> 4 -> 0)
+constexpr uint32_t later_shift(uint32_t width) { return width > 11 ? width - 11 : 0; }
+// unsigned: keys below lo wrap around
+constexpr bool in_interval(const SelInterval &s, uint32_t key) { return key - s.lo < s.span; }
+constexpr uint32_t later_bin(const SelInterval &s, uint32_t key) { return (key - s.lo) >> later_shift(s.width); }
+constexpr SelInterval next_interval(const SelInterval &s, uint32_t bin)
+{
+    const uint32_t shift = later_shift(s.width), left = s.span - (bin << shift);
+    return {s.lo + (bin << shift), left < (1u << shift) ? left : 1u << shift, shift};
+}
+
+}  // namespace tj

@@ -194,3 +194,53 @@ def test_tensors_of_many_tiles(shape, frac):
     tj.osci_suppress(gW, torch.from_numpy(dm).cuda(), torch.from_numpy(dq).cuda(), 4.0, n)
     assert int(n.item()) == want > 0
     assert np.array_equal(bits(gW.cpu().numpy()), bits(oW))
+
+
+@pytest.mark.parametrize("kind", ["nan", "inf", "all nan", "mixed"])
+def test_selection_with_non_finite_weights(kind):
+    """a NaN weight scores NaN, and so does the whole outer block of an infinite one: they rank first, in index order, and
+    exactly k entries are written, with k below, at and above their number; the other elements keep the oracle's order"""
+    import paper_2510_27527_amd as tj
+    B = tj.binding
+    rng = np.random.default_rng(8)
+    W = (rng.standard_normal((48, 256)) * 0.02).astype(np.float32)
+    flat = W.reshape(-1)
+    if kind == "all nan":
+        flat[:] = np.nan
+    if kind in ("nan", "mixed"):
+        flat[[3, 700, 701, 5000, 9000]] = np.array([0x7FC00000, 0xFFC00000, 0x7FC00123, 0x7FC00000, 0xFFFFFFFF], np.uint32).view(np.float32)
+    if kind in ("inf", "mixed"):
+        flat[[1500, 8000]] = np.inf, -np.inf
+    # scores: blocks of finite weights from the oracle; a block with a NaN has the smallest outer scale 2^-100 and scale bytes
+    # of 448 (its maximum is a NaN), so every other weight in it scores |w| / (448 * 2^-100) (bin width 1); infinity: all NaN
+    blocks = flat.reshape(-1, 128)
+    score = np.zeros(blocks.shape, np.float32)
+    for b, x in enumerate(blocks):
+        if np.isnan(x).any():
+            score[b] = np.where(np.isnan(x), np.float32(np.nan), np.abs(x) / (np.float32(448) * np.float32(2.0 ** -100)))
+        elif np.isinf(x).any():
+            score[b] = np.nan
+        else:
+            score[b] = oracle.osci_scores(x.reshape(1, 128))[1]
+    key = np.full(score.size, np.inf)
+    number = ~np.isnan(score.reshape(-1))
+    key[number] = score.reshape(-1)[number]
+    order = np.argsort(-key, kind="stable")
+    nans = int((~number).sum())
+    assert nans == {"nan": 5, "inf": 256, "all nan": flat.size, "mixed": 261}[kind]
+    gW = torch.from_numpy(W).cuda()
+    ws = torch.zeros(int(B.lib().nvfp4_osci_select_workspace_bytes(*W.shape)), dtype=torch.uint8, device="cuda")
+    for k in sorted({1, 2, min(64, flat.size), max(1, nans - 1), nans, min(nans + 1, flat.size), min(nans + 700, flat.size), flat.size}):
+        out = [torch.full((flat.size + 64,), -7, dtype=torch.int32, device="cuda")] + \
+              [torch.full((flat.size + 64,), -7.0, device="cuda") for _ in range(4)]
+        rc = B.lib().nvfp4_osci_select(gW.data_ptr(), W.shape[0], W.shape[1], k, *[t.data_ptr() for t in out], ws.data_ptr(),
+                                       ws.numel(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0
+        idx = np.sort(order[:k])
+        assert np.array_equal(u32(out[0])[:k], idx.astype(np.uint32)), k
+        snap = out[1].cpu().numpy()[:k]
+        assert np.array_equal(np.isnan(snap), np.isnan(flat[idx]))
+        ok = ~np.isnan(snap)
+        assert np.array_equal(bits(snap[ok]), bits(flat[idx][ok]))
+        assert all((t[k:] == -7).all() for t in out), k                    # nothing behind the k entries
