@@ -297,19 +297,32 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
 }
 
 // Largest dequantized magnitude of an operand with 1 x 128 outer blocks.  The group that holds a block's maximum gets the
-// scale 448 and its largest element the code 6, so the block's maximum is RN(2688 * S_g); only a block whose S_g is the
-// floor 2^-100 or exactly 1 (which an all-zero block also has) is looked into.  A tensor has one outer scale per 128
-// elements, so this reads 1/64 of the bytes the quantizer wrote; leaving the maximum to the quantizer's own workgroups
-// (one atomic each, executed one after the other on a single address) cost 20 us on 9000 x 3072 (and 12 us of 54 on 8192 x 8192); this kernel costs 2.
+// scale 448 and its largest element the code 6, so the block's maximum is RN(2688 * S_g).  S_g = 1 is also the scale of an
+// all-zero block: there the block's eight scale bytes (all 0 in an all-zero block) tell the two apart.  Only a block whose
+// S_g is the floor 2^-100 has its codes looked at.  So the kernel reads one outer scale per 128 elements, and for all-zero
+// blocks (padding tokens) eight bytes more; leaving the maximum to the quantizer's own workgroups (one atomic each, executed
+// one after the other on a single address) cost 20 us on 9000 x 3072.  Bound by the latency of its loads: four blocks per
+// thread and step have theirs in flight together, on up to 256 workgroups.  On 8192 x 8192 the kernel takes 6 us, 4 us when
+// every block is zero and 13 us when every block is at the floor.  The call (quantizer and this kernel) on sources that
+// are not cached: 38.8 us, 35.4 us all zero; with one block per thread and step on 64 workgroups, which also decoded the
+// zero blocks: 44.6 and 110; with the atomics: 54 and 34.
 struct DeqJob {
     const float *gscale;
-    const uint8_t *scales;
-    const uint32_t *codes;
+    const uint2 *scales;   // eight bytes per block
+    const uint4 *codes;    // four per block
     float *amax_deq;       // cleared by the quantizer
     int64_t nblocks;
     unsigned nwg;
 };
-constexpr int kDeqWgs = 64;
+constexpr int kDeqWgs = 256, kDeqUnroll = 4;
+
+// largest magnitude code of eight
+__device__ __forceinline__ ushort2_t max_code8(ushort2_t m, uint32_t q)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = __builtin_elementwise_max(m, as_us2((q >> (4 * e)) & 0x00070007u));
+    return m;
+}
 
 __global__ __launch_bounds__(kThreads) void deq_max_kernel(DeqJob j0, DeqJob j1)
 {
@@ -318,17 +331,35 @@ __global__ __launch_bounds__(kThreads) void deq_max_kernel(DeqJob j0, DeqJob j1)
     const DeqJob j = second ? j1 : j0;
     const int64_t stride = (int64_t)j.nwg * kThreads;
     float m = 0.0f;
-    for (int64_t b = (int64_t)(second ? blockIdx.x - j0.nwg : blockIdx.x) * kThreads + threadIdx.x; b < j.nblocks; b += stride) {
-        const float sg = j.gscale[b];
-        if (sg != 0x1p-100f && sg != 1.0f) {
-            m = fmaxf(m, 2688.0f * sg);
-            continue;
+    for (int64_t b0 = (int64_t)(second ? blockIdx.x - j0.nwg : blockIdx.x) * kThreads + threadIdx.x; b0 < j.nblocks; b0 += kDeqUnroll * stride) {
+        float sg[kDeqUnroll];
+        uint2 sc[kDeqUnroll];
+        int64_t b[kDeqUnroll];
+#pragma unroll
+        for (int u = 0; u < kDeqUnroll; ++u) {
+            b[u] = b0 + u * stride < j.nblocks ? b0 + u * stride : b0;         // past the end: the first block again
+            sg[u] = j.gscale[b[u]];
         }
-        for (int grp = 0; grp < 8; ++grp) {
-            const float sb = e4m3_value(j.scales[b * 8 + grp]);
-            for (int w = 0; w < 2; ++w) {
-                const uint32_t q = j.codes[(b * 8 + grp) * 2 + w];
-                for (int e = 0; e < 8; ++e) m = fmaxf(m, (e2m1_value((q >> (4 * e)) & 7u) * sb) * sg);
+#pragma unroll
+        for (int u = 0; u < kDeqUnroll; ++u) {
+            sc[u] = make_uint2(0, 0);
+            if (sg[u] == 1.0f || sg[u] == 0x1p-100f) sc[u] = j.scales[b[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kDeqUnroll; ++u) {
+            if (sg[u] == 1.0f) {
+                if (sc[u].x | sc[u].y) m = fmaxf(m, 2688.0f);
+            } else if (sg[u] != 0x1p-100f) {
+                m = fmaxf(m, 2688.0f * sg[u]);
+            } else {
+                for (int h = 0; h < 4; ++h) {                                  // two groups per 16 bytes of codes
+                    const uint4 q = j.codes[b[u] * 4 + h];
+                    const uint32_t two = (h < 2 ? sc[u].x : sc[u].y) >> (16 * (h & 1));
+                    const ushort2_t z = {0, 0};
+                    const ushort2_t a = max_code8(max_code8(z, q.x), q.y), d = max_code8(max_code8(z, q.z), q.w);
+                    m = fmaxf(m, (e2m1_value(a.x > a.y ? a.x : a.y) * e4m3_value(two & 0xFFu)) * sg[u]);
+                    m = fmaxf(m, (e2m1_value(d.x > d.y ? d.x : d.y) * e4m3_value((two >> 8) & 0xFFu)) * sg[u]);
+                }
             }
         }
     }
@@ -337,7 +368,7 @@ __global__ __launch_bounds__(kThreads) void deq_max_kernel(DeqJob j0, DeqJob j1)
     __syncthreads();
     if (threadIdx.x == 0) {
         m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        if (m > 0.0f) atomicMax(reinterpret_cast<unsigned int *>(j.amax_deq), f2u(m));
+        if (m > __builtin_nontemporal_load(j.amax_deq)) atomicMax(reinterpret_cast<unsigned int *>(j.amax_deq), f2u(m));
     }
 }
 
@@ -915,7 +946,8 @@ void launch_zero_scalar(float *p, hipStream_t st)
 static void launch_deq_max(const RowJob &j0, const RowJob &j1, hipStream_t st)
 {
     auto job = [](const RowJob &r) {
-        DeqJob d{r.a.gscale, r.a.scales, r.a.codes, r.a.amax_deq, r.nchunks / 16, 0};
+        DeqJob d{r.a.gscale, reinterpret_cast<const uint2 *>(r.a.scales), reinterpret_cast<const uint4 *>(r.a.codes), r.a.amax_deq,
+                 r.nchunks / 16, 0};
         const int64_t want = (d.nblocks + kThreads - 1) / kThreads;
         d.nwg = r.a.amax_deq ? (unsigned)(want < kDeqWgs ? want : kDeqWgs) : 0u;
         return d;

@@ -227,6 +227,33 @@ def test_dequantized_maximum_block128(case):
     assert_same(got, ref, case, check_amax=True)
 
 
+@pytest.mark.parametrize("case", ["padding rows", "zero", "one block of scale one", "floored", "floored but one"])
+def test_dequantized_maximum_block128_of_more_blocks_than_threads(case):
+    """263168 + 8 blocks: more than four per thread of the largest launch, the last step partly past the end; all-zero blocks
+    beside ordinary ones, all of them zero but one block whose scale is 1 as well, blocks at the floor of the outer scale"""
+    shape = (32897, 1024)
+    x = np.zeros(shape, np.float32)
+    if case == "padding rows":
+        x[:20000] = wl.bf16_to_f32(wl.normal_bf16((20000, 1024), 1.0, 491))
+        x[7, 900] = 50.0
+    elif case == "one block of scale one":
+        x[32896, 1000] = -2688.0
+    elif case.startswith("floored"):
+        # the floor holds below 2688 * 2^-100 > 2^-89; above 6 * 2^-110 > 2^-108 a group's scale is not 0
+        x = np.random.default_rng(3).standard_normal(shape).astype(np.float32) * np.float32(2.0 ** -103)
+        x[20000:] = 0
+        x[30000, 300:330] = np.float32(2.0 ** -95)
+        if case == "floored but one":
+            x[32896, 1023] = np.float32(2.0 ** -80)
+    bits = wl.f32_to_bf16(x)
+    ref = oracle.quantize_bf16(bits, 0, 0, outer=oracle.OUTER_BLOCK128)
+    assert (ref.amax_deq > 0) == (case != "zero")
+    got = tj.alloc_nvfp4(shape[0], shape[1], tj.binding.OUTER_BLOCK128)
+    got.amax_deq.fill_(123.0)
+    tj.quantize(dev_bf16(bits), 0, 0, got, outer=tj.binding.OUTER_BLOCK128)
+    assert_same(got, ref, case, check_amax=True)
+
+
 @pytest.mark.parametrize("shape", [(128, 8), (256, 512), (384, 136), (1152, 1040), (2048, 72)])
 @pytest.mark.parametrize("rounding", [0, 1])
 def test_quant_col_block128_mode(shape, rounding):
