@@ -547,9 +547,18 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
 // 2.3 TB/s, 64-byte runs 4.2, 256-byte runs 4.6; 8-byte scale pieces cost as much as all the codes).
 //
 // SLABS: a wave's slabs are a serial chain of load, decode, quantize, so short strips (more waves) hide it better and long
-// ones write longer runs.  Two slabs (64-byte runs) measured best everywhere for a packed source - 8192 x 8192 29.6 us,
-// with four 31.4, with eight 32.3; 16384 x 1024 10.6 / 11.9 / 14.6 - and for a bf16 source up to about 32 M elements; above,
-// four (8192 x 8192: 33.5 us with four, 41.7 with two, 36.8 with eight; 8192 x 4096: 19.4 / 19.9 / 19.6).
+// ones write longer runs (64, 128 or 256 bytes of codes per output row), which counts once source and output no longer fit the
+// last-level cache.  Two slabs for small tensors; above 40 M elements (both tensors of a pair together) eight for a packed
+// source; for a bf16 source four above 28 M, and eight above 40 M where it has more rows than columns.  Measured with two / four /
+// eight slabs, in us, sources and outputs rotating through more than the last-level cache:
+//   packed  16384 x 1024 12.6 / 13.2 / 16.0   8192 x 3072 17.4 / 16.7 / 21.3   6144 x 6144 25.8 / 25.7 / 28.0
+//           8192 x 6144 30.1 / 28.8 / 28.0    8192 x 8192 41.8 / 38.3 / 37.8   16384 x 8192 77.4 / 69.4 / 64.8
+//           16384 x 16384 163 / 136 / 120     (one cached tensor: 8192 x 8192 29.2 / 31.1 / 32.0)
+//   pair with the maximum of dY in the launch (X, W): 16384 x 2048 and 2048 x 2048 33.0 / 34.4 / 37.4, 8192 x 4096 and
+//           4096 x 4096 37.9 / 38.9 / 38.0, 8192 x 8192 twice 104 / 93 / 92
+//   bf16    16384 x 1024 12.2 / 12.3 / 14.3   8192 x 3072 16.0 / 16.5 / 19.2   8192 x 4096 20.8 / 20.4 / 20.3
+//           8192 x 8192 50.8 / 39.0 / 40.1    8192 x 16384 91.8 / 76.4 / 84.2  16384 x 8192 96.3 / 82.1 / 79.8
+//           65536 x 1024 42.2 / 39.7 / 36.5
 //
 // With 1 x 128 outer blocks (OUTER = 1, two slabs per wave) the workgroup's 128 rows are exactly one outer block of each
 // of its output rows: the waves decode their slabs into registers, exchange the column maxima through LDS and quantize
@@ -736,7 +745,7 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     constexpr int kRun = kWaves * 8 * SLABS, kPitch = kRun + 8, kScPitch = kWaves * SLABS;
     __shared__ __attribute__((aligned(16))) uint8_t stage[kStripC * kPitch];
     __shared__ __attribute__((aligned(16))) uint8_t sc_stage[kStripC * kScPitch];
-    uint32_t scb[2] = {0, 0};                                       // the slabs' scale bytes, per column
+    uint32_t scb[2][(SLABS + 3) / 4] = {};                          // the slabs' scale bytes, per column
     const bool wide = (int)wave < nwide;
     if (OUTER == 0 && have) fetch(std::true_type{}, 0, raw[0]);
 #pragma unroll
@@ -763,7 +772,7 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
             uint2 q;
             q.x = quant8<ROUND, SUP>(xa, r, quad0, a.k.k0, a.k.k1);
             q.y = quant8<ROUND, SUP>(xb, r, quad0 + 2, a.k.k0, a.k.k1);
-            scb[j] |= sc << (8 * s);
+            scb[j][s / 4] |= sc << (8 * (s % 4));
             if (wide) {
                 *reinterpret_cast<uint2 *>(stage + (2 * lane + j) * kPitch + wave * (8 * SLABS) + 8 * s) = q;
             } else if (colok) {
@@ -777,8 +786,9 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             uint8_t *p = sc_stage + (2 * lane + j) * kScPitch + wave * SLABS;
-            if constexpr (SLABS == 4) *reinterpret_cast<uint32_t *>(p) = scb[j];
-            else *reinterpret_cast<uint16_t *>(p) = (uint16_t)scb[j];
+            if constexpr (SLABS == 2) *reinterpret_cast<uint16_t *>(p) = (uint16_t)scb[j][0];
+            else
+                for (int h = 0; h < SLABS / 4; ++h) reinterpret_cast<uint32_t *>(p)[h] = scb[j][h];
         }
     }
     __syncthreads();
@@ -887,12 +897,23 @@ void launch_colw_s(const ColArgs &a0, const ColArgs &a1, bool pair, int rounding
     }
 }
 
+// slabs per strip of a launch (the figures are at the kernel); a1: the second tensor of a pair, or one without elements
+inline int colw_slabs(const ColArgs &a0, const ColArgs &a1, bool packed)
+{
+    const int64_t n = a0.R * a0.C + a1.R * a1.C, kLong = (int64_t)5 << 23;
+    if (n > kLong && (packed || a0.R > a0.C)) return 8;
+    return !packed && n > ((int64_t)7 << 22) ? 4 : 2;
+}
+
 template <bool PACKED, int OUTER, bool RHT>
 void launch_colw_t(const ColArgs &a0, const ColArgs &a1, bool pair, int rounding, int scale_up, hipStream_t st)
 {
-    // bf16 sources above 32 M elements: four slabs per strip (the figures are at the kernel)
-    if constexpr (OUTER == 0 && !PACKED) {
-        if (a0.R * a0.C > ((int64_t)1 << 25)) return launch_colw_s<PACKED, OUTER, RHT, 4>(a0, a1, pair, rounding, scale_up, st);
+    if constexpr (OUTER == 0) {
+        const int slabs = colw_slabs(a0, a1, PACKED);
+        if (slabs == 8) return launch_colw_s<PACKED, OUTER, RHT, 8>(a0, a1, pair, rounding, scale_up, st);
+        if constexpr (!PACKED) {
+            if (slabs == 4) return launch_colw_s<PACKED, OUTER, RHT, 4>(a0, a1, pair, rounding, scale_up, st);
+        }
     }
     launch_colw_s<PACKED, OUTER, RHT, 2>(a0, a1, pair, rounding, scale_up, st);
 }
@@ -1076,9 +1097,14 @@ hipError_t launch_requant_col_pair_amax(const PackedSrc &src0, int64_t R0, int64
     }
     const ColArgs a0 = packed_args(src0, R0, C0, p0, o0), a1 = packed_args(src1, R1, C1, p1, o1);
     const AmaxJob am{reinterpret_cast<const uint4 *>(bf16), n / 8, partials, nullptr, (unsigned)amax_grid(n / 8)};
-    const unsigned g0 = colw_grid(a0, 2), g1 = colw_grid(a1, 2);
-    hipLaunchKernelGGL((quant_colw_kernel<1, true, true, 0, false, 2, true>), dim3(am.nblocks + g0 + g1), dim3(kThreads), 0, st, a0, a1,
-                       g0, am);
+    auto launch = [&](auto slabs) {
+        constexpr int SLABS = decltype(slabs)::value;
+        const unsigned g0 = colw_grid(a0, SLABS), g1 = colw_grid(a1, SLABS);
+        hipLaunchKernelGGL((quant_colw_kernel<1, true, true, 0, false, SLABS, true>), dim3(am.nblocks + g0 + g1), dim3(kThreads), 0, st, a0,
+                           a1, g0, am);
+    };
+    if (colw_slabs(a0, a1, true) == 8) launch(std::integral_constant<int, 8>{});
+    else launch(std::integral_constant<int, 2>{});
     *npart = (int)am.nblocks;
     return hipGetLastError();
 }

@@ -202,6 +202,32 @@ def test_requant_col_strip_edges(shape, rounding):
     assert_same(got, oracle.requantize(oracle.quantize_bf16(bits, 0, 0), 1, rounding, seed=17, tensor_id=6), "requant %s" % (shape,))
 
 
+@pytest.mark.parametrize("shape", [(6592, 6384), (6608, 6384)])
+def test_column_quantizers_long_strips(shape):
+    """above 40 M elements strips of 128 rows, for a packed source and for a bf16 source with more rows than columns: the last
+    strip half as long, and a row count off the 64-row alignment of the staged stores; the last 128 columns are ragged"""
+    bits = wl.normal_bf16(shape, 1.0, 475 + shape[0], 1e-2, 30.0)
+    got = tj.quantize(dev_bf16(bits), 1, 1, seed=8, tensor_id=5)
+    assert_same(got, oracle.quantize_bf16(bits, 1, 1, seed=8, tensor_id=5), "col %s" % (shape,))
+    src = tj.quantize(dev_bf16(bits), 0, 0)
+    got = tj.quantize(src, 1, 1, seed=17, tensor_id=6)
+    assert_same(got, oracle.requantize(oracle.quantize_bf16(bits, 0, 0), 1, 1, seed=17, tensor_id=6), "requant %s" % (shape,))
+
+
+def test_backward_pair_with_long_strips_equals_the_separate_calls():
+    """the re-quantizations of one backward call share a launch, and together exceed the 40 M elements from which strips are
+    128 rows long; one at a time they stay below it"""
+    N, D, C = 4160, 5120, 4096
+    X, W, dY = (dev_bf16(b) for b in wl.linear_inputs(N, D, C, seed=5))
+    _, Xq, Wq = tj.linear_fwd(X, W)
+    dX, dW = tj.linear_bwd(dY, Xq, Wq, seed=3, layer_id=2)
+    assert torch.equal(dX, tj.linear_bwd_dx(dY, Wq, seed=3, layer_id=2)) and torch.equal(dW, tj.linear_bwd_dw(dY, Xq, seed=3, layer_id=2))
+    none = torch.empty((N, 0), dtype=torch.bfloat16, device="cuda"), torch.empty((C, 0), dtype=torch.bfloat16, device="cuda")
+    split = tj.outctl_bwd(dY, Xq, Wq, *none, 3, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(split[0], dX) and torch.equal(split[2], dW)
+
+
 @pytest.mark.parametrize("case", ["ordinary", "many blocks", "zero", "floored", "scale one"])
 def test_dequantized_maximum_block128(case):
     """the maximum of an operand with 1 x 128 outer blocks is taken from its outer scales, except for blocks whose scale is
