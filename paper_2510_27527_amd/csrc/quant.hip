@@ -302,10 +302,11 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
 // S_g is the floor 2^-100 has its codes looked at.  So the kernel reads one outer scale per 128 elements, and for all-zero
 // blocks (padding tokens) eight bytes more; leaving the maximum to the quantizer's own workgroups (one atomic each, executed
 // one after the other on a single address) cost 20 us on 9000 x 3072.  Bound by the latency of its loads: four blocks per
-// thread and step have theirs in flight together, on up to 256 workgroups.  On 8192 x 8192 the kernel takes 6 us, 4 us when
-// every block is zero and 13 us when every block is at the floor.  The call (quantizer and this kernel) on sources that
-// are not cached: 38.8 us, 35.4 us all zero; with one block per thread and step on 64 workgroups, which also decoded the
-// zero blocks: 44.6 and 110; with the atomics: 54 and 34.
+// thread and step have theirs in flight together, at least two steps per thread (one atomic per workgroup), up to 256
+// workgroups.  On 8192 x 8192 the kernel takes 5.7 us, 4.6 us when every block is zero and 12.4 us when every block is at the
+// floor; on 9000 x 3072 4 us.  The call (quantizer and this kernel) on 8192 x 8192 sources that are not cached: 37.9 us, all
+// zero 35.6; with one block per thread and step on 64 workgroups, which also decoded the zero blocks: 44.6 and 110; with
+// the atomics: 54 and 34.
 struct DeqJob {
     const float *gscale;
     const uint2 *scales;   // eight bytes per block
@@ -368,7 +369,7 @@ __global__ __launch_bounds__(kThreads) void deq_max_kernel(DeqJob j0, DeqJob j1)
     __syncthreads();
     if (threadIdx.x == 0) {
         m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        if (m > __builtin_nontemporal_load(j.amax_deq)) atomicMax(reinterpret_cast<unsigned int *>(j.amax_deq), f2u(m));
+        if (m > 0.0f) atomicMax(reinterpret_cast<unsigned int *>(j.amax_deq), f2u(m));
     }
 }
 
@@ -969,7 +970,7 @@ static void launch_deq_max(const RowJob &j0, const RowJob &j1, hipStream_t st)
     auto job = [](const RowJob &r) {
         DeqJob d{r.a.gscale, reinterpret_cast<const uint2 *>(r.a.scales), reinterpret_cast<const uint4 *>(r.a.codes), r.a.amax_deq,
                  r.nchunks / 16, 0};
-        const int64_t want = (d.nblocks + kThreads - 1) / kThreads;
+        const int64_t per_wg = kThreads * 2 * kDeqUnroll, want = (d.nblocks + per_wg - 1) / per_wg;
         d.nwg = r.a.amax_deq ? (unsigned)(want < kDeqWgs ? want : kDeqWgs) : 0u;
         return d;
     };
