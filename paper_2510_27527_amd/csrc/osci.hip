@@ -13,7 +13,7 @@ namespace tj {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxCountingWgs = 1024;     // workgroups of a kernel that ends with an addition to one counter
+constexpr int kMaxCountingWgs = 256;      // workgroups of a reset that counts: each ends with an addition to one counter
 
 struct F8 { float v[8]; };
 
@@ -117,8 +117,12 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
     __syncthreads();
     unsigned int mine = 0;
     // Two chunks per thread and iteration, all their loads in flight together.  The counter is one address for the whole
-    // chip, and additions to it are executed one after the other at about 10 ns each: with a workgroup per 256 chunks
-    // (4096 additions on 8192 x 1024) the kernel took 50 us for 134 MB; at most 1024 workgroups, one addition each: 24 us.
+    // chip, and additions to it are executed one after the other at about 10 ns each: with a workgroup per 256 chunks they
+    // outlast the reading.  One workgroup per CU, one addition each, reads as fast as the other sizes of launch or faster.
+    // Sources rotating through more than the last-level cache, at most 256 / 512 / 1024 / 4096 / any number of workgroups (us):
+    // 3072 x 768 12.4 / 14.8 / 19.7 / 21.0 / 21.1, 8192 x 1024 30.9 / 31.8 / 33.6 / 58.0 / 58.0, 8192 x 4096 108 / 110 / 113 / 110 / 214,
+    // 8192 x 8192 213 / 225 / 231 / 224 / 422, 16384 x 8192 421 / 459 / 481 / 462 / 835.  Without a counter a workgroup per 256
+    // chunks is fastest: 8192 x 1024 27.4 us (256 workgroups 30.2), 8192 x 8192 207 (213).
     const int64_t stride = (int64_t)gridDim.x * kThreads;      // a multiple of 16: rows of 16 lanes stay whole
     for (int64_t c0 = (int64_t)blockIdx.x * kThreads + threadIdx.x; c0 < nchunks; c0 += 2 * stride) {
         F8 w[2], dm[2], dq[2];
@@ -566,7 +570,7 @@ hipError_t launch_osci_suppress(float *W, const float *dist_m, const float *dist
     const int64_t nchunks = n / 8;
     if (nchunks == 0) return hipSuccess;
     const int64_t want = (nchunks + kThreads - 1) / kThreads;
-    const unsigned grid = (unsigned)(want < kMaxCountingWgs ? want : kMaxCountingWgs);
+    const unsigned grid = (unsigned)(!n_reset || want < kMaxCountingWgs ? want : kMaxCountingWgs);
     hipLaunchKernelGGL(osci_suppress_kernel, dim3(grid), dim3(kThreads), 0, st, W, dist_m, dist_q, tau, nchunks, n_reset);
     return hipGetLastError();
 }
