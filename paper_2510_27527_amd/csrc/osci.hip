@@ -4,6 +4,8 @@
 // D, round-to-nearest, nearest-even E4M3 scales, 1 x 128 FP32 outer blocks - followed by the binary32 dequantization
 // (P * S_block) * S_global.  Both kernels are elementwise streams: a lane owns 8 consecutive weights (two 128-bit
 // loads per array), two lanes a group of 16, sixteen lanes an outer block; maxima travel by DPP.
+#include <type_traits>
+
 #include "device_fmt.h"
 #include "internal.h"
 #include "osci_search.h"
@@ -432,7 +434,7 @@ __device__ __forceinline__ int64_t wave_lower_bound(const uint32_t *idx, int64_t
 // of 2048 consecutive weights: Q of the tiles goes to LDS, then their entries of the (ascending) index list are updated
 // from it.  The call is bound by its chain of dependent loads (search, entries, weights), so the weights are fetched
 // before the search (`dense`: lists in which nearly every tile has entries; otherwise tiles without a tracked weight stop
-// after the search and read nothing else), and a long tensor takes four tiles per search: 8192 x 1024 with 5 % tracked
+// after the search and read nothing else), and a long tensor takes several tiles per search: 8192 x 1024 with 5 % tracked
 // took 21 us with one tile and a one-thread search, 14 us like this.
 template <bool SUPPRESS, int T>
 __global__ __launch_bounds__(kThreads) void osci_sparse_kernel(float *W, int64_t nchunks, const uint32_t *idx, int64_t k, float *wp,
@@ -470,21 +472,44 @@ __global__ __launch_bounds__(kThreads) void osci_sparse_kernel(float *W, int64_t
         if (c0 + t * kThreads < nchunks) store8(qt + (t * kThreads + threadIdx.x) * 8, quant_dequant8(w[t], inv_tab));
     __syncthreads();                                       // every weight of the tiles has been read: resets may follow
     unsigned int mine = 0;
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += kThreads) {
-        const int64_t e = idx[j];
-        const float q = qt[e - tile0];
-        if (SUPPRESS) {
-            const float risk = dq[j] / dm[j];              // IEEE quotient; 0 / 0 is NaN and compares false
-            if (risk >= tau) {
-                W[e] = q;
-                ++mine;
+    // Four entries per thread and step, their loads in flight together: a list whose entries lie close together (equal scores
+    // are taken in index order) leaves a workgroup with up to T * 2048 of them, and one per step was a chain of 8 T round trips
+    // (8192 x 1024 zeros, 5 % tracked, four tiles: 35 us, 16.5 like this).
+    constexpr int kU = 4;
+    for (int64_t jb = j0 + threadIdx.x; jb < j1; jb += kU * kThreads) {
+        int64_t j[kU], e[kU];
+        float m[kU], d[kU], p[kU], r[kU], wv[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            j[u] = jb + u * kThreads < j1 ? jb + u * kThreads : jb;            // past the end: the first entry again, not used
+            e[u] = idx[j[u]];
+            m[u] = dm[j[u]];
+            d[u] = dq[j[u]];
+            if (!SUPPRESS) {
+                p[u] = wp[j[u]];
+                r[u] = qp[j[u]];
             }
-        } else {
-            const float wv = W[e];
-            dm[j] = dm[j] + fabsf(wv - wp[j]);
-            dq[j] = dq[j] + fabsf(q - qp[j]);
-            wp[j] = wv;
-            qp[j] = q;
+        }
+        if (!SUPPRESS) {
+#pragma unroll
+            for (int u = 0; u < kU; ++u) wv[u] = W[e[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (jb + u * kThreads >= j1) break;
+            const float q = qt[e[u] - tile0];
+            if (SUPPRESS) {
+                const float risk = d[u] / m[u];            // IEEE quotient; 0 / 0 is NaN and compares false
+                if (risk >= tau) {
+                    W[e[u]] = q;
+                    ++mine;
+                }
+            } else {
+                dm[j[u]] = m[u] + fabsf(wv[u] - p[u]);
+                dq[j[u]] = d[u] + fabsf(q - r[u]);
+                wp[j[u]] = wv[u];
+                qp[j[u]] = q;
+            }
         }
     }
     if (SUPPRESS && n_reset) {
@@ -503,13 +528,19 @@ hipError_t launch_sparse(float *W, int64_t n, const uint32_t *idx, int64_t k, fl
     if (nchunks == 0 || k == 0) return hipSuccess;
     const int64_t ntiles = (nchunks + kThreads - 1) / kThreads;
     const int dense = k >= ntiles;                         // on average at least one entry per tile
-    // four tiles per workgroup once that still leaves two workgroups per CU
-    if (ntiles >= 2048)
-        hipLaunchKernelGGL((osci_sparse_kernel<SUPPRESS, 4>), dim3((unsigned)((ntiles + 3) / 4)), dim3(kThreads), 0, st, W, nchunks, idx, k, wp,
-                           qp, dm, dq, tau, n_reset, dense);
-    else
-        hipLaunchKernelGGL((osci_sparse_kernel<SUPPRESS, 1>), dim3((unsigned)ntiles), dim3(kThreads), 0, st, W, nchunks, idx, k, wp, qp, dm, dq,
-                           tau, n_reset, dense);
+    // Several tiles per workgroup once that still leaves two workgroups per CU: four in the reset, whose workgroups each end
+    // with an addition to one counter (8192 x 1024, resets all over the tensor: 59 us with one tile, 35 with two, 23 with
+    // four).  The step has no counter: two, which keeps a list whose entries lie close together on twice the workgroups
+    // (8192 x 1024 zeros, 5 % tracked: 11.6 / 12.8 / 16.5 us; spread evenly 15.6 / 13.5 / 13.1), and four from 16384 tiles on
+    // (8192 x 8192, 5 %: 126 / 111 / 95; zeros 88 / 73 / 65).
+    auto launch = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        hipLaunchKernelGGL((osci_sparse_kernel<SUPPRESS, T>), dim3((unsigned)((ntiles + T - 1) / T)), dim3(kThreads), 0, st, W, nchunks, idx, k,
+                           wp, qp, dm, dq, tau, n_reset, dense);
+    };
+    if (ntiles < 2048) launch(std::integral_constant<int, 1>{});
+    else if (!SUPPRESS && ntiles < 16384) launch(std::integral_constant<int, SUPPRESS ? 4 : 2>{});
+    else launch(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }
 

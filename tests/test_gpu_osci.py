@@ -244,3 +244,32 @@ def test_selection_with_non_finite_weights(kind):
         ok = ~np.isnan(snap)
         assert np.array_equal(bits(snap[ok]), bits(flat[idx][ok]))
         assert all((t[k:] == -7).all() for t in out), k                    # nothing behind the k entries
+
+
+@pytest.mark.parametrize("shape,kind", [((2048, 2048), "zero"), ((4099, 1024), "constant"), ((8195, 4096), "zero"), ((2048, 2048), "spread")])
+def test_subset_of_entries_that_lie_close_together(shape, kind):
+    """equal scores are tracked in index order, so the entries of a zero or constant matrix fill its first tiles: up to four
+    per thread and step in flight, two tiles per workgroup in a step and four in a reset, four in both from 16384 tiles on
+    (8195 x 4096); the last step of a list partly past its end"""
+    import paper_2510_27527_amd as tj
+    rng = np.random.default_rng(12)
+    W0 = np.zeros(shape, np.float32) if kind == "zero" else np.full(shape, 0.3, np.float32)
+    if kind == "spread":
+        W0 = (rng.standard_normal(shape) * 0.02).astype(np.float32)
+    k = W0.size // 20 + 77
+    o = list(oracle.osci_select(W0, k))
+    g = list(tj.osci_select(torch.from_numpy(W0).cuda(), k))
+    if kind != "spread":
+        assert np.array_equal(o[0], np.arange(k, dtype=np.uint32))
+    W1 = (W0 + rng.standard_normal(shape, dtype=np.float32) * 2e-4).astype(np.float32)
+    oracle.osci_update_sparse(W1, *o)
+    tj.osci_update_sparse(torch.from_numpy(W1).cuda(), *g)
+    assert np.array_equal(u32(g[0]), o[0])
+    for a, b in zip(g[1:], o[1:]):
+        assert np.array_equal(bits(a.cpu().numpy()), bits(b))
+    oW, gW = W1.copy(), torch.from_numpy(W1).cuda()
+    n = torch.zeros(1, dtype=torch.int64, device="cuda")
+    want = oracle.osci_suppress_sparse(oW, o[0], o[3], o[4], 0.9)
+    tj.osci_suppress_sparse(gW, g[0], g[3], g[4], 0.9, n)
+    assert int(n.item()) == want > 0
+    assert np.array_equal(bits(gW.cpu().numpy()), bits(oW))
