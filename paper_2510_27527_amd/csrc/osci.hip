@@ -245,25 +245,32 @@ __global__ __launch_bounds__(kPassThreads) void osci_hist_kernel(const float *W,
     __shared__ uint32_t red[kPassWaves], flag;
     const SelInterval iv = PASS == 0 ? SelInterval{0, 0, 0} : st->iv;
     if (PASS > 0 && iv.width == 0) return;                 // uniform: the threshold is known
+    const uint32_t within = reach(iv);
     fill_inv_table(inv_tab);
     for (int b = threadIdx.x; b < kBins; b += kPassThreads) bins[b] = 0;
     __syncthreads();
-    const int64_t stride = (int64_t)gridDim.x * kPassThreads;      // a multiple of 16: rows of 16 lanes stay whole
-    int64_t c = (int64_t)blockIdx.x * kPassThreads + threadIdx.x;
-    F8 next{};
-    if (c < nchunks) next = load8(W + c * 8);
-    for (; c < nchunks; c += stride) {
-        const F8 w = next;
-        next = load8(W + (c + stride < nchunks ? c + stride : c) * 8);   // in flight while this chunk is counted
-        F8 sc;
-        quant_dequant8_t<true>(w, inv_tab, &sc);
+    // TOP: the interval holds the NaNs, whose patterns have to be turned into their key (one more instruction per element)
+    auto count = [&](auto top) {
+        constexpr bool TOP = decltype(top)::value;
+        const int64_t stride = (int64_t)gridDim.x * kPassThreads;      // a multiple of 16: rows of 16 lanes stay whole
+        int64_t c = (int64_t)blockIdx.x * kPassThreads + threadIdx.x;
+        F8 next{};
+        if (c < nchunks) next = load8(W + c * 8);
+        for (; c < nchunks; c += stride) {
+            const F8 w = next;
+            next = load8(W + (c + stride < nchunks ? c + stride : c) * 8);   // in flight while this chunk is counted
+            F8 sc;
+            quant_dequant8_t<true>(w, inv_tab, &sc);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t key = score_key(f2u(sc.v[i]));
-            if (PASS == 0) atomicAdd(&bins[first_bin(key)], 1u);
-            else if (in_interval(iv, key)) atomicAdd(&bins[later_bin(iv, key)], 1u);
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t b = f2u(sc.v[i]);
+                if (PASS == 0) atomicAdd(&bins[first_bin(b)], 1u);
+                else if (b - iv.lo < within) atomicAdd(&bins[later_bin(iv, TOP ? score_key(b) : b)], 1u);
+            }
         }
-    }
+    };
+    if (PASS > 0 && within != iv.span) count(std::true_type{});
+    else count(std::false_type{});
     __syncthreads();
     for (int b = threadIdx.x; b < kBins; b += kPassThreads)
         if (bins[b]) atomicAdd(&hist[b], bins[b]);
@@ -288,16 +295,19 @@ __global__ __launch_bounds__(kPassThreads) void osci_hist_kernel(const float *W,
     }
 }
 
-// flags of the lane's 8 elements against the threshold: bit i of gt / eq
+// flags of the lane's 8 elements against the threshold's key: bit i of gt / eq
 __device__ __forceinline__ void score_flags(const F8 &sc, uint32_t thr, uint32_t &gt, uint32_t &eq)
 {
-    gt = eq = 0;
+    const uint32_t last = last_pattern(thr);
+    uint32_t ge = 0;
+    gt = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const uint32_t key = score_key(f2u(sc.v[i]));
-        gt |= (key > thr ? 1u : 0u) << i;
-        eq |= (key == thr ? 1u : 0u) << i;
+        const uint32_t b = f2u(sc.v[i]);
+        gt |= (b > last ? 1u : 0u) << i;
+        ge |= (b >= thr ? 1u : 0u) << i;
     }
+    eq = ge ^ gt;
 }
 
 // (greater, equal) counts per tile; the last workgroup replaces them by their exclusive prefix sums.  A workgroup takes
@@ -397,9 +407,10 @@ __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int
         }
     const uint32_t taken_eq_tiles = eq_tiles < ties ? eq_tiles : ties;       // selected equal elements of earlier tiles
     uint32_t pos = gt_tiles + taken_eq_tiles + block_exclusive_scan<4>(__builtin_popcount(sel), red, total);
+    if (pos + __builtin_popcount(sel) > k) sel = 0;        // k are selected: this only keeps the stores inside the arrays
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        if (((sel >> i) & 1u) && pos < k) {                // k are selected: the bound only keeps stores inside the arrays
+        if ((sel >> i) & 1u) {
             idx[pos] = (uint32_t)(c * 8 + i);
             wp[pos] = w.v[i];
             qp[pos] = q.v[i];
@@ -477,26 +488,31 @@ __global__ __launch_bounds__(kThreads) void osci_sparse_kernel(float *W, int64_t
     // (8192 x 1024 zeros, 5 % tracked, four tiles: 35 us, 16.5 like this).
     constexpr int kU = 4;
     for (int64_t jb = j0 + threadIdx.x; jb < j1; jb += kU * kThreads) {
-        int64_t j[kU], e[kU];
+        uint32_t e[kU];
         float m[kU], d[kU], p[kU], r[kU], wv[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            j[u] = jb + u * kThreads < j1 ? jb + u * kThreads : jb;            // past the end: the first entry again, not used
-            e[u] = idx[j[u]];
-            m[u] = dm[j[u]];
-            d[u] = dq[j[u]];
+            const int64_t j = jb + u * kThreads;
+            if (j >= j1) break;
+            e[u] = idx[j];
+            m[u] = dm[j];
+            d[u] = dq[j];
             if (!SUPPRESS) {
-                p[u] = wp[j[u]];
-                r[u] = qp[j[u]];
+                p[u] = wp[j];
+                r[u] = qp[j];
             }
         }
         if (!SUPPRESS) {
 #pragma unroll
-            for (int u = 0; u < kU; ++u) wv[u] = W[e[u]];
+            for (int u = 0; u < kU; ++u) {
+                if (jb + u * kThreads >= j1) break;
+                wv[u] = W[e[u]];
+            }
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            if (jb + u * kThreads >= j1) break;
+            const int64_t j = jb + u * kThreads;
+            if (j >= j1) break;
             const float q = qt[e[u] - tile0];
             if (SUPPRESS) {
                 const float risk = d[u] / m[u];            // IEEE quotient; 0 / 0 is NaN and compares false
@@ -505,10 +521,10 @@ __global__ __launch_bounds__(kThreads) void osci_sparse_kernel(float *W, int64_t
                     ++mine;
                 }
             } else {
-                dm[j[u]] = m[u] + fabsf(wv[u] - p[u]);
-                dq[j[u]] = d[u] + fabsf(q - r[u]);
-                wp[j[u]] = wv[u];
-                qp[j[u]] = q;
+                dm[j] = m[u] + fabsf(wv[u] - p[u]);
+                dq[j] = d[u] + fabsf(q - r[u]);
+                wp[j] = wv[u];
+                qp[j] = q;
             }
         }
     }

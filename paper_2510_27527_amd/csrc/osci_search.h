@@ -7,17 +7,19 @@
 namespace tj {
 
 // Scores are non-negative, so they order like their binary32 patterns.  A NaN (the score of a NaN weight, and of the whole
-// outer block of an infinite one) ranks above infinity: all of its patterns, of either sign, get one key, so that every pass
-// counts exactly the elements that the passes before it counted.
+// outer block of an infinite one) ranks above infinity: all of its patterns, of either sign, share one key, so that every pass
+// counts exactly the elements that the passes before it counted.  The passes test the raw pattern against bounds that take
+// the NaNs in; only a pattern inside the interval is turned into its key.
 constexpr uint32_t kNaNKey = 0x7F800001u;
 constexpr uint32_t score_key(uint32_t pattern) { return pattern < kNaNKey ? pattern : kNaNKey; }
+constexpr uint32_t last_pattern(uint32_t key) { return key == kNaNKey ? 0xFFFFFFFFu : key; }   // the largest pattern of the key
 
 constexpr int kBins = 2048;
 // The first pass: 256 bins per octave in [2^-8, 1] (the last of them holds 1 itself), an open bin below and one above.
-constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kBins - 2);   // key >> 15 of bin 0; 1.0 falls into bin 2046
-constexpr int first_bin(uint32_t key)
+constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kBins - 2);   // pattern >> 15 of bin 0; 1.0 falls into bin 2046
+constexpr int first_bin(uint32_t pattern)
 {
-    const int d = (int)(key >> 15) - (int)kFirstBin;
+    const int d = (int)(pattern >> 15) - (int)kFirstBin;
     return d < 0 ? 0 : d > kBins - 1 ? kBins - 1 : d;
 }
 
@@ -37,8 +39,8 @@ static_assert((((kFirstBin + 1) << 15) >> 30) == 0, "the open bottom bin fits it
 
 // a later pass: 2048 bins of 2^shift keys (30 -> 19 -> 8 -> 0 open bits; 15 -> 4 -> 0)
 constexpr uint32_t later_shift(uint32_t width) { return width > 11 ? width - 11 : 0; }
-// unsigned: keys below lo wrap around
-constexpr bool in_interval(const SelInterval &s, uint32_t key) { return key - s.lo < s.span; }
+// a pattern belongs to the interval if pattern - lo < reach (unsigned: patterns below lo wrap around)
+constexpr uint32_t reach(const SelInterval &s) { return kNaNKey - s.lo < s.span ? 0u - s.lo : s.span; }
 constexpr uint32_t later_bin(const SelInterval &s, uint32_t key) { return (key - s.lo) >> later_shift(s.width); }
 constexpr SelInterval next_interval(const SelInterval &s, uint32_t bin)
 {

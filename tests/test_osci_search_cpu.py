@@ -34,9 +34,12 @@ extern "C" long select_k(const uint32_t *score, long n, long k, unsigned char *s
         if (pass > 0 && iv.width == 0) break;
         long hist[kBins] = {};
         for (long i = 0; i < n; ++i) {
-            const uint32_t key = score_key(score[i]);
-            if (pass == 0) ++hist[first_bin(key)];
-            else if (in_interval(iv, key)) ++hist[later_bin(iv, key)];
+            if (pass == 0) ++hist[first_bin(score[i])];
+            else if (score[i] - iv.lo < reach(iv)) {
+                const uint32_t key = reach(iv) != iv.span ? score_key(score[i]) : score[i];    // the kernel's two loops
+                if (later_bin(iv, key) >= (uint32_t)kBins) return -20 - pass;
+                ++hist[later_bin(iv, key)];
+            }
         }
         uint32_t bin = 0;
         if (!pick(hist, kneed, bin)) return -1 - pass;
@@ -45,8 +48,8 @@ extern "C" long select_k(const uint32_t *score, long n, long k, unsigned char *s
     if (iv.width != 0) return -9;
     long total = 0, ties = 0;
     for (long i = 0; i < n; ++i) {
-        const uint32_t key = score_key(score[i]);
-        sel[i] = key > iv.lo || (key == iv.lo && ties++ < kneed);
+        const bool gt = score[i] > last_pattern(iv.lo), eq = score[i] >= iv.lo && !gt;
+        sel[i] = gt || (eq && ties++ < kneed);
         total += sel[i];
     }
     return total;
