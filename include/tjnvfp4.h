@@ -223,6 +223,9 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
                      size_t ws_bytes, void *stream);
 size_t nvfp4_outctl_workspace_bytes(int backward, int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode,
                                     int out_dtype);
+/* How nvfp4_outctl_bwd splits the reduction of dW_hp over tokens: the number of splits (1: one piece) and the 32-token stages of
+ * each, the last split taking the rest.  It follows from the sizes alone.  Host-only helper. */
+int nvfp4_outctl_dw_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *split, int *stages);
 
 /*
  * OsciReset (Sec. 3.2-3.3) for one weight matrix of binary32 master weights W [C x D], all arrays device memory of

@@ -494,14 +494,20 @@ static size_t outctl_fwd_bytes(int64_t N, int64_t D_lo, int64_t C, int outer, in
            (out_dtype == NVFP4_OUT_F32 ? 0 : align_up((size_t)(N * C) * sizeof(float)));
 }
 
+// the five packed operands of a backward call, one after the other in its workspace
+static size_t outctl_operand_bytes(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer)
+{
+    return packed_bytes(N, C, outer) + packed_bytes(D_lo, C, outer) + packed_bytes(D_hp, C, outer) + packed_bytes(C, N, outer) +
+           packed_bytes(D_lo, N, outer);
+}
+
 static size_t outctl_bwd_bytes(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer)
 {
     const size_t g1 = align_up(gemm_workspace_bytes(N, D_lo, C, outer)), g2 = align_up(gemm_workspace_bytes(C, D_lo, N, outer));
     const size_t g3 = align_up(gemm_workspace_bytes(N, D_hp, C, outer));
     size_t g = g1 > g2 ? g1 : g2;
     g = g > g3 ? g : g3;
-    return 2 * partials_bytes() + packed_bytes(N, C, outer) + packed_bytes(D_lo, C, outer) + packed_bytes(D_hp, C, outer) +
-           packed_bytes(C, N, outer) + packed_bytes(D_lo, N, outer) + align_up((size_t)(N * C) * 2) +
+    return 2 * partials_bytes() + outctl_operand_bytes(N, D_lo, D_hp, C, outer) + align_up((size_t)(N * C) * 2) +
            align_up((size_t)(N * D_hp) * 2) + g;
 }
 
@@ -509,6 +515,15 @@ size_t nvfp4_outctl_workspace_bytes(int backward, int64_t N, int64_t D_lo, int64
 {
     if (N < 0 || D_lo < 0 || D_hp < 0 || C < 0 || !valid_outer(outer_mode)) return 0;
     return backward ? outctl_bwd_bytes(N, D_lo, D_hp, C, outer_mode) : outctl_fwd_bytes(N, D_lo, C, outer_mode, out_dtype);
+}
+
+int nvfp4_outctl_dw_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *split, int *stages)
+{
+    if (!split || !stages) return NVFP4_ERR_NULL;
+    if (!valid_outer(outer_mode)) return NVFP4_ERR_ENUM;
+    if (N < 0 || D_lo < 0 || D_hp < 0 || C < 0 || D_hp % 32 != 0 || check_reduction(N)) return NVFP4_ERR_SHAPE;
+    hp_gemm_split(C, D_hp, N, outctl_operand_bytes(N, D_lo, D_hp, C, outer_mode), split, stages);
+    return NVFP4_OK;
 }
 
 int nvfp4_outctl_fwd(const void *X_lo, const void *W_lo, const void *X_hp, const void *W_hp, int64_t N, int64_t D_lo,
@@ -595,8 +610,9 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     if (D_hp > 0 && C > 0) {
         if (launch_transpose_bf16(dY, dYT, N, C, st) != hipSuccess) return NVFP4_ERR_HIP;
         if (launch_transpose_bf16(X_hp, XhT, N, D_hp, st) != hipSuccess) return NVFP4_ERR_HIP;
-        // the quantized products are done with their scratch: it is free for the partial sums of this one
-        if (launch_hp_gemm_nt(dYT, XhT, C, D_hp, N, nullptr, dW_hp, out_dtype == NVFP4_OUT_F32, gws, gbytes, st) != hipSuccess)
+        // the quantized products are done: their operands' memory, from Q3 to the transposes, takes the partial sums of this one
+        if (launch_hp_gemm_nt(dYT, XhT, C, D_hp, N, nullptr, dW_hp, out_dtype == NVFP4_OUT_F32, q3.codes,
+                              outctl_operand_bytes(N, D_lo, D_hp, C, outer), st) != hipSuccess)
             return NVFP4_ERR_HIP;
     }
     return NVFP4_OK;

@@ -268,6 +268,33 @@ static hipError_t launch_hp_t(HpArgs g, int split, hipStream_t st)
     return hipGetLastError();
 }
 
+// 256 x 256 tiles when they fill the chip, else 128 x 128
+static bool hp_big_tiles(int64_t M, int64_t N) { return ((M + 255) / 256) * ((N + 255) / 256) >= 192; }
+
+// Few tiles and a long reduction (the weight gradient of a few hundred channels): the time is the chain of a tile's stages, so
+// the reduction is split over FP32 partials until every CU has a workgroup or a split has 16 stages left, at most 16 ways and
+// as far as the scratch goes, in powers of two (an odd number leaves the XCDs unequal shares).  Product + sum of the partials,
+// us, by output x tokens and number of splits (* the one taken):
+//   4096 x 384 x 4096   1: 40  2*: 25 + 5   4: 28 + 6   5: 26 + 6       3072 x 256 x 8192  1: 63  4*: 23 + 5  5: 30 + 5  10: 31 + 6
+//   8192 x 128 x 16384  1: 201 4*: 75 + 5   8: 90 + 6                   768 x 128 x 8192   1: 62  8: 12 + 5  16*: 9 + 6
+//   4096 x 512 x 16384  1: 164 2*: 116 + 5  4: 101 + 7   8: 112 + 11    2048 x 256 x 16384 1: 120 8*: 28 + 5  16: 31 + 7
+void hp_gemm_split(int64_t M, int64_t N, int64_t K, size_t scratch_bytes, int *split, int *stages)
+{
+    const int64_t mn = M * N, all = K / 32;
+    *split = 1;
+    *stages = (int)all;
+    if (mn == 0 || mn % 4 != 0 || hp_big_tiles(M, N)) return;
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
+    int64_t s = 256 / tiles;
+    if (s > all / 16) s = all / 16;
+    if (s > 16) s = 16;
+    if (s > (int64_t)scratch_bytes / (mn * 4)) s = (int64_t)scratch_bytes / (mn * 4);
+    if (s < 2) return;
+    while (s & (s - 1)) s &= s - 1;
+    *stages = (int)((all + s - 1) / s);
+    *split = (int)((all + *stages - 1) / *stages);          // no empty split
+}
+
 hipError_t launch_hp_gemm_nt(const void *A, const void *B, int64_t M, int64_t N, int64_t K, const float *addend, void *out,
                              int out_f32, void *scratch, size_t scratch_bytes, hipStream_t st)
 {
@@ -283,26 +310,17 @@ hipError_t launch_hp_gemm_nt(const void *A, const void *B, int64_t M, int64_t N,
     g.out_f32 = out_f32;
     g.tiles_n = 0;
     g.stages = (int)(K / 32);
-    // 256 x 256 tiles when they fill the chip, else 128 x 128
-    const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-    if (big >= 192) return launch_hp_t<4, 4>(g, 1, st);
-    // Few tiles and a long reduction (the weight gradient of a few hundred channels): the time is the chain of a tile's
-    // stages, so the reduction is split over FP32 partials, as far as the caller's scratch goes, until every CU has two
-    // workgroups or a split has 16 stages left.  4096 x 384 x 4096: 37 us in one piece, 28 + 5 for the sum with four.
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), mn = M * N;
-    int64_t split = addend || mn % 4 != 0 || !scratch ? 1 : 512 / tiles;
-    if (split > g.stages / 16) split = g.stages / 16;
-    if (split > 16) split = 16;
-    if (split > 1 && split * mn * 4 > (int64_t)scratch_bytes) split = (int64_t)scratch_bytes / (mn * 4);
+    if (hp_big_tiles(M, N)) return launch_hp_t<4, 4>(g, 1, st);
+    int split = 1;
+    if (!addend && scratch) hp_gemm_split(M, N, K, scratch_bytes, &split, &g.stages);
     if (split < 2) return launch_hp_t<2, 2>(g, 1, st);
-    g.stages = (int)((g.stages + split - 1) / split);
-    split = (K / 32 + g.stages - 1) / g.stages;             // no empty split
+    const int64_t mn = M * N;
     g.out = scratch;
     g.out_f32 = 1;
-    hipError_t e = launch_hp_t<2, 2>(g, (int)split, st);
+    hipError_t e = launch_hp_t<2, 2>(g, split, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(hp_reduce_kernel, dim3((unsigned)((mn / 4 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
-                       static_cast<const float *>(scratch), (int)split, mn, out, out_f32);
+                       static_cast<const float *>(scratch), split, mn, out, out_f32);
     return hipGetLastError();
 }
 

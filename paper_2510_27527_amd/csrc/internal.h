@@ -94,7 +94,9 @@ hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K,
 
 // bf16 side of the OutControl split linear: Out[M x N] = addend (optional, f32) + A[M x K] * B[N x K]^T with K % 32 == 0;
 // transpose of a bf16 [R x C] array
-// (scratch: optional, 16-byte aligned; lets a long reduction with few output tiles be split)
+// (scratch: optional, 16-byte aligned; lets a long reduction with few output tiles be split: hp_gemm_split gives the number of
+// splits and the 32-k stages of each, the last one taking what is left)
+void hp_gemm_split(int64_t M, int64_t N, int64_t K, size_t scratch_bytes, int *split, int *stages);
 hipError_t launch_hp_gemm_nt(const void *A, const void *B, int64_t M, int64_t N, int64_t K, const float *addend, void *out,
                              int out_f32, void *scratch, size_t scratch_bytes, hipStream_t st);
 hipError_t launch_transpose_bf16(const void *src, void *dst, int64_t R, int64_t C, hipStream_t st);

@@ -290,6 +290,31 @@ def test_outctl_calls_reject_bad_arguments(lib):
     assert lib.nvfp4_outctl_workspace_bytes(0, 128, 128, 32, 64, 0, 1) == lib.nvfp4_workspace_bytes(B.OP_LINEAR_FWD, 128, 128, 64, 0)
 
 
+def test_split_of_the_outlier_weight_gradient(lib):
+    """it follows from the sizes alone, never leaves a split without a stage, and its partial sums fit the quantized operands'
+    share of the workspace; bad arguments are refused"""
+    import random
+    rng = random.Random(6)
+    a, b = C.c_int(), C.c_int()
+    assert lib.nvfp4_outctl_dw_plan(64, 64, 32, 64, 0, None, C.byref(b)) == -1
+    assert lib.nvfp4_outctl_dw_plan(64, 64, 32, 64, 2, C.byref(a), C.byref(b)) == -3
+    assert lib.nvfp4_outctl_dw_plan(96, 64, 32, 64, 0, C.byref(a), C.byref(b)) == -2
+    assert lib.nvfp4_outctl_dw_plan(64, 64, 48, 64, 0, C.byref(a), C.byref(b)) == -2
+    most = 0
+    for _ in range(3000):
+        outer = rng.randrange(2)
+        N, D_lo, Cc = (128 * int(2 ** rng.uniform(0, 7)) for _ in range(3))
+        D_hp = 32 * int(2 ** rng.uniform(0, 6))
+        split, stages = B.outctl_dw_plan(N, D_lo, D_hp, Cc, outer)
+        assert split >= 1 and (split - 1) * stages < N // 32 <= split * stages
+        operands = sum(r * k * 9 // 16 for r, k in ((N, Cc), (D_lo, Cc), (D_hp, Cc), (Cc, N), (D_lo, N)))
+        assert split == 1 or split * Cc * D_hp * 4 <= operands + sum(r * k // 128 for r, k in ((N, Cc), (D_lo, Cc), (D_hp, Cc), (Cc, N), (D_lo, N))) * 4 + 15 * 256
+        most = max(most, split)
+    assert most == 16
+    for shape in ((0, 64, 32, 64), (64, 64, 0, 64), (64, 64, 32, 0)):
+        assert B.outctl_dw_plan(*shape) == (1, shape[0] // 32)
+
+
 def test_planner_keeps_products_within_the_static_scratch():
     """where a plan exists whose partial sums fit the static array of nvfp4_gemm_nt_static, a faster split that does not
     fit is not taken"""

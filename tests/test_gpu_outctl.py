@@ -111,13 +111,18 @@ def test_high_precision_product_with_256x256_tiles(N, D_lo, D_hp, C, out_dtype):
         check(g, *ref[name], name)
 
 
-@pytest.mark.parametrize("N,D_lo,D_hp,C", [(2048, 256, 96, 320), (1088, 512, 32, 192), (4160, 128, 160, 136)])
+@pytest.mark.parametrize("N,D_lo,D_hp,C,split,last", [(2048, 256, 96, 320, 4, 16), (1088, 512, 32, 192, 2, 17), (4160, 128, 160, 136, 8, 11),
+                                                      (8256, 64, 32, 64, 16, 3), (1024, 64, 480, 128, 1, 32)])
 @pytest.mark.parametrize("out_dtype", [1, 0])
-def test_weight_gradient_of_few_outlier_channels(N, D_lo, D_hp, C, out_dtype):
+def test_weight_gradient_of_few_outlier_channels(N, D_lo, D_hp, C, split, last, out_dtype):
     """few output tiles and a long reduction over tokens: the bf16 weight-gradient product is split over partial sums in the
-    scratch of the quantized products (as far as it goes), ragged tiles, a last split that is shorter than the others"""
+    memory of the quantized operands - two, four, eight and sixteen ways, the last split as long as the others (16, 17 stages),
+    shorter (11 of 17) and as short as the pipeline's three buffers (3 of 17) - and stays in one piece where that memory does
+    not hold two partial sums; ragged tiles"""
     import paper_2510_27527_amd as tj
     C = (C + 63) // 64 * 64
+    splits, stages = tj.binding.outctl_dw_plan(N, D_lo, D_hp, C)
+    assert (splits, N // 32 - (splits - 1) * stages) == (split, last)
     Xl, Wl, Xh, Wh, dYb = inputs(N, D_lo, D_hp, C, 21 + N)
     args = [dev_bf16(a) for a in (Xl, Wl, Xh, Wh)]
     _, Xq, Wq = tj.outctl_fwd(*args, out_dtype)
