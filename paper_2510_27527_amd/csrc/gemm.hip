@@ -74,9 +74,12 @@ constexpr int kNumTiles = 7;
 // 512 .. 16384), here with t_fixed shared between the workgroups of a CU like the stages: [0] per-tensor scales, [1]
 // 1 x 128 outer blocks, whose rescale in every stage and second accumulator set change the tiles' order.  Examples: 1000 x
 // 3072 x 1024 12.8 us with 128 x 128, 15.8 with 128 x 192; with outer blocks 8192 x 4096 x 4096 331 us with 256 x 128, 386 with
-// 128 x 192, and 2048 x 2048 x 2048 30.6 us with 128 x 128, 40.4 with 256 x 128.  They are used for outputs of whole 64
-// columns (a layer's weight side) and reductions that are not very short; slivers, ragged columns and short reductions
-// keep the costs above, to which the parity tests' choice of a shape for every kernel is pinned.
+// 128 x 192, and 2048 x 2048 x 2048 30.6 us with 128 x 128, 40.4 with 256 x 128.  They are used for outputs of at least 128 rows
+// and columns, ragged ones included (150 random ragged shapes where the two sets differ: these are 1.2 times as fast
+// with per-tensor scales and 1.15 with outer blocks, in three of them 0.85 to 0.9), and from the reduction length on at which they become the
+// better set: 512 with per-tensor scales (64 to 448: 0.85 times as fast as the costs above; 1384 x 2488 x 512: 9.6 us against
+// 11.3), 256 with outer blocks (256 to 640: 1.1 times as fast, 3027 x 896 x 256 8.1 us against 9.7; 128: 506 x 2496 7.1 against
+// 5.6).  Slivers keep the costs above.
 const TileCfg kTilesFit[2][kNumTiles] = {
     {{4, 4, 2.9, 7.2, 1}, {4, 2, 1.78, 4.0, 1}, {2, 4, 1.78, 4.0, 1}, {2, 2, 1.1, 4.0, 2}, {2, 3, 1.33, 5.2, 2}, {1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}},
     {{4, 4, 0, 0, 1}, {4, 2, 2.48, 3.2, 1}, {2, 4, 2.57, 3.2, 1}, {2, 2, 1.52, 4.0, 2}, {2, 3, 2.0, 3.3, 1}, {1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
@@ -84,30 +87,29 @@ constexpr int kNumCU = 256;
 
 struct Plan { int tile; int split; int chunks_per_split; };
 
-// early: the costs and tiles from before the fit
-Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, bool early)
+// kFitted: the fitted costs where they hold; kUnfitted: the costs above for every shape; kEarly: those without the small tiles
+enum Costs { kFitted, kUnfitted, kEarly };
+Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
 {
+    const bool early = costs == kEarly;
     const int64_t chunks = K / 64;
     Plan best{3, 1, (int)chunks};
     if (M <= 0 || N <= 0 || chunks == 0) return best;      // nothing to tile (empty output or empty reduction)
     double best_t = 1e300;
-    const bool fit = !early && M >= 128 && N >= 128 && N % 64 == 0 && K >= (outer ? 768 : 512);
+    const bool fit = costs == kFitted && M >= 128 && N >= 128 && K >= (outer ? 256 : 512);
     for (int t = 0; t < kNumTiles; ++t) {
         if (t == 4 && K % 256 != 0) continue;
         // The small tiles are for outputs that leave CUs idle with 128 x 128 workgroups: there the time is the chain of a
         // tile's stages, and a 64-row tile's stage is half as long (256 x 512 x 512: 9.6 us with 128 x 192, 5.6 with
         // 64 x 64; 2048 x 1024 x 1024: 14.6 us with 128 x 192, 10.4 with 64 x 128); longer chains than 16 stages are split
-        // instead.  A filled chip pays for them with twice the expansions per product (8192 x 3072 x 768: 73 us with
+        // instead (768 x 768 x 3072: 15.5 against 20.0, 512 x 512 x 8192: 17.3 against 23.3, 1000 x 520 x 3072: 16.2 against 20.2).  A
+        // filled chip pays for them with twice the expansions per product (8192 x 3072 x 768: 73 us with
         // 64 x 64, 42 with 128 x 192), and a sliver of an output with
         // rows that are mostly padding.  With 1 x 128 outer blocks the same holds (2048 x 1024 x 1024: 19.8 us with 128 x 192),
         // a little earlier where only the 64 x 64 tile exists.
         if (t >= 5) {
             if (early) break;
             const int64_t least = outer ? 256 : 128, tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
-            // Ragged outputs with reductions of more than 22 stages keep the large tiles (the parity tests of ragged edges under
-            // a K split are pinned to them), although the small ones are faster there too (1000 x 520 x 3072: 16.2 against
-            // 20.2 us; whole tiles: 768 x 768 x 3072 15.5 / 20.0, 512 x 512 x 8192 17.3 / 23.3).
-            if (K > 22 * 64 * kNC && (M % 64 != 0 || N % 64 != 0)) continue;
             if (M < least || N < least || tiles128 > (outer && K % 256 != 0 ? 3 * kNumCU / 8 : kNumCU / 2)) continue;
         }
         if (t == 6 && K % 256 != 0) continue;
@@ -127,7 +129,12 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, bool early)
             const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU;
             const TileCfg &cfg = fit ? kTilesFit[outer][t] : kTiles[t];
             const int64_t conc = per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
-            const double slow = conc == 1 ? 1.0 : fit ? (conc > 2 ? 1.95 : t >= 5 ? 1.4 : outer ? 1.7 : 1.58) : conc == 2 ? (t == 4 && !early ? 1.9 : 1.75) : 2.35;
+            // (unfitted, 128 x 192: 1.9 with a split, where 1.75 made slivers take twice the splits - 35 x 7058 x 5632 with outer
+            // blocks 37.5 against 28.2 us, 106 x 8529 x 13056 63.6 against 47.0; 1.75 without one, where 1.9 gave short reductions
+            // 256 x 256 tiles - 12864 x 4288 x 256 55.7 us against 46.4)
+            const double slow = conc == 1 ? 1.0
+                                : fit     ? (conc > 2 ? 1.95 : t >= 5 ? 1.4 : outer ? 1.7 : 1.58)
+                                : conc == 2 ? (t == 4 && split > 1 && !early ? 1.9 : 1.75) : 2.35;
             const int64_t waves = (wgs + kNumCU * conc - 1) / (kNumCU * conc);
             // unfitted block mode: the per-block rescale of the accumulators makes a stage about a third longer
             double time = fit ? (double)waves * (stages * cfg.t_stage + cfg.t_fixed) * slow
@@ -143,12 +150,15 @@ size_t split_bytes(const Plan &p, int64_t M, int64_t N) { return p.split > 1 ? (
 
 Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
 {
-    const Plan p = rank_tiles(M, N, K, outer, false);
+    const Plan p = rank_tiles(M, N, K, outer, kFitted);
     if (split_bytes(p, M, N) <= (size_t)NVFP4_STATIC_SCRATCH_BYTES) return p;
-    // A better split must not put a product out of reach of the entry point with a fixed scratch array: where the earlier
-    // costs gave a plan that fits it, that plan stays (0.7 % of the shapes with 64 to 20000 rows and columns).
-    const Plan q = rank_tiles(M, N, K, outer, true);
-    return split_bytes(q, M, N) <= (size_t)NVFP4_STATIC_SCRATCH_BYTES ? q : p;
+    // A better split must not put a product out of reach of the entry point with a fixed scratch array: where one of the
+    // earlier sets of costs gives a plan that fits it, that plan stays (0.7 % of the shapes with 64 to 20000 rows and columns).
+    for (const Costs c : {kUnfitted, kEarly}) {
+        const Plan q = rank_tiles(M, N, K, outer, c);
+        if (split_bytes(q, M, N) <= (size_t)NVFP4_STATIC_SCRATCH_BYTES) return q;
+    }
+    return p;
 }
 
 }  // namespace

@@ -11,6 +11,7 @@ import torch
 
 import oracle
 import workloads as wl
+from gemm_variants import RAGGED_SHAPES
 
 pytestmark = pytest.mark.gpu
 
@@ -382,8 +383,8 @@ def test_gemm_nt(M, N, K, out_dtype):
     check_product(got, ref, absref, "gemm %dx%dx%d" % (M, N, K))
 
 
-@pytest.mark.parametrize("M,N,K", [(8100, 700, 768), (8155, 745, 768), (3000, 770, 2304), (700, 760, 8192),
-                                   (8192, 2000, 768), (1000, 520, 3072)])
+@pytest.mark.parametrize("M,N,K", [(8100, 700, 768), (8155, 745, 768), (3333, 2222, 2304), (1500, 1801, 8192),
+                                   (8192, 2000, 768), (1000, 1902, 6144)])
 @pytest.mark.parametrize("out_dtype", [0, 1])
 def test_gemm_ragged_large_tiles_sampled_rows(M, N, K, out_dtype):
     """Shapes for which the planner takes its large workgroup tiles (128 x 192, 256 x 256, 256 x 128; with and without a
@@ -432,6 +433,24 @@ def test_gemm_every_kernel_instantiation(key, shape, out_dtype):
     check_product(got[torch.from_numpy(rows).cuda()], ref, absref, "gemm %dx%dx%d" % (M, N, K))
 
 
+@pytest.mark.parametrize("outer,M,N,K", RAGGED_SHAPES)
+def test_gemm_ragged_outputs(outer, M, N, K):
+    if outer:
+        A = oracle.quantize_bf16(_block_operand(M, K, 770 + N, 1.0), 0, 0, outer=oracle.OUTER_BLOCK128)
+        B = oracle.quantize_bf16(_block_operand(N, K, 771 + M, 0.02), 0, 1, outer=oracle.OUTER_BLOCK128, seed=6)
+    else:
+        A = oracle.quantize_bf16(wl.normal_bf16((M, K), 1.0, 770 + N, 1e-2, 50.0), 0, 0)
+        B = oracle.quantize_bf16(wl.normal_bf16((N, K), 0.02, 771 + M), 0, 1, seed=6)
+    a, b = to_dev(A), to_dev(B)
+    got, again = tj.gemm_nt(a, b, 1), tj.gemm_nt(a, b, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(got, again)                            # fixed summation order
+    rng = np.random.default_rng(M + N)
+    rows = np.unique(np.concatenate([[0, M - 1, M // 64 * 64 - 1, M // 64 * 64 % M, M // 128 * 128 % M], rng.choice(M, min(M, 32), replace=False)]))
+    ref, absref = oracle.gemm_nt(A, B, rows_a=rows)
+    check_product(got[torch.from_numpy(rows).cuda()], ref, absref, "gemm ragged %dx%dx%d" % (M, N, K))
+
+
 # (outer mode, M, N, K, workgroup tile, K split) of the small tiles: ragged in both directions; 1088: whole chunks of 64 but
 # half a stage at the end; whole tiles with a 16-byte aligned row take the staged epilogue
 SMALL_TILE_SHAPES = [(0, 154, 131, 64, (64, 64), False), (0, 135, 153, 1600, (64, 64), True), (0, 133, 151, 256, (64, 64), False),
@@ -467,7 +486,7 @@ def test_gemm_small_tiles(outer, M, N, K, tile, split, out_dtype):
 # shortest reduction with paired scale fetch (two stages, one scale pair), 768 a typical short one.
 WALK_SHAPES = [(0, 6016, 4096, 256, (128, 128)), (0, 4736, 3456, 256, (128, 192)), (0, 3200, 5120, 256, (128, 256)),
                (0, 5120, 3200, 256, (256, 128)), (0, 4352, 5888, 256, (256, 256)), (0, 4352, 5888, 768, None),
-               (0, 4736, 3456, 512, None), (1, 6016, 4096, 256, (128, 128)), (1, 4736, 3456, 256, (128, 192)),
+               (0, 4736, 3456, 512, None), (1, 5504, 4480, 512, (128, 128)), (1, 4736, 3456, 256, (128, 192)),
                (1, 3200, 5120, 256, (128, 256)), (1, 2816, 4480, 256, (256, 128)), (1, 2816, 4480, 768, None)]
 
 
