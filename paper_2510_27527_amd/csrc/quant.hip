@@ -633,9 +633,9 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
         uint32_t w[16];                                            // bf16 pairs, or bytes of two codes
         uint32_t sb[PACKED ? 16 : 1];                              // packed: scale bytes
     };
-    // packed source: the outer scale of each of the strip's 128 rows, in the wave's own corner of LDS (1 x 128 outer
-    // blocks: the strip lies inside one block column, so a row has one; per-tensor scale: 128 copies of it, so that the
-    // decode is the same code for both)
+    // packed source: the outer scale of each of the strip's rows, in the wave's own corner of LDS (1 x 128 outer blocks: the
+    // strip lies inside one block column, so a row has one; per-tensor scale: a copy of it per row, so that the decode is the
+    // same code for both)
     __shared__ float row_sg_all[PACKED ? kThreads / 64 : 1][PACKED ? kStripR : 1];
     float *row_sg = row_sg_all[PACKED ? wave : 0];
     if (PACKED && have) {
@@ -648,15 +648,14 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
         }
         // same wave writes and reads: the compiler's wait on the LDS counter orders them
     }
-    auto fetch = [&](auto stream, int s, Raw &r) {
-        constexpr bool STREAM = decltype(stream)::value;          // last use of these bytes: they need not stay cached
+    auto fetch = [&](int s, Raw &r) {
         const int64_t e0 = (R0 + 16 * s) * C + strip0;             // uniform
         if constexpr (!PACKED) {
             const uint32_t *p = reinterpret_cast<const uint32_t *>(a.src) + (e0 >> 1);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const uint32_t *rowp = p + i * (C >> 1);           // uniform
-                r.w[i] = STREAM ? __builtin_nontemporal_load(rowp + ln) : rowp[ln];
+                r.w[i] = __builtin_nontemporal_load(rowp + ln);    // read once: the line need not stay cached
             }
         } else {
             const uint8_t *pc = a.src_codes + (e0 >> 1);
@@ -670,8 +669,9 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     };
     // returns the two column maxima of the slab
     auto decode = [&](const Raw &r, int s, float (&x0)[16], float (&x1)[16], float &m0, float &m1) {
-        // RHT: the slab's 16 source rows are positions 16 (s & 1) .. + 15 of sign word (R0 + 16 s) / 32 (R0 is a multiple
-        // of 128); the word is the same for the whole wave
+        // RHT: the slab's 16 source rows are positions 16 (s & 1) .. + 15 of sign word (R0 + 16 s) / 32 (R0 is a multiple of
+        // kStripR); the word is the same for the whole wave
+        static_assert(!RHT || kStripR % 32 == 0, "a strip starts at a sign word");
         uint32_t sw = 0;
         if (RHT) sw = __builtin_amdgcn_readfirstlane(quad_bits((uint32_t)((R0 + 16 * s) >> 5), a.k.r0, a.k.r1));
         auto flips = [&](int i) { return ((sw >> rht_sign_bit(16 * (s & 1) + i)) & 1u) != 0; };   // uniform
@@ -720,8 +720,8 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     __shared__ __attribute__((aligned(16))) float2 col_max[OUTER ? kWaves : 1][OUTER ? 64 : 1];
     if constexpr (OUTER == 1) {
         // R is a multiple of 128: every wave has its two slabs
-        fetch(std::true_type{}, 0, raw[0]);
-        fetch(std::true_type{}, 1, raw[1]);
+        fetch(0, raw[0]);
+        fetch(1, raw[1]);
 #pragma unroll
         for (int s = 0; s < 2; ++s) decode(raw[s], s, xb0[s], xb1[s], mb[s][0], mb[s][1]);
         col_max[wave][lane] = make_float2(fmaxf(mb[0][0], mb[1][0]), fmaxf(mb[0][1], mb[1][1]));
@@ -748,14 +748,14 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     __shared__ __attribute__((aligned(16))) uint8_t sc_stage[kStripC * kScPitch];
     uint32_t scb[2][(SLABS + 3) / 4] = {};                          // the slabs' scale bytes, per column
     const bool wide = (int)wave < nwide;
-    if (OUTER == 0 && have) fetch(std::true_type{}, 0, raw[0]);
+    if (OUTER == 0 && have) fetch(0, raw[0]);
 #pragma unroll
     for (int s = 0; s < kSlabs; ++s) {
         if (s >= nslab) break;
         float x0[16], x1[16], mx[2];
         if constexpr (OUTER == 0) {
             const Raw &cur = raw[s & 1];
-            if (s + 1 < nslab) fetch(std::true_type{}, s + 1, raw[(s + 1) & 1]);
+            if (s + 1 < nslab) fetch(s + 1, raw[(s + 1) & 1]);
             decode(cur, s, x0, x1, mx[0], mx[1]);
         } else {
             mx[0] = mb[s][0];
@@ -809,8 +809,8 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
                 if (c < C) *reinterpret_cast<uint4 *>(out_codes + ((c * R + Rg) >> 1) + piece * 16) = make_uint4(lo.x, lo.y, hi.x, hi.y);
             }
         }
-        // scales: 4-byte pieces (the row offset c * R / 16 is a multiple of 4 only); an odd number of two-slab strips leaves
-        // two bytes over
+        // scales: 4-byte pieces (the row offset c * R / 16 is a multiple of 4 only).  The strips' bytes are a multiple of 4: with
+        // R % 64 == 0 the number of two-slab strips is even
         constexpr int kScPieces = kScPitch / 4, kScRows = kThreads / kScPieces;
         const int sp = tid % kScPieces, have_sc = SLABS * nwide;
 #pragma unroll
@@ -820,8 +820,7 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
             if (row < kStripC && c < C) {
                 uint8_t *dst = a.k.scales + ((c * R + Rg) >> 4) + sp * 4;
                 const uint32_t v = *reinterpret_cast<const uint32_t *>(sc_stage + row * kScPitch + sp * 4);
-                if (sp * 4 + 4 <= have_sc) *reinterpret_cast<uint32_t *>(dst) = v;
-                else if (SLABS == 2 && sp * 4 + 2 <= have_sc) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)v;
+                if (sp * 4 < have_sc) *reinterpret_cast<uint32_t *>(dst) = v;
             }
         }
     }
