@@ -301,9 +301,9 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
 // all-zero block: there the block's eight scale bytes (all 0 in an all-zero block) tell the two apart.  Only a block whose
 // S_g is the floor 2^-100 has its codes looked at.  So the kernel reads one outer scale per 128 elements, and for all-zero
 // blocks (padding tokens) eight bytes more; leaving the maximum to the quantizer's own workgroups (one atomic each, executed
-// one after the other on a single address) cost 20 us on 9000 x 3072.  Bound by the latency of its loads: four blocks per
-// thread and step have theirs in flight together, at least two steps per thread (one atomic per workgroup), up to 256
-// workgroups.  On 8192 x 8192 the kernel takes 5.7 us, 4.6 us when every block is zero and 12.4 us when every block is at the
+// one after the other on a single address) cost 20 us on 9000 x 3072.  Bound by the latency of its loads: one block per
+// thread for small tensors, else four per thread and step with their loads in flight together, at least two steps per thread
+// (one atomic per workgroup), up to 256 workgroups.  On 8192 x 8192 the kernel takes 5.7 us, 4.6 us when every block is zero and 12.4 us when every block is at the
 // floor; on 9000 x 3072 4 us.  The call (quantizer and this kernel) on 8192 x 8192 sources that are not cached: 37.9 us, all
 // zero 35.6; with one block per thread and step on 64 workgroups, which also decoded the zero blocks: 44.6 and 110; with
 // the atomics: 54 and 34.
@@ -315,7 +315,8 @@ struct DeqJob {
     int64_t nblocks;
     unsigned nwg;
 };
-constexpr int kDeqWgs = 256, kDeqUnroll = 4;
+constexpr int kDeqWgs = 256;
+constexpr int64_t kDeqOneStep = 1 << 15;     // blocks of the largest tensor with one block per thread
 
 // largest magnitude code of eight
 __device__ __forceinline__ ushort2_t max_code8(ushort2_t m, uint32_t q)
@@ -325,6 +326,8 @@ __device__ __forceinline__ ushort2_t max_code8(ushort2_t m, uint32_t q)
     return m;
 }
 
+// U: blocks per thread and step
+template <int U>
 __global__ __launch_bounds__(kThreads) void deq_max_kernel(DeqJob j0, DeqJob j1)
 {
     __shared__ float red[4];
@@ -332,22 +335,22 @@ __global__ __launch_bounds__(kThreads) void deq_max_kernel(DeqJob j0, DeqJob j1)
     const DeqJob j = second ? j1 : j0;
     const int64_t stride = (int64_t)j.nwg * kThreads;
     float m = 0.0f;
-    for (int64_t b0 = (int64_t)(second ? blockIdx.x - j0.nwg : blockIdx.x) * kThreads + threadIdx.x; b0 < j.nblocks; b0 += kDeqUnroll * stride) {
-        float sg[kDeqUnroll];
-        uint2 sc[kDeqUnroll];
-        int64_t b[kDeqUnroll];
+    for (int64_t b0 = (int64_t)(second ? blockIdx.x - j0.nwg : blockIdx.x) * kThreads + threadIdx.x; b0 < j.nblocks; b0 += U * stride) {
+        float sg[U];
+        uint2 sc[U];
+        int64_t b[U];
 #pragma unroll
-        for (int u = 0; u < kDeqUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             b[u] = b0 + u * stride < j.nblocks ? b0 + u * stride : b0;         // past the end: the first block again
             sg[u] = j.gscale[b[u]];
         }
 #pragma unroll
-        for (int u = 0; u < kDeqUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             sc[u] = make_uint2(0, 0);
             if (sg[u] == 1.0f || sg[u] == 0x1p-100f) sc[u] = j.scales[b[u]];
         }
 #pragma unroll
-        for (int u = 0; u < kDeqUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             if (sg[u] == 1.0f) {
                 if (sc[u].x | sc[u].y) m = fmaxf(m, 2688.0f);
             } else if (sg[u] != 0x1p-100f) {
@@ -966,15 +969,20 @@ void launch_zero_scalar(float *p, hipStream_t st)
 // the dequantized maxima of one or two operands with 1 x 128 outer blocks, after their row-wise quantization
 static void launch_deq_max(const RowJob &j0, const RowJob &j1, hipStream_t st)
 {
-    auto job = [](const RowJob &r) {
+    // one block per thread up to 32768 blocks (256 x 512 with a 512 x 512 weight: forward call 11.0 us, 12.1 with eight per thread)
+    const bool one = j0.nchunks / 16 <= kDeqOneStep && j1.nchunks / 16 <= kDeqOneStep;
+    const int64_t per_wg = one ? kThreads : kThreads * 2 * 4;
+    auto job = [&](const RowJob &r) {
         DeqJob d{r.a.gscale, reinterpret_cast<const uint2 *>(r.a.scales), reinterpret_cast<const uint4 *>(r.a.codes), r.a.amax_deq,
                  r.nchunks / 16, 0};
-        const int64_t per_wg = kThreads * 2 * kDeqUnroll, want = (d.nblocks + per_wg - 1) / per_wg;
+        const int64_t want = (d.nblocks + per_wg - 1) / per_wg;
         d.nwg = r.a.amax_deq ? (unsigned)(want < kDeqWgs ? want : kDeqWgs) : 0u;
         return d;
     };
     const DeqJob d0 = job(j0), d1 = job(j1);
-    if (d0.nwg + d1.nwg) hipLaunchKernelGGL(deq_max_kernel, dim3(d0.nwg + d1.nwg), dim3(kThreads), 0, st, d0, d1);
+    if (d0.nwg + d1.nwg == 0) return;
+    if (one) hipLaunchKernelGGL(deq_max_kernel<1>, dim3(d0.nwg + d1.nwg), dim3(kThreads), 0, st, d0, d1);
+    else hipLaunchKernelGGL(deq_max_kernel<4>, dim3(d0.nwg + d1.nwg), dim3(kThreads), 0, st, d0, d1);
 }
 
 static void launch_row_sel(const RowJob &j0, const RowJob &j1, const QuantParams &p, bool deq, hipStream_t st)
