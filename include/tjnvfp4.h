@@ -250,7 +250,7 @@ int nvfp4_osci_suppress(float *W, const float *dist_m, const float *dist_q, floa
  * (the paper tracks the top 5 % of the sensitivity score s = |W - Q(W)| / binwidth(Q(W)); the caller passes
  * k = ceil(p * C * D)).  binwidth = (length of the interval of scaled values that round to the element's FP4 magnitude:
  * 0.5 for 0 .. 1.5, 0.75 for 2, 1 for 3, 1.5 for 4, 1 for 6) * S_block * S_global; equal scores are taken in ascending
- * index order.  State of the subset, all device arrays of k entries owned by the caller: idx (flat indices into W,
+ * index order, and NaN scores (of a NaN weight, and of the whole outer block of an infinite one) count as equal and largest.  State of the subset, all device arrays of k entries owned by the caller: idx (flat indices into W,
  * ascending), W_prev_s / Q_prev_s (master / quantized snapshots), dist_m_s / dist_q_s.  C * D <= 2^31, D % 128 == 0,
  * W 16-byte aligned.
  *

@@ -547,8 +547,8 @@ hipError_t launch_sparse(float *W, int64_t n, const uint32_t *idx, int64_t k, fl
     // Several tiles per workgroup once that still leaves two workgroups per CU: four in the reset, whose workgroups each end
     // with an addition to one counter (8192 x 1024, resets all over the tensor: 59 us with one tile, 35 with two, 23 with
     // four).  The step has no counter: two, which keeps a list whose entries lie close together on twice the workgroups
-    // (8192 x 1024 zeros, 5 % tracked: 11.6 / 12.8 / 16.5 us; spread evenly 15.6 / 13.5 / 13.1), and four from 16384 tiles on
-    // (8192 x 8192, 5 %: 126 / 111 / 95; zeros 88 / 73 / 65).
+    // (8192 x 1024 zeros, 5 % tracked: 11.6 us with one, 12.8 with two, 16.5 with four; spread evenly 15.6 / 13.5 / 13.1), and
+    // four from 16384 tiles on (8192 x 8192, 5 %: 126 / 111 / 95; zeros 88 / 73 / 65).
     auto launch = [&](auto t) {
         constexpr int T = decltype(t)::value;
         hipLaunchKernelGGL((osci_sparse_kernel<SUPPRESS, T>), dim3((unsigned)((ntiles + T - 1) / T)), dim3(kThreads), 0, st, W, nchunks, idx, k,

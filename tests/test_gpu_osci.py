@@ -164,9 +164,9 @@ def test_subset_calls_empty_and_bad_arguments():
 
 @pytest.mark.parametrize("shape,frac", [((4104, 1024), 0.05), ((4097, 1024), 0.9), ((4099, 1024), 1.0 / 16384)])
 def test_tensors_of_many_tiles(shape, frac):
-    """more than 2048 tiles of 2048 weights, the last workgroup's share ragged: four tiles per workgroup on the subset
-    (with and without an entry in nearly every tile), two chunks per thread in the reset, several rounds per workgroup in
-    the selection's passes, a threshold far below and close to the largest score"""
+    """more than 2048 tiles of 2048 weights, the last workgroup's share ragged: two tiles per workgroup in a step on the subset
+    and four in its reset (with and without an entry in nearly every tile), several rounds per workgroup in the reset of all
+    weights and in the selection's passes, a threshold far below and close to the largest score"""
     import paper_2510_27527_amd as tj
     rng = np.random.default_rng(5)
     W0 = (rng.standard_normal(shape) * 0.02).astype(np.float32)

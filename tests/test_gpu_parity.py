@@ -182,7 +182,7 @@ def test_quant_col(shape, rounding):
     assert_same(got, ref, "col %s r%d" % (shape, rounding))
 
 
-# strips of 32 rows (64 for a bf16 source above 2^25 elements), four per workgroup: rows that end inside a slab's worth of a
+# strips of 32 rows (64 for a bf16 source above 28 M elements), four per workgroup: rows that end inside a slab's worth of a
 # strip, inside a workgroup, on and off the 64-row alignment of the staged stores; columns that end inside a strip
 STRIP_SHAPES = [(32, 8), (48, 136), (64, 128), (96, 264), (112, 120), (192, 136), (208, 16), (320, 392)]
 
