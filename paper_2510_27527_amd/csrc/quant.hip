@@ -563,6 +563,8 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
 //   bf16    16384 x 1024 12.2 / 12.3 / 14.3   8192 x 3072 16.0 / 16.5 / 19.2   8192 x 4096 20.8 / 20.4 / 20.3
 //           8192 x 8192 50.8 / 39.0 / 40.1    8192 x 16384 91.8 / 76.4 / 84.2  16384 x 8192 96.3 / 82.1 / 79.8
 //           65536 x 1024 42.2 / 39.7 / 36.5
+// Rows off the staged stores' alignment (R % 64 != 0) write 8 bytes per column and slab themselves, and short strips are best at
+// every size: packed 7408 x 6256 47.7 / 52.7 / 77.0, 16400 x 8208 147 / 154 / 211; bf16 59.1 / 67.8 / 81.0, 179 / 201 / 238.
 //
 // With 1 x 128 outer blocks (OUTER = 1, two slabs per wave) the workgroup's 128 rows are exactly one outer block of each
 // of its output rows: the waves decode their slabs into registers, exchange the column maxima through LDS and quantize
@@ -903,6 +905,7 @@ void launch_colw_s(const ColArgs &a0, const ColArgs &a1, bool pair, int rounding
 // slabs per strip of a launch (the figures are at the kernel); a1: the second tensor of a pair, or one without elements
 inline int colw_slabs(const ColArgs &a0, const ColArgs &a1, bool packed)
 {
+    if ((a0.R | a1.R) & 63) return 2;
     const int64_t n = a0.R * a0.C + a1.R * a1.C, kLong = (int64_t)5 << 23;
     if (n > kLong && (packed || a0.R > a0.C)) return 8;
     return !packed && n > ((int64_t)7 << 22) ? 4 : 2;

@@ -206,7 +206,8 @@ def test_requant_col_strip_edges(shape, rounding):
 @pytest.mark.parametrize("shape", [(6592, 6384), (6608, 6384)])
 def test_column_quantizers_long_strips(shape):
     """above 40 M elements strips of 128 rows, for a packed source and for a bf16 source with more rows than columns: the last
-    strip half as long, and a row count off the 64-row alignment of the staged stores; the last 128 columns are ragged"""
+    strip half as long; a row count off the 64-row alignment of the staged stores keeps the short strips; the last 128 columns
+    are ragged"""
     bits = wl.normal_bf16(shape, 1.0, 475 + shape[0], 1e-2, 30.0)
     got = tj.quantize(dev_bf16(bits), 1, 1, seed=8, tensor_id=5)
     assert_same(got, oracle.quantize_bf16(bits, 1, 1, seed=8, tensor_id=5), "col %s" % (shape,))
