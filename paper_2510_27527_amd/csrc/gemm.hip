@@ -75,11 +75,11 @@ constexpr int kNumTiles = 7;
 // 1 x 128 outer blocks, whose rescale in every stage and second accumulator set change the tiles' order.  Examples: 1000 x
 // 3072 x 1024 12.8 us with 128 x 128, 15.8 with 128 x 192; with outer blocks 8192 x 4096 x 4096 331 us with 256 x 128, 386 with
 // 128 x 192, and 2048 x 2048 x 2048 30.6 us with 128 x 128, 40.4 with 256 x 128.  They are used for outputs of at least 128 rows
-// and columns, ragged ones included (150 random ragged shapes where the two sets differ: these are 1.2 times as fast
-// with per-tensor scales and 1.15 with outer blocks, in three of them 0.85 to 0.9), and from the reduction length on at which they become the
+// and columns, ragged ones included (360 random ragged shapes where the two sets differ: these are 1.17 times as fast
+// with per-tensor scales and 1.13 with outer blocks; eight of them are 0.80 to 0.9), and from the reduction length on at which they become the
 // better set: 512 with per-tensor scales (64 to 448: 0.85 times as fast as the costs above; 1384 x 2488 x 512: 9.6 us against
-// 11.3), 256 with outer blocks (256 to 640: 1.1 times as fast, 3027 x 896 x 256 8.1 us against 9.7; 128: 506 x 2496 7.1 against
-// 5.6).  Slivers keep the costs above.
+// 11.3), 256 with outer blocks (256 to 640, 160 shapes: 1.16 times as fast, 3027 x 896 x 256 8.1 us against 9.7; 128: 506 x 2496
+// 7.1 against 5.6).  Slivers keep the costs above.
 const TileCfg kTilesFit[2][kNumTiles] = {
     {{4, 4, 2.9, 7.2, 1}, {4, 2, 1.78, 4.0, 1}, {2, 4, 1.78, 4.0, 1}, {2, 2, 1.1, 4.0, 2}, {2, 3, 1.33, 5.2, 2}, {1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}},
     {{4, 4, 0, 0, 1}, {4, 2, 2.48, 3.2, 1}, {2, 4, 2.57, 3.2, 1}, {2, 2, 1.52, 4.0, 2}, {2, 3, 2.0, 3.3, 1}, {1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
@@ -128,7 +128,12 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
             // workgroups sharing a CU slow each other down (128 x 128 tiles: up to three per CU)
             const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU;
             const TileCfg &cfg = fit ? kTilesFit[outer][t] : kTiles[t];
-            const int64_t conc = per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
+            // A third 128 x 128 workgroup with outer blocks still runs beside the other two when it makes the launch a single round
+            // (513 to 768 tiles in one piece: 16640 x 640 x 256 17.8 us, 21.8 with 256 x 128; 76 shapes 1.07 times as fast, 0.98 at
+            // worst); above K = 3072 split plans are the better ones (1600 x 5888 x 8320: 279 us with 256 x 128 in three, 311), and
+            // counted on in every round it costs 10 % on larger outputs (9674 x 7936 x 4480: 1079 against 968 us).
+            const bool third = fit && outer && t == 3 && split == 1 && per_cu == 3 && K <= 3072;
+            const int64_t conc = third ? 3 : per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
             // (unfitted, 128 x 192: 1.9 with a split, where 1.75 made slivers take twice the splits - 35 x 7058 x 5632 with outer
             // blocks 37.5 against 28.2 us, 106 x 8529 x 13056 63.6 against 47.0; 1.75 without one, where 1.9 gave short reductions
             // 256 x 256 tiles - 12864 x 4288 x 256 55.7 us against 46.4)
