@@ -13,8 +13,10 @@ LIB = os.path.join(HERE, "libtjnvfp4.so")
 SOURCES = [("api.hip", "api.o", []), ("quant.hip", "quant.o", []), ("osci.hip", "osci.o", []), ("hp.hip", "hp.o", []), ("gemm.hip", "gemm.o", [])] + [
     ("gemm_inst.hip", "gemm_inst_ps%d_out%d_outer%d.o" % (ps, out, outer),
      ["-DTJ_GEMM_PS=%d" % ps, "-DTJ_GEMM_OUT=%d" % out, "-DTJ_GEMM_OUTER=%d" % outer])
-    for outer in (0, 1) for ps in (1, 0) for out in (0, 2, 1)]
-HEADERS = ["device_fmt.h", "internal.h", "gemm_args.h", "gemm_kernel.h", "osci_search.h", os.path.join("..", "..", "include", "tjnvfp4.h")]
+    for outer in (0, 1) for ps in (1, 0) for out in (0, 2, 1)] + [
+    ("gemm_kw_inst.hip", "gemm_kw_out%d_outer%d.o" % (out, outer), ["-DTJ_GEMM_OUT=%d" % out, "-DTJ_GEMM_OUTER=%d" % outer])
+    for outer in (0, 1) for out in (0, 2, 1)]
+HEADERS = ["device_fmt.h", "internal.h", "gemm_args.h", "gemm_kernel.h", "gemm_kw_kernel.h", "osci_search.h", os.path.join("..", "..", "include", "tjnvfp4.h")]
 
 # -ffp-contract=off: the quantizer arithmetic is one IEEE rounding per written operation.
 # packed-fp32-ops is switched off: hipcc then never forms v_pk_{add,mul,fma}_f32 on its own.

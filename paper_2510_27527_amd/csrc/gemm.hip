@@ -68,8 +68,8 @@ struct TileCfg { int tm, tn; double t_stage; double t_fixed; int occupancy; };
 // t_stage: one 128-k pipeline stage of one workgroup with the CU to itself; t_fixed: prologue + epilogue
 // the 128 x 192 tile exists for the paired scale fetch only (K a multiple of 256)
 const TileCfg kTiles[] = {{4, 4, 3.2, 6.0, 1}, {4, 2, 2.0, 5.0, 1}, {2, 4, 2.0, 5.0, 1}, {2, 2, 1.5, 5.0, 3}, {2, 3, 1.4, 5.0, 2},
-                          {1, 1, 0.6, 3.2, 3}, {1, 2, 0.9, 3.2, 2}};
-constexpr int kNumTiles = 7;
+                          {1, 1, 0.6, 3.2, 3}, {1, 2, 0.9, 3.2, 2}, {2, 2, 1.5, 5.0, 1}};
+constexpr int kNumTiles = 8;
 // Costs fitted to sustained runs of the tiles on whole layers' products (64 x 64 to 256 x 256 tiles; 1000 to 16384 rows, K =
 // 512 .. 16384), here with t_fixed shared between the workgroups of a CU like the stages: [0] per-tensor scales, [1]
 // 1 x 128 outer blocks, whose rescale in every stage and second accumulator set change the tiles' order.  Examples: 1000 x
@@ -81,11 +81,25 @@ constexpr int kNumTiles = 7;
 // 11.3), 256 with outer blocks (256 to 640, 160 shapes: 1.16 times as fast, 3027 x 896 x 256 8.1 us against 9.7; 128: 506 x 2496
 // 7.1 against 5.6).  Slivers keep the costs above.
 const TileCfg kTilesFit[2][kNumTiles] = {
-    {{4, 4, 2.9, 7.2, 1}, {4, 2, 1.78, 4.0, 1}, {2, 4, 1.78, 4.0, 1}, {2, 2, 1.1, 4.0, 2}, {2, 3, 1.33, 5.2, 2}, {1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}},
-    {{4, 4, 0, 0, 1}, {4, 2, 2.48, 3.2, 1}, {2, 4, 2.57, 3.2, 1}, {2, 2, 1.52, 4.0, 2}, {2, 3, 2.0, 3.3, 1}, {1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
+    {{4, 4, 2.9, 7.2, 1}, {4, 2, 1.78, 4.0, 1}, {2, 4, 1.78, 4.0, 1}, {2, 2, 1.1, 4.0, 2}, {2, 3, 1.33, 5.2, 2}, {1, 1, 0.285, 3.9, 2}, {1, 2, 0.55, 5.3, 1}, {2, 2, 0.84, 7.3, 1}},
+    {{4, 4, 0, 0, 1}, {4, 2, 2.48, 3.2, 1}, {2, 4, 2.57, 3.2, 1}, {2, 2, 1.52, 4.0, 2}, {2, 3, 2.0, 3.3, 1}, {1, 1, 0.41, 4.6, 1}, {1, 2, 0.78, 5.6, 1}, {2, 2, 0, 0, 1}}};
+// Tiles 5, 6 and 7 above are costs of gemm_kw_kernel, for whole outputs (rows and columns in 64s).  Measured: 64 x 64 with one
+// workgroup per CU 3.9 us + 0.29 per 128 k (1024 x 1024: K = 512 5.3 us, 1024 6.5, 2048 8.9), with two 5.5 + 0.5; 64 x 128 5.4 +
+// 0.57 (2048 x 1024 x 1024 9.9); 128 x 128 7.3 + 0.6 to 0.8 (2048 x 2048 x 2048 19.7 us, 20.8 with gemm_nt_kernel's tile of that size;
+// 2752 x 1088 x 4416 33.5, 41.5); with outer blocks 64 x 64 4.6 + 0.41 and 64 x 128 5.6 + 0.78.  Ragged outputs keep the costs that the
+// 64 x 64 and 64 x 128 tiles have in gemm_nt_kernel, whichever kernel runs them.
+const TileCfg kSmallRagged[2][2] = {{{1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}}, {{1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
 constexpr int kNumCU = 256;
 
 struct Plan { int tile; int split; int chunks_per_split; };
+
+// Whether the 64 x 64 (5) and 64 x 128 (6) tiles run on gemm_kw_kernel: below these reductions, per split, its four waves have too
+// little to share (64 x 64: K = 256 5.5 us both, 128 5.8 against 5.1; with outer blocks K = 512 6.3 against 6.4, 640 8.5 against
+// 7.9, 1152 10.0 against 11.1; 64 x 128: K = 512 7.7 against 7.1, 1024 9.9 against 10.4, with outer blocks 8.7 against 8.2, 12.0 against 12.6).
+bool waves_split_k(int tile, int64_t chunks, int outer)
+{
+    return tile == 7 || (tile >= 5 && chunks >= (tile == 5 && !outer ? 4 : 12));
+}
 
 // kFitted: the fitted costs where they hold; kUnfitted: the costs above for every shape; kEarly: those without the small tiles
 enum Costs { kFitted, kUnfitted, kEarly };
@@ -97,6 +111,7 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
     if (M <= 0 || N <= 0 || chunks == 0) return best;      // nothing to tile (empty output or empty reduction)
     double best_t = 1e300;
     const bool fit = costs == kFitted && M >= 128 && N >= 128 && K >= (outer ? 256 : 512);
+    const bool whole = M % 64 == 0 && N % 64 == 0;
     for (int t = 0; t < kNumTiles; ++t) {
         if (t == 4 && K % 256 != 0) continue;
         // The small tiles are for outputs that leave CUs idle with 128 x 128 workgroups: there the time is the chain of a
@@ -107,27 +122,29 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
         // 64 x 64, 42 with 128 x 192), and a sliver of an output with
         // rows that are mostly padding.  With 1 x 128 outer blocks the same holds (2048 x 1024 x 1024: 19.8 us with 128 x 192),
         // a little earlier where only the 64 x 64 tile exists.
-        if (t >= 5) {
-            if (early) break;
+        if (t == 5 || t == 6) {
+            if (early) continue;
             const int64_t least = outer ? 256 : 128, tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
             if (M < least || N < least || tiles128 > (outer && K % 256 != 0 ? 3 * kNumCU / 8 : kNumCU / 2)) continue;
         }
-        if (t == 6 && K % 256 != 0) continue;
+        if (t == 7 && (!fit || !whole || outer)) continue;
         if (t == 0 && outer) continue;                      // block mode keeps two accumulator sets: at most 2 x 4 tiles per wave
         const int64_t bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
         const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         for (int split = 1; split <= 16; ++split) {
-            if (split > 1 && chunks / split < 8) break;
+            if (split > 1 && (chunks / split < 8 || t == 7)) break;
             int64_t cps = (chunks + split - 1) / split;
             if (chunks % 4 == 0) cps = (cps + 3) / 4 * 4;                       // splits on 256-k boundaries
             else if (outer) cps = (cps + 1) / 2 * 2;                            // block mode: on 128-k boundaries
             if (split > 1 && (chunks + cps - 1) / cps != split) continue;      // same launch as a smaller split
-            if (t >= 5 && cps > 16 * kNC) continue;                                          // small tiles: at most 16 stages
+            const bool kw = fit && whole && waves_split_k(t, cps, outer);
+            if (t == 6 && K % 256 != 0 && !kw) continue;             // the other kernel has no such instantiation
+            if (t >= 5 && !kw && cps > 16 * kNC) continue;                                          // small tiles: at most 16 stages
             const int64_t wgs = tiles * split;
             const double stages = (double)((cps + kNC - 1) / kNC);
             // workgroups sharing a CU slow each other down (128 x 128 tiles: up to three per CU)
             const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU;
-            const TileCfg &cfg = fit ? kTilesFit[outer][t] : kTiles[t];
+            const TileCfg &cfg = !fit ? kTiles[t] : t >= 5 && !kw ? kSmallRagged[outer][t - 5] : kTilesFit[outer][t];
             // A third 128 x 128 workgroup with outer blocks still runs beside the other two when it makes the launch a single round
             // (513 to 768 tiles in one piece: 16640 x 640 x 256 17.8 us, 21.8 with 256 x 128; 76 shapes 1.07 times as fast, 0.98 at
             // worst); above K = 3072 split plans are the better ones (1600 x 5888 x 8320: 279 us with 256 x 128 in three, 311), and
@@ -138,13 +155,16 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
             // blocks 37.5 against 28.2 us, 106 x 8529 x 13056 63.6 against 47.0; 1.75 without one, where 1.9 gave short reductions
             // 256 x 256 tiles - 12864 x 4288 x 256 55.7 us against 46.4)
             const double slow = conc == 1 ? 1.0
-                                : fit     ? (conc > 2 ? 1.95 : t >= 5 ? 1.4 : outer ? 1.7 : 1.58)
+                                : fit     ? (conc > 2 ? 1.95 : t >= 5 && !kw ? 1.4 : outer ? 1.7 : 1.58)
                                 : conc == 2 ? (t == 4 && split > 1 && !early ? 1.9 : 1.75) : 2.35;
             const int64_t waves = (wgs + kNumCU * conc - 1) / (kNumCU * conc);
+            // 128 x 128 with split waves: a stage takes longer the more CUs draw on the L2 caches (144 workgroups 0.64 us, 198 0.76, 256 0.8)
+            const double t_stage = t == 7 ? 0.55 + 0.29 * (wgs < kNumCU ? (double)wgs / kNumCU : 1.0) : cfg.t_stage;
             // unfitted block mode: the per-block rescale of the accumulators makes a stage about a third longer
-            double time = fit ? (double)waves * (stages * cfg.t_stage + cfg.t_fixed) * slow
+            double time = fit ? (double)waves * (stages * t_stage + cfg.t_fixed) * slow
                               : (double)waves * (stages * cfg.t_stage * (outer ? 1.35 : 1.0) * slow + cfg.t_fixed);
-            if (split > 1) time += 4.0 + (double)(split + 1) * (double)(M * N) * 4.0 / 3.5e6;   // partials out and back in
+            // partials out and back in (768 x 768 x 8192: 64 x 64 tiles of gemm_kw_kernel in three 22.1 us, in one piece 22.6)
+            if (split > 1) time += (kw && !outer ? 3.2 : 4.0) + (double)(split + 1) * (double)(M * N) * 4.0 / 3.5e6;
             if (time < best_t) { best_t = time; best = Plan{t, split, (int)cps}; }
         }
     }
@@ -218,7 +238,10 @@ hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K,
          {launch_gemm_inst_ps1_out0_outer0, launch_gemm_inst_ps1_out1_outer0, launch_gemm_inst_ps1_out2_outer0}},
         {{launch_gemm_inst_ps0_out0_outer1, launch_gemm_inst_ps0_out1_outer1, launch_gemm_inst_ps0_out2_outer1},
          {launch_gemm_inst_ps1_out0_outer1, launch_gemm_inst_ps1_out1_outer1, launch_gemm_inst_ps1_out2_outer1}}};
-    hipError_t e = inst[outer ? 1 : 0][ps ? 1 : 0][split > 1 ? 2 : (out_f32 ? 1 : 0)](p.tile, g, grid, st);
+    static const InstFn kw[2][3] = {{launch_gemm_kw_out0_outer0, launch_gemm_kw_out1_outer0, launch_gemm_kw_out2_outer0},
+                                    {launch_gemm_kw_out0_outer1, launch_gemm_kw_out1_outer1, launch_gemm_kw_out2_outer1}};
+    const int kind = split > 1 ? 2 : (out_f32 ? 1 : 0);
+    hipError_t e = (waves_split_k(p.tile, p.chunks_per_split, outer) ? kw[outer ? 1 : 0][kind] : inst[outer ? 1 : 0][ps ? 1 : 0][kind])(p.tile, g, grid, st);
     if (e != hipSuccess) return e;
     if (split > 1) {
         const int64_t mn = M * N;

@@ -39,5 +39,11 @@ TJ_DECL_GEMM_INST(1, 0, 0) TJ_DECL_GEMM_INST(1, 1, 0) TJ_DECL_GEMM_INST(1, 2, 0)
 TJ_DECL_GEMM_INST(0, 0, 1) TJ_DECL_GEMM_INST(0, 1, 1) TJ_DECL_GEMM_INST(0, 2, 1)
 TJ_DECL_GEMM_INST(1, 0, 1) TJ_DECL_GEMM_INST(1, 1, 1) TJ_DECL_GEMM_INST(1, 2, 1)
 #undef TJ_DECL_GEMM_INST
+// The kernel whose waves split the reduction, for any K >= 256 (outer 1: 768): tile 5 64x64, 6 64x128, 7 128x128 (outer 0 only).
+#define TJ_DECL_GEMM_KW(out, outer) \
+    hipError_t launch_gemm_kw_out##out##_outer##outer(int tile, const GemmArgs &g, dim3 grid, hipStream_t st);
+TJ_DECL_GEMM_KW(0, 0) TJ_DECL_GEMM_KW(1, 0) TJ_DECL_GEMM_KW(2, 0)
+TJ_DECL_GEMM_KW(0, 1) TJ_DECL_GEMM_KW(1, 1) TJ_DECL_GEMM_KW(2, 1)
+#undef TJ_DECL_GEMM_KW
 
 }  // namespace tj

@@ -27,7 +27,7 @@ __device__ __forceinline__ half2_t scale_pair(uint32_t sc)
 {
     // E4M3 byte << 7 is the FP16 pattern of S_block * 2^-8 (same field layout, bias 15 vs 7; E4M3 subnormals become
     // FP16 subnormals of the same value)
-    return __builtin_bit_cast(half2_t, sc * 0x00800080u);
+    return __builtin_bit_cast(half2_t, __umul24(sc, 0x00800080u));
 }
 
 // eight codes (one dword) times the block scale -> eight FP16 holding P * S_block * 2^-4.  The conversion's scale
@@ -69,6 +69,60 @@ __device__ __forceinline__ const void *to_scalar(const void *p)
 }
 
 __device__ __forceinline__ uint32_t pick(uint4 v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+
+// workgroup -> tile: consecutive ids of one XCD (ids are dealt round-robin over 8 XCDs) walk
+// down a column of tiles, in groups of 8 tile rows
+__device__ __forceinline__ void tile_of_workgroup(const GemmArgs &g, int &tile_m, int &tile_n)
+{
+    const int total = g.tiles_m * g.tiles_n;
+    int pid = blockIdx.x;
+    {
+        const int per_xcd = total / 8;
+        if (pid < per_xcd * 8) pid = (pid & 7) * per_xcd + (pid >> 3);
+    }
+    constexpr int GROUP = 8;
+    const int group_sz = GROUP * g.tiles_n;
+    const int gid = pid / group_sz;
+    const int first_m = gid * GROUP;
+    const int gm = (g.tiles_m - first_m) < GROUP ? (g.tiles_m - first_m) : GROUP;
+    tile_m = first_m + (pid % group_sz) % gm;
+    tile_n = (pid % group_sz) / gm;
+}
+
+// 1 x 128 outer blocks, end of a block: total += block sum * S_A[m] * S_B[n].  ga, gb: the block's outer scales of the wave's
+// rows of A and B, in LDS.  The side that varies with the accumulator element (columns when SWAP, rows otherwise) is read as four
+// runs of four consecutive floats, the other side is one float per lane and tile.
+template <int TM, int TN, bool SWAP>
+__device__ __forceinline__ void rescale_add(float16_t (&acc)[TM][TN], const float16_t (&part)[TM][TN], const float *ga, const float *gb,
+                                            int lr, int kg)
+{
+    float s_lane[SWAP ? TM : TN];
+    if (SWAP) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) s_lane[i] = ga[i * 32 + lr];
+    } else {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) s_lane[j] = gb[j * 32 + lr];
+    }
+#pragma unroll
+    for (int v = 0; v < (SWAP ? TN : TM); ++v) {
+        const float *base = (SWAP ? gb : ga) + v * 32 + 4 * kg;
+        float4 sv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sv[q] = *reinterpret_cast<const float4 *>(base + 8 * q);
+#pragma unroll
+        for (int w = 0; w < (SWAP ? TM : TN); ++w) {
+            const int i = SWAP ? w : v, j = SWAP ? v : w;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc[i][j][4 * q + 0] = __builtin_fmaf(part[i][j][4 * q + 0], sv[q].x * s_lane[w], acc[i][j][4 * q + 0]);
+                acc[i][j][4 * q + 1] = __builtin_fmaf(part[i][j][4 * q + 1], sv[q].y * s_lane[w], acc[i][j][4 * q + 1]);
+                acc[i][j][4 * q + 2] = __builtin_fmaf(part[i][j][4 * q + 2], sv[q].z * s_lane[w], acc[i][j][4 * q + 2]);
+                acc[i][j][4 * q + 3] = __builtin_fmaf(part[i][j][4 * q + 3], sv[q].w * s_lane[w], acc[i][j][4 * q + 3]);
+            }
+        }
+    }
+}
 
 // Epilogue of both product kernels: outer scales, conversion, stores.
 // SWAP (bf16 output): a lane holds one output row (m = lane % 32) and, per 32 x 32 block, four runs of four consecutive
@@ -232,22 +286,8 @@ __global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) voi
     const int lr = lane & 31, kg = lane >> 5;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem_raw;
 
-    // workgroup -> tile: consecutive ids of one XCD (ids are dealt round-robin over 8 XCDs) walk
-    // down a column of tiles, in groups of 8 tile rows
-    const int total = g.tiles_m * g.tiles_n;
-    int pid = blockIdx.x;
-    {
-        const int per_xcd = total / 8;
-        if (pid < per_xcd * 8) pid = (pid & 7) * per_xcd + (pid >> 3);
-    }
-    constexpr int GROUP = 8;
-    const int group_sz = GROUP * g.tiles_n;
-    const int gid = pid / group_sz;
-    const int first_m = gid * GROUP;
-    const int gm = (g.tiles_m - first_m) < GROUP ? (g.tiles_m - first_m) : GROUP;
-    const int tile_m = first_m + (pid % group_sz) % gm;
-    const int tile_n = (pid % group_sz) / gm;
-
+    int tile_m, tile_n;
+    tile_of_workgroup(g, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int64_t chunks_total = g.K / 64;
     const int64_t cbeg = (int64_t)blockIdx.z * g.chunks_per_split;
@@ -265,7 +305,7 @@ __global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) voi
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    float16_t part[OUTER ? TM : 1][OUTER ? TN : 1];      // OUTER: the running sum of the current 128-k block
+    float16_t part[TM][TN];      // OUTER: the running sum of the current 128-k block
     float16_t zero16;
 #pragma unroll
     for (int e = 0; e < 16; ++e) zero16[e] = 0.0f;
@@ -509,35 +549,8 @@ __global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) voi
                 // end of the stage = end of outer block kt: total += stage_sum * S_A[m] * S_B[n].  The block's scales
                 // landed before the previous stage's barrier; ring slot kt % 4 is next written by the copies of stage
                 // kt + 4, which are issued after the NEXT stage's barrier, so every wave is done reading by then.
-                // The side that varies with the accumulator element (columns when SWAP, rows otherwise) is read as four
-                // runs of four consecutive floats, the other side is one float per lane and tile.
                 const float *gsr = reinterpret_cast<const float *>(smem_raw + GS_BASE) + (kt & 3) * ROWS;
-                float s_lane[SWAP ? TM : TN];
-                if (SWAP) {
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) s_lane[i] = gsr[(wm * TM + i) * 32 + lr];
-                } else {
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) s_lane[j] = gsr[BM + (wn * TN + j) * 32 + lr];
-                }
-#pragma unroll
-                for (int v = 0; v < (SWAP ? TN : TM); ++v) {
-                    const float *base = SWAP ? gsr + BM + (wn * TN + v) * 32 + 4 * kg : gsr + (wm * TM + v) * 32 + 4 * kg;
-                    float4 sv[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) sv[q] = *reinterpret_cast<const float4 *>(base + 8 * q);
-#pragma unroll
-                    for (int w = 0; w < (SWAP ? TM : TN); ++w) {
-                        const int i = SWAP ? w : v, j = SWAP ? v : w;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            acc[i][j][4 * q + 0] = __builtin_fmaf(part[i][j][4 * q + 0], sv[q].x * s_lane[w], acc[i][j][4 * q + 0]);
-                            acc[i][j][4 * q + 1] = __builtin_fmaf(part[i][j][4 * q + 1], sv[q].y * s_lane[w], acc[i][j][4 * q + 1]);
-                            acc[i][j][4 * q + 2] = __builtin_fmaf(part[i][j][4 * q + 2], sv[q].z * s_lane[w], acc[i][j][4 * q + 2]);
-                            acc[i][j][4 * q + 3] = __builtin_fmaf(part[i][j][4 * q + 3], sv[q].w * s_lane[w], acc[i][j][4 * q + 3]);
-                        }
-                    }
-                }
+                rescale_add<TM, TN, SWAP>(acc, part, gsr + wm * TM * 32, gsr + BM + wn * TN * 32, lr, kg);
             }
             buf = nbuf;
         }
@@ -578,8 +591,7 @@ hipError_t launch_tile(int tile, const GemmArgs &g, dim3 grid, hipStream_t st)
         case 4:
             if constexpr (PS) return launch_cfg<2, 3, OUT, true, OUTER>(g, grid, st);
             else return hipErrorInvalidValue;
-        case 5:
-            return launch_cfg<1, 1, OUT, PS, OUTER>(g, grid, st);
+        case 5: return launch_cfg<1, 1, OUT, PS, OUTER>(g, grid, st);
         case 6:
             if constexpr (PS) return launch_cfg<1, 2, OUT, true, OUTER>(g, grid, st);
             else return hipErrorInvalidValue;

@@ -482,6 +482,36 @@ def test_gemm_small_tiles(outer, M, N, K, tile, split, out_dtype):
     check_product(got[torch.from_numpy(rows).cuda()], ref, absref, "gemm small tiles %dx%dx%d" % (M, N, K))
 
 
+# (outer mode, M, N, K, tile): whole outputs whose workgroups' waves split the reduction in stages of 256 k (512 with outer
+# blocks), a chunk of 64 (a block of 128) per wave: a single stage; last stages with one, two or three waves' work; odd numbers of
+# stages; one row of tiles; tiles that end outside the output
+SPLIT_WAVES_SHAPES = [(0, 128, 256, 256, (64, 64)), (0, 192, 448, 576, (64, 64)), (0, 704, 192, 704, (64, 64)), (0, 704, 832, 1600, (64, 64)),
+                      (0, 256, 512, 2048, (64, 64)), (0, 2048, 1024, 1024, (64, 128)), (0, 1472, 1472, 2112, (128, 128)),
+                      (0, 1984, 1600, 2048, (128, 128)), (1, 384, 512, 1152, (64, 64)), (1, 256, 1408, 2944, (64, 64)),
+                      (1, 384, 256, 896, (64, 64)), (1, 1664, 896, 1408, (64, 128)), (1, 2048, 1024, 1024, (64, 128))]
+
+
+@pytest.mark.parametrize("outer,M,N,K,tile", SPLIT_WAVES_SHAPES)
+@pytest.mark.parametrize("out_dtype", [0, 1])
+def test_gemm_waves_split_the_reduction(outer, M, N, K, tile, out_dtype):
+    assert tj.binding.gemm_plan(M, N, K, outer) == (*tile, 1)
+    if outer:
+        A = oracle.quantize_bf16(_block_operand(M, K, 780 + N, 1.0), 0, 0, outer=oracle.OUTER_BLOCK128)
+        B = oracle.quantize_bf16(_block_operand(N, K, 781 + M, 0.02), 0, 1, outer=oracle.OUTER_BLOCK128, seed=6)
+    else:
+        A = oracle.quantize_bf16(wl.normal_bf16((M, K), 1.0, 780 + N, 1e-2, 50.0), 0, 0)
+        B = oracle.quantize_bf16(wl.normal_bf16((N, K), 0.02, 781 + M), 0, 1, seed=6)
+    a, b = to_dev(A), to_dev(B)
+    got, again = tj.gemm_nt(a, b, out_dtype), tj.gemm_nt(a, b, out_dtype)
+    torch.cuda.synchronize()
+    assert torch.equal(got, again)                            # fixed summation order
+    rng = np.random.default_rng(M + 3 * N + K)
+    tiles = np.arange(0, M, tile[0])
+    rows = np.unique(np.concatenate([tiles, np.minimum(tiles + tile[0] - 1, M - 1), rng.choice(M, 32, replace=False)]))
+    ref, absref = oracle.gemm_nt(A, B, rows_a=rows)
+    check_product(got[torch.from_numpy(rows).cuda()], ref, absref, "gemm split waves %dx%dx%d" % (M, N, K))
+
+
 # (outer mode, M, N, K, tile): whole tiles, K a multiple of 256, more workgroups than the chip holds of that tile at
 # once and not a multiple of that number, so tiles start and end at different times on one compute unit.  K = 256 is the
 # shortest reduction with paired scale fetch (two stages, one scale pair), 768 a typical short one.
