@@ -89,7 +89,6 @@ const TileCfg kTilesFit[2][kNumTiles] = {
 // 2752 x 1088 x 4416 33.5, 41.5); with outer blocks 64 x 64 4.6 + 0.41 and 64 x 128 5.6 + 0.78.  Ragged outputs keep the costs that the
 // 64 x 64 and 64 x 128 tiles have in gemm_nt_kernel, whichever kernel runs them.
 const TileCfg kSmallRagged[2][2] = {{{1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}}, {{1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
-constexpr int kNumCU = 256;
 
 struct Plan { int tile; int split; int chunks_per_split; };
 
@@ -155,8 +154,10 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
             // blocks 37.5 against 28.2 us, 106 x 8529 x 13056 63.6 against 47.0; 1.75 without one, where 1.9 gave short reductions
             // 256 x 256 tiles - 12864 x 4288 x 256 55.7 us against 46.4)
             const double slow = conc == 1 ? 1.0
-                                : fit     ? (conc > 2 ? 1.95 : t >= 5 && !kw ? 1.4 : outer ? 1.7 : 1.58)
+                                : fit     ? (conc > 2 ? 1.95 : t >= 5 && !kw ? 1.4 : outer ? (K < 512 || split > 1 ? 1.7 : 1.52) : 1.58)
                                 : conc == 2 ? (t == 4 && split > 1 && !early ? 1.9 : 1.75) : 2.35;
+            // (outer blocks: 1.52 is the 128 x 128 tile's since it keeps both accumulator sets in ordinary registers; split plans keep
+            // the 1.7 from before, so that no product comes to need a workspace by it)
             const int64_t waves = (wgs + kNumCU * conc - 1) / (kNumCU * conc);
             // 128 x 128 with split waves: a stage takes longer the more CUs draw on the L2 caches (144 workgroups 0.64 us, 198 0.76, 256 0.8)
             const double t_stage = t == 7 ? 0.55 + 0.29 * (wgs < kNumCU ? (double)wgs / kNumCU : 1.0) : cfg.t_stage;

@@ -9,6 +9,7 @@
 namespace tj {
 
 constexpr int kGemmThreads = 256;
+constexpr int kNumCU = 256;
 
 struct GemmArgs {
     const uint8_t *a_codes, *a_scales;

@@ -251,8 +251,13 @@ struct OpFrags {
 // MFMA takes zero as addend) and at its end  total += stage_sum * S_A[m, kb] * S_B[n, kb]  in FP32 (two vector
 // instructions per accumulator element and stage, which is why this mode keeps at most 2 x 4 tiles per wave).  The
 // outer scales of a stage travel global -> LDS with the same direct copies, one float per row, into a ring of four.
-template <int TM, int TN, int NC, int OUT, bool PS, int OUTER>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
-__global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) void gemm_nt_kernel(GemmArgs g)
+// PACK (2 x 2 tiles with OUTER): two waves per SIMD asked for.  Both accumulator sets then live in ordinary registers (210 in all),
+// where one wave's allowance puts the matrix instructions' results into accumulation registers, from which the rescale first copies
+// them: one instruction in seven of the loop.  With two workgroups on a CU, where the loop is bound by its instructions, this is the
+// faster form (1664 x 6528 x 896 41.7 -> 33.9 us; 8192 x 4096 x 4096 on this tile 345, on 256 x 128 353); a workgroup with the CU to
+// itself waits for results more often and is 6 % slower with it (1280 x 2688 x 5760 77.7 against 82.6).
+template <int TM, int TN, int NC, int OUT, bool PS, int OUTER, bool PACK>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
+__global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1) void gemm_nt_kernel(GemmArgs g)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN, ROWS = BM + BN;
     constexpr int SLOTS = 2 * NC;                       // 16-byte pieces per row per stage
@@ -563,12 +568,12 @@ __global__ __launch_bounds__(kThreads, (TM * TN * (OUTER + 1) >= 8 ? 1 : 2)) voi
     store_tile<TM, TN, OUT, SWAP, OUTER>(acc, g, m0, n0, wm, wn, lr, kg, smem_raw);
 }
 
-template <int TM, int TN, int OUT, bool PS, int OUTER>
+template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK = false>
 hipError_t launch_cfg(const GemmArgs &g, dim3 grid, hipStream_t st)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
     constexpr int lds = 3 * ((BM + BN) * 2 * kNC * 16 + (BM + BN) * (PS ? 16 : kNC * 4)) + (OUTER ? 4 * (BM + BN) * 4 : 0);
-    auto kern = gemm_nt_kernel<TM, TN, kNC, OUT, PS, OUTER>;
+    auto kern = gemm_nt_kernel<TM, TN, kNC, OUT, PS, OUTER, PACK>;
     // once per instantiation; the initialisation of a function-local static is thread-safe
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -595,7 +600,11 @@ hipError_t launch_tile(int tile, const GemmArgs &g, dim3 grid, hipStream_t st)
         case 6:
             if constexpr (PS) return launch_cfg<1, 2, OUT, true, OUTER>(g, grid, st);
             else return hipErrorInvalidValue;
-        default: return launch_cfg<2, 2, OUT, PS, OUTER>(g, grid, st);
+        default:
+            if constexpr (OUTER == 1) {
+                if ((int64_t)grid.x * grid.z > kNumCU) return launch_cfg<2, 2, OUT, PS, OUTER, true>(g, grid, st);
+            }
+            return launch_cfg<2, 2, OUT, PS, OUTER>(g, grid, st);
     }
 }
 
