@@ -30,11 +30,13 @@ __device__ __forceinline__ void store8(float *p, const F8 &x)
     *reinterpret_cast<float4 *>(p + 4) = make_float4(x.v[4], x.v[5], x.v[6], x.v[7]);
 }
 
-// Q(x) for the lane's 8 weights; all 16 lanes of the outer block must be active.  SCORE: also the sensitivity score of
-// Appendix Alg. 3, |x - Q(x)| / binwidth(Q(x)), binwidth = (length of the interval of scaled values that round to the
-// code's magnitude) * RN(S_block * S_global); 0 in a block whose scale is 0.
-template <bool SCORE>
-__device__ __forceinline__ F8 quant_dequant8_t(const F8 &x, const float *inv_tab, F8 *score)
+// The lane's 8 weights quantized; all 16 lanes of the outer block must be active.
+struct Quant8 {
+    uint32_t codes;      // eight E2M1 codes
+    uint32_t top;        // pattern of the largest magnitude of the lane's weights
+    float sb, S_g;       // block and outer scale
+};
+__device__ __forceinline__ Quant8 quantize8(const F8 &x, const float *inv_tab)
 {
     uint32_t hm = 0;
 #pragma unroll
@@ -56,27 +58,17 @@ __device__ __forceinline__ F8 quant_dequant8_t(const F8 &x, const float *inv_tab
     codes = e2m1_rtn_pair<1>(codes, x.v[2] * r, x.v[3] * r);
     codes = e2m1_rtn_pair<2>(codes, x.v[4] * r, x.v[5] * r);
     codes = e2m1_rtn_pair<3>(codes, x.v[6] * r, x.v[7] * r);
-    const float sb = e4m3_value(sc);
-    const float2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, 1.0f, 0) * sb;   // exact: 6 significant bits
-    const float2_t p1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, 1.0f, 1) * sb;
-    const float2_t p2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, 1.0f, 2) * sb;
-    const float2_t p3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, 1.0f, 3) * sb;
-    const F8 q{{p0.x * os.S_g, p0.y * os.S_g, p1.x * os.S_g, p1.y * os.S_g, p2.x * os.S_g, p2.y * os.S_g, p3.x * os.S_g,
-                p3.y * os.S_g}};
-    if (SCORE) {
-        const float unit = sb * os.S_g;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t m = (codes >> (4 * i)) & 7u;
-            const float bin = m < 4 ? 0.5f : m == 4 ? 0.75f : m == 6 ? 1.5f : 1.0f;
-            const float width = bin * unit;
-            const float num = fabsf(x.v[i] - q.v[i]);
-            score->v[i] = width == 0.0f ? 0.0f : num / width;
-        }
-    }
-    return q;
+    return Quant8{codes, hm, e4m3_value(sc), os.S_g};
 }
-__device__ __forceinline__ F8 quant_dequant8(const F8 &x, const float *inv_tab) { return quant_dequant8_t<false>(x, inv_tab, nullptr); }
+__device__ __forceinline__ F8 dequantize8(const Quant8 &k)
+{
+    const float2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(k.codes, 1.0f, 0) * k.sb;   // exact: 6 significant bits
+    const float2_t p1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(k.codes, 1.0f, 1) * k.sb;
+    const float2_t p2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(k.codes, 1.0f, 2) * k.sb;
+    const float2_t p3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(k.codes, 1.0f, 3) * k.sb;
+    return F8{{p0.x * k.S_g, p0.y * k.S_g, p1.x * k.S_g, p1.y * k.S_g, p2.x * k.S_g, p2.y * k.S_g, p3.x * k.S_g, p3.y * k.S_g}};
+}
+__device__ __forceinline__ F8 quant_dequant8(const F8 &x, const float *inv_tab) { return dequantize8(quantize8(x, inv_tab)); }
 
 // nchunks = C * D / 8 is a multiple of 16 (D % 128 == 0), so a 16-lane row is either whole or absent
 __global__ __launch_bounds__(kThreads) void osci_update_kernel(const float *W, float *W_prev, float *dist_m, float *dist_q,
@@ -166,11 +158,11 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
 // Scores are non-negative binary32 values, so they order like their bit patterns (a NaN counts as one value above
 // infinity).  The k-th largest pattern is found by
 // narrowing an interval [lo, lo + span) that holds it: a histogram pass over the tensor counts the patterns of the
-// interval in 2048 bins, and the workgroup that finishes last picks the bin.  The first pass splits the patterns where
+// interval in bins (2048, then 32768), and the workgroup that finishes last picks the bin.  The first pass splits the patterns where
 // scores live (|x - Q(x)| / binwidth is at most 1, and all but a few lie above 2^-8) into 256 bins per octave, with one
-// open bin below and one above: 15 bits are left after it, 4 after the second pass, none after the third.  (An equal
+// open bin below and one above: 15 bits are left after it, none after the second pass.  (An equal
 // split of all patterns put the scores of normal weights into a dozen bins, and their LDS counters became the bound: 76
-// us for the first pass on 8192 x 1024, 19 us now.)  Only a threshold in an open bin needs the fourth pass; otherwise it
+// us for the first pass on 8192 x 1024, 19 us now.)  Only a threshold in an open bin needs the third pass; otherwise it
 // ends at once.  The tensor is then compacted in index order: a count of (greater, equal) per 2048-element tile, whose
 // last workgroup turns the counts into exclusive sums, and a pass that ranks every selected element and writes its index
 // and the states of the tracked subset.  Every pass recomputes Q(W) (the scores are never stored: the point of the
@@ -181,6 +173,20 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
 //
 // Additions to one address are executed one after the other (about 8 ns each), so the passes that end with additions to
 // shared counters run as at most kPassWgs workgroups of 1024 threads: 256 of them cost 2 us, 1024 of 256 threads 8 us.
+//
+// The sensitivity score of Appendix Alg. 3 is |x - Q(x)| / binwidth(Q(x)), binwidth = (length of the interval of scaled values
+// that round to the code's magnitude) * RN(S_block * S_global); 0 in a block whose scale is 0.  Its correctly rounded quotient was
+// a third of the passes' instructions, and the choice of the bin's length a fifth.  The passes therefore look at an estimate, num *
+// rcp(unit) * (1 / bin), and take the quotient only where the estimate is within kNear patterns of a value at which their
+// answer changes: a boundary between bins in the first pass (one chunk of 64 lanes in four), the interval that holds the
+// threshold in a later one (these elements are put aside and divided at the end, all lanes busy), the threshold itself after
+// that.  Error of the estimate, in units of 2^-24 relative: reciprocal 2, the two products 2, 4/3 and 2/3 rounded 1, the
+// rounding of 0.75 * unit or 1.5 * unit 1, of the quotient 1; 7 in all, at most 7 patterns, 14 across a power of two.
+// 8192 x 1024, 5 % selected: passes of 18.8, 15.8, 15.5, 4.6 (ends at once), 21.3 (count) and 17.4 us (emit) before; 14.3, 19.5, 4.5
+// (ends at once), 17.3 and 14.2 with the estimate, the choice of the first bin in the second pass, and the rest of the interval
+// resolved by that pass in 32768 bins.  Two chunks in flight per thread instead of one changed nothing: the passes wait for the
+// vector ALU, not for memory.
+constexpr uint32_t kNear = 16;
 constexpr int kTile = kThreads * 8;
 constexpr int kPassThreads = 1024, kPassWgs = 256, kPassWaves = kPassThreads / 64;
 
@@ -189,7 +195,7 @@ struct SelState {
     uint32_t kneed;       // how many elements are still to be taken among those of the interval
     uint32_t thr;         // width 0: the key of the k-th largest score
     uint32_t ties;        // elements equal to thr that belong to the selection (the first ones in index order)
-    uint32_t done[5];     // workgroups that have finished, per pass
+    uint32_t done[3];     // workgroups that have finished, per pass
 };
 
 __device__ __forceinline__ uint32_t load_dev(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -208,9 +214,49 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t *counter, uint32_t *flag
 __global__ __launch_bounds__(kThreads) void osci_zero_kernel(SelState *st, uint32_t *hist)
 {
     const int i = blockIdx.x * kThreads + threadIdx.x;
-    if (i < kBins) hist[i] = 0;
-    if (i < 5) st->done[i] = 0;
+    if (i < kFirstBins + kBins) hist[i] = 0;
+    if (i < 3) st->done[i] = 0;
 }
+
+// 1 / bin, by the code's magnitude
+__device__ __forceinline__ void fill_inv_bins(float *tab)
+{
+    if (threadIdx.x < 8) tab[threadIdx.x] = threadIdx.x < 4 ? 2.0f : threadIdx.x == 4 ? 4.0f / 3.0f : threadIdx.x == 6 ? 2.0f / 3.0f : 1.0f;
+}
+__device__ __forceinline__ float bin_width(uint32_t codes, int i, float unit)
+{
+    const uint32_t m = (codes >> (4 * i)) & 7u;
+    return (m < 4 ? 0.5f : m == 4 ? 0.75f : m == 6 ? 1.5f : 1.0f) * unit;
+}
+__device__ __forceinline__ uint32_t score_bits(float num, float width) { return f2u(width == 0.0f ? 0.0f : num / width); }
+
+// Patterns of the estimated scores of the lane's 8 weights, and the factors of the exact ones.  ok: the estimate holds - the unit is
+// a normal number whose reciprocal is one too, and every weight of the lane is finite and at most 8 units (so is its
+// distance from Q(x), and nothing overflows).
+struct Scores8 {
+    uint32_t p[8];
+    F8 q, num;
+    float unit;
+    uint32_t codes;
+    bool ok;
+};
+__device__ __forceinline__ Scores8 scores8(const F8 &x, const float *inv_tab, const float *inv_bins)
+{
+    Scores8 s;
+    const Quant8 k = quantize8(x, inv_tab);
+    s.q = dequantize8(k);
+    s.codes = k.codes;
+    s.unit = k.sb * k.S_g;
+    const float y = __builtin_amdgcn_rcpf(s.unit);
+    s.ok = s.unit > 0x1p-100f && s.unit < 0x1p100f && u2f(k.top) * y <= 8.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        s.num.v[i] = fabsf(x.v[i] - s.q.v[i]);
+        s.p[i] = f2u(s.num.v[i] * y * inv_bins[(k.codes >> (4 * i)) & 7u]);
+    }
+    return s;
+}
+__device__ __forceinline__ uint32_t exact_score(const Scores8 &s, int i) { return score_bits(s.num.v[i], bin_width(s.codes, i, s.unit)); }
 
 // exclusive prefix sum of v over the workgroup's threads (thread order) and their total; red: one word of LDS per wave
 template <int WAVES>
@@ -236,87 +282,181 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *r
     return base + incl - v;
 }
 
-// PASS 0: the whole range; later passes: the interval of the state
-template <int PASS>
-__global__ __launch_bounds__(kPassThreads) void osci_hist_kernel(const float *W, int64_t nchunks, SelState *st, uint32_t *hist, uint32_t k_total)
+// The bin, counted from the top, that holds the kneed-th key of the BINS counted in LDS, and the kneed that is left inside
+// it; in every thread.  A thread's BINS / kPassThreads consecutive bins are read in rotated order, so that the lanes of a wave meet
+// different banks.
+template <int BINS>
+__device__ __forceinline__ uint2 pick_bin(const uint32_t *bins, uint32_t *red, uint2 *picked, uint32_t kneed)
 {
-    __shared__ float inv_tab[128];
-    __shared__ uint32_t bins[kBins];
-    __shared__ uint32_t red[kPassWaves], flag;
-    const SelInterval iv = PASS == 0 ? SelInterval{0, 0, 0} : st->iv;
-    if (PASS > 0 && iv.width == 0) return;                 // uniform: the threshold is known
+    constexpr int PER = BINS / kPassThreads;
+    const uint32_t *own = bins + (kPassThreads - 1 - threadIdx.x) * PER;   // thread 0 holds the top ones
+    uint32_t n = 0, total;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) n += own[(i + threadIdx.x) & (PER - 1)];
+    uint32_t above = block_exclusive_scan<kPassWaves>(n, red, total);
+    if (above < kneed && kneed <= above + n) {             // exactly one thread
+        int i = PER - 1;
+        while (kneed > above + own[i]) above += own[i--];  // ends at own[0] at the latest
+        *picked = make_uint2((uint32_t)(own - bins + i), kneed - above);
+    }
+    __syncthreads();
+    return *picked;
+}
+
+// the first pass: the whole range
+__global__ __launch_bounds__(kPassThreads) void osci_first_kernel(const float *W, int64_t nchunks, uint32_t *hist)
+{
+    __shared__ float inv_tab[128], inv_bins[8];
+    __shared__ uint32_t bins[kFirstBins];
+    fill_inv_table(inv_tab);
+    fill_inv_bins(inv_bins);
+    for (int b = threadIdx.x; b < kFirstBins; b += kPassThreads) bins[b] = 0;
+    __syncthreads();
+    constexpr uint32_t kLow = (kFirstBin << 15) + 0x4000u;              // some pattern of bin 0, far from its ends
+    const int64_t stride = (int64_t)gridDim.x * kPassThreads;          // a multiple of 16: rows of 16 lanes stay whole
+    int64_t c = (int64_t)blockIdx.x * kPassThreads + threadIdx.x;
+    F8 next{};
+    if (c < nchunks) next = load8(W + c * 8);
+    for (; c < nchunks; c += stride) {
+        const F8 w = next;
+        next = load8(W + (c + stride < nchunks ? c + stride : c) * 8);   // in flight while this chunk is counted
+        Scores8 s = scores8(w, inv_tab, inv_bins);
+        uint32_t nearest = 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            s.p[i] = s.p[i] > kLow ? s.p[i] : kLow;
+            const uint32_t d = (s.p[i] + kNear) & 0x7FFFu;
+            nearest = nearest < d ? nearest : d;
+        }
+        if (!s.ok || nearest <= 2 * kNear) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s.p[i] = exact_score(s, i);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) atomicAdd(&bins[first_bin(s.p[i])], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < kFirstBins; b += kPassThreads)
+        if (bins[b]) atomicAdd(&hist[b], bins[b]);
+}
+
+// A later pass, in kBins bins.  PASS 1: the interval is the bin that every workgroup picks from the first pass's counts while its
+// first weights are on their way (by the last workgroup of the first pass the choice took 2.5 us); PASS 2: that of the state.
+constexpr int kAside = 2048;                               // elements put aside for an exact quotient
+constexpr int kLaterLds = kBins * 4 + kAside * 8;
+template <int PASS>
+__global__ __launch_bounds__(kPassThreads) void osci_later_kernel(const float *W, int64_t nchunks, SelState *st, const uint32_t *first, uint32_t *hist, uint32_t k_total)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t bins[];
+    float2 *aside = reinterpret_cast<float2 *>(bins + kBins);
+    __shared__ float inv_tab[128], inv_bins[8];
+    __shared__ uint32_t red[kPassWaves], flag, n_aside;
+    __shared__ uint2 picked;
+    const int64_t stride = (int64_t)gridDim.x * kPassThreads;
+    int64_t c = (int64_t)blockIdx.x * kPassThreads + threadIdx.x;
+    F8 next{};
+    SelInterval iv;
+    uint32_t kneed;
+    if (PASS == 1) {
+        if (c < nchunks) next = load8(W + c * 8);
+        for (int b = threadIdx.x; b < kFirstBins; b += kPassThreads) bins[b] = first[b];
+        __syncthreads();
+        const uint2 bin = pick_bin<kFirstBins>(bins, red, &picked, k_total);
+        iv = first_interval(bin.x);
+        kneed = bin.y;
+    } else {
+        iv = st->iv;
+        if (iv.width == 0) return;                         // uniform: the threshold is known
+        kneed = st->kneed;
+        if (c < nchunks) next = load8(W + c * 8);
+    }
     const uint32_t within = reach(iv);
     fill_inv_table(inv_tab);
-    for (int b = threadIdx.x; b < kBins; b += kPassThreads) bins[b] = 0;
+    fill_inv_bins(inv_bins);
+    for (int b = threadIdx.x; b < kBins / 4; b += kPassThreads) reinterpret_cast<uint4 *>(bins)[b] = make_uint4(0, 0, 0, 0);
+    if (threadIdx.x == 0) n_aside = 0;
     __syncthreads();
-    // TOP: the interval holds the NaNs, whose patterns have to be turned into their key (one more instruction per element)
-    auto count = [&](auto top) {
-        constexpr bool TOP = decltype(top)::value;
-        const int64_t stride = (int64_t)gridDim.x * kPassThreads;      // a multiple of 16: rows of 16 lanes stay whole
-        int64_t c = (int64_t)blockIdx.x * kPassThreads + threadIdx.x;
-        F8 next{};
-        if (c < nchunks) next = load8(W + c * 8);
-        for (; c < nchunks; c += stride) {
-            const F8 w = next;
-            next = load8(W + (c + stride < nchunks ? c + stride : c) * 8);   // in flight while this chunk is counted
-            F8 sc;
-            quant_dequant8_t<true>(w, inv_tab, &sc);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t b = f2u(sc.v[i]);
-                if (PASS == 0) atomicAdd(&bins[first_bin(b)], 1u);
-                else if (b - iv.lo < within) atomicAdd(&bins[later_bin(iv, TOP ? score_key(b) : b)], 1u);
-            }
-        }
+    auto count = [&](uint32_t b) {
+        if (b - iv.lo < within) atomicAdd(&bins[later_bin(iv, score_key(b))], 1u);
     };
-    if (PASS > 0 && within != iv.span) count(std::true_type{});
-    else count(std::false_type{});
+    for (; c < nchunks; c += stride) {
+        const F8 w = next;
+        next = load8(W + (c + stride < nchunks ? c + stride : c) * 8);
+        const Scores8 s = scores8(w, inv_tab, inv_bins);
+        if (s.ok) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (s.p[i] - (iv.lo - kNear) <= within + 2 * kNear) {
+                    const float width = bin_width(s.codes, i, s.unit);
+                    const uint32_t a = atomicAdd(&n_aside, 1u);
+                    if (a < kAside) aside[a] = make_float2(s.num.v[i], width);
+                    else count(score_bits(s.num.v[i], width));
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) count(exact_score(s, i));
+        }
+    }
+    __syncthreads();
+    const uint32_t n = n_aside < kAside ? n_aside : kAside;
+    for (uint32_t a = threadIdx.x; a < n; a += kPassThreads) count(score_bits(aside[a].x, aside[a].y));
     __syncthreads();
     for (int b = threadIdx.x; b < kBins; b += kPassThreads)
         if (bins[b]) atomicAdd(&hist[b], bins[b]);
-    if (!last_to_arrive(&st->done[PASS], &flag)) return;
-    // the last workgroup: thread t holds bins 2047 - 2 t and 2046 - 2 t, so that the sums run from the top
-    const uint32_t kneed = PASS == 0 ? k_total : st->kneed;
-    const int b0 = kBins - 1 - 2 * (int)threadIdx.x;
-    const uint32_t n0 = load_dev(&hist[b0]), n1 = load_dev(&hist[b0 - 1]);
-    store_dev(&hist[b0], 0u);                              // for the next pass
-    store_dev(&hist[b0 - 1], 0u);
-    uint32_t total;
-    uint32_t above = block_exclusive_scan<kPassWaves>(n0 + n1, red, total);
-    if (above < kneed && kneed <= above + n0 + n1) {       // exactly one thread
-        const bool first = kneed <= above + n0;
-        const uint32_t digit = (uint32_t)(first ? b0 : b0 - 1);
-        if (!first) above += n0;
-        const SelInterval next = PASS == 0 ? first_interval(digit) : next_interval(iv, digit);
-        st->iv = next;
-        st->thr = next.lo;
-        st->kneed = kneed - above;
-        st->ties = kneed - above;
+    if (!last_to_arrive(&st->done[PASS - 1], &flag)) return;
+    uint32_t n_all[kBins / kPassThreads];                  // all loads in flight together
+#pragma unroll
+    for (int u = 0; u < kBins / kPassThreads; ++u) n_all[u] = load_dev(&hist[u * kPassThreads + threadIdx.x]);
+#pragma unroll
+    for (int u = 0; u < kBins / kPassThreads; ++u) {
+        bins[u * kPassThreads + threadIdx.x] = n_all[u];
+        store_dev(&hist[u * kPassThreads + threadIdx.x], 0u);   // for the next pass
+    }
+    __syncthreads();
+    const uint2 bin = pick_bin<kBins>(bins, red, &picked, kneed);
+    if (threadIdx.x == 0) {
+        const SelInterval in = next_interval(iv, bin.x);
+        st->iv = in;
+        st->thr = in.lo;
+        st->kneed = bin.y;
+        st->ties = bin.y;
     }
 }
 
 // flags of the lane's 8 elements against the threshold's key: bit i of gt / eq
-__device__ __forceinline__ void score_flags(const F8 &sc, uint32_t thr, uint32_t &gt, uint32_t &eq)
+__device__ __forceinline__ void score_flags(const Scores8 &s, uint32_t thr, uint32_t &gt, uint32_t &eq)
 {
-    const uint32_t last = last_pattern(thr);
-    uint32_t ge = 0;
-    gt = 0;
+    uint32_t below = 0, nearest = 0xFFFFFFFFu;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint32_t b = f2u(sc.v[i]);
-        gt |= (b > last ? 1u : 0u) << i;
-        ge |= (b >= thr ? 1u : 0u) << i;
+    for (int i = 7; i >= 0; --i) {
+        const uint32_t d = s.p[i] - (thr - kNear);
+        nearest = nearest < d ? nearest : d;
+        below = (below << 1) | (d >> 31);                  // both lie below 2^31
     }
-    eq = ge ^ gt;
+    gt = ~below & 0xFFu;
+    eq = 0;
+    if (!s.ok || nearest <= 2 * kNear) {
+        const uint32_t last = last_pattern(thr);
+        uint32_t ge = 0;
+        gt = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t b = exact_score(s, i);
+            gt |= (b > last ? 1u : 0u) << i;
+            ge |= (b >= thr ? 1u : 0u) << i;
+        }
+        eq = ge ^ gt;
+    }
 }
 
 // (greater, equal) counts per tile; the last workgroup replaces them by their exclusive prefix sums.  A workgroup takes
 // four tiles at a time, four waves each.
 __global__ __launch_bounds__(kPassThreads) void osci_count_kernel(const float *W, int64_t nchunks, SelState *st, uint32_t *counts, int64_t ntiles)
 {
-    __shared__ float inv_tab[128];
+    __shared__ float inv_tab[128], inv_bins[8];
     __shared__ uint32_t red[2][kPassWaves], flag;
     fill_inv_table(inv_tab);
+    fill_inv_bins(inv_bins);
     __syncthreads();
     const uint32_t thr = st->thr;
     const int64_t stride = (int64_t)gridDim.x * kPassThreads;
@@ -329,11 +469,7 @@ __global__ __launch_bounds__(kPassThreads) void osci_count_kernel(const float *W
         const F8 w = next;
         if (c + stride < nchunks) next = load8(W + (c + stride) * 8);
         uint32_t gt = 0, eq = 0;
-        if (c < nchunks) {
-            F8 sc;
-            quant_dequant8_t<true>(w, inv_tab, &sc);
-            score_flags(sc, thr, gt, eq);
-        }
+        if (c < nchunks) score_flags(scores8(w, inv_tab, inv_bins), thr, gt, eq);
         // both counts fit 16 bits (2048 elements per tile)
         uint32_t n = (uint32_t)__builtin_popcount(gt) | ((uint32_t)__builtin_popcount(eq) << 16);
         for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
@@ -348,7 +484,7 @@ __global__ __launch_bounds__(kPassThreads) void osci_count_kernel(const float *W
             store_dev(&counts[2 * t + 1], sum >> 16);
         }
     }
-    if (!last_to_arrive(&st->done[4], &flag)) return;
+    if (!last_to_arrive(&st->done[2], &flag)) return;
     constexpr int kPer = 4;                                // tiles per thread and round
     uint32_t base_g = 0, base_e = 0;
     for (int64_t t0 = 0; t0 < ntiles; t0 += kPer * kPassThreads) {
@@ -380,9 +516,10 @@ __global__ __launch_bounds__(kPassThreads) void osci_count_kernel(const float *W
 __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int64_t nchunks, const SelState *st, const uint32_t *offs,
                                                              uint32_t *idx, float *wp, float *qp, float *dm, float *dq, uint32_t k)
 {
-    __shared__ float inv_tab[128];
+    __shared__ float inv_tab[128], inv_bins[8];
     __shared__ uint32_t red[4];
     fill_inv_table(inv_tab);
+    fill_inv_bins(inv_bins);
     __syncthreads();
     const int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const uint32_t thr = st->thr, ties = st->ties;
@@ -390,9 +527,9 @@ __global__ __launch_bounds__(kThreads) void osci_emit_kernel(const float *W, int
     uint32_t gt = 0, eq = 0;
     if (c < nchunks) {
         w = load8(W + c * 8);
-        F8 sc;
-        q = quant_dequant8_t<true>(w, inv_tab, &sc);
-        score_flags(sc, thr, gt, eq);
+        const Scores8 s = scores8(w, inv_tab, inv_bins);
+        q = s.q;
+        score_flags(s, thr, gt, eq);
     }
     // equal elements are ranked in index order over the whole tensor; the first `ties` of them are selected
     const uint32_t eq_tiles = offs[2 * blockIdx.x + 1], gt_tiles = offs[2 * blockIdx.x];
@@ -565,7 +702,7 @@ hipError_t launch_sparse(float *W, int64_t n, const uint32_t *idx, int64_t k, fl
 size_t osci_select_workspace_bytes(int64_t n)
 {
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    return 256 + 2048 * sizeof(uint32_t) + (size_t)ntiles * 2 * sizeof(uint32_t);
+    return 256 + (kFirstBins + kBins) * sizeof(uint32_t) + (size_t)ntiles * 2 * sizeof(uint32_t);
 }
 
 hipError_t launch_osci_select(const float *W, int64_t n, int64_t k, uint32_t *idx, float *wp, float *qp, float *dm, float *dq,
@@ -573,17 +710,24 @@ hipError_t launch_osci_select(const float *W, int64_t n, int64_t k, uint32_t *id
 {
     const int64_t nchunks = n / 8;
     if (nchunks == 0 || k == 0) return hipSuccess;
+    static const hipError_t attr = []() {                  // once; the initialisation of a function-local static is thread-safe
+        for (auto kern : {osci_later_kernel<1>, osci_later_kernel<2>}) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLaterLds);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (attr != hipSuccess) return attr;
     SelState *state = static_cast<SelState *>(ws);
     uint32_t *hist = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(ws) + 256);
-    uint32_t *counts = hist + 2048;
+    uint32_t *later = hist + kFirstBins, *counts = later + kBins;
     const int64_t ntiles = (nchunks + kThreads - 1) / kThreads;
     const int64_t want = (nchunks + kPassThreads - 1) / kPassThreads;
     const dim3 grid((unsigned)(want < kPassWgs ? want : kPassWgs)), block(kPassThreads);
-    hipLaunchKernelGGL(osci_zero_kernel, dim3(kBins / kThreads), dim3(kThreads), 0, st, state, hist);
-    hipLaunchKernelGGL(osci_hist_kernel<0>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
-    hipLaunchKernelGGL(osci_hist_kernel<1>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
-    hipLaunchKernelGGL(osci_hist_kernel<2>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
-    hipLaunchKernelGGL(osci_hist_kernel<3>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
+    hipLaunchKernelGGL(osci_zero_kernel, dim3((kFirstBins + kBins) / kThreads), dim3(kThreads), 0, st, state, hist);
+    hipLaunchKernelGGL(osci_first_kernel, grid, block, 0, st, W, nchunks, hist);
+    hipLaunchKernelGGL(osci_later_kernel<1>, grid, block, kLaterLds, st, W, nchunks, state, hist, later, (uint32_t)k);
+    hipLaunchKernelGGL(osci_later_kernel<2>, grid, block, kLaterLds, st, W, nchunks, state, hist, later, (uint32_t)k);
     hipLaunchKernelGGL(osci_count_kernel, grid, block, 0, st, W, nchunks, state, counts, ntiles);
     hipLaunchKernelGGL(osci_emit_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, st, W, nchunks, state, counts, idx, wp, qp, dm, dq,
                        (uint32_t)k);

@@ -14,13 +14,13 @@ constexpr uint32_t kNaNKey = 0x7F800001u;
 constexpr uint32_t score_key(uint32_t pattern) { return pattern < kNaNKey ? pattern : kNaNKey; }
 constexpr uint32_t last_pattern(uint32_t key) { return key == kNaNKey ? 0xFFFFFFFFu : key; }   // the largest pattern of the key
 
-constexpr int kBins = 2048;
+constexpr int kFirstBins = 2048, kBits = 15, kBins = 1 << kBits;       // bins of the first pass and of a later one
 // The first pass: 256 bins per octave in [2^-8, 1] (the last of them holds 1 itself), an open bin below and one above.
-constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kBins - 2);   // pattern >> 15 of bin 0; 1.0 falls into bin 2046
+constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kFirstBins - 2);   // pattern >> 15 of bin 0; 1.0 falls into bin 2046
 constexpr int first_bin(uint32_t pattern)
 {
     const int d = (int)(pattern >> 15) - (int)kFirstBin;
-    return d < 0 ? 0 : d > kBins - 1 ? kBins - 1 : d;
+    return d < 0 ? 0 : d > kFirstBins - 1 ? kFirstBins - 1 : d;
 }
 
 struct SelInterval {
@@ -31,14 +31,14 @@ constexpr SelInterval first_interval(uint32_t bin)
 {
     if (bin == 0) return {0u, (kFirstBin + 1) << 15, 30u};
     const uint32_t lo = (kFirstBin + bin) << 15;
-    if (bin == kBins - 1) return {lo, 1u << 30, 30u};
+    if (bin == kFirstBins - 1) return {lo, 1u << 30, 30u};
     return {lo, 1u << 15, 15u};
 }
-static_assert(first_interval(kBins - 1).lo + (1u << 30) > kNaNKey, "the open top bin ends above the largest key");
+static_assert(first_interval(kFirstBins - 1).lo + (1u << 30) > kNaNKey, "the open top bin ends above the largest key");
 static_assert((((kFirstBin + 1) << 15) >> 30) == 0, "the open bottom bin fits its width");
 
-// a later pass: 2048 bins of 2^shift keys (30 -> 19 -> 8 -> 0 open bits; 15 -> 4 -> 0)
-constexpr uint32_t later_shift(uint32_t width) { return width > 11 ? width - 11 : 0; }
+// a later pass: 32768 bins of 2^shift keys (30 -> 15 -> 0 open bits; 15 -> 0)
+constexpr uint32_t later_shift(uint32_t width) { return width > kBits ? width - kBits : 0; }
 // a pattern belongs to the interval if pattern - lo < reach (unsigned: patterns below lo wrap around)
 constexpr uint32_t reach(const SelInterval &s) { return kNaNKey - s.lo < s.span ? 0u - s.lo : s.span; }
 constexpr uint32_t later_bin(const SelInterval &s, uint32_t key) { return (key - s.lo) >> later_shift(s.width); }

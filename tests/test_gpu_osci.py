@@ -120,6 +120,38 @@ def test_tracked_subset_matches_the_oracle(shape, frac):
         assert want > 0                                 # the hopping elements sit next to thresholds: they are tracked
 
 
+@pytest.mark.parametrize("case", ["tiny", "huge", "one score", "no score", "bin edges"])
+def test_selection_where_estimated_scores_do_not_decide(case):
+    """units outside the range of the estimate; more elements at the threshold than a workgroup puts aside; scores of zero; scores
+    at and next to the boundaries between the first pass's bins"""
+    import paper_2510_27527_amd as tj
+    rng = np.random.default_rng(12)
+    W = rng.standard_normal((72, 1024)).astype(np.float32) * np.float32(0.02)
+    if case == "tiny":
+        W[::2] *= np.float32(1e-30)
+        W[1::4] *= np.float32(1e-33)
+    elif case == "huge":
+        W[::2] *= np.float32(1e33)
+    elif case == "one score":
+        W[:] = 2.5625
+        W[:, ::16] = 6.0
+        W[5] = rng.standard_normal(1024) * 0.02
+    elif case == "no score":
+        W[3:] = 0.0
+    else:
+        # in units of the block's scale: a code's value plus (bin boundary +- a few patterns) of its interval's length
+        edge = ((np.uint32(0x3F000000 - (3 << 23)) + rng.integers(0, 3 * 256, W.size).astype(np.uint32) * np.uint32(1 << 15)) +
+                rng.integers(-3, 4, W.size).astype(np.int32).astype(np.uint32)).view(np.float32).reshape(W.shape)
+        W = (np.float32(2.0) + edge * np.float32(0.75)).astype(np.float32)
+        W[:, ::16] = 6.0
+    for k in (1, 700, 3686, 40000, W.size - 1):
+        o = oracle.osci_select(W, k)
+        g = tj.osci_select(torch.from_numpy(W).cuda(), k)
+        assert np.array_equal(u32(g[0]), o[0]), k
+        for a, b in zip(g[1:], o[1:]):
+            assert np.array_equal(bits(a.cpu().numpy()), bits(b)), k
+
+
 def test_selection_with_many_equal_scores():
     """weights on a coarse grid give scores with long runs of exact ties, also at the selection threshold: the first
     ones in index order belong to the subset"""
