@@ -255,8 +255,9 @@ int nvfp4_osci_suppress(float *W, const float *dist_m, const float *dist_q, floa
  * W 16-byte aligned.
  *
  * nvfp4_osci_select - first step of a period (t0 = 0): finds the k largest scores, writes idx, the two snapshots and
- *   zero distances.  ws: nvfp4_osci_select_workspace_bytes(C, D) bytes, 16-byte aligned.  Seven launches, five reads of W (six when the
- *   threshold lies outside the range of ordinary scores).
+ *   zero distances.  ws: nvfp4_osci_select_workspace_bytes(C, D) bytes, 16-byte aligned.  Six launches, four reads of W (five when the
+ *   threshold lies outside the range of ordinary scores); one launch and one read more for k < 32768.  idx serves as scratch
+ *   memory until the indices are written.
  * nvfp4_osci_update_sparse - a later step: dist_m_s += |W[idx] - W_prev_s|, dist_q_s += |Q(W)[idx] - Q_prev_s|, then
  *   the snapshots are replaced.
  * nvfp4_osci_suppress_sparse - Alg. 1 on the subset: W[idx[j]] = Q(W)[idx[j]] where dist_q_s[j] / dist_m_s[j] >= tau;

@@ -195,7 +195,7 @@ struct SelState {
     uint32_t kneed;       // how many elements are still to be taken among those of the interval
     uint32_t thr;         // width 0: the key of the k-th largest score
     uint32_t ties;        // elements equal to thr that belong to the selection (the first ones in index order)
-    uint32_t done[3];     // workgroups that have finished, per pass
+    uint32_t done[5];     // workgroups that have finished, per pass
 };
 
 __device__ __forceinline__ uint32_t load_dev(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -211,11 +211,12 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t *counter, uint32_t *flag
     return *flag != 0;
 }
 
-__global__ __launch_bounds__(kThreads) void osci_zero_kernel(SelState *st, uint32_t *hist)
+__global__ __launch_bounds__(kThreads) void osci_zero_kernel(SelState *st, uint32_t *first, uint32_t *later)
 {
     const int i = blockIdx.x * kThreads + threadIdx.x;
-    if (i < kFirstBins + kBins) hist[i] = 0;
-    if (i < 3) st->done[i] = 0;
+    if (i < kFirstBins) first[i] = 0;
+    else if (i < kFirstBins + kBins) later[i - kFirstBins] = 0;
+    if (i < 5) st->done[i] = 0;
 }
 
 // 1 / bin, by the code's magnitude
@@ -303,11 +304,39 @@ __device__ __forceinline__ uint2 pick_bin(const uint32_t *bins, uint32_t *red, u
     return *picked;
 }
 
-// the first pass: the whole range
-__global__ __launch_bounds__(kPassThreads) void osci_first_kernel(const float *W, int64_t nchunks, uint32_t *hist)
+// The last workgroup's choice from the counts of all: read (all loads in flight together) and cleared for the next pass.
+template <int BINS>
+__device__ __forceinline__ uint2 pick_from_memory(uint32_t *hist, uint32_t *bins, uint32_t *red, uint2 *picked, uint32_t kneed)
+{
+    uint32_t n[BINS / kPassThreads];
+#pragma unroll
+    for (int u = 0; u < BINS / kPassThreads; ++u) n[u] = load_dev(&hist[u * kPassThreads + threadIdx.x]);
+#pragma unroll
+    for (int u = 0; u < BINS / kPassThreads; ++u) {
+        bins[u * kPassThreads + threadIdx.x] = n[u];
+        store_dev(&hist[u * kPassThreads + threadIdx.x], 0u);
+    }
+    __syncthreads();
+    return pick_bin<BINS>(bins, red, picked, kneed);
+}
+__device__ __forceinline__ void store_interval(SelState *st, const SelInterval &iv, uint32_t kneed)
+{
+    if (threadIdx.x == 0) {
+        st->iv = iv;
+        st->thr = iv.lo;
+        st->kneed = kneed;
+        st->ties = kneed;
+    }
+}
+
+// The first pass: the whole range.  BITS (of the later passes) 15: the next pass picks the bin; otherwise the last workgroup.
+template <int BITS>
+__global__ __launch_bounds__(kPassThreads) void osci_first_kernel(const float *W, int64_t nchunks, SelState *st, uint32_t *hist, uint32_t k_total)
 {
     __shared__ float inv_tab[128], inv_bins[8];
     __shared__ uint32_t bins[kFirstBins];
+    __shared__ uint32_t red[kPassWaves], flag;
+    __shared__ uint2 picked;
     fill_inv_table(inv_tab);
     fill_inv_bins(inv_bins);
     for (int b = threadIdx.x; b < kFirstBins; b += kPassThreads) bins[b] = 0;
@@ -338,17 +367,22 @@ __global__ __launch_bounds__(kPassThreads) void osci_first_kernel(const float *W
     __syncthreads();
     for (int b = threadIdx.x; b < kFirstBins; b += kPassThreads)
         if (bins[b]) atomicAdd(&hist[b], bins[b]);
+    if (BITS == kBits || !last_to_arrive(&st->done[0], &flag)) return;
+    const uint2 bin = pick_from_memory<kFirstBins>(hist, bins, red, &picked, k_total);
+    store_interval(st, first_interval(bin.x), bin.y);
 }
 
-// A later pass, in kBins bins.  PASS 1: the interval is the bin that every workgroup picks from the first pass's counts while its
-// first weights are on their way (by the last workgroup of the first pass the choice took 2.5 us); PASS 2: that of the state.
+// A later pass, in 2^BITS bins.  With 15 bits PASS 1 takes the bin that every workgroup picks from the first pass's counts while its
+// first weights are on their way (by the last workgroup of the first pass the choice took 2.5 us); otherwise the interval is
+// that of the state.
 constexpr int kAside = 2048;                               // elements put aside for an exact quotient
-constexpr int kLaterLds = kBins * 4 + kAside * 8;
-template <int PASS>
+constexpr int later_lds(int bits) { return (4 << bits) + kAside * 8; }
+template <int PASS, int BITS>
 __global__ __launch_bounds__(kPassThreads) void osci_later_kernel(const float *W, int64_t nchunks, SelState *st, const uint32_t *first, uint32_t *hist, uint32_t k_total)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t bins[];
-    float2 *aside = reinterpret_cast<float2 *>(bins + kBins);
+    constexpr int BINS = 1 << BITS;
+    float2 *aside = reinterpret_cast<float2 *>(bins + BINS);
     __shared__ float inv_tab[128], inv_bins[8];
     __shared__ uint32_t red[kPassWaves], flag, n_aside;
     __shared__ uint2 picked;
@@ -357,7 +391,7 @@ __global__ __launch_bounds__(kPassThreads) void osci_later_kernel(const float *W
     F8 next{};
     SelInterval iv;
     uint32_t kneed;
-    if (PASS == 1) {
+    if (PASS == 1 && BITS == kBits) {
         if (c < nchunks) next = load8(W + c * 8);
         for (int b = threadIdx.x; b < kFirstBins; b += kPassThreads) bins[b] = first[b];
         __syncthreads();
@@ -373,11 +407,11 @@ __global__ __launch_bounds__(kPassThreads) void osci_later_kernel(const float *W
     const uint32_t within = reach(iv);
     fill_inv_table(inv_tab);
     fill_inv_bins(inv_bins);
-    for (int b = threadIdx.x; b < kBins / 4; b += kPassThreads) reinterpret_cast<uint4 *>(bins)[b] = make_uint4(0, 0, 0, 0);
+    for (int b = threadIdx.x; b < BINS / 4; b += kPassThreads) reinterpret_cast<uint4 *>(bins)[b] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x == 0) n_aside = 0;
     __syncthreads();
     auto count = [&](uint32_t b) {
-        if (b - iv.lo < within) atomicAdd(&bins[later_bin(iv, score_key(b))], 1u);
+        if (b - iv.lo < within) atomicAdd(&bins[later_bin(iv, score_key(b), BITS)], 1u);
     };
     for (; c < nchunks; c += stride) {
         const F8 w = next;
@@ -401,26 +435,11 @@ __global__ __launch_bounds__(kPassThreads) void osci_later_kernel(const float *W
     const uint32_t n = n_aside < kAside ? n_aside : kAside;
     for (uint32_t a = threadIdx.x; a < n; a += kPassThreads) count(score_bits(aside[a].x, aside[a].y));
     __syncthreads();
-    for (int b = threadIdx.x; b < kBins; b += kPassThreads)
+    for (int b = threadIdx.x; b < BINS; b += kPassThreads)
         if (bins[b]) atomicAdd(&hist[b], bins[b]);
-    if (!last_to_arrive(&st->done[PASS - 1], &flag)) return;
-    uint32_t n_all[kBins / kPassThreads];                  // all loads in flight together
-#pragma unroll
-    for (int u = 0; u < kBins / kPassThreads; ++u) n_all[u] = load_dev(&hist[u * kPassThreads + threadIdx.x]);
-#pragma unroll
-    for (int u = 0; u < kBins / kPassThreads; ++u) {
-        bins[u * kPassThreads + threadIdx.x] = n_all[u];
-        store_dev(&hist[u * kPassThreads + threadIdx.x], 0u);   // for the next pass
-    }
-    __syncthreads();
-    const uint2 bin = pick_bin<kBins>(bins, red, &picked, kneed);
-    if (threadIdx.x == 0) {
-        const SelInterval in = next_interval(iv, bin.x);
-        st->iv = in;
-        st->thr = in.lo;
-        st->kneed = bin.y;
-        st->ties = bin.y;
-    }
+    if (!last_to_arrive(&st->done[PASS], &flag)) return;
+    const uint2 bin = pick_from_memory<BINS>(hist, bins, red, &picked, kneed);
+    store_interval(st, next_interval(iv, bin.x, BITS), bin.y);
 }
 
 // flags of the lane's 8 elements against the threshold's key: bit i of gt / eq
@@ -484,7 +503,7 @@ __global__ __launch_bounds__(kPassThreads) void osci_count_kernel(const float *W
             store_dev(&counts[2 * t + 1], sum >> 16);
         }
     }
-    if (!last_to_arrive(&st->done[2], &flag)) return;
+    if (!last_to_arrive(&st->done[4], &flag)) return;
     constexpr int kPer = 4;                                // tiles per thread and round
     uint32_t base_g = 0, base_e = 0;
     for (int64_t t0 = 0; t0 < ntiles; t0 += kPer * kPassThreads) {
@@ -702,7 +721,7 @@ hipError_t launch_sparse(float *W, int64_t n, const uint32_t *idx, int64_t k, fl
 size_t osci_select_workspace_bytes(int64_t n)
 {
     const int64_t ntiles = (n + kTile - 1) / kTile;
-    return 256 + (kFirstBins + kBins) * sizeof(uint32_t) + (size_t)ntiles * 2 * sizeof(uint32_t);
+    return 256 + kFirstBins * sizeof(uint32_t) + (size_t)ntiles * 2 * sizeof(uint32_t);
 }
 
 hipError_t launch_osci_select(const float *W, int64_t n, int64_t k, uint32_t *idx, float *wp, float *qp, float *dm, float *dq,
@@ -711,8 +730,8 @@ hipError_t launch_osci_select(const float *W, int64_t n, int64_t k, uint32_t *id
     const int64_t nchunks = n / 8;
     if (nchunks == 0 || k == 0) return hipSuccess;
     static const hipError_t attr = []() {                  // once; the initialisation of a function-local static is thread-safe
-        for (auto kern : {osci_later_kernel<1>, osci_later_kernel<2>}) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLaterLds);
+        for (auto kern : {osci_later_kernel<1, kBits>, osci_later_kernel<2, kBits>}) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, later_lds(kBits));
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -720,14 +739,24 @@ hipError_t launch_osci_select(const float *W, int64_t n, int64_t k, uint32_t *id
     if (attr != hipSuccess) return attr;
     SelState *state = static_cast<SelState *>(ws);
     uint32_t *hist = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(ws) + 256);
-    uint32_t *later = hist + kFirstBins, *counts = later + kBins;
+    uint32_t *counts = hist + kFirstBins;
     const int64_t ntiles = (nchunks + kThreads - 1) / kThreads;
     const int64_t want = (nchunks + kPassThreads - 1) / kPassThreads;
     const dim3 grid((unsigned)(want < kPassWgs ? want : kPassWgs)), block(kPassThreads);
-    hipLaunchKernelGGL(osci_zero_kernel, dim3((kFirstBins + kBins) / kThreads), dim3(kThreads), 0, st, state, hist);
-    hipLaunchKernelGGL(osci_first_kernel, grid, block, 0, st, W, nchunks, hist);
-    hipLaunchKernelGGL(osci_later_kernel<1>, grid, block, kLaterLds, st, W, nchunks, state, hist, later, (uint32_t)k);
-    hipLaunchKernelGGL(osci_later_kernel<2>, grid, block, kLaterLds, st, W, nchunks, state, hist, later, (uint32_t)k);
+    // The counts of the 32768 bins take the place of the indices, which are written last; fewer indices than bins: 2048 bins in
+    // the workspace, and one pass more (256 x 256, 5 %: a launch-bound call either way).
+    if (k >= kBins) {
+        hipLaunchKernelGGL(osci_zero_kernel, dim3((kFirstBins + kBins) / kThreads), dim3(kThreads), 0, st, state, hist, idx);
+        hipLaunchKernelGGL(osci_first_kernel<kBits>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
+        hipLaunchKernelGGL((osci_later_kernel<1, kBits>), grid, block, later_lds(kBits), st, W, nchunks, state, hist, idx, (uint32_t)k);
+        hipLaunchKernelGGL((osci_later_kernel<2, kBits>), grid, block, later_lds(kBits), st, W, nchunks, state, hist, idx, (uint32_t)k);
+    } else {
+        hipLaunchKernelGGL(osci_zero_kernel, dim3(kFirstBins / kThreads), dim3(kThreads), 0, st, state, hist, nullptr);
+        hipLaunchKernelGGL(osci_first_kernel<kFewBits>, grid, block, 0, st, W, nchunks, state, hist, (uint32_t)k);
+        hipLaunchKernelGGL((osci_later_kernel<1, kFewBits>), grid, block, later_lds(kFewBits), st, W, nchunks, state, nullptr, hist, (uint32_t)k);
+        hipLaunchKernelGGL((osci_later_kernel<2, kFewBits>), grid, block, later_lds(kFewBits), st, W, nchunks, state, nullptr, hist, (uint32_t)k);
+        hipLaunchKernelGGL((osci_later_kernel<3, kFewBits>), grid, block, later_lds(kFewBits), st, W, nchunks, state, nullptr, hist, (uint32_t)k);
+    }
     hipLaunchKernelGGL(osci_count_kernel, grid, block, 0, st, W, nchunks, state, counts, ntiles);
     hipLaunchKernelGGL(osci_emit_kernel, dim3((unsigned)ntiles), dim3(kThreads), 0, st, W, nchunks, state, counts, idx, wp, qp, dm, dq,
                        (uint32_t)k);

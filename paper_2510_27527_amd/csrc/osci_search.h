@@ -15,6 +15,7 @@ constexpr uint32_t score_key(uint32_t pattern) { return pattern < kNaNKey ? patt
 constexpr uint32_t last_pattern(uint32_t key) { return key == kNaNKey ? 0xFFFFFFFFu : key; }   // the largest pattern of the key
 
 constexpr int kFirstBins = 2048, kBits = 15, kBins = 1 << kBits;       // bins of the first pass and of a later one
+constexpr int kFewBits = 11;                                           // of a later one where memory for kBins is not at hand
 // The first pass: 256 bins per octave in [2^-8, 1] (the last of them holds 1 itself), an open bin below and one above.
 constexpr uint32_t kFirstBin = (0x3F800000u >> 15) - (kFirstBins - 2);   // pattern >> 15 of bin 0; 1.0 falls into bin 2046
 constexpr int first_bin(uint32_t pattern)
@@ -37,14 +38,14 @@ constexpr SelInterval first_interval(uint32_t bin)
 static_assert(first_interval(kFirstBins - 1).lo + (1u << 30) > kNaNKey, "the open top bin ends above the largest key");
 static_assert((((kFirstBin + 1) << 15) >> 30) == 0, "the open bottom bin fits its width");
 
-// a later pass: 32768 bins of 2^shift keys (30 -> 15 -> 0 open bits; 15 -> 0)
-constexpr uint32_t later_shift(uint32_t width) { return width > kBits ? width - kBits : 0; }
+// a later pass: 2^bits bins of 2^shift keys (15 bits: 30 -> 15 -> 0 open bits, 15 -> 0; 11 bits: 30 -> 19 -> 8 -> 0, 15 -> 4 -> 0)
+constexpr uint32_t later_shift(uint32_t width, int bits = kBits) { return width > (uint32_t)bits ? width - bits : 0; }
 // a pattern belongs to the interval if pattern - lo < reach (unsigned: patterns below lo wrap around)
 constexpr uint32_t reach(const SelInterval &s) { return kNaNKey - s.lo < s.span ? 0u - s.lo : s.span; }
-constexpr uint32_t later_bin(const SelInterval &s, uint32_t key) { return (key - s.lo) >> later_shift(s.width); }
-constexpr SelInterval next_interval(const SelInterval &s, uint32_t bin)
+constexpr uint32_t later_bin(const SelInterval &s, uint32_t key, int bits = kBits) { return (key - s.lo) >> later_shift(s.width, bits); }
+constexpr SelInterval next_interval(const SelInterval &s, uint32_t bin, int bits = kBits)
 {
-    const uint32_t shift = later_shift(s.width), left = s.span - (bin << shift);
+    const uint32_t shift = later_shift(s.width, bits), left = s.span - (bin << shift);
     return {s.lo + (bin << shift), left < (1u << shift) ? left : 1u << shift, shift};
 }
 
