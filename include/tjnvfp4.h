@@ -226,6 +226,9 @@ size_t nvfp4_outctl_workspace_bytes(int backward, int64_t N, int64_t D_lo, int64
 /* How nvfp4_outctl_bwd splits the reduction of dW_hp over tokens: the number of splits (1: one piece) and the 32-token stages of
  * each, the last split taking the rest.  It follows from the sizes alone.  Host-only helper. */
 int nvfp4_outctl_dw_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *split, int *stages);
+/* The workgroup tile with which nvfp4_linear_bwd (D_hp 0) or nvfp4_outctl_bwd computes its products in one launch, or 0 x 0 where
+ * they are launched one after the other.  It follows from the sizes alone.  Host-only helper. */
+int nvfp4_backward_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *tile_m, int *tile_n);
 
 /*
  * OsciReset (Sec. 3.2-3.3) for one weight matrix of binary32 master weights W [C x D], all arrays device memory of

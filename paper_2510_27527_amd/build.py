@@ -9,13 +9,16 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtjnvfp4.so")
-# (source, object name, extra flags): the product kernel's instantiations are compiled in twelve slices, in parallel
+# output kind of a product, and whether a launch holds one or a group of them (a group is never split into partials)
+GEMM_KINDS = [(0, "GemmArgs"), (0, "GemmGroup"), (2, "GemmArgs"), (1, "GemmArgs"), (1, "GemmGroup")]
+# (source, object name, extra flags): the product kernels' instantiations are compiled in thirty slices, in parallel
 SOURCES = [("api.hip", "api.o", []), ("quant.hip", "quant.o", []), ("osci.hip", "osci.o", []), ("hp.hip", "hp.o", []), ("gemm.hip", "gemm.o", [])] + [
-    ("gemm_inst.hip", "gemm_inst_ps%d_out%d_outer%d.o" % (ps, out, outer),
-     ["-DTJ_GEMM_PS=%d" % ps, "-DTJ_GEMM_OUT=%d" % out, "-DTJ_GEMM_OUTER=%d" % outer])
-    for outer in (0, 1) for ps in (1, 0) for out in (0, 2, 1)] + [
-    ("gemm_kw_inst.hip", "gemm_kw_out%d_outer%d.o" % (out, outer), ["-DTJ_GEMM_OUT=%d" % out, "-DTJ_GEMM_OUTER=%d" % outer])
-    for outer in (0, 1) for out in (0, 2, 1)]
+    ("gemm_inst.hip", "gemm_inst_ps%d_out%d_outer%d_%s.o" % (ps, out, outer, args),
+     ["-DTJ_GEMM_PS=%d" % ps, "-DTJ_GEMM_OUT=%d" % out, "-DTJ_GEMM_OUTER=%d" % outer, "-DTJ_GEMM_ARGS=" + args])
+    for outer in (0, 1) for ps in (1, 0) for out, args in GEMM_KINDS] + [
+    ("gemm_kw_inst.hip", "gemm_kw_out%d_outer%d_%s.o" % (out, outer, args),
+     ["-DTJ_GEMM_OUT=%d" % out, "-DTJ_GEMM_OUTER=%d" % outer, "-DTJ_GEMM_ARGS=" + args])
+    for outer in (0, 1) for out, args in GEMM_KINDS]
 HEADERS = ["device_fmt.h", "internal.h", "gemm_args.h", "gemm_kernel.h", "gemm_kw_kernel.h", "osci_search.h", os.path.join("..", "..", "include", "tjnvfp4.h")]
 
 # -ffp-contract=off: the quantizer arithmetic is one IEEE rounding per written operation.

@@ -292,6 +292,19 @@ int run_gemm(const nvfp4_tensor *A, const nvfp4_tensor *B, void *Out, int out_dt
     return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
+// products of one backward call, in one launch where that is faster
+struct Product { const nvfp4_tensor *A, *B; void *out; };
+int run_gemm_group(const Product *p, int n, int out_dtype, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    GemmProduct g[3];
+    for (int i = 0; i < n; ++i) {
+        const int outer = p[i].A->outer_mode == NVFP4_OUTER_BLOCK128 ? 1 : 0;
+        g[i] = GemmProduct{GemmOperand{p[i].A->codes, p[i].A->scales, p[i].A->gscale, p[i].A->rows, outer},
+                           GemmOperand{p[i].B->codes, p[i].B->scales, p[i].B->gscale, p[i].B->rows, outer}, p[i].A->K, p[i].out};
+    }
+    return launch_gemm_group(g, n, out_dtype == NVFP4_OUT_F32, ws, ws_bytes, st) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
+}
+
 int check_out(const void *p, int out_dtype)
 {
     if (!p) return NVFP4_ERR_NULL;
@@ -526,6 +539,16 @@ int nvfp4_outctl_dw_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int o
     return NVFP4_OK;
 }
 
+int nvfp4_backward_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *tile_m, int *tile_n)
+{
+    if (!tile_m || !tile_n) return NVFP4_ERR_NULL;
+    if (!valid_outer(outer_mode)) return NVFP4_ERR_ENUM;
+    if (N < 0 || D_lo < 0 || D_hp < 0 || C < 0 || D_hp % 32 != 0 || check_reduction(N) || check_reduction(C)) return NVFP4_ERR_SHAPE;
+    const int64_t mnk[3][3] = {{N, D_lo, C}, {C, D_lo, N}, {N, D_hp, C}};
+    gemm_group_plan(mnk, D_hp > 0 ? 3 : 2, outer_mode == NVFP4_OUTER_BLOCK128 ? 1 : 0, tile_m, tile_n);
+    return NVFP4_OK;
+}
+
 int nvfp4_outctl_fwd(const void *X_lo, const void *W_lo, const void *X_hp, const void *W_hp, int64_t N, int64_t D_lo,
                      int64_t D_hp, int64_t C, void *Y, int out_dtype, nvfp4_tensor *Xq_ctx, nvfp4_tensor *Wq_ctx,
                      int outer_mode, void *ws, size_t ws_bytes, void *stream)
@@ -602,9 +625,8 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     if (!rc && D_hp > 0) rc = run_quantize(W_hp, p9, &c9, &q4h, part2, st);
     if (rc) return rc;
     // dX over all input channels in FP4 (one Q3 operand serves both column sets); dW of the ordinary channels in FP4
-    rc = run_gemm(&q3, &q4, dX_lo, out_dtype, gws, gbytes, st);
-    if (!rc && D_hp > 0) rc = run_gemm(&q3, &q4h, dX_hp, out_dtype, gws, gbytes, st);
-    if (!rc) rc = run_gemm(&q5, &q6, dW_lo, out_dtype, gws, gbytes, st);
+    const Product products[] = {{&q3, &q4, dX_lo}, {&q5, &q6, dW_lo}, {&q3, &q4h, dX_hp}};
+    rc = run_gemm_group(products, D_hp > 0 ? 3 : 2, out_dtype, gws, gbytes, st);
     if (rc) return rc;
     // dW of the outlier channels in bf16: dY^T [C x N] times X_hp^T [D_hp x N]^T, the reduction running over tokens
     if (D_hp > 0 && C > 0) {
@@ -891,9 +913,8 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
         rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st);
         if (rc) return rc;
     }
-    rc = run_gemm(&q3, &q4, dX, out_dtype, gws, gbytes, st);
-    if (rc) return rc;
-    return run_gemm(&q5, &q6, dW, out_dtype, gws, gbytes, st);
+    const Product products[] = {{&q3, &q4, dX}, {&q5, &q6, dW}};
+    return run_gemm_group(products, 2, out_dtype, gws, gbytes, st);
 }
 
 }  // extern "C"

@@ -1,5 +1,8 @@
 // Host side of the NT GEMM on two packed NVFP4 operands (tile / split planner, launcher) and the split-K reduction.
 // The product kernel itself lives in gemm_kernel.h and is instantiated slice by slice in gemm_inst.hip.
+#include <climits>
+#include <utility>
+
 #include "../../include/tjnvfp4.h"
 #include "gemm_args.h"
 #include "internal.h"
@@ -90,7 +93,10 @@ const TileCfg kTilesFit[2][kNumTiles] = {
 // 64 x 64 and 64 x 128 tiles have in gemm_nt_kernel, whichever kernel runs them.
 const TileCfg kSmallRagged[2][2] = {{{1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}}, {{1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
 
-struct Plan { int tile; int split; int chunks_per_split; };
+// a group is launched together where that is expected to take less than this share of the separate launches
+constexpr double kGroupGain = 0.95;
+
+struct Plan { int tile; int split; int chunks_per_split; double time; };
 
 // Whether the 64 x 64 (5) and 64 x 128 (6) tiles run on gemm_kw_kernel: below these reductions, per split, its four waves have too
 // little to share (64 x 64: K = 256 5.5 us both, 128 5.8 against 5.1; with outer blocks K = 512 6.3 against 6.4, 640 8.5 against
@@ -106,7 +112,7 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
 {
     const bool early = costs == kEarly;
     const int64_t chunks = K / 64;
-    Plan best{3, 1, (int)chunks};
+    Plan best{3, 1, (int)chunks, 0.0};
     if (M <= 0 || N <= 0 || chunks == 0) return best;      // nothing to tile (empty output or empty reduction)
     double best_t = 1e300;
     const bool fit = costs == kFitted && M >= 128 && N >= 128 && K >= (outer ? 256 : 512);
@@ -166,7 +172,7 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
                               : (double)waves * (stages * cfg.t_stage * (outer ? 1.35 : 1.0) * slow + cfg.t_fixed);
             // partials out and back in (768 x 768 x 8192: 64 x 64 tiles of gemm_kw_kernel in three 22.1 us, in one piece 22.6)
             if (split > 1) time += (kw && !outer ? 3.2 : 4.0) + (double)(split + 1) * (double)(M * N) * 4.0 / 3.5e6;
-            if (time < best_t) { best_t = time; best = Plan{t, split, (int)cps}; }
+            if (time < best_t) { best_t = time; best = Plan{t, split, (int)cps, time}; }
         }
     }
     return best;
@@ -187,7 +193,160 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int outer)
     return p;
 }
 
+GemmArgs args_of(const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32, int tile, int chunks_per_split)
+{
+    GemmArgs g;
+    g.a_codes = A.codes; g.a_scales = A.scales; g.a_gscale = A.gscale;
+    g.b_codes = B.codes; g.b_scales = B.scales; g.b_gscale = B.gscale;
+    g.M = A.rows; g.N = B.rows; g.K = K;
+    const int bm = 64 * kTiles[tile].tm, bn = 64 * kTiles[tile].tn;
+    g.tiles_m = (int)((g.M + bm - 1) / bm);
+    g.tiles_n = (int)((g.N + bn - 1) / bn);
+    g.chunks_per_split = chunks_per_split;
+    g.out_f32 = out_f32;
+    g.outer = A.outer;
+    g.out = out;
+    return g;
+}
+
+// kind: 0 bf16, 1 f32, 2 split partials; ps: K a multiple of 256 with splits on 256-boundaries, scale bytes fetched 16 per row;
+// kw: the kernel whose waves split the reduction
+hipError_t launch_tiles(int tile, int outer, bool ps, int kind, bool kw, const GemmArgs &g, dim3 grid, hipStream_t st)
+{
+    typedef hipError_t (*InstFn)(int, const GemmArgs &, dim3, hipStream_t);
+    static const InstFn inst[2][2][3] = {
+        {{launch_gemm_inst_ps0_out0_outer0, launch_gemm_inst_ps0_out1_outer0, launch_gemm_inst_ps0_out2_outer0},
+         {launch_gemm_inst_ps1_out0_outer0, launch_gemm_inst_ps1_out1_outer0, launch_gemm_inst_ps1_out2_outer0}},
+        {{launch_gemm_inst_ps0_out0_outer1, launch_gemm_inst_ps0_out1_outer1, launch_gemm_inst_ps0_out2_outer1},
+         {launch_gemm_inst_ps1_out0_outer1, launch_gemm_inst_ps1_out1_outer1, launch_gemm_inst_ps1_out2_outer1}}};
+    static const InstFn kws[2][3] = {{launch_gemm_kw_out0_outer0, launch_gemm_kw_out1_outer0, launch_gemm_kw_out2_outer0},
+                                     {launch_gemm_kw_out0_outer1, launch_gemm_kw_out1_outer1, launch_gemm_kw_out2_outer1}};
+    return (kw ? kws[outer ? 1 : 0][kind] : inst[outer ? 1 : 0][ps ? 1 : 0][kind])(tile, g, grid, st);
+}
+
+hipError_t launch_tiles(int tile, int outer, bool ps, bool out_f32, bool kw, const GemmGroup &g, dim3 grid, hipStream_t st)
+{
+    typedef hipError_t (*InstFn)(int, const GemmGroup &, dim3, hipStream_t);
+    static const InstFn inst[2][2][2] = {{{launch_gemm_inst_ps0_out0_outer0, launch_gemm_inst_ps0_out1_outer0},
+                                          {launch_gemm_inst_ps1_out0_outer0, launch_gemm_inst_ps1_out1_outer0}},
+                                         {{launch_gemm_inst_ps0_out0_outer1, launch_gemm_inst_ps0_out1_outer1},
+                                          {launch_gemm_inst_ps1_out0_outer1, launch_gemm_inst_ps1_out1_outer1}}};
+    static const InstFn kws[2][2] = {{launch_gemm_kw_out0_outer0, launch_gemm_kw_out1_outer0}, {launch_gemm_kw_out0_outer1, launch_gemm_kw_out1_outer1}};
+    return (kw ? kws[outer ? 1 : 0][out_f32] : inst[outer ? 1 : 0][ps][out_f32])(tile, g, grid, st);
+}
+
+// Products in one launch.  Alone, each of them ends with a round of workgroups that leaves CUs idle (928 tiles on 512 places: the
+// second round fills four fifths of them), and the next waits for its last one; together they share the last round.  They keep
+// their own plans' order of summation - the reduction in one piece, by the same kernel, whose tiles all add in the same order -
+// so that their bits do not depend on what is launched with them.  (The third, the outlier channels' part of dX, exists in no
+// other call: it takes the kernel of the other two.)
+struct GroupPlan { int tile; bool kw; };
+
+GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
+{
+    const GroupPlan none{-1, false};
+    double apart = 0.0, best_t = 1e300;
+    bool kw = false, ps = true, whole = true;
+    for (int i = 0; i < n; ++i) {
+        const int64_t M = mnk[i][0], N = mnk[i][1], K = mnk[i][2];
+        if (M < (i < 2 ? 128 : 1) || N < (i < 2 ? 128 : 1) || K < 256) return none;
+        const Plan p = make_plan(M, N, K, outer);
+        const bool w = waves_split_k(p.tile, K / 64, outer);
+        if (i < 2 && (p.split > 1 || (i > 0 && w != kw))) return none;
+        if (i < 2) kw = w;
+        apart += p.time;
+        ps = ps && K % 256 == 0;
+        whole = whole && M % 64 == 0 && N % 64 == 0;
+    }
+    int order[kMaxGroup] = {0, 1, 2};                      // the longest reduction first
+    for (int i = 1; i < n; ++i)
+        for (int j = i; j > 0 && mnk[order[j]][2] > mnk[order[j - 1]][2]; --j) std::swap(order[j], order[j - 1]);
+    int best = -1;
+    for (int t = 0; t < kNumTiles; ++t) {
+        bool same = true;
+        int64_t wgs = 0, longest = 0;
+        for (int i = 0; i < n; ++i) {
+            const int64_t bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
+            same = same && waves_split_k(t, mnk[i][2] / 64, outer) == kw;
+            wgs += ((mnk[i][0] + bm - 1) / bm) * ((mnk[i][1] + bn - 1) / bn);
+            longest = longest < mnk[i][2] ? mnk[i][2] : longest;
+        }
+        if (!same || (t == 0 && outer) || (t == 7 && (outer || !whole)) || ((t == 4 || (t == 6 && !kw)) && !ps)) continue;
+        if (t >= 5 && !kw && longest > 16 * 64 * kNC) continue;
+        const TileCfg &cfg = t >= 5 && !(kw && whole) ? t == 7 ? kTilesFit[outer][t] : kSmallRagged[outer][t - 5] : kTilesFit[outer][t];
+        const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU, conc = per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
+        if (wgs > 16 * kNumCU * conc) continue;            // many rounds: the last one counts for little
+        const double slow = conc == 1 ? 1.0 : conc > 2 ? 1.95 : t >= 5 && !kw ? 1.4 : outer ? 1.52 : 1.58;
+        // places of the chip and when they fall free, in order; the products' workgroups take them one after the other
+        double at[64];
+        int64_t places[64];
+        int classes = 1;
+        at[0] = 0.0;
+        places[0] = kNumCU * conc;
+        double end = 0.0;
+        for (int o = 0; o < n; ++o) {
+            const int64_t *s = mnk[order[o]], bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
+            int64_t left = ((s[0] + bm - 1) / bm) * ((s[1] + bn - 1) / bn);
+            const double time = ((double)((s[2] / 64 + kNC - 1) / kNC) * cfg.t_stage + cfg.t_fixed) * slow;
+            while (left > 0 && classes < 63) {
+                const int64_t take = left < places[0] ? left : places[0];
+                const double until = at[0] + time;
+                left -= take;
+                places[0] -= take;
+                if (places[0] == 0) {
+                    for (int c = 1; c < classes; ++c) { at[c - 1] = at[c]; places[c - 1] = places[c]; }
+                    --classes;
+                }
+                int c = classes++;
+                for (; c > 0 && at[c - 1] > until; --c) { at[c] = at[c - 1]; places[c] = places[c - 1]; }
+                at[c] = until;
+                places[c] = take;
+                end = end < until ? until : end;
+            }
+            if (left > 0) end = 1e300;
+        }
+        if (end < best_t) { best_t = end; best = t; }
+    }
+    return best_t < kGroupGain * apart ? GroupPlan{best, kw} : none;
+}
+
 }  // namespace
+
+void gemm_group_plan(const int64_t (*mnk)[3], int n, int outer, int *bm, int *bn)
+{
+    const int t = plan_group(mnk, n, outer).tile;
+    *bm = t < 0 ? 0 : 64 * kTiles[t].tm;
+    *bn = t < 0 ? 0 : 64 * kTiles[t].tn;
+}
+
+hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    int64_t mnk[kMaxGroup][3];
+    for (int i = 0; i < n; ++i) { mnk[i][0] = p[i].A.rows; mnk[i][1] = p[i].B.rows; mnk[i][2] = p[i].K; }
+    const int outer = p[0].A.outer;
+    const GroupPlan plan = plan_group(mnk, n, outer);
+    if (plan.tile < 0) {
+        for (int i = 0; i < n; ++i) {
+            const hipError_t e = launch_gemm_nt(p[i].A, p[i].B, p[i].K, p[i].out, out_f32, ws, ws_bytes, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    int order[kMaxGroup] = {0, 1, 2};
+    for (int i = 1; i < n; ++i)
+        for (int j = i; j > 0 && mnk[order[j]][2] > mnk[order[j - 1]][2]; --j) std::swap(order[j], order[j - 1]);
+    GemmGroup g;
+    int wgs = 0;
+    bool ps = true;
+    for (int i = 0; i < kMaxGroup; ++i) {
+        const GemmProduct &q = p[order[i < n ? i : 0]];
+        g.g[i] = args_of(q.A, q.B, q.K, q.out, out_f32, plan.tile, (int)(q.K / 64));
+        g.first[i] = i < n ? wgs : INT_MAX;
+        if (i < n) wgs += g.g[i].tiles_m * g.g[i].tiles_n;
+        ps = ps && q.K % 256 == 0;
+    }
+    return launch_tiles(plan.tile, outer, ps, out_f32 != 0, plan.kw, g, dim3((unsigned)wgs, 1, 1), st);
+}
 
 void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int *split)
 {
@@ -217,32 +376,12 @@ hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K,
     const int outer = A.outer;
     Plan p = make_plan(M, N, K, outer);
     if (p.split > 1 && (ws == nullptr || ws_bytes < (size_t)p.split * M * N * sizeof(float))) return hipErrorInvalidValue;
-    GemmArgs g;
-    g.a_codes = A.codes; g.a_scales = A.scales; g.a_gscale = A.gscale;
-    g.b_codes = B.codes; g.b_scales = B.scales; g.b_gscale = B.gscale;
-    g.M = M; g.N = N; g.K = K;
-    const int bm = 64 * kTiles[p.tile].tm, bn = 64 * kTiles[p.tile].tn;
-    g.tiles_m = (int)((M + bm - 1) / bm);
-    g.tiles_n = (int)((N + bn - 1) / bn);
-    g.chunks_per_split = p.chunks_per_split;
-    g.out_f32 = out_f32;
-    g.outer = outer;
     const int64_t chunks = K / 64;
     const int split = p.split > 1 ? (int)((chunks + p.chunks_per_split - 1) / p.chunks_per_split) : 1;
-    g.out = split > 1 ? ws : out;
-    dim3 grid((unsigned)(g.tiles_m * g.tiles_n), 1, (unsigned)split);
-    // K a multiple of 256 with splits on 256-boundaries: scale bytes are fetched 16 per row
-    const bool ps = K % 256 == 0 && p.chunks_per_split % 4 == 0;
-    typedef hipError_t (*InstFn)(int, const GemmArgs &, dim3, hipStream_t);
-    static const InstFn inst[2][2][3] = {
-        {{launch_gemm_inst_ps0_out0_outer0, launch_gemm_inst_ps0_out1_outer0, launch_gemm_inst_ps0_out2_outer0},
-         {launch_gemm_inst_ps1_out0_outer0, launch_gemm_inst_ps1_out1_outer0, launch_gemm_inst_ps1_out2_outer0}},
-        {{launch_gemm_inst_ps0_out0_outer1, launch_gemm_inst_ps0_out1_outer1, launch_gemm_inst_ps0_out2_outer1},
-         {launch_gemm_inst_ps1_out0_outer1, launch_gemm_inst_ps1_out1_outer1, launch_gemm_inst_ps1_out2_outer1}}};
-    static const InstFn kw[2][3] = {{launch_gemm_kw_out0_outer0, launch_gemm_kw_out1_outer0, launch_gemm_kw_out2_outer0},
-                                    {launch_gemm_kw_out0_outer1, launch_gemm_kw_out1_outer1, launch_gemm_kw_out2_outer1}};
-    const int kind = split > 1 ? 2 : (out_f32 ? 1 : 0);
-    hipError_t e = (waves_split_k(p.tile, p.chunks_per_split, outer) ? kw[outer ? 1 : 0][kind] : inst[outer ? 1 : 0][ps ? 1 : 0][kind])(p.tile, g, grid, st);
+    const GemmArgs g = args_of(A, B, K, split > 1 ? ws : out, out_f32, p.tile, p.chunks_per_split);
+    const dim3 grid((unsigned)(g.tiles_m * g.tiles_n), 1, (unsigned)split);
+    hipError_t e = launch_tiles(p.tile, outer, K % 256 == 0 && p.chunks_per_split % 4 == 0, split > 1 ? 2 : (out_f32 ? 1 : 0),
+                                waves_split_k(p.tile, p.chunks_per_split, outer), g, grid, st);
     if (e != hipSuccess) return e;
     if (split > 1) {
         const int64_t mn = M * N;

@@ -70,12 +70,27 @@ __device__ __forceinline__ const void *to_scalar(const void *p)
 
 __device__ __forceinline__ uint32_t pick(uint4 v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
+// The workgroup's product and its number wg among that product's workgroups.  A launch of one product has a kernel of its own:
+// with one kernel for both, which takes the arguments of three products, launches of one took 0.3 to 0.5 us longer, and
+// the larger tiles with outer blocks ran 1 % slower.
+__device__ __forceinline__ const GemmArgs &product_of_workgroup(const GemmArgs &g, int &wg)
+{
+    wg = blockIdx.x;
+    return g;
+}
+__device__ __forceinline__ GemmArgs product_of_workgroup(const GemmGroup &p, int &wg)
+{
+    wg = blockIdx.x;
+    const int i = wg < p.first[1] ? 0 : wg < p.first[2] ? 1 : 2;
+    wg -= p.first[i];
+    return p.g[i];
+}
+
 // workgroup -> tile: consecutive ids of one XCD (ids are dealt round-robin over 8 XCDs) walk
 // down a column of tiles, in groups of 8 tile rows
-__device__ __forceinline__ void tile_of_workgroup(const GemmArgs &g, int &tile_m, int &tile_n)
+__device__ __forceinline__ void tile_of_workgroup(const GemmArgs &g, int pid, int &tile_m, int &tile_n)
 {
     const int total = g.tiles_m * g.tiles_n;
-    int pid = blockIdx.x;
     {
         const int per_xcd = total / 8;
         if (pid < per_xcd * 8) pid = (pid & 7) * per_xcd + (pid >> 3);
@@ -256,8 +271,8 @@ struct OpFrags {
 // them: one instruction in seven of the loop.  With two workgroups on a CU, where the loop is bound by its instructions, this is the
 // faster form (1664 x 6528 x 896 41.7 -> 33.9 us; 8192 x 4096 x 4096 on this tile 345, on 256 x 128 353); a workgroup with the CU to
 // itself waits for results more often and is 6 % slower with it (1280 x 2688 x 5760 77.7 against 82.6).
-template <int TM, int TN, int NC, int OUT, bool PS, int OUTER, bool PACK>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
-__global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1) void gemm_nt_kernel(GemmArgs g)
+template <int TM, int TN, int NC, int OUT, bool PS, int OUTER, bool PACK, class Args>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
+__global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1) void gemm_nt_kernel(Args args)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN, ROWS = BM + BN;
     constexpr int SLOTS = 2 * NC;                       // 16-byte pieces per row per stage
@@ -291,8 +306,9 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
     const int lr = lane & 31, kg = lane >> 5;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem_raw;
 
-    int tile_m, tile_n;
-    tile_of_workgroup(g, tile_m, tile_n);
+    int tile_m, tile_n, wg;
+    const GemmArgs &g = product_of_workgroup(args, wg);
+    tile_of_workgroup(g, wg, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int64_t chunks_total = g.K / 64;
     const int64_t cbeg = (int64_t)blockIdx.z * g.chunks_per_split;
@@ -568,12 +584,12 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
     store_tile<TM, TN, OUT, SWAP, OUTER>(acc, g, m0, n0, wm, wn, lr, kg, smem_raw);
 }
 
-template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK = false>
-hipError_t launch_cfg(const GemmArgs &g, dim3 grid, hipStream_t st)
+template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK = false, class Args>
+hipError_t launch_cfg(const Args &g, dim3 grid, hipStream_t st)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
     constexpr int lds = 3 * ((BM + BN) * 2 * kNC * 16 + (BM + BN) * (PS ? 16 : kNC * 4)) + (OUTER ? 4 * (BM + BN) * 4 : 0);
-    auto kern = gemm_nt_kernel<TM, TN, kNC, OUT, PS, OUTER, PACK>;
+    auto kern = gemm_nt_kernel<TM, TN, kNC, OUT, PS, OUTER, PACK, Args>;
     // once per instantiation; the initialisation of a function-local static is thread-safe
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -584,8 +600,8 @@ hipError_t launch_cfg(const GemmArgs &g, dim3 grid, hipStream_t st)
 
 // tile: 0 256x256 (tensor mode only: block mode needs two accumulator sets), 1 256x128, 2 128x256, 3 128x128,
 // 4 128x192 (paired scale fetch only), 5 64x64, 6 64x128 (paired scale fetch only)
-template <int OUT, bool PS, int OUTER>
-hipError_t launch_tile(int tile, const GemmArgs &g, dim3 grid, hipStream_t st)
+template <int OUT, bool PS, int OUTER, class Args>
+hipError_t launch_tile(int tile, const Args &g, dim3 grid, hipStream_t st)
 {
     switch (tile) {
         case 0:

@@ -44,8 +44,8 @@ struct KwShape {
     static constexpr int LDS = RING > RED ? RING : RED;
 };
 
-template <int TM, int TN, int OUT, int OUTER>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
-__global__ __launch_bounds__(kThreads, (TM * TN == 4 ? 2 : 1)) void gemm_kw_kernel(GemmArgs g)
+template <int TM, int TN, int OUT, int OUTER, class Args>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
+__global__ __launch_bounds__(kThreads, (TM * TN == 4 ? 2 : 1)) void gemm_kw_kernel(Args args)
 {
     typedef KwShape<TM, TN, OUTER> S;
     constexpr int BM = 32 * TM, BN = 32 * TN, ROWS = S::ROWS, D = S::D, NCW = S::NCW, SLOTS = S::SLOTS;
@@ -66,8 +66,9 @@ __global__ __launch_bounds__(kThreads, (TM * TN == 4 ? 2 : 1)) void gemm_kw_kern
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem_raw;
     constexpr int SC_BASE = D * S::CODE + 32, GS_BASE = D * (S::CODE + S::SC);
 
-    int tile_m, tile_n;
-    tile_of_workgroup(g, tile_m, tile_n);
+    int tile_m, tile_n, wg;
+    const GemmArgs &g = product_of_workgroup(args, wg);
+    tile_of_workgroup(g, wg, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int64_t cbeg = (int64_t)blockIdx.z * g.chunks_per_split;
     int64_t cend = cbeg + g.chunks_per_split;
@@ -303,12 +304,12 @@ __global__ __launch_bounds__(kThreads, (TM * TN == 4 ? 2 : 1)) void gemm_kw_kern
     store_tile<RM, RN, OUT, SWAP, OUTER>(sum, g, m0, n0, wm, wn, lr, kg, smem_raw);
 }
 
-template <int TM, int TN, int OUT, int OUTER>
-hipError_t launch_kw_cfg(const GemmArgs &g, dim3 grid, hipStream_t st)
+template <int TM, int TN, int OUT, int OUTER, class Args>
+hipError_t launch_kw_cfg(const Args &g, dim3 grid, hipStream_t st)
 {
     constexpr int lds = KwShape<TM, TN, OUTER>::LDS;
     static_assert(lds <= 160 * 1024, "LDS of one CU");
-    auto kern = gemm_kw_kernel<TM, TN, OUT, OUTER>;
+    auto kern = gemm_kw_kernel<TM, TN, OUT, OUTER, Args>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, st, g);
@@ -316,8 +317,8 @@ hipError_t launch_kw_cfg(const GemmArgs &g, dim3 grid, hipStream_t st)
 }
 
 // tile: 5 64x64, 6 64x128, 7 128x128 (tensor mode only)
-template <int OUT, int OUTER>
-hipError_t launch_kw_tile(int tile, const GemmArgs &g, dim3 grid, hipStream_t st)
+template <int OUT, int OUTER, class Args>
+hipError_t launch_kw_tile(int tile, const Args &g, dim3 grid, hipStream_t st)
 {
     switch (tile) {
         case 5: return launch_kw_cfg<2, 2, OUT, OUTER>(g, grid, st);

@@ -92,6 +92,17 @@ void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int
 hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32,
                           void *ws, size_t ws_bytes, hipStream_t st);
 
+// Up to three independent products of one output type and outer mode, in one launch where that is faster; the results are those of
+// launch_gemm_nt (launches one after the other share the workspace).
+struct GemmProduct {
+    GemmOperand A, B;
+    int64_t K;
+    void *out;
+};
+hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws, size_t ws_bytes, hipStream_t st);
+// the tile that a group of products (M, N, K each) is launched with, 0 x 0 where they run one after the other
+void gemm_group_plan(const int64_t (*mnk)[3], int n, int outer, int *bm, int *bn);
+
 // bf16 side of the OutControl split linear: Out[M x N] = addend (optional, f32) + A[M x K] * B[N x K]^T with K % 32 == 0;
 // transpose of a bf16 [R x C] array
 // (scratch: optional, 16-byte aligned; lets a long reduction with few output tiles be split: hp_gemm_split gives the number of

@@ -60,6 +60,28 @@ def test_split_linear_forward_and_backward(N, D_lo, D_hp, C, outer, rht, out_dty
     assert torch.equal(got[0], dX0) and torch.equal(got[2], dW0)
 
 
+@pytest.mark.parametrize("N,D_lo,D_hp,C,outer,tile", [(256, 640, 64, 640, 1, (64, 64)), (576, 704, 64, 1472, 0, (64, 64)),
+                                                      (640, 1280, 32, 640, 1, (64, 64))])
+def test_three_products_in_one_launch(N, D_lo, D_hp, C, outer, tile):
+    """dX of both kinds of channels and dW of the ordinary ones in one launch: the outlier channels' dX, which has fewer columns
+    than a tile, against the oracle; the others have the bytes of the plain layer"""
+    import paper_2510_27527_amd as tj
+    B = tj.binding
+    assert B.backward_plan(N, D_lo, D_hp, C, outer) == tile
+    Xl, Wl, Xh, Wh, dYb = inputs(N, D_lo, D_hp, C, 91)
+    dXl, dWl, dXh, dWh, dY = (dev_bf16(a) for a in (Xl, Wl, Xh, Wh, dYb))
+    _, Xq, Wq = tj.outctl_fwd(dXl, dWl, dXh, dWh, B.OUT_F32, outer=outer)
+    oXq, oWq, _, _ = oracle.outctl_fwd(Xl, Wl, Xh, Wh, outer=outer)
+    got = tj.outctl_bwd(dY, Xq, Wq, dXh, dWh, 9, 3, B.OUT_F32)
+    ref = oracle.outctl_bwd(dYb, oXq, oWq, Xh, Wh, 9, 3)
+    dX0 = tj.linear_bwd_dx(dY, Wq, 9, 3, B.OUT_F32)
+    dW0 = tj.linear_bwd_dw(dY, Xq, 9, 3, B.OUT_F32)
+    torch.cuda.synchronize()
+    for name, g in zip(("dX_lo", "dX_hp", "dW_lo", "dW_hp"), got):
+        check(g, *ref[name], name)
+    assert torch.equal(got[0], dX0) and torch.equal(got[2], dW0)
+
+
 def test_high_precision_product_and_transpose_on_ragged_shapes():
     """the bf16 products on shapes that are no multiples of their 128 x 128 tile (token counts 64, 192, 320; 96 and 160
     outlier channels; 192 and 320 outputs)"""

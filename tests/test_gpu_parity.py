@@ -813,6 +813,24 @@ def test_fused_backward_equals_separate_calls(N, D, C):
     check_product(dW2, ref, absref, "fused dW")
 
 
+@pytest.mark.parametrize("N,D,C,outer,tile", [
+    (832, 896, 384, 0, (64, 64)), (832, 768, 832, 0, (64, 128)), (1472, 1024, 1664, 0, (128, 128)), (4736, 2816, 2176, 0, (256, 256)),
+    (1152, 7744, 384, 0, (128, 256)), (384, 1792, 640, 1, (64, 64)), (1792, 768, 1408, 1, (64, 128)), (896, 3328, 3456, 1, (128, 128))])
+def test_backward_products_in_one_launch(N, D, C, outer, tile):
+    """both products of a backward call in one launch, each tile that such launches take: the bytes of the separate calls"""
+    B = tj.binding
+    assert B.backward_plan(N, D, 0, C, outer) == tile
+    Xb, Wb, dYb = wl.linear_inputs(N, D, C, seed=22)
+    X, W, dY = dev_bf16(Xb), dev_bf16(Wb), dev_bf16(dYb)
+    for out_dtype in (1, 0):
+        _, Xq, Wq = tj.linear_fwd(X, W, out_dtype, outer=outer)
+        dX1 = tj.linear_bwd_dx(dY, Wq, 17, 3, out_dtype)
+        dW1 = tj.linear_bwd_dw(dY, Xq, 17, 3, out_dtype)
+        dX2, dW2 = tj.linear_bwd(dY, Xq, Wq, 17, 3, out_dtype)
+        torch.cuda.synchronize()
+        assert torch.equal(dX1, dX2) and torch.equal(dW1, dW2)
+
+
 # ------------------------------------------------------------------ degenerate sizes
 
 def test_empty_inputs_are_accepted_and_write_nothing():
