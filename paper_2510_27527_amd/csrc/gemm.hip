@@ -127,17 +127,29 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
         // 64 x 64, 42 with 128 x 192), and a sliver of an output with
         // rows that are mostly padding.  With 1 x 128 outer blocks the same holds (2048 x 1024 x 1024: 19.8 us with 128 x 192),
         // a little earlier where only the 64 x 64 tile exists.
+        // Whole outputs with per-tensor scales may take any number of 64 x 64 tiles of gemm_kw_kernel in one piece (`many`): two on a CU
+        // have nearly the rate of the 128 x 128 tile, with a quarter of its granularity.  Measured with r rounds of 512 of them
+        // (us, and the best other plan): r = 0.96 1088 x 1856 x 14400 67 (84), 1.74 11392 x 320 x 7104 68 (98), 1.95 1728 x 2368 x 4224 42 (58),
+        // 2.3 4416 x 1088 x 2752 37.5 (48.3), 2.4 5696 x 896 x 6016 71 (88); but 3.4 2688 x 2624 x 13632 214 (192).  All follow 5 us +
+        // 1.3 per round + 0.54 per round and stage, a last round that is begun after the second counting 0.4 more than its share; a
+        // plan of at most four rounds (the measured range) has to be 8 % better by that, because the other tiles' costs are that much too high for some long reductions (11136 x
+        // 384 x 6656 63, 71 with 64 x 64).
+        bool many = false;
         if (t == 5 || t == 6) {
             if (early) continue;
             const int64_t least = outer ? 256 : 128, tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
-            if (M < least || N < least || tiles128 > (outer && K % 256 != 0 ? 3 * kNumCU / 8 : kNumCU / 2)) continue;
+            if (M < least || N < least) continue;
+            if (tiles128 > (outer && K % 256 != 0 ? 3 * kNumCU / 8 : kNumCU / 2)) {
+                if (t == 6 || outer || !fit || !whole) continue;
+                many = true;
+            }
         }
         if (t == 7 && (!fit || !whole || outer)) continue;
         if (t == 0 && outer) continue;                      // block mode keeps two accumulator sets: at most 2 x 4 tiles per wave
         const int64_t bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
         const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         for (int split = 1; split <= 16; ++split) {
-            if (split > 1 && (chunks / split < 8 || t == 7)) break;
+            if (split > 1 && (chunks / split < 8 || t == 7 || many)) break;
             int64_t cps = (chunks + split - 1) / split;
             if (chunks % 4 == 0) cps = (cps + 3) / 4 * 4;                       // splits on 256-k boundaries
             else if (outer) cps = (cps + 1) / 2 * 2;                            // block mode: on 128-k boundaries
@@ -170,6 +182,11 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
             // unfitted block mode: the per-block rescale of the accumulators makes a stage about a third longer
             double time = fit ? (double)waves * (stages * t_stage + cfg.t_fixed) * slow
                               : (double)waves * (stages * cfg.t_stage * (outer ? 1.35 : 1.0) * slow + cfg.t_fixed);
+            if (many) {
+                const double r = (double)wgs / (2 * kNumCU), up = (double)((wgs + 2 * kNumCU - 1) / (2 * kNumCU));
+                const double rounds = r > 2.0 && r + 0.4 < up ? r + 0.4 : up;
+                time = r > 4.0 ? 1e300 : 1.08 * (rounds * (stages * 0.54 + 1.3) + 5.0);
+            }
             // partials out and back in (768 x 768 x 8192: 64 x 64 tiles of gemm_kw_kernel in three 22.1 us, in one piece 22.6)
             if (split > 1) time += (kw && !outer ? 3.2 : 4.0) + (double)(split + 1) * (double)(M * N) * 4.0 / 3.5e6;
             if (time < best_t) { best_t = time; best = Plan{t, split, (int)cps, time}; }

@@ -488,7 +488,9 @@ def test_gemm_small_tiles(outer, M, N, K, tile, split, out_dtype):
 SPLIT_WAVES_SHAPES = [(0, 128, 256, 256, (64, 64)), (0, 192, 448, 576, (64, 64)), (0, 704, 192, 704, (64, 64)), (0, 704, 832, 1600, (64, 64)),
                       (0, 256, 512, 2048, (64, 64)), (0, 2048, 1024, 1024, (64, 128)), (0, 1472, 1472, 2112, (128, 128)),
                       (0, 1984, 1600, 2048, (128, 128)), (1, 384, 512, 1152, (64, 64)), (1, 256, 1408, 2944, (64, 64)),
-                      (1, 384, 256, 896, (64, 64)), (1, 1664, 896, 1408, (64, 128)), (1, 2048, 1024, 1024, (64, 128))]
+                      (1, 384, 256, 896, (64, 64)), (1, 1664, 896, 1408, (64, 128)), (1, 2048, 1024, 1024, (64, 128)),
+                      # one round of 64 x 64 tiles that nearly fills the chip, and between two and three rounds
+                      (0, 448, 4608, 960, (64, 64)), (0, 1536, 1344, 1344, (64, 64)), (0, 4800, 832, 3904, (64, 64)), (0, 832, 4928, 3264, (64, 64))]
 
 
 @pytest.mark.parametrize("outer,M,N,K,tile", SPLIT_WAVES_SHAPES)
