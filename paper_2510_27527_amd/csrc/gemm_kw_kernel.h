@@ -248,8 +248,9 @@ __global__ __launch_bounds__(kThreads, (TM * TN == 4 ? 2 : 1)) void gemm_kw_kern
                     __builtin_amdgcn_sched_group_barrier(0x002, (8 * (TM + TN) + TM * TN - 1) / (TM * TN) + 1, 0);
                 }
             }
-            if (OUTER) {
-                // end of the wave's outer block: total += block sum * S_A[m] * S_B[n], as in gemm_nt_kernel
+            if (OUTER && kt * NC + wave * NCW < nchunks) {
+                // end of the wave's outer block: total += block sum * S_A[m] * S_B[n], as in gemm_nt_kernel.  A wave without a block in the
+                // last stage adds nothing: the scales in its place are another block's, and an infinite one would make its zero sum a NaN.
                 const float *gsr = reinterpret_cast<const float *>(smem_raw + GS_BASE + (kt & 3) * S::GS) + wave * ROWS;
                 rescale_add<TM, TN, SWAP>(acc, part, gsr, gsr + BM, lr, kg);
             }

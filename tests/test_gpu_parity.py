@@ -514,6 +514,37 @@ def test_gemm_waves_split_the_reduction(outer, M, N, K, tile, out_dtype):
     check_product(got[torch.from_numpy(rows).cuda()], ref, absref, "gemm split waves %dx%dx%d" % (M, N, K))
 
 
+# block counts whose last stage of four leaves one, two or three waves without a block, on both tiles; 512: the other kernel
+@pytest.mark.parametrize("M,N,K,tile", [(384, 512, 1152, (64, 64)), (256, 1408, 2816, (64, 64)), (384, 256, 896, (64, 64)),
+                                        (1664, 896, 1408, (64, 128)), (256, 512, 512, (64, 64))])
+@pytest.mark.parametrize("out_dtype", [0, 1])
+def test_gemm_infinite_outer_scales(M, N, K, tile, out_dtype):
+    """An infinite scale of the first outer block, and two finite ones whose product overflows: the block's sum gives an infinity
+    of its sign (and a NaN only where it is zero), and no other result changes."""
+    assert tj.binding.gemm_plan(M, N, K, 1) == (*tile, 1)
+    A = oracle.quantize_bf16(_block_operand(M, K, 790 + N, 1.0), 0, 0, outer=oracle.OUTER_BLOCK128)
+    B = oracle.quantize_bf16(_block_operand(N, K, 791 + M, 0.02), 0, 0, outer=oracle.OUTER_BLOCK128)
+    a, b = to_dev(A), to_dev(B)
+    plain = tj.gemm_nt(a, b, out_dtype)
+    ga, gb = a.gscale.view(M, K // 128), b.gscale.view(N, K // 128)
+    ga[5, 0] = float("inf")
+    ga[M - 3, 0] = 1e30
+    gb[N - 2, 0] = 1e30
+    got = tj.gemm_nt(a, b, out_dtype)
+    torch.cuda.synchronize()
+    # sign of the first block's sums, from its 128 columns alone with the scales as they were
+    def first(q):
+        return oracle.dequant_f64(q)[:, :128]
+    s = torch.from_numpy(first(A) @ first(B).T).cuda()
+    want_row = torch.where(s[5] > 0, float("inf"), float("-inf"))
+    some = s[5].abs() > 1e-9 * s[5].abs().max()
+    assert int(some.sum()) > N // 2 and torch.equal(got[5].double()[some], want_row.double()[some])
+    assert s[M - 3, N - 2] != 0 and float(got[M - 3, N - 2]) == (float("inf") if s[M - 3, N - 2] > 0 else float("-inf"))
+    rows = [m for m in range(M) if m not in (5, M - 3)]
+    cols = [n for n in range(N) if n != N - 2]
+    assert torch.equal(got[rows][:, cols], plain[rows][:, cols])
+
+
 # (outer mode, M, N, K, tile): whole tiles, K a multiple of 256, more workgroups than the chip holds of that tile at
 # once and not a multiple of that number, so tiles start and end at different times on one compute unit.  K = 256 is the
 # shortest reduction with paired scale fetch (two stages, one scale pair), 768 a typical short one.
