@@ -113,34 +113,37 @@ __global__ __launch_bounds__(kThreads, (TM * TN == 4 ? 2 : 1)) void gemm_kw_kern
         const float *b_gbase = OUTER ? g.b_gscale + n0 * nkb + (cbeg >> 1) : nullptr;
         const int last_start = (int)(sstride - S::SC_ROW - cbeg * 4);   // of a row's last stage of scales
 
-        // all copies of stage kt into ring slot `slot`; pieces past the end take the row's first bytes instead (never used)
+        // All copies of stage kt into ring slot `slot`.  The waits count them, so a stage past the end and pieces past the last chunk are
+        // copied too (never used), from the first bytes of the tile: one cache line for a whole instruction.
         auto issue = [&](int kt, int slot) {
             const bool stage_ok = kt < nk;
-            const int c0 = stage_ok ? kt * NC : 0;
+            const int c0 = stage_ok ? kt * NC : 0, have = stage_ok ? nchunks - c0 : 0;
             const uint8_t *ac = a_cbase + (int64_t)c0 * 32, *bc = b_cbase + (int64_t)c0 * 32;
-            if (c0 + NC <= nchunks) {
+            const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_base + slot * S::CODE + wave * 1024);
+            if (have >= NC) {
 #pragma unroll
-                for (int u = 0; u < LC; ++u) lds_dma16(u < LA ? ac : bc, coff[u], lds_base + slot * S::CODE + (u * 4 + wave) * 1024);
+                for (int u = 0; u < LC; ++u) lds_dma16(u < LA ? ac : bc, coff[u], dst + u * 4096);
             } else {
 #pragma unroll
                 for (int u = 0; u < LC; ++u) {
                     const int p = piece0 ^ swz((u * 4 + wave) * ROWS_I + lane / SLOTS);
-                    lds_dma16(u < LA ? ac : bc, coff[u] - (p < 2 * (nchunks - c0) ? 0u : 16u * p), lds_base + slot * S::CODE + (u * 4 + wave) * 1024);
+                    lds_dma16(u < LA ? ac : bc, p < 2 * have ? coff[u] : 0u, dst + u * 4096);
                 }
             }
+            const uint32_t used = stage_ok ? 0xFFFFFFFFu : 0u;
             const int start = kt * S::SC_ROW < last_start ? kt * S::SC_ROW : last_start;
             const int back = -start & (S::SC_ROW - 1);
 #pragma unroll
             for (int u = 0; u < LS; ++u) {
                 const int row0 = ((u * 4 + wave) * SROWS_I) % ROWS;
-                lds_dma16((row0 < BM ? a_sbase : b_sbase) + start, soff[u], lds_base + SC_BASE + slot * S::SC + row0 * S::SC_ROW - back);
+                lds_dma16((row0 < BM ? a_sbase : b_sbase) + start, soff[u] & used, lds_base + SC_BASE + slot * S::SC + row0 * S::SC_ROW - back);
             }
             if (OUTER) {
                 int kb = (c0 >> 1) + wave;
                 if (kb * 2 >= nchunks) kb = 0;
 #pragma unroll
                 for (int u = 0; u < LG; ++u)
-                    lds_dma4((u < BM / 64 ? a_gbase : b_gbase) + kb, goff[u], lds_base + GS_BASE + (kt & 3) * S::GS + (wave * ROWS + u * 64) * 4);
+                    lds_dma4((u < BM / 64 ? a_gbase : b_gbase) + kb, goff[u] & used, lds_base + GS_BASE + (kt & 3) * S::GS + (wave * ROWS + u * 64) * 4);
             }
         };
         struct Raw { uint4 qa[TM], qb[TN]; };                        // 32 codes per fragment
