@@ -285,6 +285,8 @@ size_t nvfp4_workspace_bytes(int op, int64_t N, int64_t D, int64_t C, int outer_
 /* Launch configuration nvfp4_gemm_nt uses for an [M x K] * [N x K]^T product of operands in outer_mode: workgroup tile (rows x columns of the
  * output) and the number of K splits (> 1 means FP32 partials in ws plus a reduction kernel).  Host-only helper. */
 int nvfp4_gemm_plan(int64_t M, int64_t N, int64_t K, int outer_mode, int *tile_m, int *tile_n, int *split);
+/* The kernel of that launch: 1 where a workgroup's waves split the reduction of its tile, 0 where they split the tile.  Host-only helper. */
+int nvfp4_gemm_plan_kernel(int64_t M, int64_t N, int64_t K, int outer_mode, int *split_waves);
 
 /* Tensor maximum of |x| of a bf16 device array of n elements (n % 8 == 0) into amax_out (device [1]): the max |X| of
  * Sec. 2.2's S_global = max |X| / (448 * 6) for a per-tensor outer group.  ws: nvfp4_workspace_bytes(NVFP4_OP_QUANTIZE, ..). */

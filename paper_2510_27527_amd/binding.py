@@ -25,7 +25,7 @@ OUT_BF16, OUT_F32 = 0, 1
 OP_QUANTIZE, OP_GEMM, OP_LINEAR_FWD, OP_LINEAR_BWD_DX, OP_LINEAR_BWD_DW, OP_LINEAR_BWD = 0, 1, 2, 3, 4, 5
 
 EXPORTS = ["nvfp4_quantize", "nvfp4_quantize_dual", "nvfp4_gemm_nt", "nvfp4_gemm_nt_static", "nvfp4_linear_fwd", "nvfp4_linear_bwd_dx", "nvfp4_linear_bwd_dw", "nvfp4_linear_bwd", "nvfp4_osci_update", "nvfp4_osci_suppress", "nvfp4_osci_select", "nvfp4_osci_update_sparse", "nvfp4_osci_suppress_sparse", "nvfp4_osci_select_workspace_bytes", "nvfp4_outctl_fwd", "nvfp4_outctl_bwd", "nvfp4_outctl_workspace_bytes", "nvfp4_outctl_dw_plan", "nvfp4_backward_plan",
-           "nvfp4_workspace_bytes", "nvfp4_gemm_plan", "nvfp4_amax_bf16", "nvfp4_stream_key", "nvfp4_strerror", "nvfp4_version"]
+           "nvfp4_workspace_bytes", "nvfp4_gemm_plan", "nvfp4_gemm_plan_kernel", "nvfp4_amax_bf16", "nvfp4_stream_key", "nvfp4_strerror", "nvfp4_version"]
 
 
 class NVFP4Error(RuntimeError):
@@ -99,6 +99,8 @@ def lib():
         L.nvfp4_workspace_bytes.argtypes = [i32, i64, i64, i64, i32]
         L.nvfp4_gemm_plan.restype = i32
         L.nvfp4_gemm_plan.argtypes = [i64, i64, i64, i32, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        L.nvfp4_gemm_plan_kernel.restype = i32
+        L.nvfp4_gemm_plan_kernel.argtypes = [i64, i64, i64, i32, C.POINTER(C.c_int)]
         L.nvfp4_backward_plan.restype = i32
         L.nvfp4_backward_plan.argtypes = [i64, i64, i64, i64, i32, C.POINTER(C.c_int), C.POINTER(C.c_int)]
         L.nvfp4_outctl_dw_plan.restype = i32
@@ -178,6 +180,13 @@ def gemm_plan(M: int, N: int, K: int, outer: int = OUTER_TENSOR):
     a, b, c = C.c_int(), C.c_int(), C.c_int()
     _check(lib().nvfp4_gemm_plan(M, N, K, outer, C.byref(a), C.byref(b), C.byref(c)), "nvfp4_gemm_plan")
     return a.value, b.value, c.value
+
+
+def gemm_splits_waves(M: int, N: int, K: int, outer: int = OUTER_TENSOR) -> bool:
+    """Whether the planned launch runs the kernel whose waves split the reduction."""
+    a = C.c_int(0)
+    _check(lib().nvfp4_gemm_plan_kernel(M, N, K, outer, C.byref(a)), "nvfp4_gemm_plan_kernel")
+    return bool(a.value)
 
 
 def backward_plan(N: int, D_lo: int, D_hp: int, Cc: int, outer: int = OUTER_TENSOR):

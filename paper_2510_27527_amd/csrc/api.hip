@@ -400,7 +400,19 @@ int nvfp4_gemm_plan(int64_t M, int64_t N, int64_t K, int outer_mode, int *tile_m
     if (!valid_outer(outer_mode)) return NVFP4_ERR_ENUM;
     if (M < 0 || N < 0 || K < 0 || K % 64 != 0) return NVFP4_ERR_SHAPE;
     if (outer_mode == NVFP4_OUTER_BLOCK128 && K % 128 != 0) return NVFP4_ERR_SHAPE;
-    gemm_plan(M, N, K, outer_mode, tile_m, tile_n, split);
+    int split_waves;
+    gemm_plan(M, N, K, outer_mode, tile_m, tile_n, split, &split_waves);
+    return NVFP4_OK;
+}
+
+int nvfp4_gemm_plan_kernel(int64_t M, int64_t N, int64_t K, int outer_mode, int *split_waves)
+{
+    if (!split_waves) return NVFP4_ERR_NULL;
+    if (!valid_outer(outer_mode)) return NVFP4_ERR_ENUM;
+    if (M < 0 || N < 0 || K < 0 || K % 64 != 0) return NVFP4_ERR_SHAPE;
+    if (outer_mode == NVFP4_OUTER_BLOCK128 && K % 128 != 0) return NVFP4_ERR_SHAPE;
+    int tile_m, tile_n, split;
+    gemm_plan(M, N, K, outer_mode, &tile_m, &tile_n, &split, split_waves);
     return NVFP4_OK;
 }
 

@@ -96,14 +96,27 @@ const TileCfg kSmallRagged[2][2] = {{{1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}},
 // a group is launched together where that is expected to take less than this share of the separate launches
 constexpr double kGroupGain = 0.95;
 
-struct Plan { int tile; int split; int chunks_per_split; double time; };
+struct Plan { int tile; int split; int chunks_per_split; bool kw; double time; };   // kw: by gemm_kw_kernel
 
-// Whether the 64 x 64 (5) and 64 x 128 (6) tiles run on gemm_kw_kernel: below these reductions, per split, its four waves have too
-// little to share (64 x 64: K = 256 5.5 us both, 128 5.8 against 5.1; with outer blocks K = 512 6.3 against 6.4, 640 8.5 against
-// 7.9, 1152 10.0 against 11.1; 64 x 128: K = 512 7.7 against 7.1, 1024 9.9 against 10.4, with outer blocks 8.7 against 8.2, 12.0 against 12.6).
-bool waves_split_k(int tile, int64_t chunks, int outer)
+// Whether the 64 x 64 (5) and 64 x 128 (6) tiles run on gemm_kw_kernel, for a reduction of `chunks` 64s per split: below these its four
+// waves have too little to share (device times of 700 random shapes, gemm_nt_kernel's over gemm_kw_kernel's: 64 x 64, 4 to 6 chunks
+// 1.00, 7 1.10, 12 1.1 to 1.25, 30 1.4; 64 x 128, 8 chunks 0.96, 12 0.99, 16 1.06; with outer blocks 64 x 64, 10 chunks 0.99, 12 1.06, 14 1.2,
+// 64 x 128, 12 chunks 0.95, 16 1.1).
+// ragged_wgs: the workgroups of a ragged output, 0 for a whole one.  The kernel's rings and closing sums leave room for two workgroups on a
+// CU with the 64 x 64 tile, for one with 64 x 128 and with outer blocks, where gemm_nt_kernel runs three.  A ragged output is planned with the
+// latter's costs, so it may come with more workgroups than that; they are left to that kernel (gemm_kw_kernel would have 0.72 to 0.98 of
+// its speed with outer blocks - 275 x 2895 x 3072 32.5 us against 26.1, 2162 x 513 x 1152 20.0 against 17.0 -, 0.91 to 0.97 with 64 x 128; from 30 chunks on
+// it has 1.02), as are the shortest reductions (64 x 64 on more than 256 workgroups, 5 and 6 chunks 0.95, 7 1.08; 64 x 128 with outer
+// blocks, see above): 160 random shapes that change kernel by it are 1.08 times as fast, 1.00 at worst.  Whole outputs are planned with this kernel's own
+// costs, and keep it for the shortest reductions too, because the products of a backward call, which are all whole, share a
+// launch only if they run the same kernel (320 x 960 -> 1536: the call's launches 19.8 us together, 25.2 one by one).
+bool waves_split_k(int tile, int64_t chunks, int64_t ragged_wgs, int outer)
 {
-    return tile == 7 || (tile >= 5 && chunks >= (tile == 5 && !outer ? 4 : 12));
+    if (tile == 7) return true;
+    if (tile < 5) return false;
+    const bool crowded = ragged_wgs > kNumCU;
+    if (crowded && (tile == 6 || outer)) return chunks >= 30;
+    return chunks >= (tile == 6 ? (outer && ragged_wgs > 0 ? 13 : 12) : outer ? 12 : crowded ? 7 : 4);
 }
 
 // kFitted: the fitted costs where they hold; kUnfitted: the costs above for every shape; kEarly: those without the small tiles
@@ -112,7 +125,7 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
 {
     const bool early = costs == kEarly;
     const int64_t chunks = K / 64;
-    Plan best{3, 1, (int)chunks, 0.0};
+    Plan best{3, 1, (int)chunks, false, 0.0};
     if (M <= 0 || N <= 0 || chunks == 0) return best;      // nothing to tile (empty output or empty reduction)
     double best_t = 1e300;
     const bool fit = costs == kFitted && M >= 128 && N >= 128 && K >= (outer ? 256 : 512);
@@ -154,10 +167,10 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
             if (chunks % 4 == 0) cps = (cps + 3) / 4 * 4;                       // splits on 256-k boundaries
             else if (outer) cps = (cps + 1) / 2 * 2;                            // block mode: on 128-k boundaries
             if (split > 1 && (chunks + cps - 1) / cps != split) continue;      // same launch as a smaller split
-            const bool kw = fit && whole && waves_split_k(t, cps, outer);
+            const int64_t wgs = tiles * split;
+            const bool runs_kw = waves_split_k(t, cps, whole ? 0 : wgs, outer), kw = fit && whole && runs_kw;   // kw: and has its costs
             if (t == 6 && K % 256 != 0 && !kw) continue;             // the other kernel has no such instantiation
             if (t >= 5 && !kw && cps > 16 * kNC) continue;                                          // small tiles: at most 16 stages
-            const int64_t wgs = tiles * split;
             const double stages = (double)((cps + kNC - 1) / kNC);
             // workgroups sharing a CU slow each other down (128 x 128 tiles: up to three per CU)
             const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU;
@@ -189,7 +202,7 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
             }
             // partials out and back in (768 x 768 x 8192: 64 x 64 tiles of gemm_kw_kernel in three 22.1 us, in one piece 22.6)
             if (split > 1) time += (kw && !outer ? 3.2 : 4.0) + (double)(split + 1) * (double)(M * N) * 4.0 / 3.5e6;
-            if (time < best_t) { best_t = time; best = Plan{t, split, (int)cps, time}; }
+            if (time < best_t) { best_t = time; best = Plan{t, split, (int)cps, runs_kw, time}; }
         }
     }
     return best;
@@ -268,9 +281,8 @@ GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
         const int64_t M = mnk[i][0], N = mnk[i][1], K = mnk[i][2];
         if (M < (i < 2 ? 128 : 1) || N < (i < 2 ? 128 : 1) || K < 256) return none;
         const Plan p = make_plan(M, N, K, outer);
-        const bool w = waves_split_k(p.tile, K / 64, outer);
-        if (i < 2 && (p.split > 1 || (i > 0 && w != kw))) return none;
-        if (i < 2) kw = w;
+        if (i < 2 && (p.split > 1 || (i > 0 && p.kw != kw))) return none;
+        if (i < 2) kw = p.kw;
         apart += p.time;
         ps = ps && K % 256 == 0;
         whole = whole && M % 64 == 0 && N % 64 == 0;
@@ -284,7 +296,7 @@ GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
         int64_t wgs = 0, longest = 0;
         for (int i = 0; i < n; ++i) {
             const int64_t bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
-            same = same && waves_split_k(t, mnk[i][2] / 64, outer) == kw;
+            same = same && waves_split_k(t, mnk[i][2] / 64, 0, outer) == kw;
             wgs += ((mnk[i][0] + bm - 1) / bm) * ((mnk[i][1] + bn - 1) / bn);
             longest = longest < mnk[i][2] ? mnk[i][2] : longest;
         }
@@ -365,12 +377,13 @@ hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws,
     return launch_tiles(plan.tile, outer, ps, out_f32 != 0, plan.kw, g, dim3((unsigned)wgs, 1, 1), st);
 }
 
-void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int *split)
+void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int *split, int *split_waves)
 {
     const Plan p = make_plan(M, N, K, outer);
     *bm = 64 * kTiles[p.tile].tm;
     *bn = 64 * kTiles[p.tile].tn;
     *split = p.split;
+    *split_waves = p.kw ? 1 : 0;
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer)
@@ -398,7 +411,7 @@ hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K,
     const GemmArgs g = args_of(A, B, K, split > 1 ? ws : out, out_f32, p.tile, p.chunks_per_split);
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n), 1, (unsigned)split);
     hipError_t e = launch_tiles(p.tile, outer, K % 256 == 0 && p.chunks_per_split % 4 == 0, split > 1 ? 2 : (out_f32 ? 1 : 0),
-                                waves_split_k(p.tile, p.chunks_per_split, outer), g, grid, st);
+                                p.kw, g, grid, st);
     if (e != hipSuccess) return e;
     if (split > 1) {
         const int64_t mn = M * N;

@@ -88,7 +88,7 @@ struct GemmOperand {
 // Out[M x N] = A[M x K] * B[N x K]^T; splitk_ws holds split * M * N floats when split > 1
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer);
 // workgroup tile and K split the launcher will use for this shape
-void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int *split);
+void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int *split, int *split_waves);
 hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32,
                           void *ws, size_t ws_bytes, hipStream_t st);
 

@@ -210,6 +210,20 @@ def test_gemm_variant_table_reaches_every_kernel_instantiation():
         assert M % 64 and N % 4 and K % 128 == 0
 
 
+def test_kernel_of_small_tiles():
+    """Which kernel a 64-row tile runs on: ragged outputs of more workgroups than CUs stay with the one of which three share a CU
+    (two for the other on 64 x 64 with per-tensor scales, one else); whole outputs keep the one that their products share a launch on."""
+    T, O = B.OUTER_TENSOR, B.OUTER_BLOCK128
+    for M, N, K, outer, tile, split, waves in [
+            (2162, 513, 1152, O, (64, 64), 1, False), (1862, 449, 1152, O, (64, 64), 1, True), (275, 2895, 3072, O, (64, 128), 4, False),
+            (270, 1719, 5376, T, (64, 128), 7, False), (507, 2931, 1536, T, (64, 128), 1, True), (1342, 1131, 768, O, (64, 128), 1, False),
+            (222, 4901, 320, T, (64, 64), 1, False), (222, 4901, 448, T, (64, 64), 1, True), (222, 3901, 320, T, (64, 64), 1, True),
+            (320, 1536, 960, T, (64, 64), 1, True), (1536, 960, 320, T, (64, 64), 1, True)]:
+        assert B.gemm_plan(M, N, K, outer) == (*tile, split), (M, N, K)
+        assert B.gemm_splits_waves(M, N, K, outer) == waves, (M, N, K)
+    assert B.lib().nvfp4_gemm_plan_kernel(64, 64, 64, 0, None) == B.lib().nvfp4_gemm_plan(64, 64, 64, 0, None, None, None) != 0
+
+
 def test_static_scratch_entry_rejects_bad_arguments_and_oversized_products(lib):
     """nvfp4_gemm_nt_static validates like nvfp4_gemm_nt and, before any HIP call, refuses a product whose split
     reduction needs more scratch than the library's static array."""
