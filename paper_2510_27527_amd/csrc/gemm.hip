@@ -93,10 +93,7 @@ const TileCfg kTilesFit[2][kNumTiles] = {
 // 64 x 64 and 64 x 128 tiles have in gemm_nt_kernel, whichever kernel runs them.
 const TileCfg kSmallRagged[2][2] = {{{1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}}, {{1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
 
-// a group is launched together where that is expected to take less than this share of the separate launches
-constexpr double kGroupGain = 0.95;
-
-struct Plan { int tile; int split; int chunks_per_split; bool kw; double time; };   // kw: by gemm_kw_kernel
+struct Plan { int tile; int split; int chunks_per_split; bool kw; double time; };   // kw: by gemm_kw_kernel; time: the estimate
 
 // Whether the 64 x 64 (5) and 64 x 128 (6) tiles run on gemm_kw_kernel, for a reduction of `chunks` 64s per split: below these its four
 // waves have too little to share (device times of 700 random shapes, gemm_nt_kernel's over gemm_kw_kernel's: 64 x 64, 4 to 6 chunks
@@ -198,11 +195,12 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
             if (many) {
                 const double r = (double)wgs / (2 * kNumCU), up = (double)((wgs + 2 * kNumCU - 1) / (2 * kNumCU));
                 const double rounds = r > 2.0 && r + 0.4 < up ? r + 0.4 : up;
-                time = r > 4.0 ? 1e300 : 1.08 * (rounds * (stages * 0.54 + 1.3) + 5.0);
+                time = r > 4.0 ? 1e300 : rounds * (stages * 0.54 + 1.3) + 5.0;
             }
             // partials out and back in (768 x 768 x 8192: 64 x 64 tiles of gemm_kw_kernel in three 22.1 us, in one piece 22.6)
             if (split > 1) time += (kw && !outer ? 3.2 : 4.0) + (double)(split + 1) * (double)(M * N) * 4.0 / 3.5e6;
-            if (time < best_t) { best_t = time; best = Plan{t, split, (int)cps, runs_kw, time}; }
+            const double rank = many ? 1.08 * time : time;
+            if (rank < best_t) { best_t = rank; best = Plan{t, split, (int)cps, runs_kw, time}; }
         }
     }
     return best;
@@ -265,78 +263,142 @@ hipError_t launch_tiles(int tile, int outer, bool ps, bool out_f32, bool kw, con
     return (kw ? kws[outer ? 1 : 0][out_f32] : inst[outer ? 1 : 0][ps][out_f32])(tile, g, grid, st);
 }
 
+hipError_t launch_planned(const Plan &p, const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32, void *ws,
+                          size_t ws_bytes, hipStream_t st)
+{
+    const int64_t M = A.rows, N = B.rows;
+    if (M == 0 || N == 0) return hipSuccess;
+    if (K == 0) {
+        const int64_t n16 = M * N * (out_f32 ? 2 : 1);
+        const int64_t want = (n16 + kThreads - 1) / kThreads;
+        hipLaunchKernelGGL(zero_out_kernel, dim3((unsigned)(want > 4096 ? 4096 : want)), dim3(kThreads), 0, st,
+                           static_cast<uint16_t *>(out), n16);
+        return hipGetLastError();
+    }
+    const int outer = A.outer;
+    if (p.split > 1 && (ws == nullptr || ws_bytes < (size_t)p.split * M * N * sizeof(float))) return hipErrorInvalidValue;
+    const int64_t chunks = K / 64;
+    const int split = p.split > 1 ? (int)((chunks + p.chunks_per_split - 1) / p.chunks_per_split) : 1;
+    const GemmArgs g = args_of(A, B, K, split > 1 ? ws : out, out_f32, p.tile, p.chunks_per_split);
+    const dim3 grid((unsigned)(g.tiles_m * g.tiles_n), 1, (unsigned)split);
+    hipError_t e = launch_tiles(p.tile, outer, K % 256 == 0 && p.chunks_per_split % 4 == 0, split > 1 ? 2 : (out_f32 ? 1 : 0),
+                                p.kw, g, grid, st);
+    if (e != hipSuccess) return e;
+    if (split > 1) {
+        const int64_t mn = M * N;
+        const unsigned rgrid = (unsigned)((mn + (int64_t)kThreads * 4 - 1) / ((int64_t)kThreads * 4));
+        hipLaunchKernelGGL(splitk_reduce_kernel, dim3(rgrid), dim3(kThreads), 0, st,
+                           reinterpret_cast<const float *>(ws), split, mn, A.gscale, B.gscale, outer, out, out_f32);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
 // Products in one launch.  Alone, each of them ends with a round of workgroups that leaves CUs idle (928 tiles on 512 places: the
 // second round fills four fifths of them), and the next waits for its last one; together they share the last round.  They keep
 // their own plans' order of summation - the reduction in one piece, by the same kernel, whose tiles all add in the same order -
 // so that their bits do not depend on what is launched with them.  (The third, the outlier channels' part of dX, exists in no
 // other call: it takes the kernel of the other two.)
-struct GroupPlan { int tile; bool kw; };
+//
+// A launch together is taken where its estimate is below a share of the sum of the separate ones (0.95, see the sizes below).  Measured on 1965
+// random layers, device time of the whole backward call against the separate launches: the 1600 that are joined run 1.07 to 1.25 times as fast,
+// by tile, 15 of them slower (0.92 to 0.995: long reductions on 256-row tiles).
+// - Split waves with per-tensor scales, 64 x 64 up to the four rounds that a product alone may have, and 128 x 128: 1.12 to 1.22, while the
+//   estimate is 8 % too high in the median.  1.03 of the separate time is enough there (81 layers between 0.95 and 1.03: 1.10, eight of them
+//   slower, 0.94 at worst; with more rounds of 64 x 64, 11200 x 448 -> 7936 in 2093 workgroups, 0.95).
+// - Outer blocks: 128 x 128 takes 6 % less than its estimate in the median, because the last round's workgroups have their CU to themselves, and
+//   is preferred at 0.95 of it (3 % and 5 % more than their estimate with 128 x 256 and 256 x 128).
+// - Outer blocks, 256 x 128 and 128 x 256, one workgroup per CU: down to 0.86 where the second round was nearly full.  Workgroups are dealt to
+//   the 32 groups of 8 CUs in turn (over the XCDs, then inside each), and one that is due on a group full of long ones waits although another has room:
+//   896 x 4352 -> 1664, 136 long ones and 238 short, took 56 us where one pool of 256 places gives 41.  Up to three rounds they must not
+//   be 5 % slower than the separate launches in the pool of one such group.
+constexpr int kDealGroups = 32;
+
+// When the last of the workgroups ends: count[i] of time[i] each, taken in order by `places` places.
+double time_of_pool(const int64_t *count, const double *time, int n, int64_t places_all)
+{
+    double at[64], end = 0.0;                              // places and when they fall free, the earliest first
+    int64_t places[64];
+    int classes = 1;
+    at[0] = 0.0;
+    places[0] = places_all;
+    for (int i = 0; i < n; ++i) {
+        for (int64_t left = count[i]; left > 0;) {
+            if (classes >= 63) return 1e300;
+            const int64_t take = left < places[0] ? left : places[0];
+            const double until = at[0] + time[i];
+            left -= take;
+            places[0] -= take;
+            if (places[0] == 0) {
+                for (int c = 1; c < classes; ++c) { at[c - 1] = at[c]; places[c - 1] = places[c]; }
+                --classes;
+            }
+            int c = classes++;
+            for (; c > 0 && at[c - 1] > until; --c) { at[c] = at[c - 1]; places[c] = places[c - 1]; }
+            at[c] = until;
+            places[c] = take;
+            end = end < until ? until : end;
+        }
+    }
+    return end;
+}
+
+struct GroupPlan { int tile; bool kw; int order[kMaxGroup]; int planned; Plan own[kMaxGroup]; };   // own: of the first `planned` products
 
 GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
 {
-    const GroupPlan none{-1, false};
-    double apart = 0.0, best_t = 1e300;
-    bool kw = false, ps = true, whole = true;
+    GroupPlan g{-1, false, {0, 1, 2}, 0, {}};
+    bool ps = true, whole = true;
     for (int i = 0; i < n; ++i) {
         const int64_t M = mnk[i][0], N = mnk[i][1], K = mnk[i][2];
-        if (M < (i < 2 ? 128 : 1) || N < (i < 2 ? 128 : 1) || K < 256) return none;
-        const Plan p = make_plan(M, N, K, outer);
-        if (i < 2 && (p.split > 1 || (i > 0 && p.kw != kw))) return none;
-        if (i < 2) kw = p.kw;
-        apart += p.time;
+        if (M < (i < 2 ? 128 : 1) || N < (i < 2 ? 128 : 1) || K < 256) return g;
         ps = ps && K % 256 == 0;
         whole = whole && M % 64 == 0 && N % 64 == 0;
     }
-    int order[kMaxGroup] = {0, 1, 2};                      // the longest reduction first
-    for (int i = 1; i < n; ++i)
-        for (int j = i; j > 0 && mnk[order[j]][2] > mnk[order[j - 1]][2]; --j) std::swap(order[j], order[j - 1]);
-    int best = -1;
+    double apart = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const Plan p = make_plan(mnk[i][0], mnk[i][1], mnk[i][2], outer);
+        g.own[g.planned++] = p;
+        if (i < 2 && (p.split > 1 || (i > 0 && p.kw != g.kw))) return g;
+        if (i < 2) g.kw = p.kw;
+        apart += p.time;
+    }
+    const bool kw = g.kw;
+    for (int i = 1; i < n; ++i)                            // the longest reduction first
+        for (int j = i; j > 0 && mnk[g.order[j]][2] > mnk[g.order[j - 1]][2]; --j) std::swap(g.order[j], g.order[j - 1]);
+    const int64_t longest = mnk[g.order[0]][2];
+    double best_t = 1e300;
     for (int t = 0; t < kNumTiles; ++t) {
-        bool same = true;
-        int64_t wgs = 0, longest = 0;
-        for (int i = 0; i < n; ++i) {
-            const int64_t bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
-            same = same && waves_split_k(t, mnk[i][2] / 64, 0, outer) == kw;
-            wgs += ((mnk[i][0] + bm - 1) / bm) * ((mnk[i][1] + bn - 1) / bn);
-            longest = longest < mnk[i][2] ? mnk[i][2] : longest;
-        }
-        if (!same || (t == 0 && outer) || (t == 7 && (outer || !whole)) || ((t == 4 || (t == 6 && !kw)) && !ps)) continue;
+        if ((t == 0 && outer) || (t == 7 && (outer || !whole)) || ((t == 4 || (t == 6 && !kw)) && !ps)) continue;
         if (t >= 5 && !kw && longest > 16 * 64 * kNC) continue;
-        const TileCfg &cfg = t >= 5 && !(kw && whole) ? t == 7 ? kTilesFit[outer][t] : kSmallRagged[outer][t - 5] : kTilesFit[outer][t];
+        const TileCfg &cfg = (t == 5 || t == 6) && !(kw && whole) ? kSmallRagged[outer][t - 5] : kTilesFit[outer][t];
+        const int64_t bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
+        bool same = true;
+        int64_t count[kMaxGroup], wgs = 0;
+        for (int i = 0; i < n; ++i) {
+            const int64_t *s = mnk[g.order[i]];
+            same = same && waves_split_k(t, s[2] / 64, 0, outer) == kw;
+            count[i] = ((s[0] + bm - 1) / bm) * ((s[1] + bn - 1) / bn);
+            wgs += count[i];
+        }
+        if (!same) continue;
         const int64_t per_cu = (wgs + kNumCU - 1) / kNumCU, conc = per_cu < cfg.occupancy ? per_cu : cfg.occupancy;
         if (wgs > 16 * kNumCU * conc) continue;            // many rounds: the last one counts for little
         const double slow = conc == 1 ? 1.0 : conc > 2 ? 1.95 : t >= 5 && !kw ? 1.4 : outer ? 1.52 : 1.58;
-        // places of the chip and when they fall free, in order; the products' workgroups take them one after the other
-        double at[64];
-        int64_t places[64];
-        int classes = 1;
-        at[0] = 0.0;
-        places[0] = kNumCU * conc;
-        double end = 0.0;
-        for (int o = 0; o < n; ++o) {
-            const int64_t *s = mnk[order[o]], bm = 64 * kTiles[t].tm, bn = 64 * kTiles[t].tn;
-            int64_t left = ((s[0] + bm - 1) / bm) * ((s[1] + bn - 1) / bn);
-            const double time = ((double)((s[2] / 64 + kNC - 1) / kNC) * cfg.t_stage + cfg.t_fixed) * slow;
-            while (left > 0 && classes < 63) {
-                const int64_t take = left < places[0] ? left : places[0];
-                const double until = at[0] + time;
-                left -= take;
-                places[0] -= take;
-                if (places[0] == 0) {
-                    for (int c = 1; c < classes; ++c) { at[c - 1] = at[c]; places[c - 1] = places[c]; }
-                    --classes;
-                }
-                int c = classes++;
-                for (; c > 0 && at[c - 1] > until; --c) { at[c] = at[c - 1]; places[c] = places[c - 1]; }
-                at[c] = until;
-                places[c] = take;
-                end = end < until ? until : end;
-            }
-            if (left > 0) end = 1e300;
+        double time[kMaxGroup];
+        for (int i = 0; i < n; ++i)
+            time[i] = ((double)((mnk[g.order[i]][2] / 64 + kNC - 1) / kNC) * cfg.t_stage + cfg.t_fixed) * slow;
+        const bool sure = kw && !outer && (t == 7 || (t == 5 && wgs <= 4 * 2 * kNumCU));
+        const double end = time_of_pool(count, time, n, kNumCU * conc), rank = outer && t == 3 ? 0.95 * end : end;
+        if (end >= apart * (sure ? 1.03 : 0.95) || rank >= best_t) continue;
+        if (outer && (t == 1 || t == 2) && wgs <= 3 * kNumCU) {
+            for (int i = 0; i < n; ++i) count[i] = (count[i] + kDealGroups - 1) / kDealGroups;
+            if (time_of_pool(count, time, n, kNumCU / kDealGroups * conc) >= 1.05 * apart) continue;
         }
-        if (end < best_t) { best_t = end; best = t; }
+        best_t = rank;
+        g.tile = t;
     }
-    return best_t < kGroupGain * apart ? GroupPlan{best, kw} : none;
+    return g;
 }
 
 }  // namespace
@@ -356,19 +418,17 @@ hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws,
     const GroupPlan plan = plan_group(mnk, n, outer);
     if (plan.tile < 0) {
         for (int i = 0; i < n; ++i) {
-            const hipError_t e = launch_gemm_nt(p[i].A, p[i].B, p[i].K, p[i].out, out_f32, ws, ws_bytes, st);
+            const Plan own = i < plan.planned ? plan.own[i] : make_plan(mnk[i][0], mnk[i][1], mnk[i][2], outer);
+            const hipError_t e = launch_planned(own, p[i].A, p[i].B, p[i].K, p[i].out, out_f32, ws, ws_bytes, st);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
     }
-    int order[kMaxGroup] = {0, 1, 2};
-    for (int i = 1; i < n; ++i)
-        for (int j = i; j > 0 && mnk[order[j]][2] > mnk[order[j - 1]][2]; --j) std::swap(order[j], order[j - 1]);
     GemmGroup g;
     int wgs = 0;
     bool ps = true;
     for (int i = 0; i < kMaxGroup; ++i) {
-        const GemmProduct &q = p[order[i < n ? i : 0]];
+        const GemmProduct &q = p[plan.order[i < n ? i : 0]];
         g.g[i] = args_of(q.A, q.B, q.K, q.out, out_f32, plan.tile, (int)(q.K / 64));
         g.first[i] = i < n ? wgs : INT_MAX;
         if (i < n) wgs += g.g[i].tiles_m * g.g[i].tiles_n;
@@ -394,33 +454,7 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer)
 hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32,
                           void *ws, size_t ws_bytes, hipStream_t st)
 {
-    const int64_t M = A.rows, N = B.rows;
-    if (M == 0 || N == 0) return hipSuccess;
-    if (K == 0) {
-        const int64_t n16 = M * N * (out_f32 ? 2 : 1);
-        const int64_t want = (n16 + kThreads - 1) / kThreads;
-        hipLaunchKernelGGL(zero_out_kernel, dim3((unsigned)(want > 4096 ? 4096 : want)), dim3(kThreads), 0, st,
-                           static_cast<uint16_t *>(out), n16);
-        return hipGetLastError();
-    }
-    const int outer = A.outer;
-    Plan p = make_plan(M, N, K, outer);
-    if (p.split > 1 && (ws == nullptr || ws_bytes < (size_t)p.split * M * N * sizeof(float))) return hipErrorInvalidValue;
-    const int64_t chunks = K / 64;
-    const int split = p.split > 1 ? (int)((chunks + p.chunks_per_split - 1) / p.chunks_per_split) : 1;
-    const GemmArgs g = args_of(A, B, K, split > 1 ? ws : out, out_f32, p.tile, p.chunks_per_split);
-    const dim3 grid((unsigned)(g.tiles_m * g.tiles_n), 1, (unsigned)split);
-    hipError_t e = launch_tiles(p.tile, outer, K % 256 == 0 && p.chunks_per_split % 4 == 0, split > 1 ? 2 : (out_f32 ? 1 : 0),
-                                p.kw, g, grid, st);
-    if (e != hipSuccess) return e;
-    if (split > 1) {
-        const int64_t mn = M * N;
-        const unsigned rgrid = (unsigned)((mn + (int64_t)kThreads * 4 - 1) / ((int64_t)kThreads * 4));
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3(rgrid), dim3(kThreads), 0, st,
-                           reinterpret_cast<const float *>(ws), split, mn, A.gscale, B.gscale, outer, out, out_f32);
-        e = hipGetLastError();
-    }
-    return e;
+    return launch_planned(make_plan(A.rows, B.rows, K, A.outer), A, B, K, out, out_f32, ws, ws_bytes, st);
 }
 
 }  // namespace tj

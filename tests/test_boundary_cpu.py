@@ -224,6 +224,19 @@ def test_kernel_of_small_tiles():
     assert B.lib().nvfp4_gemm_plan_kernel(64, 64, 64, 0, None) == B.lib().nvfp4_gemm_plan(64, 64, 64, 0, None, None, None) != 0
 
 
+def test_products_that_share_a_launch():
+    """The tile of a backward call's joint launch on both sides of the rules that decide it."""
+    T, O = B.OUTER_TENSOR, B.OUTER_BLOCK128
+    for N, D, H, Cc, outer, tile in [
+            # outer blocks: 256 x 128 tiles whose second round is nearly full run one after the other on a crowded group of CUs
+            (896, 4352, 0, 1664, O, (0, 0)), (1152, 5760, 0, 4864, O, (128, 128)), (512, 6528, 0, 1408, O, (128, 128)),
+            # split waves: joined for an estimate of up to 1.03 of the separate time, 64 x 64 tiles up to four rounds
+            (3648, 1152, 0, 3904, T, (128, 128)), (704, 512, 0, 1984, T, (64, 64)), (11200, 448, 0, 7936, T, (0, 0)),
+            # different kernels, or a reduction in pieces: never
+            (8192, 768, 0, 3072, T, (0, 0)), (4096, 128, 0, 8192, T, (0, 0))]:
+        assert B.backward_plan(N, D, H, Cc, outer) == tile, (N, D, H, Cc)
+
+
 def test_static_scratch_entry_rejects_bad_arguments_and_oversized_products(lib):
     """nvfp4_gemm_nt_static validates like nvfp4_gemm_nt and, before any HIP call, refuses a product whose split
     reduction needs more scratch than the library's static array."""
