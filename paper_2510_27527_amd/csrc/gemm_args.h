@@ -40,7 +40,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
 // One translation unit per (output kind, scale-fetch variant, outer mode) instantiates the product kernel for every
 // tile shape: out 0 bf16, 1 f32, 2 raw f32 split-K partial; ps = paired scale fetch (K a multiple of 256); outer = 1:
 // one FP32 outer scale per row and 128 k.  tile: 0 256x256 (outer 0 only), 1 256x128, 2 128x256, 3 128x128,
-// 4 128x192 (ps only), 5 64x64, 6 64x128 (ps only).
+// 4 128x192 (ps only), 5 64x64 (outer 0: one product in one piece, short reductions), 6 64x128 (ps only).
 // Each for one product and, but for the partials, for a group.
 #define TJ_DECL_GEMM_INST(ps, out, outer) \
     hipError_t launch_gemm_inst_ps##ps##_out##out##_outer##outer(int tile, const GemmArgs &g, dim3 grid, hipStream_t st); \
@@ -50,7 +50,8 @@ TJ_DECL_GEMM_INST(1, 0, 0) TJ_DECL_GEMM_INST(1, 1, 0) TJ_DECL_GEMM_INST(1, 2, 0)
 TJ_DECL_GEMM_INST(0, 0, 1) TJ_DECL_GEMM_INST(0, 1, 1) TJ_DECL_GEMM_INST(0, 2, 1)
 TJ_DECL_GEMM_INST(1, 0, 1) TJ_DECL_GEMM_INST(1, 1, 1) TJ_DECL_GEMM_INST(1, 2, 1)
 #undef TJ_DECL_GEMM_INST
-// The kernel whose waves split the reduction, for any K >= 256 (outer 1: 768): tile 5 64x64, 6 64x128, 7 128x128 (outer 0 only).
+// The kernel whose waves split the reduction, for any K >= 256 (outer 1: 768): tile 5 64x64, 6 64x128, 7 128x128 (outer 0 only, no
+// partials).
 #define TJ_DECL_GEMM_KW(out, outer) \
     hipError_t launch_gemm_kw_out##out##_outer##outer(int tile, const GemmArgs &g, dim3 grid, hipStream_t st); \
     hipError_t launch_gemm_kw_out##out##_outer##outer(int tile, const GemmGroup &g, dim3 grid, hipStream_t st);

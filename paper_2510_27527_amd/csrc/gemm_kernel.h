@@ -13,6 +13,8 @@
 // so the order of k inside a chunk does not matter.  Small outputs with a long reduction (the
 // weight gradient) are split along K into FP32 partials that a second kernel sums in a fixed order.
 #pragma once
+#include <type_traits>
+
 #include "gemm_args.h"
 
 namespace tj {
@@ -599,7 +601,7 @@ hipError_t launch_cfg(const Args &g, dim3 grid, hipStream_t st)
 }
 
 // tile: 0 256x256 (tensor mode only: block mode needs two accumulator sets), 1 256x128, 2 128x256, 3 128x128,
-// 4 128x192 (paired scale fetch only), 5 64x64, 6 64x128 (paired scale fetch only)
+// 4 128x192 (paired scale fetch only), 5 64x64 (tensor mode: one product, not split), 6 64x128 (paired scale fetch only)
 template <int OUT, bool PS, int OUTER, class Args>
 hipError_t launch_tile(int tile, const Args &g, dim3 grid, hipStream_t st)
 {
@@ -612,7 +614,10 @@ hipError_t launch_tile(int tile, const Args &g, dim3 grid, hipStream_t st)
         case 4:
             if constexpr (PS) return launch_cfg<2, 3, OUT, true, OUTER>(g, grid, st);
             else return hipErrorInvalidValue;
-        case 5: return launch_cfg<1, 1, OUT, PS, OUTER>(g, grid, st);
+        case 5:
+            // with per-tensor scales the waves split any reduction of seven chunks and more, and any that shares a launch
+            if constexpr (OUTER == 0 && (OUT == 2 || std::is_same<Args, GemmGroup>::value)) return hipErrorInvalidValue;
+            else return launch_cfg<1, 1, OUT, PS, OUTER>(g, grid, st);
         case 6:
             if constexpr (PS) return launch_cfg<1, 2, OUT, true, OUTER>(g, grid, st);
             else return hipErrorInvalidValue;

@@ -320,7 +320,7 @@ hipError_t launch_kw_cfg(const Args &g, dim3 grid, hipStream_t st)
     return hipGetLastError();
 }
 
-// tile: 5 64x64, 6 64x128, 7 128x128 (tensor mode only)
+// tile: 5 64x64, 6 64x128, 7 128x128 (tensor mode only, never split over workgroups)
 template <int OUT, int OUTER, class Args>
 hipError_t launch_kw_tile(int tile, const Args &g, dim3 grid, hipStream_t st)
 {
@@ -328,7 +328,7 @@ hipError_t launch_kw_tile(int tile, const Args &g, dim3 grid, hipStream_t st)
         case 5: return launch_kw_cfg<2, 2, OUT, OUTER>(g, grid, st);
         case 6: return launch_kw_cfg<2, 4, OUT, OUTER>(g, grid, st);
         default:
-            if constexpr (OUTER == 0) return launch_kw_cfg<4, 4, OUT, 0>(g, grid, st);
+            if constexpr (OUTER == 0 && OUT != 2) return launch_kw_cfg<4, 4, OUT, 0>(g, grid, st);
             else return hipErrorInvalidValue;
     }
 }
