@@ -50,3 +50,35 @@ VARIANT_SHAPES_BLOCK128 = {
 RAGGED_SHAPES = [(0, 10762, 150, 1856), (0, 3105, 393, 2560), (0, 11069, 134, 2880), (0, 16564, 193, 3072), (0, 3000, 770, 2304),
                  (0, 700, 760, 8192), (0, 1000, 520, 3072), (1, 16897, 2141, 512), (1, 181, 1495, 256), (1, 4409, 281, 1920),
                  (1, 6016, 4096, 256), (0, 309, 205, 3712), (0, 196, 174, 6016), (1, 287, 279, 3712), (1, 481, 213, 12544)]
+
+# Small tiles and the kernel of each, (outer mode, M, N, K, tile, K split, whether the waves split the reduction).  Split waves work in stages
+# of 4 chunks of 64 (8 with outer blocks): whole and ragged outputs, in one piece and split, with a last split shorter than a
+# stage, one that ends inside a stage, and whole ones; neighbours that stay with the other kernel.
+SMALL_TILE_KERNELS = [
+    (0, 130, 129, 640, (64, 64), 1, True), (0, 144, 5505, 2048, (64, 128), 1, True), (0, 181, 128, 5248, (64, 64), 9, True),
+    (0, 128, 128, 5824, (64, 64), 10, True), (0, 145, 131, 1664, (64, 64), 3, True), (0, 128, 128, 2304, (64, 64), 3, True),
+    (0, 129, 451, 11264, (64, 128), 15, True), (1, 263, 263, 896, (64, 64), 1, True), (1, 921, 802, 1664, (64, 64), 1, True),
+    (1, 3303, 260, 1792, (64, 128), 1, True), (1, 258, 275, 1792, (64, 64), 3, True), (1, 256, 320, 2688, (64, 64), 4, True),
+    (1, 257, 274, 8704, (64, 64), 9, True), (1, 256, 704, 4096, (64, 64), 4, True), (1, 321, 267, 13056, (64, 128), 13, True),
+    (1, 332, 270, 12544, (64, 128), 13, True), (1, 512, 704, 5760, (64, 128), 5, True),
+    (0, 222, 4901, 320, (64, 64), 1, False), (0, 204, 513, 5632, (64, 128), 11, False), (0, 726, 372, 3072, (64, 128), 6, False),
+    (1, 2162, 513, 1152, (64, 64), 1, False), (1, 290, 838, 10240, (64, 128), 14, False), (1, 257, 260, 2048, (64, 64), 4, False)]
+
+# Layers whose backward products share a launch, (outer mode, N, D, C, tile, whether the waves split the reduction): every tile that such
+# launches take, with both reductions (N and C) multiples of 256 (paired scale fetch; 128 x 256 is not chosen for these), neither, and one of them - the launch then
+# fetches chunk by chunk what the product alone fetches in pairs.
+JOINT_LAYERS = [
+    (0, 320, 128, 256, (64, 64), True), (0, 320, 128, 320, (64, 64), True), (0, 256, 128, 256, (64, 64), True),
+    (0, 768, 640, 896, (64, 128), True), (0, 832, 640, 832, (64, 128), True), (0, 768, 704, 768, (64, 128), True),
+    (0, 512, 2560, 320, (128, 128), True), (0, 320, 3328, 320, (128, 128), True), (0, 768, 1408, 768, (128, 128), True),
+    (0, 320, 4160, 512, (128, 128), False), (0, 576, 6464, 576, (128, 128), False), (0, 256, 4160, 256, (128, 128), False),
+    (0, 512, 5504, 256, (128, 192), False), (0, 320, 6592, 768, (128, 256), False), (0, 576, 6592, 320, (128, 256), False),
+    (0, 320, 4672, 512, (256, 128), False), (0, 320, 5568, 320, (256, 128), False), (0, 512, 6272, 512, (256, 128), False),
+    (0, 576, 6592, 768, (256, 256), False), (0, 576, 6720, 576, (256, 256), False), (0, 1024, 6720, 1024, (256, 256), False),
+    (1, 896, 256, 768, (64, 64), True), (1, 896, 256, 896, (64, 64), True), (1, 768, 256, 768, (64, 64), True),
+    (1, 384, 128, 256, (64, 64), False), (1, 384, 128, 384, (64, 64), False), (1, 256, 128, 256, (64, 64), False),
+    (1, 768, 640, 896, (64, 128), True), (1, 896, 640, 896, (64, 128), True), (1, 768, 768, 768, (64, 128), True),
+    (1, 256, 2176, 256, (64, 128), False), (1, 256, 128, 896, (128, 128), False), (1, 384, 128, 896, (128, 128), False),
+    (1, 256, 128, 768, (128, 128), False), (1, 896, 3328, 3456, (128, 128), False), (1, 512, 5504, 256, (128, 192), False),
+    (1, 768, 6656, 384, (128, 256), False), (1, 384, 6272, 640, (128, 256), False), (1, 384, 6656, 256, (256, 128), False),
+    (1, 384, 5504, 384, (256, 128), False), (1, 512, 6272, 512, (256, 128), False)]

@@ -224,6 +224,17 @@ def test_kernel_of_small_tiles():
     assert B.lib().nvfp4_gemm_plan_kernel(64, 64, 64, 0, None) == B.lib().nvfp4_gemm_plan(64, 64, 64, 0, None, None, None) != 0
 
 
+def test_small_tile_and_joint_launch_tables():
+    """The planner's choices for the tables that the GPU tests of small tiles and of joint launches run over."""
+    from gemm_variants import JOINT_LAYERS, SMALL_TILE_KERNELS
+    for outer, M, N, K, tile, split, waves in SMALL_TILE_KERNELS:
+        assert (B.gemm_plan(M, N, K, outer), B.gemm_splits_waves(M, N, K, outer)) == ((*tile, split), waves), (outer, M, N, K)
+    for outer, N, D, Cc, tile, waves in JOINT_LAYERS:
+        assert B.backward_plan(N, D, 0, Cc, outer) == tile, (outer, N, D, Cc)
+        for M, Nn, K in ((N, D, Cc), (Cc, D, N)):
+            assert B.gemm_splits_waves(M, Nn, K, outer) == waves and B.gemm_plan(M, Nn, K, outer)[2] == 1, (outer, N, D, Cc)
+
+
 def test_products_that_share_a_launch():
     """The tile of a backward call's joint launch on both sides of the rules that decide it."""
     T, O = B.OUTER_TENSOR, B.OUTER_BLOCK128

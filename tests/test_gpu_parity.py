@@ -11,7 +11,7 @@ import torch
 
 import oracle
 import workloads as wl
-from gemm_variants import RAGGED_SHAPES
+from gemm_variants import JOINT_LAYERS, RAGGED_SHAPES, SMALL_TILE_KERNELS
 
 pytestmark = pytest.mark.gpu
 
@@ -493,10 +493,11 @@ SPLIT_WAVES_SHAPES = [(0, 128, 256, 256, (64, 64)), (0, 192, 448, 576, (64, 64))
                       (0, 448, 4608, 960, (64, 64)), (0, 1536, 1344, 1344, (64, 64)), (0, 4800, 832, 3904, (64, 64)), (0, 832, 4928, 3264, (64, 64))]
 
 
-@pytest.mark.parametrize("outer,M,N,K,tile", SPLIT_WAVES_SHAPES)
+@pytest.mark.parametrize("outer,M,N,K,tile,split,waves", [(*s, 1, True) for s in SPLIT_WAVES_SHAPES] + SMALL_TILE_KERNELS)
 @pytest.mark.parametrize("out_dtype", [0, 1])
-def test_gemm_waves_split_the_reduction(outer, M, N, K, tile, out_dtype):
-    assert tj.binding.gemm_plan(M, N, K, outer) == (*tile, 1)
+def test_gemm_waves_split_the_reduction(outer, M, N, K, tile, split, waves, out_dtype):
+    assert tj.binding.gemm_plan(M, N, K, outer) == (*tile, split)
+    assert tj.binding.gemm_splits_waves(M, N, K, outer) == waves
     if outer:
         A = oracle.quantize_bf16(_block_operand(M, K, 780 + N, 1.0), 0, 0, outer=oracle.OUTER_BLOCK128)
         B = oracle.quantize_bf16(_block_operand(N, K, 781 + M, 0.02), 0, 1, outer=oracle.OUTER_BLOCK128, seed=6)
@@ -846,11 +847,11 @@ def test_fused_backward_equals_separate_calls(N, D, C):
     check_product(dW2, ref, absref, "fused dW")
 
 
-@pytest.mark.parametrize("N,D,C,outer,tile", [
+@pytest.mark.parametrize("N,D,C,outer,tile", [(N, D, C, outer, tile) for outer, N, D, C, tile, _ in JOINT_LAYERS] + [
     (832, 896, 384, 0, (64, 64)), (832, 768, 832, 0, (64, 128)), (1472, 1024, 1664, 0, (128, 128)), (4736, 2816, 2176, 0, (256, 256)),
     (1152, 7744, 384, 0, (128, 256)), (384, 1792, 640, 1, (64, 64)), (1792, 768, 1408, 1, (64, 128)), (896, 3328, 3456, 1, (128, 128))])
 def test_backward_products_in_one_launch(N, D, C, outer, tile):
-    """both products of a backward call in one launch, each tile that such launches take: the bytes of the separate calls"""
+    """both products of a backward call in one launch: the bytes of the separate calls"""
     B = tj.binding
     assert B.backward_plan(N, D, 0, C, outer) == tile
     Xb, Wb, dYb = wl.linear_inputs(N, D, C, seed=22)
