@@ -186,7 +186,6 @@ __global__ __launch_bounds__(kThreads) void osci_suppress_kernel(float *W, const
 // (ends at once), 17.3 and 14.2 with the estimate, the choice of the first bin in the second pass, and the rest of the interval
 // resolved by that pass in 32768 bins.  Two chunks in flight per thread instead of one changed nothing: the passes wait for the
 // vector ALU, not for memory.
-constexpr uint32_t kNear = 16;
 constexpr int kTile = kThreads * 8;
 constexpr int kPassThreads = 1024, kPassWgs = 256, kPassWaves = kPassThreads / 64;
 

@@ -49,4 +49,7 @@ constexpr SelInterval next_interval(const SelInterval &s, uint32_t bin, int bits
     return {s.lo + (bin << shift), left < (1u << shift) ? left : 1u << shift, shift};
 }
 
+// An estimate further than this many patterns from a value is on the same side of it as the exact score (osci.hip has the bound).
+constexpr uint32_t kNear = 16;
+
 }  // namespace tj

@@ -228,15 +228,18 @@ def test_tensors_of_many_tiles(shape, frac):
     assert np.array_equal(bits(gW.cpu().numpy()), bits(oW))
 
 
-@pytest.mark.parametrize("kind", ["nan", "inf", "all nan", "mixed"])
+@pytest.mark.parametrize("kind", ["nan", "inf", "all nan", "mixed", "many"])
 def test_selection_with_non_finite_weights(kind):
     """a NaN weight scores NaN, and so does the whole outer block of an infinite one: they rank first, in index order, and
-    exactly k entries are written, with k below, at and above their number; the other elements keep the oracle's order"""
+    exactly k entries are written, with k below, at and above their number; the other elements keep the oracle's order.  "many": more of
+    them than a later pass of 2048 bins is taken for, so that the threshold lies in the open top bin of the 32768"""
     import paper_2510_27527_amd as tj
     B = tj.binding
     rng = np.random.default_rng(8)
-    W = (rng.standard_normal((48, 256)) * 0.02).astype(np.float32)
+    W = (rng.standard_normal((512 if kind == "many" else 48, 256)) * 0.02).astype(np.float32)
     flat = W.reshape(-1)
+    if kind == "many":
+        flat[rng.choice(1024, 300, replace=False) * 128 + 5] = np.inf
     if kind == "all nan":
         flat[:] = np.nan
     if kind in ("nan", "mixed"):
@@ -259,10 +262,10 @@ def test_selection_with_non_finite_weights(kind):
     key[number] = score.reshape(-1)[number]
     order = np.argsort(-key, kind="stable")
     nans = int((~number).sum())
-    assert nans == {"nan": 5, "inf": 256, "all nan": flat.size, "mixed": 261}[kind]
+    assert nans == {"nan": 5, "inf": 256, "all nan": flat.size, "mixed": 261, "many": 38400}[kind]
     gW = torch.from_numpy(W).cuda()
     ws = torch.zeros(int(B.lib().nvfp4_osci_select_workspace_bytes(*W.shape)), dtype=torch.uint8, device="cuda")
-    for k in sorted({1, 2, min(64, flat.size), max(1, nans - 1), nans, min(nans + 1, flat.size), min(nans + 700, flat.size), flat.size}):
+    for k in sorted({1, 2, min(64, flat.size), max(1, nans - 1), nans, min(nans + 1, flat.size), min(nans + 700, flat.size), flat.size} | ({32767, 32768} if kind == "many" else set())):
         out = [torch.full((flat.size + 64,), -7, dtype=torch.int32, device="cuda")] + \
               [torch.full((flat.size + 64,), -7.0, device="cuda") for _ in range(4)]
         rc = B.lib().nvfp4_osci_select(gW.data_ptr(), W.shape[0], W.shape[1], k, *[t.data_ptr() for t in out], ws.data_ptr(),
