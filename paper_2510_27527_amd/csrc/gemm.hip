@@ -76,8 +76,8 @@ constexpr int kNumTiles = 8;
 // Costs fitted to sustained runs of the tiles on whole layers' products (64 x 64 to 256 x 256 tiles; 1000 to 16384 rows, K =
 // 512 .. 16384), here with t_fixed shared between the workgroups of a CU like the stages: [0] per-tensor scales, [1]
 // 1 x 128 outer blocks, whose rescale in every stage and second accumulator set change the tiles' order.  Examples: 1000 x
-// 3072 x 1024 12.8 us with 128 x 128, 15.8 with 128 x 192; with outer blocks 8192 x 4096 x 4096 331 us with 256 x 128, 386 with
-// 128 x 192, and 2048 x 2048 x 2048 30.6 us with 128 x 128, 40.4 with 256 x 128.  They are used for outputs of at least 128 rows
+// 3072 x 1024 12.8 us with 128 x 128, 15.8 with 128 x 192; with outer blocks 8192 x 4096 x 4096 311 us with 128 x 128, 320 with 256 x 128,
+// 385 with 128 x 192, and 2048 x 2048 x 2048 28.4 us with 128 x 128, 40.1 with 256 x 128.  They are used for outputs of at least 128 rows
 // and columns, ragged ones included (360 random ragged shapes where the two sets differ: these are 1.17 times as fast
 // with per-tensor scales and 1.13 with outer blocks; eight of them are 0.80 to 0.9), and from the reduction length on at which they become the
 // better set: 512 with per-tensor scales (64 to 448: 0.85 times as fast as the costs above; 1384 x 2488 x 512: 9.6 us against
@@ -90,7 +90,8 @@ const TileCfg kTilesFit[2][kNumTiles] = {
 // workgroup per CU 3.9 us + 0.29 per 128 k (1024 x 1024: K = 512 5.3 us, 1024 6.5, 2048 8.9), with two 5.5 + 0.5; 64 x 128 5.4 +
 // 0.57 (2048 x 1024 x 1024 9.9); 128 x 128 7.3 + 0.6 to 0.8 (2048 x 2048 x 2048 19.7 us, 20.8 with gemm_nt_kernel's tile of that size;
 // 2752 x 1088 x 4416 33.5, 41.5); with outer blocks 64 x 64 4.6 + 0.41 and 64 x 128 5.6 + 0.78.  Ragged outputs keep the costs that the
-// 64 x 64 and 64 x 128 tiles have in gemm_nt_kernel, whichever kernel runs them.
+// 64 x 64 and 64 x 128 tiles have in gemm_nt_kernel: those are tested on ragged shapes, these are fitted to whole ones only, and waves_split_k then takes the kernel
+// that is the faster one for the tile and split that they give.
 const TileCfg kSmallRagged[2][2] = {{{1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}}, {{1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
 
 struct Plan { int tile; int split; int chunks_per_split; bool kw; double time; };   // kw: by gemm_kw_kernel; time: the estimate
@@ -185,7 +186,9 @@ Plan rank_tiles(int64_t M, int64_t N, int64_t K, int outer, Costs costs)
                                 : fit     ? (conc > 2 ? 1.95 : t >= 5 && !kw ? 1.4 : outer ? (K < 512 || split > 1 ? 1.7 : 1.52) : 1.58)
                                 : conc == 2 ? (t == 4 && split > 1 && !early ? 1.9 : 1.75) : 2.35;
             // (outer blocks: 1.52 is the 128 x 128 tile's since it keeps both accumulator sets in ordinary registers; split plans keep
-            // the 1.7 from before, so that no product comes to need a workspace by it)
+            // the 1.7 from before, so that no product comes to need a workspace by it.  125 random products that take that tile instead of a larger one
+            // for the 1.52: 1.07 times as fast, up to 1.32 where the larger tile's second round is short, 0.97 to 1.00 at 290 to 490 tiles
+            // of long reductions - 3072 x 2432 x 20224 360 -> 372 us)
             const int64_t waves = (wgs + kNumCU * conc - 1) / (kNumCU * conc);
             // 128 x 128 with split waves: a stage takes longer the more CUs draw on the L2 caches (144 workgroups 0.64 us, 198 0.76, 256 0.8)
             const double t_stage = t == 7 ? 0.55 + 0.29 * (wgs < kNumCU ? (double)wgs / kNumCU : 1.0) : cfg.t_stage;

@@ -271,7 +271,7 @@ struct OpFrags {
 // PACK (2 x 2 tiles with OUTER): two waves per SIMD asked for.  Both accumulator sets then live in ordinary registers (210 in all),
 // where one wave's allowance puts the matrix instructions' results into accumulation registers, from which the rescale first copies
 // them: one instruction in seven of the loop.  With two workgroups on a CU, where the loop is bound by its instructions, this is the
-// faster form (1664 x 6528 x 896 41.7 -> 33.9 us; 8192 x 4096 x 4096 on this tile 345, on 256 x 128 353); a workgroup with the CU to
+// faster form (1664 x 6528 x 896 41.7 -> 33.9 us; 8192 x 4096 x 4096 on this tile 311, on 256 x 128 320); a workgroup with the CU to
 // itself waits for results more often and is 6 % slower with it (1280 x 2688 x 5760 77.7 against 82.6).
 template <int TM, int TN, int NC, int OUT, bool PS, int OUTER, bool PACK, class Args>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
 __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1) void gemm_nt_kernel(Args args)

@@ -8,8 +8,10 @@
 // to add their four partial sums through LDS in a fixed order.
 // Before (gemm_nt_kernel's tile of that output) and after, in us: 1024 x 1024 x 1024 8.6 -> 6.5, x 2048 13.6 -> 8.9 (64 x 64);
 // 704 x 832 x 1600 11.7 -> 8.9; 640 x 1536 x 2496 22.2 (split over workgroups) -> 12.1; 2752 x 1088 x 4416 41.5 -> 33.5 (128 x 128);
-// 3072 x 768 x 8192 54.4 (split) -> 48.6; outer blocks 1024 x 384 x 1024 10.5 -> 8.7.  Bound now by the vector ALU (64 x 64: 12 of 16
-// instructions per MFMA are the expansion) and, for 128 x 128, by L2 -> LDS copies and the closing sums (1.7 us).
+// 3072 x 768 x 8192 54.4 (split) -> 48.6; outer blocks 1024 x 384 x 1024 10.5 -> 8.7, 1024 x 1024 x 1152 8.5.
+// Bound now by the vector ALU (64 x 64: 12 of 16 instructions per MFMA are the expansion).  With 128 x 128 tiles counters show 5.0 to 5.6 vector
+// instructions per MFMA and the matrix pipes busy 60 % of the time on the CUs that have a workgroup (768 x 3072 x 8192, 144 of them; 50 % with 198,
+// 2752 x 1088 x 4416): a stage takes longer the more CUs draw on the L2 caches (0.64 us with 144, 0.8 with 256), and the closing sums 1.7 us.
 //
 // A pipeline stage is 256 k (512 with 1 x 128 outer blocks, a block per wave): 128 or 256 bytes of a row's codes at a time, whole
 // cache lines, copied global -> LDS directly, two stages ahead in a ring of three (64 x 128 with outer blocks: one ahead in a ring
