@@ -309,12 +309,13 @@ hipError_t launch_planned(const Plan &p, const GemmOperand &A, const GemmOperand
 // - Split waves with per-tensor scales, 64 x 64 up to the four rounds that a product alone may have, and 128 x 128: 1.12 to 1.22, while the
 //   estimate is 8 % too high in the median.  1.03 of the separate time is enough there (81 layers between 0.95 and 1.03: 1.10, eight of them
 //   slower, 0.94 at worst; with more rounds of 64 x 64, 11200 x 448 -> 7936 in 2093 workgroups, 0.95).
-// - Outer blocks: 128 x 128 takes 6 % less than its estimate in the median, because the last round's workgroups have their CU to themselves, and
-//   is preferred at 0.95 of it (3 % and 5 % more than their estimate with 128 x 256 and 256 x 128).
-// - Outer blocks, 256 x 128 and 128 x 256, one workgroup per CU: down to 0.86 where the second round was nearly full.  Workgroups are dealt to
-//   the 32 groups of 8 CUs in turn (over the XCDs, then inside each), and one that is due on a group full of long ones waits although another has room:
-//   896 x 4352 -> 1664, 136 long ones and 238 short, took 56 us where one pool of 256 places gives 41.  Up to three rounds they must not
-//   be 5 % slower than the separate launches in the pool of one such group.
+// - Outer blocks: 128 x 128 takes 6 % less than its estimate in the median (which slows the workgroups of the last round as if each still shared
+//   its CU), and is preferred at 0.95 of it (3 % and 5 % more than their estimate with 128 x 256 and 256 x 128).
+// - Outer blocks, 256 x 128 and 128 x 256, one workgroup per CU: down to 0.86 where the second round was nearly full.  Workgroups are dealt in
+//   turn over the XCDs and, inside each, over its four shader engines, and one that is due on an engine full of long ones waits although another has
+//   room.  896 x 4352 -> 1664 has 136 long ones (35 us) and 238 short (21), which one pool of 256 places would finish in 41 us: workgroups that only
+//   wait for these times take 57, and 43 with 119 and 221.  Up to three rounds these tiles must not be 5 % slower than the separate launches in the
+//   pool of one engine's 8 CUs.
 constexpr int kDealGroups = 32;
 
 // When the last of the workgroups ends: count[i] of time[i] each, taken in order by `places` places.
