@@ -55,9 +55,11 @@ size_t gscale_bytes(int64_t rows, int64_t K, int outer)
 {
     return outer == NVFP4_OUTER_BLOCK128 ? sizeof(float) * (size_t)(rows * (K / 128)) : sizeof(float);
 }
-size_t packed_bytes(int64_t rows, int64_t K, int outer)
+// blocked: with the scale bytes of whole 256 k
+size_t packed_bytes(int64_t rows, int64_t K, int outer, bool blocked = false)
 {
-    return align_up((size_t)(rows * K / 2)) + align_up((size_t)(rows * K / 16)) + align_up(gscale_bytes(rows, K, outer));
+    return align_up((size_t)(rows * K / 2)) + align_up(blocked ? blocked_scale_bytes(rows, K) : (size_t)(rows * K / 16)) +
+           align_up(gscale_bytes(rows, K, outer));
 }
 bool valid_outer(int outer) { return outer == NVFP4_OUTER_TENSOR || outer == NVFP4_OUTER_BLOCK128; }
 
@@ -160,7 +162,7 @@ void set_rht(QuantParams &p, const QuantPlan &pl, const nvfp4_qcfg *cfg)
 }
 
 int run_quantize(const void *src, const QuantPlan &pl, const nvfp4_qcfg *cfg, nvfp4_tensor *out, float *partials,
-                 hipStream_t st)
+                 hipStream_t st, bool blocked = false)
 {
     QuantParams p{};
     p.rounding = pl.rounding;
@@ -170,7 +172,7 @@ int run_quantize(const void *src, const QuantPlan &pl, const nvfp4_qcfg *cfg, nv
     p.k0 = (uint32_t)key;
     p.k1 = (uint32_t)(key >> 32);
     set_rht(p, pl, cfg);
-    QuantOut o{out->codes, out->scales, out->gscale, out->amax_deq};
+    QuantOut o{out->codes, out->scales, out->gscale, out->amax_deq, blocked};
     out->rows = pl.out_rows;
     out->K = pl.out_K;
     out->outer_mode = pl.outer;
@@ -244,8 +246,8 @@ int run_quantize_row_pair(const void *src0, const QuantPlan &pl0, nvfp4_tensor *
         return rc ? rc : run_quantize(src1, pl1, cfg, out1, partials1, st);
     }
     QuantParams p0 = params_of(pl0, cfg), p1 = params_of(pl1, cfg);
-    QuantOut o0{out0->codes, out0->scales, out0->gscale, out0->amax_deq};
-    QuantOut o1{out1->codes, out1->scales, out1->gscale, out1->amax_deq};
+    QuantOut o0{out0->codes, out0->scales, out0->gscale, out0->amax_deq, 0};
+    QuantOut o1{out1->codes, out1->scales, out1->gscale, out1->amax_deq, 0};
     if (pl0.rounding != NVFP4_ROUND_RTN) o0.amax_deq = o1.amax_deq = nullptr;
     stamp(out0, pl0);
     stamp(out1, pl1);
@@ -263,19 +265,20 @@ int run_quantize_row_pair(const void *src0, const QuantPlan &pl0, nvfp4_tensor *
 // partial maxima of that array of n elements come from the same launch.
 int run_requant_pair(const nvfp4_tensor *s0, const QuantPlan &pl0, const nvfp4_qcfg *c0, nvfp4_tensor *out0,
                      const nvfp4_tensor *s1, const QuantPlan &pl1, const nvfp4_qcfg *c1, nvfp4_tensor *out1,
-                     hipStream_t st, const void *bf16 = nullptr, int64_t n = 0, float *partials = nullptr, int *npart = nullptr)
+                     hipStream_t st, bool blocked0, bool blocked1, const void *bf16 = nullptr, int64_t n = 0, float *partials = nullptr,
+                     int *npart = nullptr)
 {
     QuantParams p0 = params_of(pl0, c0), p1 = params_of(pl1, c1);
     p0.amax_scalar = pl0.outer == NVFP4_OUTER_TENSOR ? (c0->amax_in ? c0->amax_in : s0->amax_deq) : nullptr;
     p1.amax_scalar = pl1.outer == NVFP4_OUTER_TENSOR ? (c1->amax_in ? c1->amax_in : s1->amax_deq) : nullptr;
     if (p0.rounding != p1.rounding || p0.scale_up != p1.scale_up || p0.outer != p1.outer || p0.rht != p1.rht) {
         if (bf16) *npart = launch_amax_partials(bf16, n, partials, nullptr, st);
-        const int rc = run_quantize(s0, pl0, c0, out0, nullptr, st);
-        return rc ? rc : run_quantize(s1, pl1, c1, out1, nullptr, st);
+        const int rc = run_quantize(s0, pl0, c0, out0, nullptr, st, blocked0);
+        return rc ? rc : run_quantize(s1, pl1, c1, out1, nullptr, st, blocked1);
     }
     stamp(out0, pl0);
     stamp(out1, pl1);
-    QuantOut o0{out0->codes, out0->scales, out0->gscale, nullptr}, o1{out1->codes, out1->scales, out1->gscale, nullptr};
+    QuantOut o0{out0->codes, out0->scales, out0->gscale, nullptr, blocked0}, o1{out1->codes, out1->scales, out1->gscale, nullptr, blocked1};
     PackedSrc ps0{s0->codes, s0->scales, s0->gscale, s0->outer_mode}, ps1{s1->codes, s1->scales, s1->gscale, s1->outer_mode};
     const hipError_t e = bf16 ? launch_requant_col_pair_amax(ps0, pl0.R, pl0.C, p0, o0, ps1, pl1.R, pl1.C, p1, o1, bf16, n, partials, npart, st)
                               : launch_requant_col_pair(ps0, pl0.R, pl0.C, p0, o0, ps1, pl1.R, pl1.C, p1, o1, st);
@@ -283,24 +286,24 @@ int run_requant_pair(const nvfp4_tensor *s0, const QuantPlan &pl0, const nvfp4_q
 }
 
 int run_gemm(const nvfp4_tensor *A, const nvfp4_tensor *B, void *Out, int out_dtype, void *ws, size_t ws_bytes,
-             hipStream_t st)
+             hipStream_t st, bool blocked = false)
 {
     const int outer = A->outer_mode == NVFP4_OUTER_BLOCK128 ? 1 : 0;
-    GemmOperand a{A->codes, A->scales, A->gscale, A->rows, outer};
-    GemmOperand b{B->codes, B->scales, B->gscale, B->rows, outer};
+    GemmOperand a{A->codes, A->scales, A->gscale, A->rows, outer, blocked};
+    GemmOperand b{B->codes, B->scales, B->gscale, B->rows, outer, blocked};
     const hipError_t e = launch_gemm_nt(a, b, A->K, Out, out_dtype == NVFP4_OUT_F32, ws, ws_bytes, st);
     return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
 // products of one backward call, in one launch where that is faster
-struct Product { const nvfp4_tensor *A, *B; void *out; };
+struct Product { const nvfp4_tensor *A, *B; void *out; bool blocked; };
 int run_gemm_group(const Product *p, int n, int out_dtype, void *ws, size_t ws_bytes, hipStream_t st)
 {
     GemmProduct g[3];
     for (int i = 0; i < n; ++i) {
         const int outer = p[i].A->outer_mode == NVFP4_OUTER_BLOCK128 ? 1 : 0;
-        g[i] = GemmProduct{GemmOperand{p[i].A->codes, p[i].A->scales, p[i].A->gscale, p[i].A->rows, outer},
-                           GemmOperand{p[i].B->codes, p[i].B->scales, p[i].B->gscale, p[i].B->rows, outer}, p[i].A->K, p[i].out};
+        g[i] = GemmProduct{GemmOperand{p[i].A->codes, p[i].A->scales, p[i].A->gscale, p[i].A->rows, outer, p[i].blocked},
+                           GemmOperand{p[i].B->codes, p[i].B->scales, p[i].B->gscale, p[i].B->rows, outer, p[i].blocked}, p[i].A->K, p[i].out};
     }
     return launch_gemm_group(g, n, out_dtype == NVFP4_OUT_F32, ws, ws_bytes, st) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
@@ -333,10 +336,10 @@ int static_scratch(void **out)
 }
 
 // carve a temporary operand [rows x K] out of the workspace
-bool carve_tensor(Carver &cv, int64_t rows, int64_t K, int outer, nvfp4_tensor *t)
+bool carve_tensor(Carver &cv, int64_t rows, int64_t K, int outer, nvfp4_tensor *t, bool blocked)
 {
     t->codes = static_cast<uint8_t *>(cv.take((size_t)(rows * K / 2)));
-    t->scales = static_cast<uint8_t *>(cv.take((size_t)(rows * K / 16)));
+    t->scales = static_cast<uint8_t *>(cv.take(blocked ? blocked_scale_bytes(rows, K) : (size_t)(rows * K / 16)));
     t->gscale = static_cast<float *>(cv.take(gscale_bytes(rows, K, outer)));
     t->amax_deq = nullptr;
     t->rows = rows;
@@ -373,6 +376,16 @@ const char *nvfp4_version(void) { return "tjnvfp4 0.1 gfx950"; }
 
 uint64_t nvfp4_stream_key(uint64_t seed, uint32_t tensor_id) { return stream_key(seed, tensor_id); }
 
+// A backward call's workspace.  Its operands are blocked along K where their products can read that; a workspace that has no room for the
+// scale bytes' whole 256 k (blocked = false: the least that a call accepts) keeps them row-major.
+static size_t backward_bytes(int op, int64_t N, int64_t D, int64_t C, int o, size_t gemm_ws, bool blocked)
+{
+    size_t n = partials_bytes() + align_up(gemm_ws) + (op == NVFP4_OP_LINEAR_BWD ? align_up(sizeof(float)) : 0);
+    if (op != NVFP4_OP_LINEAR_BWD_DW) n += packed_bytes(N, C, o, blocked) + packed_bytes(D, C, o, blocked);
+    if (op != NVFP4_OP_LINEAR_BWD_DX) n += packed_bytes(C, N, o, blocked) + packed_bytes(D, N, o, blocked);
+    return n;
+}
+
 size_t nvfp4_workspace_bytes(int op, int64_t N, int64_t D, int64_t C, int outer_mode)
 {
     if (N < 0 || D < 0 || C < 0 || !valid_outer(outer_mode)) return 0;
@@ -381,14 +394,11 @@ size_t nvfp4_workspace_bytes(int op, int64_t N, int64_t D, int64_t C, int outer_
         case NVFP4_OP_QUANTIZE: return partials_bytes();
         case NVFP4_OP_GEMM: return align_up(gemm_workspace_bytes(N, C, D, o));
         case NVFP4_OP_LINEAR_FWD: return 2 * partials_bytes() + align_up(gemm_workspace_bytes(N, C, D, o));
-        case NVFP4_OP_LINEAR_BWD_DX:
-            return partials_bytes() + packed_bytes(N, C, o) + packed_bytes(D, C, o) + align_up(gemm_workspace_bytes(N, D, C, o));
-        case NVFP4_OP_LINEAR_BWD_DW:
-            return partials_bytes() + packed_bytes(C, N, o) + packed_bytes(D, N, o) + align_up(gemm_workspace_bytes(C, D, N, o));
+        case NVFP4_OP_LINEAR_BWD_DX: return backward_bytes(op, N, D, C, o, gemm_workspace_bytes(N, D, C, o), true);
+        case NVFP4_OP_LINEAR_BWD_DW: return backward_bytes(op, N, D, C, o, gemm_workspace_bytes(C, D, N, o), true);
         case NVFP4_OP_LINEAR_BWD: {
-            const size_t g1 = align_up(gemm_workspace_bytes(N, D, C, o)), g2 = align_up(gemm_workspace_bytes(C, D, N, o));
-            return partials_bytes() + align_up(sizeof(float)) + packed_bytes(N, C, o) + packed_bytes(D, C, o) +
-                   packed_bytes(C, N, o) + packed_bytes(D, N, o) + (g1 > g2 ? g1 : g2);
+            const size_t g1 = gemm_workspace_bytes(N, D, C, o), g2 = gemm_workspace_bytes(C, D, N, o);
+            return backward_bytes(op, N, D, C, o, g1 > g2 ? g1 : g2, true);
         }
         default: return 0;
     }
@@ -465,8 +475,8 @@ int nvfp4_quantize_dual(const void *src, int64_t R, int64_t C, const nvfp4_qcfg 
         pr.amax_partials = pc.amax_partials = static_cast<float *>(ws);
     }
     // the dequantized maximum is only produced by the deterministic row-wise quantizer of nvfp4_quantize
-    QuantOut orow{out_row->codes, out_row->scales, out_row->gscale, nullptr};
-    QuantOut ocol{out_col->codes, out_col->scales, out_col->gscale, nullptr};
+    QuantOut orow{out_row->codes, out_row->scales, out_row->gscale, nullptr, 0};
+    QuantOut ocol{out_col->codes, out_col->scales, out_col->gscale, nullptr, 0};
     return launch_quant_dual_bf16(src, R, C, pr, orow, pc, ocol, st) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
@@ -520,26 +530,32 @@ static size_t outctl_fwd_bytes(int64_t N, int64_t D_lo, int64_t C, int outer, in
 }
 
 // the five packed operands of a backward call, one after the other in its workspace
-static size_t outctl_operand_bytes(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer)
+static size_t outctl_operand_bytes(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer, bool blocked = false)
 {
-    return packed_bytes(N, C, outer) + packed_bytes(D_lo, C, outer) + packed_bytes(D_hp, C, outer) + packed_bytes(C, N, outer) +
-           packed_bytes(D_lo, N, outer);
+    return packed_bytes(N, C, outer, blocked) + packed_bytes(D_lo, C, outer, blocked) + packed_bytes(D_hp, C, outer, blocked) +
+           packed_bytes(C, N, outer, blocked) + packed_bytes(D_lo, N, outer, blocked);
 }
 
-static size_t outctl_bwd_bytes(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer)
+static size_t outctl_bwd_bytes(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer, size_t gemm_ws, bool blocked)
 {
-    const size_t g1 = align_up(gemm_workspace_bytes(N, D_lo, C, outer)), g2 = align_up(gemm_workspace_bytes(C, D_lo, N, outer));
-    const size_t g3 = align_up(gemm_workspace_bytes(N, D_hp, C, outer));
-    size_t g = g1 > g2 ? g1 : g2;
-    g = g > g3 ? g : g3;
-    return 2 * partials_bytes() + outctl_operand_bytes(N, D_lo, D_hp, C, outer) + align_up((size_t)(N * C) * 2) +
-           align_up((size_t)(N * D_hp) * 2) + g;
+    return 2 * partials_bytes() + outctl_operand_bytes(N, D_lo, D_hp, C, outer, blocked) + align_up((size_t)(N * C) * 2) +
+           align_up((size_t)(N * D_hp) * 2) + align_up(gemm_ws);
+}
+
+// of its three products: dX_lo, dW_lo, dX_hp
+struct OutctlNeeds { GemmNeeds lo, w, hp; size_t ws; };
+static OutctlNeeds outctl_needs(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer)
+{
+    OutctlNeeds n{gemm_needs(N, D_lo, C, outer), gemm_needs(C, D_lo, N, outer), gemm_needs(N, D_hp, C, outer), 0};
+    n.ws = n.lo.ws > n.w.ws ? n.lo.ws : n.w.ws;
+    n.ws = n.ws > n.hp.ws ? n.ws : n.hp.ws;
+    return n;
 }
 
 size_t nvfp4_outctl_workspace_bytes(int backward, int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int out_dtype)
 {
     if (N < 0 || D_lo < 0 || D_hp < 0 || C < 0 || !valid_outer(outer_mode)) return 0;
-    return backward ? outctl_bwd_bytes(N, D_lo, D_hp, C, outer_mode) : outctl_fwd_bytes(N, D_lo, C, outer_mode, out_dtype);
+    return backward ? outctl_bwd_bytes(N, D_lo, D_hp, C, outer_mode, outctl_needs(N, D_lo, D_hp, C, outer_mode).ws, true) : outctl_fwd_bytes(N, D_lo, C, outer_mode, out_dtype);
 }
 
 int nvfp4_outctl_dw_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *split, int *stages)
@@ -602,20 +618,28 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     const int outer = Xq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
     if (!aligned16(dY) || !aligned16(X_hp) || !aligned16(W_hp)) return NVFP4_ERR_ALIGN;
-    if (!ws || ws_bytes < outctl_bwd_bytes(N, D_lo, D_hp, C, outer)) return NVFP4_ERR_WORKSPACE;
+    const OutctlNeeds need = outctl_needs(N, D_lo, D_hp, C, outer);
+    if (!ws || ws_bytes < outctl_bwd_bytes(N, D_lo, D_hp, C, outer, need.ws, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
     float *part = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     float *part2 = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     nvfp4_tensor q3{}, q4{}, q4h{}, q5{}, q6{};
-    if (!carve_tensor(cv, N, C, outer, &q3) || !carve_tensor(cv, D_lo, C, outer, &q4) || !carve_tensor(cv, D_hp, C, outer, &q4h) ||
-        !carve_tensor(cv, C, N, outer, &q5) || !carve_tensor(cv, D_lo, N, outer, &q6))
+    const bool room = ws_bytes >= outctl_bwd_bytes(N, D_lo, D_hp, C, outer, need.ws, true);
+    // Q3 serves both column sets: the outlier channels' product, whatever kernel it would take alone, has to be launched together with the others
+    bool hp_blocked = need.hp.blocked || D_hp == 0;
+    if (!hp_blocked && need.lo.blocked && need.w.blocked) {
+        const int64_t mnk[3][3] = {{N, D_lo, C}, {C, D_lo, N}, {N, D_hp, C}};
+        int bm, bn;
+        gemm_group_plan(mnk, 3, outer, &bm, &bn);
+        hp_blocked = bm > 0 && D_hp <= (1 << 24);
+    }
+    const bool bx = room && need.lo.blocked && hp_blocked && (!outer || need.w.blocked), bw = room && need.w.blocked && (!outer || bx);
+    if (!carve_tensor(cv, N, C, outer, &q3, bx) || !carve_tensor(cv, D_lo, C, outer, &q4, bx) || !carve_tensor(cv, D_hp, C, outer, &q4h, bx) ||
+        !carve_tensor(cv, C, N, outer, &q5, bw) || !carve_tensor(cv, D_lo, N, outer, &q6, bw))
         return NVFP4_ERR_WORKSPACE;
     void *dYT = cv.take((size_t)(N * C) * 2), *XhT = cv.take((size_t)(N * D_hp) * 2);
-    const size_t g1 = gemm_workspace_bytes(N, D_lo, C, outer), g2 = gemm_workspace_bytes(C, D_lo, N, outer),
-                 g3 = gemm_workspace_bytes(N, D_hp, C, outer);
-    size_t gbytes = g1 > g2 ? g1 : g2;
-    gbytes = gbytes > g3 ? gbytes : g3;
+    const size_t gbytes = need.ws;
     void *gws = gbytes ? cv.take(gbytes) : nullptr;
     if (!dYT || !XhT || (gbytes && !gws)) return NVFP4_ERR_WORKSPACE;
 
@@ -631,13 +655,13 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     if (!rc && D_hp > 0) rc = plan_quantize(W_hp, NVFP4_SRC_BF16, C, D_hp, 1, &c9, &q4h, &p9);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = run_quantize(dY, p3, &c3, &q3, part, st);
-    if (!rc) rc = run_quantize(dY, p5, &c5, &q5, part, st);
-    if (!rc) rc = run_requant_pair(Wq_ctx, p4, &c4, &q4, Xq_ctx, p6, &c6, &q6, st);
-    if (!rc && D_hp > 0) rc = run_quantize(W_hp, p9, &c9, &q4h, part2, st);
+    rc = run_quantize(dY, p3, &c3, &q3, part, st, bx);
+    if (!rc) rc = run_quantize(dY, p5, &c5, &q5, part, st, bw);
+    if (!rc) rc = run_requant_pair(Wq_ctx, p4, &c4, &q4, Xq_ctx, p6, &c6, &q6, st, bx, bw);
+    if (!rc && D_hp > 0) rc = run_quantize(W_hp, p9, &c9, &q4h, part2, st, bx);
     if (rc) return rc;
     // dX over all input channels in FP4 (one Q3 operand serves both column sets); dW of the ordinary channels in FP4
-    const Product products[] = {{&q3, &q4, dX_lo}, {&q5, &q6, dW_lo}, {&q3, &q4h, dX_hp}};
+    const Product products[] = {{&q3, &q4, dX_lo, bx}, {&q5, &q6, dW_lo, bw}, {&q3, &q4h, dX_hp, bx}};
     rc = run_gemm_group(products, D_hp > 0 ? 3 : 2, out_dtype, gws, gbytes, st);
     if (rc) return rc;
     // dW of the outlier channels in bf16: dY^T [C x N] times X_hp^T [D_hp x N]^T, the reduction running over tokens
@@ -791,13 +815,15 @@ int nvfp4_linear_bwd_dx(const void *dY, const nvfp4_tensor *Wq_ctx, int64_t N, i
     if (Wq_ctx->rows != C || Wq_ctx->K != D) return NVFP4_ERR_MISMATCH;
     const int outer = Wq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
-    if (!ws || ws_bytes < nvfp4_workspace_bytes(NVFP4_OP_LINEAR_BWD_DX, N, D, C, outer)) return NVFP4_ERR_WORKSPACE;
+    const GemmNeeds need = gemm_needs(N, D, C, outer);
+    if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD_DX, N, D, C, outer, need.ws, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
     float *part = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     nvfp4_tensor dYq{}, Wq2{};
-    if (!carve_tensor(cv, N, C, outer, &dYq) || !carve_tensor(cv, D, C, outer, &Wq2)) return NVFP4_ERR_WORKSPACE;
-    const size_t gbytes = gemm_workspace_bytes(N, D, C, outer);
+    const bool blk = need.blocked && ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD_DX, N, D, C, outer, need.ws, true);
+    if (!carve_tensor(cv, N, C, outer, &dYq, blk) || !carve_tensor(cv, D, C, outer, &Wq2, blk)) return NVFP4_ERR_WORKSPACE;
+    const size_t gbytes = need.ws;
     void *gws = gbytes ? cv.take(gbytes) : nullptr;
 
     nvfp4_qcfg c3 = bwd_cfg(seed, layer_id, 3, outer, rht), c4 = bwd_cfg(seed, layer_id, 4, outer, rht);
@@ -807,11 +833,11 @@ int nvfp4_linear_bwd_dx(const void *dY, const nvfp4_tensor *Wq_ctx, int64_t N, i
     rc = plan_quantize(Wq_ctx, NVFP4_SRC_NVFP4, C, D, 1, &c4, &Wq2, &p4);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = run_quantize(dY, p3, &c3, &dYq, part, st);
+    rc = run_quantize(dY, p3, &c3, &dYq, part, st, blk);
     if (rc) return rc;
-    rc = run_quantize(Wq_ctx, p4, &c4, &Wq2, nullptr, st);
+    rc = run_quantize(Wq_ctx, p4, &c4, &Wq2, nullptr, st, blk);
     if (rc) return rc;
-    return run_gemm(&dYq, &Wq2, dX, out_dtype, gws, gbytes, st);
+    return run_gemm(&dYq, &Wq2, dX, out_dtype, gws, gbytes, st, blk);
 }
 
 int nvfp4_linear_bwd_dw(const void *dY, const nvfp4_tensor *Xq_ctx, int64_t N, int64_t D, int64_t C, void *dW,
@@ -825,13 +851,15 @@ int nvfp4_linear_bwd_dw(const void *dY, const nvfp4_tensor *Xq_ctx, int64_t N, i
     if (Xq_ctx->rows != N || Xq_ctx->K != D) return NVFP4_ERR_MISMATCH;
     const int outer = Xq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
-    if (!ws || ws_bytes < nvfp4_workspace_bytes(NVFP4_OP_LINEAR_BWD_DW, N, D, C, outer)) return NVFP4_ERR_WORKSPACE;
+    const GemmNeeds need = gemm_needs(C, D, N, outer);
+    if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD_DW, N, D, C, outer, need.ws, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
     float *part = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     nvfp4_tensor dYq{}, Xq2{};
-    if (!carve_tensor(cv, C, N, outer, &dYq) || !carve_tensor(cv, D, N, outer, &Xq2)) return NVFP4_ERR_WORKSPACE;
-    const size_t gbytes = gemm_workspace_bytes(C, D, N, outer);
+    const bool blk = need.blocked && ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD_DW, N, D, C, outer, need.ws, true);
+    if (!carve_tensor(cv, C, N, outer, &dYq, blk) || !carve_tensor(cv, D, N, outer, &Xq2, blk)) return NVFP4_ERR_WORKSPACE;
+    const size_t gbytes = need.ws;
     void *gws = gbytes ? cv.take(gbytes) : nullptr;
 
     nvfp4_qcfg c5 = bwd_cfg(seed, layer_id, 5, outer, rht), c6 = bwd_cfg(seed, layer_id, 6, outer, rht);
@@ -841,11 +869,11 @@ int nvfp4_linear_bwd_dw(const void *dY, const nvfp4_tensor *Xq_ctx, int64_t N, i
     rc = plan_quantize(Xq_ctx, NVFP4_SRC_NVFP4, N, D, 1, &c6, &Xq2, &p6);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = run_quantize(dY, p5, &c5, &dYq, part, st);
+    rc = run_quantize(dY, p5, &c5, &dYq, part, st, blk);
     if (rc) return rc;
-    rc = run_quantize(Xq_ctx, p6, &c6, &Xq2, nullptr, st);
+    rc = run_quantize(Xq_ctx, p6, &c6, &Xq2, nullptr, st, blk);
     if (rc) return rc;
-    return run_gemm(&dYq, &Xq2, dW, out_dtype, gws, gbytes, st);
+    return run_gemm(&dYq, &Xq2, dW, out_dtype, gws, gbytes, st, blk);
 }
 
 int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_tensor *Wq_ctx, int64_t N, int64_t D,
@@ -864,17 +892,19 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     const int outer = Xq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
     if (!aligned16(dY)) return NVFP4_ERR_ALIGN;
-    if (!ws || ws_bytes < nvfp4_workspace_bytes(NVFP4_OP_LINEAR_BWD, N, D, C, outer)) return NVFP4_ERR_WORKSPACE;
+    const GemmNeeds nx = gemm_needs(N, D, C, outer), nw = gemm_needs(C, D, N, outer);
+    const size_t gbytes = nx.ws > nw.ws ? nx.ws : nw.ws;
+    if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD, N, D, C, outer, gbytes, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
     float *part = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     float *amax = static_cast<float *>(cv.take(sizeof(float)));
     nvfp4_tensor q3{}, q4{}, q5{}, q6{};
-    if (!carve_tensor(cv, N, C, outer, &q3) || !carve_tensor(cv, D, C, outer, &q4) || !carve_tensor(cv, C, N, outer, &q5) ||
-        !carve_tensor(cv, D, N, outer, &q6))
+    const bool room = ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD, N, D, C, outer, gbytes, true);
+    const bool bx = room && nx.blocked && (!outer || nw.blocked), bw = room && nw.blocked && (!outer || nx.blocked);
+    if (!carve_tensor(cv, N, C, outer, &q3, bx) || !carve_tensor(cv, D, C, outer, &q4, bx) || !carve_tensor(cv, C, N, outer, &q5, bw) ||
+        !carve_tensor(cv, D, N, outer, &q6, bw))
         return NVFP4_ERR_WORKSPACE;
-    const size_t g1 = gemm_workspace_bytes(N, D, C, outer), g2 = gemm_workspace_bytes(C, D, N, outer);
-    const size_t gbytes = g1 > g2 ? g1 : g2;
     void *gws = gbytes ? cv.take(gbytes) : nullptr;
 
     nvfp4_qcfg c[4];
@@ -899,7 +929,7 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
             // one launch for the maximum of dY and the re-quantizations Q4, Q6 (which do not need it); every workgroup of
             // the quantizer after it reduces the partial maxima itself
             int npart = 0;
-            rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st, dY, N * C, part, &npart);
+            rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st, bx, bw, dY, N * C, part, &npart);
             if (rc) return rc;
             QuantParams pr{}, pc{};
             pr.rounding = pc.rounding = 1;
@@ -909,23 +939,23 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
             const uint64_t k3 = stream_key(seed, c[0].tensor_id), k5 = stream_key(seed, c[2].tensor_id);
             pr.k0 = (uint32_t)k3; pr.k1 = (uint32_t)(k3 >> 32);
             pc.k0 = (uint32_t)k5; pc.k1 = (uint32_t)(k5 >> 32);
-            QuantOut orow{q3.codes, q3.scales, q3.gscale, nullptr}, ocol{q5.codes, q5.scales, q5.gscale, nullptr};
+            QuantOut orow{q3.codes, q3.scales, q3.gscale, nullptr, bx}, ocol{q5.codes, q5.scales, q5.gscale, nullptr, bw};
             if (launch_quant_dual_bf16(dY, N, C, pr, orow, pc, ocol, st) != hipSuccess) return NVFP4_ERR_HIP;
         } else {
-            rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st);
+            rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st, bx, bw);
             if (rc) return rc;
         }
         q3.rows = N; q3.K = C; q5.rows = C; q5.K = N;
     } else {
         // 1 x 128 outer blocks: no maximum pass at all; dY is read once per operand, each a single pass
-        rc = run_quantize(dY, p3, &c[0], &q3, nullptr, st);
+        rc = run_quantize(dY, p3, &c[0], &q3, nullptr, st, bx);
         if (rc) return rc;
-        rc = run_quantize(dY, p5, &c[2], &q5, nullptr, st);
+        rc = run_quantize(dY, p5, &c[2], &q5, nullptr, st, bw);
         if (rc) return rc;
-        rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st);
+        rc = run_requant_pair(Wq_ctx, p4, &c[1], &q4, Xq_ctx, p6, &c[3], &q6, st, bx, bw);
         if (rc) return rc;
     }
-    const Product products[] = {{&q3, &q4, dX}, {&q5, &q6, dW}};
+    const Product products[] = {{&q3, &q4, dX, bx}, {&q5, &q6, dW, bw}};
     return run_gemm_group(products, 2, out_dtype, gws, gbytes, st);
 }
 

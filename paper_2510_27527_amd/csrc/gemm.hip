@@ -236,6 +236,7 @@ GemmArgs args_of(const GemmOperand &A, const GemmOperand &B, int64_t K, void *ou
     g.chunks_per_split = chunks_per_split;
     g.out_f32 = out_f32;
     g.outer = A.outer;
+    g.blocked = A.blocked;
     g.out = out;
     return g;
 }
@@ -448,6 +449,14 @@ void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int
     *bn = 64 * kTiles[p.tile].tn;
     *split = p.split;
     *split_waves = p.kw ? 1 : 0;
+}
+
+GemmNeeds gemm_needs(int64_t M, int64_t N, int64_t K, int outer)
+{
+    const Plan p = make_plan(M, N, K, outer);
+    const bool narrow = M <= (1 << 24) && N <= (1 << 24);  // 32-bit offsets over the chunks of a stage
+    const bool takes = !p.kw && (outer ? K % 256 == 0 : p.split == 1 || p.chunks_per_split % 2 == 0);
+    return GemmNeeds{split_bytes(p, M, N), narrow && takes};
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer)

@@ -11,15 +11,28 @@ namespace tj {
 constexpr int kGemmThreads = 256;
 constexpr int kNumCU = 256;
 
+// Where an operand's bytes are: row-major, or blocked along K as the backward quantizers write for the products (GemmOperand).  Strides of the
+// codes by row and 64-k chunk, of the scale bytes by row and 256 k (four bytes per chunk inside), of the outer scales (floats) by row
+// and 128 k.
+struct OperandStrides {
+    int64_t row, srow, grow, chunk, s256, g128;
+};
+__device__ __forceinline__ OperandStrides strides_of(bool blocked, int64_t rows, int64_t K)
+{
+    if (blocked) return OperandStrides{32, 16, 1, rows * 32, rows * 16, rows};
+    return OperandStrides{K / 2, K / 16, K >> 7, 32, 16, 1};
+}
+
 struct GemmArgs {
     const uint8_t *a_codes, *a_scales;
     const uint8_t *b_codes, *b_scales;
-    const float *a_gscale, *b_gscale;   // one float (tensor mode) or [rows][K/128] (block mode)
+    const float *a_gscale, *b_gscale;   // one float (tensor mode) or one per row and 128 k (block mode)
     void *out;          // bf16 / f32 [M x N], or f32 partials [split][M x N]
     int64_t M, N, K;
     int chunks_per_split;   // 64-wide K chunks per split
-    int out_f32;
+    int blocked;            // the operands are blocked along K (gemm_nt_kernel, all products of a group alike; the other kernel reads row-major ones)
     int tiles_m, tiles_n;
+    int out_f32;
     int outer;              // 0 one outer scale per operand, 1 one per row and 128 k
 };
 

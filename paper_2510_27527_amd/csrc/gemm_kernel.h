@@ -7,6 +7,9 @@
 // pre-scale: exact and normal in FP16), feed v_mfma_f32_32x32x16_f16 with FP32 accumulation and
 // multiply by the two FP32 outer scales (and 2^8) in the epilogue.
 //
+// Operands are row-major, or blocked along K (BLK; see GemmOperand): what a stage copies of a tile's rows is then contiguous, whole cache lines
+// instead of 64 bytes of codes and 16 (or four times 4) scale bytes per row.
+//
 // Work split: 256 threads = 2 x 2 waves; each wave owns TM x TN tiles of 32 x 32.  Within one
 // 64-wide K chunk a lane (row r = lane % 32, kg = lane / 32) holds the 32 codes k = 32 kg .. 32 kg + 31
 // of its row (one 128-bit LDS read) and uses 8 of them per MFMA; A and B use the same assignment,
@@ -47,6 +50,14 @@ __device__ __forceinline__ half8_t expand8(uint32_t q, half2_t f)
     return r;
 }
 
+// a wave-uniform pointer the compiler computed in vector registers, moved to scalar registers
+__device__ __forceinline__ const void *to_scalar(const void *p)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
+}
+
 // Global -> LDS copies that bypass registers: every lane supplies a global address, the wave's data
 // lands at lds_addr + lane * 16 (or * 4).  Written as inline assembly so that completion is tracked only
 // by the explicit s_waitcnt vmcnt(n) of the pipeline (the compiler would otherwise wait for every
@@ -60,14 +71,6 @@ __device__ __forceinline__ void lds_dma16(const void *base, uint32_t off, uint32
 __device__ __forceinline__ void lds_dma4(const void *base, uint32_t off, uint32_t lds_addr)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_addr), "v"(off), "s"(base) : "memory", "m0");
-}
-
-// a wave-uniform pointer the compiler computed in vector registers, moved to scalar registers
-__device__ __forceinline__ const void *to_scalar(const void *p)
-{
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo);
 }
 
 __device__ __forceinline__ uint32_t pick(uint4 v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
@@ -273,7 +276,7 @@ struct OpFrags {
 // them: one instruction in seven of the loop.  With two workgroups on a CU, where the loop is bound by its instructions, this is the
 // faster form (1664 x 6528 x 896 41.7 -> 33.9 us; 8192 x 4096 x 4096 on this tile 311, on 256 x 128 320); a workgroup with the CU to
 // itself waits for results more often and is 6 % slower with it (1280 x 2688 x 5760 77.7 against 82.6).
-template <int TM, int TN, int NC, int OUT, bool PS, int OUTER, bool PACK, class Args>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
+template <int TM, int TN, int NC, int OUT, bool PS, int OUTER, bool PACK, bool BLK, class Args>   // OUT: 0 bf16, 1 f32, 2 raw f32 split-K partial
 __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1) void gemm_nt_kernel(Args args)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN, ROWS = BM + BN;
@@ -318,7 +321,9 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
     if (cend > chunks_total) cend = chunks_total;
     const int nchunks = (int)(cend - cbeg);
     const int nk = (nchunks + NC - 1) / NC;
-    const int64_t cstride = g.K / 2, sstride = g.K / 16;
+
+    // BLK: the operands are blocked along K.  (With strides passed or chosen at run time, row-major products take 1 to 2 % longer.)
+    const OperandStrides sa = strides_of(BLK, g.M, g.K), sb = strides_of(BLK, g.N, g.K);
 
     float16_t acc[TM][TN];
 #pragma unroll
@@ -343,7 +348,8 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
             const bool isA = u < LA;
             const int slot = ((isA ? u : u - LA) * 4 + wave) * 64 + lane, row = slot / SLOTS, pos = slot % SLOTS;
             const int piece = pos ^ ((row >> 2) & (SLOTS - 1));
-            coff[u] = (uint32_t)row * (uint32_t)cstride + (uint32_t)piece * 16u;
+            coff[u] = (uint32_t)row * (uint32_t)(isA ? sa.row : sb.row) +
+                      (BLK ? (uint32_t)(piece >> 1) * (uint32_t)(isA ? sa.chunk : sb.chunk) + (uint32_t)(piece & 1) * 16u : (uint32_t)piece * 16u);
             cpieces |= (uint32_t)piece << (4 * u);
             if ((isA ? m0 : n0) + row < (isA ? g.M : g.N)) rowmask |= 1u << u;
         }
@@ -352,7 +358,7 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
             for (int u = 0; u < LS; ++u) {
                 const int q = u * 4 + wave, c = q / (ROWS / 64), row = (q % (ROWS / 64)) * 64 + lane;
                 const bool isA = row < BM;
-                soff[u] = (uint32_t)(isA ? row : row - BM) * (uint32_t)sstride + (uint32_t)c * 4u;
+                soff[u] = (uint32_t)(isA ? row : row - BM) * (uint32_t)(isA ? sa.srow : sb.srow) + (uint32_t)c * 4u;
                 schunks |= (uint32_t)c << (4 * u);
                 if ((isA ? m0 + row : n0 + row - BM) < (isA ? g.M : g.N)) rowmask |= 1u << (LA + LB + u);
             }
@@ -363,47 +369,56 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
                 const int row = ((h * 4 + wave) % (ROWS / 64)) * 64 + lane;
                 const bool isA = row < BM;
                 const bool ok = (isA ? m0 + row : n0 + row - BM) < (isA ? g.M : g.N);
-                soff[h] = ok ? (uint32_t)(isA ? row : row - BM) * (uint32_t)sstride : 0u;
+                soff[h] = ok ? (uint32_t)(isA ? row : row - BM) * (uint32_t)(isA ? sa.srow : sb.srow) : 0u;
             }
         }
         // OUTER: copy u of a stage brings the outer scales of rows (q % (ROWS/64)) * 64 .. + 63, q = 4 u + wave (when
         // ROWS/64 is no multiple of four the surplus copies repeat a block: same values to the same place)
         uint32_t goff[OUTER ? LG : 1];
-        const int64_t nkb = g.K >> 7;
         if (OUTER) {
 #pragma unroll
             for (int u = 0; u < LG; ++u) {
                 const int row = ((u * 4 + wave) % (ROWS / 64)) * 64 + lane;
                 const bool isA = row < BM;
                 const bool ok = (isA ? m0 + row : n0 + row - BM) < (isA ? g.M : g.N);
-                goff[u] = ok ? (uint32_t)(isA ? row : row - BM) * (uint32_t)nkb * 4u : 0u;
+                goff[u] = ok ? (uint32_t)(isA ? row : row - BM) * (uint32_t)(isA ? sa.grow : sb.grow) * 4u : 0u;
             }
         }
         const bool tile_full = m0 + BM <= g.M && n0 + BN <= g.N;
-        const uint8_t *a_cbase = g.a_codes + m0 * cstride + cbeg * 32, *b_cbase = g.b_codes + n0 * cstride + cbeg * 32;
-        const uint8_t *a_sbase = g.a_scales + m0 * sstride + cbeg * 4, *b_sbase = g.b_scales + n0 * sstride + cbeg * 4;
+        const uint8_t *a_cbase = g.a_codes + m0 * sa.row + cbeg * sa.chunk, *b_cbase = g.b_codes + n0 * sb.row + cbeg * sb.chunk;
+        const uint8_t *a_sbase = g.a_scales + m0 * sa.srow + (BLK ? (cbeg >> 2) * sa.s256 + (cbeg & 3) * 4 : cbeg * 4);
+        const uint8_t *b_sbase = g.b_scales + n0 * sb.srow + (BLK ? (cbeg >> 2) * sb.s256 + (cbeg & 3) * 4 : cbeg * 4);
         // OUTER: outer scales of the tile's rows for the split's first 128-k block (a split starts on a block boundary)
-        const float *a_gbase = OUTER ? g.a_gscale + m0 * nkb + (cbeg >> 1) : nullptr;
-        const float *b_gbase = OUTER ? g.b_gscale + n0 * nkb + (cbeg >> 1) : nullptr;
+        const float *a_gbase = OUTER ? g.a_gscale + m0 * sa.grow + (cbeg >> 1) * sa.g128 : nullptr;
+        const float *b_gbase = OUTER ? g.b_gscale + n0 * sb.grow + (cbeg >> 1) * sb.g128 : nullptr;
+        // Stages are fetched in order: blocked operands keep running pointers, *_next.
+        const float *ag_next = a_gbase, *bg_next = b_gbase;
         auto issue_outer = [&](int kt) {
             // stage kt = block kt of the split, into ring slot kt % 4; stages past the end re-fetch block 0 (never used)
             const int kb = (int64_t)kt * NC < nchunks ? kt : 0;
+            const float *const ag = !BLK ? a_gbase + kb : kb == kt ? ag_next : a_gbase, *const bg = !BLK ? b_gbase + kb : kb == kt ? bg_next : b_gbase;
+            if (BLK) {
+                ag_next += sa.g128;
+                bg_next += sb.g128;
+            }
 #pragma unroll
             for (int u = 0; u < LG; ++u) {
                 const int rb = (u * 4 + wave) % (ROWS / 64);
-                lds_dma4(to_scalar((rb * 64 < BM ? a_gbase : b_gbase) + kb), goff[u], lds_base + GS_BASE + ((kt & 3) * ROWS + rb * 64) * 4);
+                lds_dma4(to_scalar(rb * 64 < BM ? ag : bg), goff[u], lds_base + GS_BASE + ((kt & 3) * ROWS + rb * 64) * 4);
             }
         };
 
         // All loads of stage kt.  Interior tiles and stages fully inside the split take the straight path;
         // otherwise loads of missing rows or of chunks past the end are skipped (their LDS slots keep stale
         // bytes: missing rows are never stored, late chunks get zero scales when they are read).
+        const uint8_t *ac_next = a_cbase, *bc_next = b_cbase, *as_next = a_sbase, *bs_next = b_sbase;
         auto issue_loads = [&](int kt, int buf) {
+
             const int64_t c0 = (int64_t)kt * NC;                  // first chunk of the stage, relative to cbeg
             const uint32_t dst = lds_base + buf * CODE_BYTES;
             const uint32_t sdst = lds_base + SC_BASE + buf * SC_BYTES;
-            const uint8_t *ac = a_cbase + c0 * 32, *bc = b_cbase + c0 * 32;
-            const uint8_t *as = a_sbase + c0 * 4, *bs = b_sbase + c0 * 4;
+            const uint8_t *const ac = BLK ? ac_next : a_cbase + c0 * 32, *const bc = BLK ? bc_next : b_cbase + c0 * 32;
+            const uint8_t *const as = BLK ? as_next : a_sbase + c0 * 4, *const bs = BLK ? bs_next : b_sbase + c0 * 4;
             if (tile_full && c0 + NC <= nchunks) {
 #pragma unroll
                 for (int u = 0; u < LA + LB; ++u) {
@@ -438,15 +453,28 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
                 }
             }
             if (OUTER) issue_outer(kt);
+            if (BLK) {
+                ac_next += NC * sa.chunk;
+                bc_next += NC * sb.chunk;
+                // two chunks on: inside the 256 k, or into the next ones
+                as_next += ((cbeg + c0) & 2) ? sa.s256 - 8 : 8;
+                bs_next += ((cbeg + c0) & 2) ? sb.s256 - 8 : 8;
+            }
         };
         // PS: half h of scale pair P (16 scale bytes = 256 k per row) into pair buffer P % 3; pairs past the end
         // re-fetch pair 0 (valid memory, never consumed)
         const int npairs = nchunks / 4;
+        const uint8_t *asp_next = a_sbase, *bsp_next = b_sbase;
         auto issue_scale_half = [&](int P, int h) {
             const int rb = (h * 4 + wave) % (ROWS / 64);
             const bool isA = rb * 64 < BM;
             const int Pl = P < npairs ? P : 0;
-            const uint8_t *base = (isA ? a_sbase : b_sbase) + (int64_t)Pl * 16;
+            const uint8_t *const as = P == Pl ? asp_next : a_sbase, *const bs = P == Pl ? bsp_next : b_sbase;
+            const uint8_t *base = BLK ? (isA ? as : bs) : (isA ? a_sbase : b_sbase) + (int64_t)Pl * 16;
+            if (BLK && h == 1) {                               // pairs are fetched in order, too
+                asp_next += sa.s256;
+                bsp_next += sb.s256;
+            }
             lds_dma16(base, soff[h], lds_base + SC_BASE + (P % 3) * SC_BYTES + rb * 64 * 16);
         };
 
@@ -586,18 +614,33 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
     store_tile<TM, TN, OUT, SWAP, OUTER>(acc, g, m0, n0, wm, wn, lr, kg, smem_raw);
 }
 
-template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK = false, class Args>
-hipError_t launch_cfg(const Args &g, dim3 grid, hipStream_t st)
+template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK, bool BLK, class Args>
+hipError_t launch_layout(const Args &g, dim3 grid, hipStream_t st)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;
     constexpr int lds = 3 * ((BM + BN) * 2 * kNC * 16 + (BM + BN) * (PS ? 16 : kNC * 4)) + (OUTER ? 4 * (BM + BN) * 4 : 0);
-    auto kern = gemm_nt_kernel<TM, TN, kNC, OUT, PS, OUTER, PACK, Args>;
+    auto kern = gemm_nt_kernel<TM, TN, kNC, OUT, PS, OUTER, PACK, BLK, Args>;
     // once per instantiation; the initialisation of a function-local static is thread-safe
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), lds, st, g);
     return hipGetLastError();
+}
+
+__host__ inline bool is_blocked(const GemmArgs &g) { return g.blocked != 0; }
+__host__ inline bool is_blocked(const GemmGroup &p) { return p.g[0].blocked != 0; }
+
+template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK = false, class Args>
+hipError_t launch_cfg(const Args &g, dim3 grid, hipStream_t st)
+{
+    // (with outer blocks, blocked operands come with the paired scale fetch)
+    if constexpr (PS || OUTER == 0) {
+        if (is_blocked(g)) return launch_layout<TM, TN, OUT, PS, OUTER, PACK, true>(g, grid, st);
+    } else if (is_blocked(g)) {
+        return hipErrorInvalidValue;
+    }
+    return launch_layout<TM, TN, OUT, PS, OUTER, PACK, false>(g, grid, st);
 }
 
 // tile: 0 256x256 (tensor mode only: block mode needs two accumulator sets), 1 256x128, 2 128x256, 3 128x128,

@@ -13,6 +13,7 @@ struct QuantOut {
     uint8_t *scales;
     float *gscale;
     float *amax_deq;   // may be null
+    int blocked;       // 1: codes, scale bytes and outer scales in the order described at GemmOperand
 };
 
 struct QuantParams {
@@ -77,16 +78,29 @@ hipError_t launch_requant_col_pair_amax(const PackedSrc &src0, int64_t R0, int64
                                         const PackedSrc &src1, int64_t R1, int64_t C1, const QuantParams &p1, const QuantOut &o1,
                                         const void *bf16, int64_t n, float *partials, int *npart, hipStream_t st);
 
+// Operands that only products read (the backward quantizers') can be blocked along K, so that what a workgroup copies for a pipeline
+// stage is whole cache lines one after the other: codes [K/64][rows][32 bytes], scale bytes [ceil(K/256)][rows][16], outer scales [K/128][rows].
+// Row-major, a stage takes 64 bytes of codes and 16 (or 4) scale bytes of every row.  Measured row-major -> blocked, us:
+// 8192 x 3072 x 768 45.5 -> 42.8, 16384 x 1024 x 8192 225 -> 217, 8192 cubed 802 -> 773, 4096 x 4096 x 3712 119 -> 110; with 1 x 128 outer blocks
+// 8192 x 4096 x 4096 352 -> 325, 8192 cubed 1282 -> 1158, 4096 x 4096 x 3712 197 -> 183.
 struct GemmOperand {
     const uint8_t *codes;
     const uint8_t *scales;
-    const float *gscale;   // one float, or [rows][K/128] floats
+    const float *gscale;   // one float, or one per row and 128 k
     int64_t rows;
     int outer;             // 0 tensor mode, 1 one outer scale per row and 128 k (both operands alike)
+    int blocked;           // both operands alike
 };
+inline size_t blocked_scale_bytes(int64_t rows, int64_t K) { return (size_t)rows * (size_t)((K + 255) / 256) * 16; }
 
 // Out[M x N] = A[M x K] * B[N x K]^T; splitk_ws holds split * M * N floats when split > 1
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer);
+// the same, and whether the product takes blocked operands, from one plan (making one takes the host 0.4 to 1.1 us): not on the kernel whose waves
+// split the reduction (it gains 3 % on long ones - 3072 x 768 x 8192 52.1 -> 50.3 us - and small layers lose as much to the longer prologue);
+// with per-tensor scales where its splits start where the scale bytes' blocks, or halves of them, do; with 1 x 128 outer blocks where K is a multiple of 256,
+// and in one launch with others only if they do too
+struct GemmNeeds { size_t ws; bool blocked; };
+GemmNeeds gemm_needs(int64_t M, int64_t N, int64_t K, int outer);
 // workgroup tile and K split the launcher will use for this shape
 void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int *split, int *split_waves);
 hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32,

@@ -36,7 +36,13 @@ struct KArgs {
     int npart;
     uint32_t k0, k1;
     uint32_t r0, r1;      // random Hadamard transform: key words of the sign stream
+    int blocked;          // the output is blocked along K (GemmOperand in internal.h)
 };
+
+// Blocked outputs: byte offset of the eight-element-aligned position (row, k), of its scale byte, index of its outer scale
+__device__ __forceinline__ int64_t blocked_code(int64_t rows, int64_t row, int64_t k) { return ((k >> 6) * rows + row) * 32 + ((k & 63) >> 1); }
+__device__ __forceinline__ int64_t blocked_scale(int64_t rows, int64_t row, int64_t k) { return ((k >> 8) * rows + row) * 16 + ((k & 255) >> 4); }
+__device__ __forceinline__ int64_t blocked_outer(int64_t rows, int64_t row, int64_t k) { return (k >> 7) * rows + row; }
 
 // tensor maximum for this workgroup: a scalar, or the maximum of the partials
 __device__ __forceinline__ float block_tensor_amax(const KArgs &a, float *red)
@@ -156,13 +162,19 @@ struct RowJob {
     int64_t nchunks;
     KArgs a;
     uint32_t nblk;       // RHT: 128-element blocks per row (K / 128)
+    int64_t rows, K;
 };
 
 // first_second: first workgroup of the second job (0xFFFFFFFF when the launch has one job)
 // RHT (1 x 128 outer blocks only): every group of 16 is first multiplied by S H_16 (Sec. 4.1).  The two lanes of a
 // group do the strides 1, 2, 4 on their own eight values and the stride 8 across the pair; the signs come from a
 // table of the 256 sign words (32 positions each) that the workgroup's 64 outer blocks can touch.
-template <int ROUND, bool SUP, int OUTER, bool DEQ, bool RHT = false>
+//
+// BLK (0, 256 or 512): the output is blocked along K.  A workgroup then takes BLK columns of 8192 / BLK rows instead of 8192 consecutive elements, 16 rows x
+// 128 at a time, so that it writes runs of 512 bytes (16 rows of 32), in bands of tiles per XCD as in the column kernel: 512 where that covers no more
+// columns past K than 256 does.  Bound by the vector ALU like the row-major form, and 4 % slower than it (8192 x 4096 with the transform, 1 x 128 outer blocks: 25.9 ->
+// 27.0 us; 32 x 256 tiles 27.5): the product that reads the result gains ten times that.
+template <int ROUND, bool SUP, int OUTER, bool DEQ, bool RHT = false, int BLK = 0>
 __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j1, unsigned first_second)
 {
     static_assert(!RHT || (OUTER == 1 && !DEQ), "the transform is provided with 1 x 128 outer blocks");
@@ -176,16 +188,35 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
     const KArgs a = second ? j1.a : j0.a;
     const unsigned bid = second ? blockIdx.x - first_second : blockIdx.x;
     // the workgroup's data first: these loads do not depend on the scale set-up below and overlap with it
-    const int64_t c0 = (int64_t)bid * kRowIter * kThreads + tid;
-    const bool full = ((int64_t)bid + 1) * kRowIter * kThreads <= nchunks;
+    static_assert(!BLK || !DEQ, "only the forward quantizer reports the dequantized maximum");
+    constexpr int kBlkCols = BLK ? BLK : 256, kBlkRows = kRowIter * kThreads * 8 / kBlkCols;
+    int64_t r0 = 0, k0 = 0;                                        // BLK: the tile's first row and element
+    int64_t c0 = (int64_t)bid * kRowIter * kThreads + tid;
+    bool full = ((int64_t)bid + 1) * kRowIter * kThreads <= nchunks;
+    if constexpr (BLK != 0) {
+        uint32_t t = bid;
+        const uint32_t per_xcd = gridDim.x / 8, tiles_k = (uint32_t)((j0.K + kBlkCols - 1) / kBlkCols);
+        if (t < per_xcd * 8) t = (t & 7) * per_xcd + (t >> 3);
+        r0 = (int64_t)(t / tiles_k) * kBlkRows;
+        k0 = (int64_t)(t % tiles_k) * kBlkCols;
+        full = r0 + kBlkRows <= j0.rows && k0 + kBlkCols <= j0.K;
+    }
+    // chunk (eight elements) `it` of this thread
+    constexpr int kRowSteps = kBlkRows / 16;
+    auto row_of = [&](int it) { return r0 + 16 * (it % kRowSteps) + (tid >> 4); };
+    auto col_of = [&](int it) { return k0 + 128 * (it / kRowSteps) + 8 * (tid & 15); };
+    auto chunk_of = [&](int it) { return BLK ? row_of(it) * (j0.K >> 3) + (col_of(it) >> 3) : c0 + it * kThreads; };
+    auto exists = [&](int it) { return BLK ? row_of(it) < j0.rows && col_of(it) < j0.K : c0 + it * kThreads < nchunks; };
     uint4 vs[kRowIter];
 #pragma unroll
     for (int it = 0; it < kRowIter; ++it) {
         vs[it] = make_uint4(0, 0, 0, 0);
-        if (full || c0 + it * kThreads < nchunks) vs[it] = ld_stream(src + c0 + it * kThreads);
+        if (full || exists(it)) vs[it] = ld_stream(src + chunk_of(it));
     }
     fill_inv_table(inv_tab);
-    if (RHT) {
+    if (RHT && BLK) {
+        if (tid < kBlkCols / 32) sign_tab[tid] = quad_bits((uint32_t)(k0 >> 7) * 4u + (uint32_t)tid, a.r0, a.r1);   // the tile's outer blocks
+    } else if (RHT) {
         // entry t: sign word (t & 3) of the (t >> 2)-th outer block this workgroup covers; blocks wrap at the end of a row
         const uint32_t nblk = second ? j1.nblk : j0.nblk;
         const uint32_t kb = (uint32_t)(((uint64_t)bid * (kRowIter * kThreads / 16) + (uint32_t)(tid >> 2)) % nblk);
@@ -214,8 +245,8 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
         constexpr bool CHECK = decltype(chk)::value;
 #pragma unroll
         for (int it = 0; it < kRowIter; ++it) {
-            const int64_t c = c0 + it * kThreads;
-            const bool valid = !CHECK || c < nchunks;
+            const int64_t c = chunk_of(it);
+            const bool valid = !CHECK || exists(it);
             uint4 v = vs[it];
             float x[8];
             uint32_t bm;                                       // group maximum: bf16 pattern, or binary32 pattern with RHT
@@ -227,7 +258,7 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
                 x[4] = bf16_lo(v.z); x[5] = bf16_hi(v.z); x[6] = bf16_lo(v.w); x[7] = bf16_hi(v.w);
             } else {
                 // signs: this chunk is run (tid & 3) of eight positions of its sign word
-                const uint32_t w = sign_tab[it * (kThreads / 4) + (tid >> 2)];
+                const uint32_t w = sign_tab[BLK ? 4 * (it / kRowSteps) + ((tid & 15) >> 2) : it * (kThreads / 4) + (tid >> 2)];
                 const int rot = 4 * (tid & 3);
                 v.x ^= __builtin_amdgcn_alignbit(w, w, rot) & 0x80008000u;
                 v.y ^= __builtin_amdgcn_alignbit(w, w, rot + 1) & 0x80008000u;
@@ -263,18 +294,21 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
                 t = dpp<DPP_ROW_HALF_MIRROR>(gm); gm = gm > t ? gm : t;
                 t = dpp<DPP_ROW_MIRROR>(gm);      gm = gm > t ? gm : t;
                 os = outer_scale(RHT ? u2f(gm) : u2f(gm << 16));
-                if (valid && (tid & 15) == 0) a.gscale[c >> 4] = os.S_g;
+                if (valid && (tid & 15) == 0) a.gscale[BLK ? blocked_outer(j0.rows, row_of(it), col_of(it)) : c >> 4] = os.S_g;
             }
             const float amax_b = RHT ? u2f(bm) : u2f(bm << 16);
             const float s = amax_b * os.inv_cg;
             const uint32_t sc = e4m3_round<SUP>(s);
             const float r = os.inv_sg * inv_tab[sc];
             const uint32_t q = quant8<ROUND, SUP>(x, r, (uint32_t)(c * 2), a.k0, a.k1);
-            if (valid) a.codes[c] = q;
+            if (valid) a.codes[BLK ? blocked_code(j0.rows, row_of(it), col_of(it)) >> 2 : c] = q;
             // four scale bytes (lanes c, c+2, c+4, c+6) travel to the lane with c % 8 == 0
             const uint32_t s2 = sc | (dpp<DPP_ROW_SHL2>(sc) << 8);
             const uint32_t s4 = s2 | (dpp<DPP_ROW_SHL4>(s2) << 16);
-            if (valid && (tid & 7) == 0) {
+            if (BLK) {
+                // (K is a multiple of 64: the four bytes exist or none does)
+                if (valid && (tid & 7) == 0) *reinterpret_cast<uint32_t *>(a.scales + blocked_scale(j0.rows, row_of(it), col_of(it))) = s4;
+            } else if (valid && (tid & 7) == 0) {
                 if (!CHECK || c + 8 <= nchunks) {
                     reinterpret_cast<uint32_t *>(a.scales)[c >> 3] = s4;
                 } else {
@@ -402,7 +436,9 @@ __device__ __forceinline__ int tile_pos(int row, int dwcol) { return row * 32 + 
 // as bf16 pairs (rotated so that the 128-bit row writes and the per-column reads are both conflict free); on the way in,
 // while a row passes through registers, it is quantized row-wise (groups along C); after the transpose a lane owns
 // two columns x 16 rows = two groups of the column-wise operand.
-template <int ROUND, bool SUP>
+// BROW, BCOL: the row-wise / column-wise operand is blocked along K (the source's columns / rows are then a multiple of 64): the four passes
+// over a tile's rows write 4 KB of codes in one run, where row-major rows get 32 bytes each (16384 x 8192: 127 -> 105 us; the rest is the vector ALU).
+template <int ROUND, bool SUP, bool BROW = false, bool BCOL = false>
 __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint32_t tile[kTileR * 32];
@@ -489,11 +525,13 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
                                     bf16_lo(v.z), bf16_hi(v.z), bf16_lo(v.w), bf16_hi(v.w)};
                 const int64_t e0 = (R0 + pass * 32) * C + ld_lane;
                 const uint32_t qd = quant8<ROUND, SUP>(x, r, (uint32_t)(e0 >> 2), a.krow.k0, a.krow.k1);
-                if (valid) a.krow.codes[e0 >> 3] = qd;
+                if (valid) a.krow.codes[BROW ? blocked_code(R, gr, ld_col) >> 2 : e0 >> 3] = qd;
                 const uint32_t s2 = sc | (dpp<DPP_ROW_SHL2>(sc) << 8);
                 const uint32_t s4 = s2 | (dpp<DPP_ROW_SHL4>(s2) << 16);
                 if (valid && q == 0) {
-                    if ((C & 63) == 0) {
+                    if (BROW) {
+                        *reinterpret_cast<uint32_t *>(a.krow.scales + blocked_scale(R, gr, C0)) = s4;
+                    } else if ((C & 63) == 0) {
                         *reinterpret_cast<uint32_t *>(a.krow.scales + (e0 >> 4)) = s4;
                     } else {
                         for (int b = 0; b < 4; ++b)
@@ -532,8 +570,9 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
             uint2 q;
             q.x = quant8<ROUND, SUP>(x0, r, quad0, a.k.k0, a.k.k1);
             q.y = quant8<ROUND, SUP>(x1, r, quad0 + 2, a.k.k0, a.k.k1);
-            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(a.k.codes) + (e >> 1)) = q;
-            a.k.scales[e >> 4] = (uint8_t)sc;
+            const int64_t kr = R0 + 16 * rb;
+            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(a.k.codes) + (BCOL ? blocked_code(C, c_first + j, kr) : e >> 1)) = q;
+            a.k.scales[BCOL ? blocked_scale(C, c_first + j, kr) : e >> 4] = (uint8_t)sc;
         }
     }
 }
@@ -741,8 +780,8 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
         os[1] = outer_scale(m.y);
         if (colok && wave == 0) {
             const int64_t nb = R >> 7;
-            a.k.gscale[c0 * nb + trg] = os[0].S_g;
-            a.k.gscale[(c0 + 1) * nb + trg] = os[1].S_g;
+            a.k.gscale[a.k.blocked ? trg * C + c0 : c0 * nb + trg] = os[0].S_g;
+            a.k.gscale[a.k.blocked ? trg * C + c0 + 1 : (c0 + 1) * nb + trg] = os[1].S_g;
         }
     }
 
@@ -782,8 +821,9 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
             if (wide) {
                 *reinterpret_cast<uint2 *>(stage + (2 * lane + j) * kPitch + wave * (8 * SLABS) + 8 * s) = q;
             } else if (colok) {
-                *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(a.k.codes) + (e >> 1)) = q;
-                a.k.scales[e >> 4] = (uint8_t)sc;
+                const int64_t kr = R0 + 16 * s;
+                *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(a.k.codes) + (a.k.blocked ? blocked_code(C, c0 + j, kr) : e >> 1)) = q;
+                a.k.scales[a.k.blocked ? blocked_scale(C, c0 + j, kr) : e >> 4] = (uint8_t)sc;
             }
         }
     }
@@ -798,6 +838,31 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
         }
     }
     __syncthreads();
+    if (a.k.blocked) {
+        // (against runs of 64 bytes per output row: 8192 x 4096 with outer blocks and transform 22.7 -> 20.8 us, the pair X, W of that layer 31.6 -> 30.4)
+        // codes: 4 KB per 64 k, 128 output rows of 32 bytes; scale bytes: min(16, 4 SLABS) per output row and 256 k (or part of them)
+        const int64_t Rg = (int64_t)trg * kWaves * kStripR;
+        uint8_t *out_codes = reinterpret_cast<uint8_t *>(a.k.codes);
+        const int row = tid >> 1, half = tid & 1;
+        const int64_t c = strip0 + row;
+#pragma unroll
+        for (int ch = 0; ch < kRun / 32; ++ch) {
+            if (ch * 32 >= 8 * SLABS * nwide) break;
+            const uint2 lo = *reinterpret_cast<const uint2 *>(stage + row * kPitch + ch * 32 + half * 16);
+            const uint2 hi = *reinterpret_cast<const uint2 *>(stage + row * kPitch + ch * 32 + half * 16 + 8);
+            if (c < C) *reinterpret_cast<uint4 *>(out_codes + blocked_code(C, c, Rg + 64 * ch) + half * 16) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+        // (a lane's four bytes are 64 k: Rg is a multiple of 128)
+        constexpr int kScPieces = kScPitch / 4, kScRows = kThreads / kScPieces;
+        const int sp = tid % kScPieces;
+#pragma unroll
+        for (int it = 0; it < (kStripC + kScRows - 1) / kScRows; ++it) {
+            const int r = it * kScRows + tid / kScPieces;
+            if (r < kStripC && strip0 + r < C && sp * 4 < SLABS * nwide)
+                *reinterpret_cast<uint32_t *>(a.k.scales + blocked_scale(C, strip0 + r, Rg + 64 * sp)) = *reinterpret_cast<const uint32_t *>(sc_stage + r * kScPitch + sp * 4);
+        }
+        return;
+    }
     {
         // codes: kPieces lanes x 16 bytes cover one output row's run
         constexpr int kPieces = kRun / 16, kRowsPass = kThreads / kPieces;
@@ -863,12 +928,31 @@ KArgs make_kargs(const QuantParams &p, const QuantOut &o)
     k.k1 = p.k1;
     k.r0 = p.r0;
     k.r1 = p.r1;
+    k.blocked = o.blocked;
     return k;
 }
 
 template <int ROUND, bool SUP, int OUTER>
 void launch_row_t(const RowJob &j0, const RowJob &j1, bool deq, bool rht, hipStream_t st)
 {
+    if constexpr (ROUND == 1 && SUP) {
+        if (j0.a.blocked) {                                        // (one job: the backward call's Q3)
+            auto launch = [&](auto cols) {
+                constexpr int BLK = decltype(cols)::value, kRows = kRowIter * kThreads * 8 / BLK;
+                const dim3 grid((unsigned)(((j0.rows + kRows - 1) / kRows) * ((j0.K + BLK - 1) / BLK)));
+                if constexpr (OUTER == 1) {
+                    if (rht) {
+                        hipLaunchKernelGGL((quant_row_kernel<1, true, 1, false, true, BLK>), grid, dim3(kThreads), 0, st, j0, j1, 0xFFFFFFFFu);
+                        return;
+                    }
+                }
+                hipLaunchKernelGGL((quant_row_kernel<1, true, OUTER, false, false, BLK>), grid, dim3(kThreads), 0, st, j0, j1, 0xFFFFFFFFu);
+            };
+            if ((j0.K + 255) / 256 % 2 == 0) launch(std::integral_constant<int, 512>{});
+            else launch(std::integral_constant<int, 256>{});
+            return;
+        }
+    }
     const int64_t per_wg = (int64_t)kThreads * kRowIter;
     const unsigned g0 = (unsigned)((j0.nchunks + per_wg - 1) / per_wg), g1 = (unsigned)((j1.nchunks + per_wg - 1) / per_wg);
     const unsigned first_second = g1 ? g0 : 0xFFFFFFFFu;
@@ -1009,7 +1093,7 @@ hipError_t launch_quant_row_bf16(const void *src, int64_t rows, int64_t K, const
 {
     const int64_t nchunks = rows * K / 8;
     if (nchunks == 0) return hipSuccess;
-    RowJob j0{reinterpret_cast<const uint4 *>(src), nchunks, make_kargs(p, o), (uint32_t)(K / 128)}, j1{};
+    RowJob j0{reinterpret_cast<const uint4 *>(src), nchunks, make_kargs(p, o), (uint32_t)(K / 128), rows, K}, j1{};
     const bool deq = o.amax_deq != nullptr && p.rounding == 0 && !p.rht;
     launch_row_sel(j0, j1, p, deq, st);
     if (deq && p.outer) launch_deq_max(j0, j1, st);
@@ -1022,8 +1106,8 @@ hipError_t launch_quant_row_bf16_pair(const void *src0, int64_t rows0, int64_t K
 {
     if (rows0 * K0 == 0) return launch_quant_row_bf16(src1, rows1, K1, p1, o1, st);
     if (rows1 * K1 == 0) return launch_quant_row_bf16(src0, rows0, K0, p0, o0, st);
-    RowJob j0{reinterpret_cast<const uint4 *>(src0), rows0 * K0 / 8, make_kargs(p0, o0), (uint32_t)(K0 / 128)};
-    RowJob j1{reinterpret_cast<const uint4 *>(src1), rows1 * K1 / 8, make_kargs(p1, o1), (uint32_t)(K1 / 128)};
+    RowJob j0{reinterpret_cast<const uint4 *>(src0), rows0 * K0 / 8, make_kargs(p0, o0), (uint32_t)(K0 / 128), rows0, K0};
+    RowJob j1{reinterpret_cast<const uint4 *>(src1), rows1 * K1 / 8, make_kargs(p1, o1), (uint32_t)(K1 / 128), rows1, K1};
     const bool deq = (o0.amax_deq != nullptr || o1.amax_deq != nullptr) && p0.rounding == 0;
     launch_row_sel(j0, j1, p0, deq, st);
     if (deq && p0.outer) launch_deq_max(j0, j1, st);
@@ -1060,7 +1144,12 @@ hipError_t launch_quant_dual_bf16(const void *src, int64_t R, int64_t C, const Q
         case 0: hipLaunchKernelGGL((quant_dual_kernel<0, false>), grid, dim3(kThreads), 0, st, a); break;
         case 1: hipLaunchKernelGGL((quant_dual_kernel<0, true>), grid, dim3(kThreads), 0, st, a); break;
         case 2: hipLaunchKernelGGL((quant_dual_kernel<1, false>), grid, dim3(kThreads), 0, st, a); break;
-        default: hipLaunchKernelGGL((quant_dual_kernel<1, true>), grid, dim3(kThreads), 0, st, a); break;
+        default:
+            if (orow.blocked && ocol.blocked) hipLaunchKernelGGL((quant_dual_kernel<1, true, true, true>), grid, dim3(kThreads), 0, st, a);
+            else if (orow.blocked) hipLaunchKernelGGL((quant_dual_kernel<1, true, true, false>), grid, dim3(kThreads), 0, st, a);
+            else if (ocol.blocked) hipLaunchKernelGGL((quant_dual_kernel<1, true, false, true>), grid, dim3(kThreads), 0, st, a);
+            else hipLaunchKernelGGL((quant_dual_kernel<1, true>), grid, dim3(kThreads), 0, st, a);
+            break;
     }
     return hipGetLastError();
 }

@@ -1,0 +1,90 @@
+"""The backward quantizers write their operands blocked along K for the products (codes [K/64][rows][32 bytes], scale bytes
+[ceil(K/256)][rows][16], outer scales [K/128][rows]).  The layout changes no value, so the gradients have to be, byte for byte, the products of
+the row-major operands that the public quantizer calls write, which are compared with the oracle elsewhere."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+# (outer mode, transform, N, D, C): every tile of the product kernel that reads blocked operands, with K = N or C of 0, 64, 128 and 192 mod 256, in
+# one piece and split (split on an odd number of 64s: row-major), outputs that end inside a tile, row-wise tiles of 256 and 512 columns
+CASES = [
+    (0, 0, 64, 64, 64), (0, 0, 192, 128, 128), (0, 0, 128, 64, 192), (0, 0, 256, 64, 256), (0, 0, 1024, 64, 64), (0, 0, 64, 64, 1088),
+    (0, 0, 1152, 64, 64), (0, 0, 64, 80, 1216), (0, 0, 640, 1664, 256), (0, 0, 512, 3520, 576), (0, 0, 2112, 3776, 64), (0, 0, 64, 2496, 3200),
+    (0, 0, 192, 3648, 1088), (0, 0, 3840, 1600, 256), (0, 0, 128, 4544, 2816), (0, 0, 1600, 1216, 512), (0, 0, 3520, 3520, 128), (0, 0, 4096, 768, 3072),
+    (1, 0, 256, 256, 256), (1, 1, 2048, 256, 256), (1, 0, 256, 4224, 256), (1, 1, 256, 128, 1024), (1, 0, 256, 1280, 3328), (1, 1, 3328, 1792, 256),
+    (1, 0, 256, 4096, 1536), (1, 1, 384, 256, 512), (1, 0, 512, 256, 640),
+]
+# long strips of the column-wise quantizers (four and eight slabs of 16 rows a wave), the last of them cut short
+LONG = [(0, 0, 8256, 5120, 1088), (0, 0, 12352, 2048, 3456), (0, 0, 8256, 1024, 3584)]
+
+
+def _tensors(N, D, C, outer, seed):
+    import paper_2510_27527_amd as tj
+    B = tj.binding
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    new = lambda r, c, s: (torch.randn((r, c), generator=g, device="cuda") * s).bfloat16()  # noqa: E731
+    Xq = tj.quantize(new(N, D, 1.0), 0, B.ROUND_RTN, outer=outer)
+    Wq = tj.quantize(new(C, D, 0.02), 0, B.ROUND_RTN, outer=outer)
+    return new(N, C, 1e-3), Xq, Wq
+
+
+def _row_major(dY, Xq, Wq, seed, layer, outer, rht):
+    """Q3 .. Q6 by the quantizer's own call"""
+    import paper_2510_27527_amd as tj
+    B = tj.binding
+
+    def q(src, axis, k):
+        rid = (layer * 16 + (7 if k in (3, 4) else 8)) if rht else None
+        return tj.quantize(src, axis, B.ROUND_SR, outer=outer, seed=seed, tensor_id=layer * 16 + k, rht_id=rid)
+    return q(dY, 0, 3), q(Wq, 1, 4), q(dY, 1, 5), q(Xq, 1, 6)
+
+
+def _least_workspace(N, D, C, outer):
+    """bytes of a call's workspace without the scale bytes that only whole 256 k need"""
+    import paper_2510_27527_amd as tj
+    B = tj.binding
+    up = lambda v: (v + 255) // 256 * 256  # noqa: E731
+    more = sum(up(r * ((k + 255) // 256) * 16) - up(r * k // 16) for r, k in ((N, C), (D, C), (C, N), (D, N)))
+    return B.workspace_bytes(B.OP_LINEAR_BWD, N, D, C, outer) - more
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("outer,rht,N,D,C", CASES + LONG)
+def test_gradients_of_blocked_operands(outer, rht, N, D, C, f32):
+    import paper_2510_27527_amd as tj
+    B = tj.binding
+    if f32 and (outer, rht, N, D, C) in LONG:
+        pytest.skip("the quantizers are the same for both output types")
+    dt = B.OUT_F32 if f32 else B.OUT_BF16
+    dY, Xq, Wq = _tensors(N, D, C, outer, 7)
+    dX, dW = tj.linear_bwd(dY, Xq, Wq, 11, 5, dt, rht=bool(rht))
+    q3, q4, q5, q6 = _row_major(dY, Xq, Wq, 11, 5, outer, rht)
+    assert torch.equal(dX, tj.gemm_nt(q3, q4, dt))
+    assert torch.equal(dW, tj.gemm_nt(q5, q6, dt))
+    assert torch.equal(dX, tj.linear_bwd_dx(dY, Wq, 11, 5, dt, rht=bool(rht)))
+    assert torch.equal(dW, tj.linear_bwd_dw(dY, Xq, 11, 5, dt, rht=bool(rht)))
+    # a workspace without room for the blocked scale bytes
+    least = _least_workspace(N, D, C, outer)
+    assert least <= B.workspace_bytes(B.OP_LINEAR_BWD, N, D, C, outer)
+    aX, aW = tj.linear_bwd(dY, Xq, Wq, 11, 5, dt, rht=bool(rht), ws=tj.alloc_workspace(least))
+    assert torch.equal(dX, aX) and torch.equal(dW, aW)
+
+
+def test_cases_reach_both_kernels_and_every_fetch():
+    """what the table says of itself, by the planner (no GPU)"""
+    import paper_2510_27527_amd.binding as B
+    seen = set()
+    for outer, _, N, D, C in CASES + LONG:
+        for M, Nn, K in ((N, D, C), (C, D, N)):
+            if not B.gemm_splits_waves(M, Nn, K, outer):
+                bm, bn, split = B.gemm_plan(M, Nn, K, outer)
+                seen.add((outer, bm, bn))
+                seen.add((outer, "split", split > 1))
+                seen.add((outer, "mod", K % 256))
+    for outer, tiles in ((0, [(64, 64), (64, 128), (128, 128), (128, 192), (128, 256), (256, 128), (256, 256)]),
+                         (1, [(64, 64), (64, 128), (128, 128), (128, 192), (256, 128)])):
+        assert {(outer, *t) for t in tiles} <= seen
+        assert {(outer, "split", False), (outer, "split", True)} <= seen
+    assert {(0, "mod", m) for m in (0, 64, 128, 192)} <= seen
