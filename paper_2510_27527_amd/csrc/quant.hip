@@ -172,8 +172,8 @@ struct RowJob {
 //
 // BLK (0, 256 or 512): the output is blocked along K.  A workgroup then takes BLK columns of 8192 / BLK rows instead of 8192 consecutive elements, 16 rows x
 // 128 at a time, so that it writes runs of 512 bytes (16 rows of 32), in bands of tiles per XCD as in the column kernel: 512 where that covers no more
-// columns past K than 256 does.  Bound by the vector ALU like the row-major form, and 4 % slower than it (8192 x 4096 with the transform, 1 x 128 outer blocks: 25.9 ->
-// 27.0 us; 32 x 256 tiles 27.5): the product that reads the result gains ten times that.
+// columns past K than 256 does.  Bound by the vector ALU like the row-major form (8192 x 4096 with the transform, 1 x 128 outer blocks: 25.9 -> 25.8 us; 27.0 with
+// 64-bit addresses per lane).
 template <int ROUND, bool SUP, int OUTER, bool DEQ, bool RHT = false, int BLK = 0>
 __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j1, unsigned first_second)
 {
@@ -205,7 +205,13 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
     constexpr int kRowSteps = kBlkRows / 16;
     auto row_of = [&](int it) { return r0 + 16 * (it % kRowSteps) + (tid >> 4); };
     auto col_of = [&](int it) { return k0 + 128 * (it / kRowSteps) + 8 * (tid & 15); };
-    auto chunk_of = [&](int it) { return BLK ? row_of(it) * (j0.K >> 3) + (col_of(it) >> 3) : c0 + it * kThreads; };
+    // BLK: uniform parts per chunk and 32-bit parts per lane of the source index and of the places in the output
+    const uint32_t src_lane = (uint32_t)(tid >> 4) * (uint32_t)(j0.K >> 3) + (uint32_t)(tid & 15);
+    auto src_uni = [&](int it) { return (r0 + 16 * (it % kRowSteps)) * (j0.K >> 3) + (k0 >> 3) + 16 * (it / kRowSteps); };
+    const uint32_t code_lane = (uint32_t)((tid & 15) >> 3) * (uint32_t)(j0.rows * 32) + (uint32_t)(tid >> 4) * 32u + (uint32_t)(tid & 7) * 4u;
+    auto uni_row = [&](int it) { return r0 + 16 * (it % kRowSteps); };
+    auto uni_col = [&](int it) { return k0 + 128 * (it / kRowSteps); };
+    auto chunk_of = [&](int it) { return BLK ? src_uni(it) + src_lane : c0 + it * kThreads; };
     auto exists = [&](int it) { return BLK ? row_of(it) < j0.rows && col_of(it) < j0.K : c0 + it * kThreads < nchunks; };
     uint4 vs[kRowIter];
 #pragma unroll
@@ -294,20 +300,29 @@ __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j
                 t = dpp<DPP_ROW_HALF_MIRROR>(gm); gm = gm > t ? gm : t;
                 t = dpp<DPP_ROW_MIRROR>(gm);      gm = gm > t ? gm : t;
                 os = outer_scale(RHT ? u2f(gm) : u2f(gm << 16));
-                if (valid && (tid & 15) == 0) a.gscale[BLK ? blocked_outer(j0.rows, row_of(it), col_of(it)) : c >> 4] = os.S_g;
+                if (valid && (tid & 15) == 0) {
+                    if (BLK) (a.gscale + blocked_outer(j0.rows, uni_row(it), uni_col(it)))[tid >> 4] = os.S_g;
+                    else a.gscale[c >> 4] = os.S_g;
+                }
             }
             const float amax_b = RHT ? u2f(bm) : u2f(bm << 16);
             const float s = amax_b * os.inv_cg;
             const uint32_t sc = e4m3_round<SUP>(s);
             const float r = os.inv_sg * inv_tab[sc];
-            const uint32_t q = quant8<ROUND, SUP>(x, r, (uint32_t)(c * 2), a.k0, a.k1);
-            if (valid) a.codes[BLK ? blocked_code(j0.rows, row_of(it), col_of(it)) >> 2 : c] = q;
+            const uint32_t quad0 = BLK ? (uint32_t)src_uni(it) * 2u + src_lane * 2u : (uint32_t)(c * 2);
+            const uint32_t q = quant8<ROUND, SUP>(x, r, quad0, a.k0, a.k1);
+            if (valid) {
+                if (BLK) *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(a.codes) + blocked_code(j0.rows, uni_row(it), uni_col(it)) + code_lane) = q;
+                else a.codes[c] = q;
+            }
             // four scale bytes (lanes c, c+2, c+4, c+6) travel to the lane with c % 8 == 0
             const uint32_t s2 = sc | (dpp<DPP_ROW_SHL2>(sc) << 8);
             const uint32_t s4 = s2 | (dpp<DPP_ROW_SHL4>(s2) << 16);
             if (BLK) {
                 // (K is a multiple of 64: the four bytes exist or none does)
-                if (valid && (tid & 7) == 0) *reinterpret_cast<uint32_t *>(a.scales + blocked_scale(j0.rows, row_of(it), col_of(it))) = s4;
+                // (128 columns, so the same 256 k for all lanes)
+                if (valid && (tid & 7) == 0)
+                    *reinterpret_cast<uint32_t *>(a.scales + blocked_scale(j0.rows, uni_row(it), uni_col(it)) + ((uint32_t)(tid >> 4) * 16u + (uint32_t)((tid & 15) >> 3) * 4u)) = s4;
             } else if (valid && (tid & 7) == 0) {
                 if (!CHECK || c + 8 <= nchunks) {
                     reinterpret_cast<uint32_t *>(a.scales)[c >> 3] = s4;
@@ -437,7 +452,8 @@ __device__ __forceinline__ int tile_pos(int row, int dwcol) { return row * 32 + 
 // while a row passes through registers, it is quantized row-wise (groups along C); after the transpose a lane owns
 // two columns x 16 rows = two groups of the column-wise operand.
 // BROW, BCOL: the row-wise / column-wise operand is blocked along K (the source's columns / rows are then a multiple of 64): the four passes
-// over a tile's rows write 4 KB of codes in one run, where row-major rows get 32 bytes each (16384 x 8192: 127 -> 105 us; the rest is the vector ALU).
+// over a tile's rows write 4 KB of codes in one run, where row-major rows get 32 bytes each (16384 x 8192: 127 -> 105 us;
+// 102.6 with uniform addresses and 32-bit offsets, which took a tenth of the vector instructions: the vector ALU bounds it).
 template <int ROUND, bool SUP, bool BROW = false, bool BCOL = false>
 __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
 {
@@ -502,10 +518,17 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
     const int rb = tid & 7, cp = tid >> 3;
     const int64_t c_first = C0 + 2 * cp;
     const int64_t out_lane = c_first * R + 16 * rb;        // + R0 (+ R for the second column): output element index
+    // Blocked outputs: a uniform address per tile plus a 32-bit offset per lane.  (R and C are at most 2^24 there.)
+    const uint32_t ccode = (uint32_t)(rb >> 2) * (uint32_t)(C * 32) + (uint32_t)cp * 64u + (uint32_t)(rb & 3) * 8u;
+    // numbers of the first quads (four elements): the lane's part, modulo 2^32; R, C and the tile's rows are multiples of 4 there
+    const uint32_t rquad = (uint32_t)(ld_lane >> 2), cquad = (uint32_t)(out_lane >> 2);
 
     for (int t = 0; t < ntile; ++t) {
         const int64_t R0 = (int64_t)(rt0 + t) * kTileR;
         if (t > 0) __syncthreads();                         // everyone is done reading the previous tile
+        uint32_t *const ut_rc = a.krow.codes + ((int64_t)bx * R + R0) * 8;
+        uint8_t *const ut_rs = a.krow.scales + blocked_scale(R, R0, C0);
+        uint8_t *const ut_cc = reinterpret_cast<uint8_t *>(a.k.codes) + blocked_code(C, C0, R0), *const ut_cs = a.k.scales + blocked_scale(C, C0, R0);
         // phase 1: tile -> LDS as bf16 pairs, row-major with rotated columns
 #pragma unroll
         for (int pass = 0; pass < 4; ++pass) {
@@ -524,13 +547,17 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
                 const float x[8] = {bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y),
                                     bf16_lo(v.z), bf16_hi(v.z), bf16_lo(v.w), bf16_hi(v.w)};
                 const int64_t e0 = (R0 + pass * 32) * C + ld_lane;
-                const uint32_t qd = quant8<ROUND, SUP>(x, r, (uint32_t)(e0 >> 2), a.krow.k0, a.krow.k1);
-                if (valid) a.krow.codes[BROW ? blocked_code(R, gr, ld_col) >> 2 : e0 >> 3] = qd;
+                const uint32_t uquad = (uint32_t)((R0 + pass * 32) * (C >> 2));        // uniform
+                const uint32_t qd = quant8<ROUND, SUP>(x, r, BROW ? rquad + uquad : (uint32_t)(e0 >> 2), a.krow.k0, a.krow.k1);
+                if (valid) {
+                    if (BROW) (ut_rc + pass * 256)[tid] = qd;
+                    else a.krow.codes[e0 >> 3] = qd;
+                }
                 const uint32_t s2 = sc | (dpp<DPP_ROW_SHL2>(sc) << 8);
                 const uint32_t s4 = s2 | (dpp<DPP_ROW_SHL4>(s2) << 16);
                 if (valid && q == 0) {
                     if (BROW) {
-                        *reinterpret_cast<uint32_t *>(a.krow.scales + blocked_scale(R, gr, C0)) = s4;
+                        *reinterpret_cast<uint32_t *>(ut_rs + (uint32_t)row * 16u) = s4;
                     } else if ((C & 63) == 0) {
                         *reinterpret_cast<uint32_t *>(a.krow.scales + (e0 >> 4)) = s4;
                     } else {
@@ -566,13 +593,17 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
             const uint32_t sc = e4m3_round<SUP>(s);
             const float r = os.inv_sg * inv_tab[sc];
             const int64_t e = out_lane + R0 + (j ? R : 0);
-            const uint32_t quad0 = (uint32_t)(e >> 2);
+            const uint32_t quad0 = BCOL ? cquad + (uint32_t)(R0 >> 2) + (j ? (uint32_t)(R >> 2) : 0u) : (uint32_t)(e >> 2);
             uint2 q;
             q.x = quant8<ROUND, SUP>(x0, r, quad0, a.k.k0, a.k.k1);
             q.y = quant8<ROUND, SUP>(x1, r, quad0 + 2, a.k.k0, a.k.k1);
-            const int64_t kr = R0 + 16 * rb;
-            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(a.k.codes) + (BCOL ? blocked_code(C, c_first + j, kr) : e >> 1)) = q;
-            a.k.scales[BCOL ? blocked_scale(C, c_first + j, kr) : e >> 4] = (uint8_t)sc;
+            if (BCOL) {
+                *reinterpret_cast<uint2 *>(ut_cc + (ccode + 32u * j)) = q;
+                ut_cs[(uint32_t)(2 * cp + j) * 16u + (uint32_t)rb] = (uint8_t)sc;
+            } else {
+                *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(a.k.codes) + (e >> 1)) = q;
+                a.k.scales[e >> 4] = (uint8_t)sc;
+            }
         }
     }
 }
