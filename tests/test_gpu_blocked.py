@@ -15,6 +15,9 @@ CASES = [
     (1, 0, 256, 4096, 1536), (1, 1, 384, 256, 512), (1, 0, 512, 256, 640),
 ]
 # long strips of the column-wise quantizers (four and eight slabs of 16 rows a wave), the last of them cut short
+# products with outer blocks planned with 256 x 128 or 128 x 256 tiles that 128 x 128 ones take once blocked (dX, then dW, some ending inside a planned tile)
+RETILED = [(1, 0, 5504, 1024, 256), (1, 1, 4224, 1408, 512), (1, 0, 256, 1024, 5504), (1, 1, 512, 1408, 4224),
+           (1, 0, 640, 11264, 768)]
 LONG = [(0, 0, 8256, 5120, 1088), (0, 0, 12352, 2048, 3456), (0, 0, 8256, 1024, 3584)]
 
 
@@ -51,7 +54,7 @@ def _least_workspace(N, D, C, outer):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("f32", [False, True])
-@pytest.mark.parametrize("outer,rht,N,D,C", CASES + LONG)
+@pytest.mark.parametrize("outer,rht,N,D,C", CASES + RETILED + LONG)
 def test_gradients_of_blocked_operands(outer, rht, N, D, C, f32):
     import paper_2510_27527_amd as tj
     B = tj.binding
@@ -88,3 +91,13 @@ def test_cases_reach_both_kernels_and_every_fetch():
         assert {(outer, *t) for t in tiles} <= seen
         assert {(outer, "split", False), (outer, "split", True)} <= seen
     assert {(0, "mod", m) for m in (0, 64, 128, 192)} <= seen
+
+
+@pytest.mark.parametrize("outer,rht,N,D,C", RETILED)
+def test_retiled_cases_are_planned_otherwise(outer, rht, N, D, C):
+    import paper_2510_27527_amd as tj
+    M, K = (N, C) if C % 256 == 0 else (C, N)
+    if K % 256 or (M // 128) * (D // 128) <= 256:
+        M, K = C, N
+    assert K % 256 == 0 and (M // 128) * (D // 128) > 256
+    assert tj.binding.gemm_plan(M, D, K, outer) in ((256, 128, 1), (128, 256, 1))
