@@ -272,9 +272,9 @@ hipError_t launch_tiles(int tile, int outer, bool ps, bool out_f32, bool kw, con
 // M x N x K, the planned 256 x 128 tile -> 128 x 128 in us: 8192 x 3072 x 768 63.4 -> 57.6, 16384 x 8192 x 1024 399 -> 354, 6144 x 6144 x 1024
 // 116.8 -> 92.7, 4096 x 2048 x 2048 44.8 -> 42.5, 9984 x 7936 x 256 87.4 -> 68.4, 9088 x 2944 x 768 74.3 -> 56.1, 1664 x 9344 x 1280 57.9 -> 50.5; a planned 128 x 256 one:
 // 3456 x 12032 x 1024 125.4 -> 111.8, 4480 x 11008 x 256 53.7 -> 46.1, 640 x 11264 x 768 22.7 -> 21.9.
-// The estimate only ranks against plan.time, in whose scale its constants are chosen: against the measured times it lies between 10 % below (3 full
-// rounds of 512) and 19 % above (a last round that is part full).  With no more than a workgroup per CU the planned tile stays.  All these tiles
-// add in the same order.
+// The estimate only ranks against plan.time, in whose scale its constants are chosen: against the times of 19 products that change tile it lies
+// between 21 % below (one round of 512, part full) and 24 % above (a last round that is part full).  Up to 256 tiles the planned one stays.  All these
+// tiles add in the same order.
 int tile_of_blocked(const Plan &p, int64_t M, int64_t N, int64_t K)
 {
     if (p.split > 1 || p.kw || (p.tile != 1 && p.tile != 2)) return p.tile;
