@@ -284,10 +284,24 @@ int tile_of_blocked(const Plan &p, int64_t M, int64_t N, int64_t K)
     return time < p.time ? 3 : p.tile;
 }
 
+// Whether the plan's launch can read operands that are blocked along K (the reasons are at gemm_needs).
+bool takes_blocked(const Plan &p, int64_t M, int64_t N, int64_t K, int outer)
+{
+    const bool narrow = M <= (1 << 24) && N <= (1 << 24);  // 32-bit offsets over the chunks of a stage
+    return narrow && !p.kw && (outer ? K % 256 == 0 : p.split == 1 || p.chunks_per_split % 2 == 0);
+}
+
+// Operands in a layout that the launch would read as another one are refused: the product would be wrong without an error.
+bool layout_fits(const Plan &p, const GemmOperand &A, const GemmOperand &B, int64_t K)
+{
+    return A.blocked == B.blocked && (!A.blocked || takes_blocked(p, A.rows, B.rows, K, A.outer));
+}
+
 hipError_t launch_planned(const Plan &plan, const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32, void *ws,
                           size_t ws_bytes, hipStream_t st)
 {
     const int64_t M = A.rows, N = B.rows;
+    if (!layout_fits(plan, A, B, K)) return hipErrorInvalidValue;
     Plan p = plan;
     if (A.blocked && A.outer) p.tile = tile_of_blocked(plan, M, N, K);
     if (M == 0 || N == 0) return hipSuccess;
@@ -441,9 +455,13 @@ hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws,
     const int outer = p[0].A.outer;
     const GroupPlan plan = plan_group(mnk, n, outer);
     if (plan.tile < 0) {
+        Plan own[kMaxGroup];
+        for (int i = 0; i < n; ++i) {                      // all of them before the first launch
+            own[i] = i < plan.planned ? plan.own[i] : make_plan(mnk[i][0], mnk[i][1], mnk[i][2], outer);
+            if (!layout_fits(own[i], p[i].A, p[i].B, p[i].K)) return hipErrorInvalidValue;
+        }
         for (int i = 0; i < n; ++i) {
-            const Plan own = i < plan.planned ? plan.own[i] : make_plan(mnk[i][0], mnk[i][1], mnk[i][2], outer);
-            const hipError_t e = launch_planned(own, p[i].A, p[i].B, p[i].K, p[i].out, out_f32, ws, ws_bytes, st);
+            const hipError_t e = launch_planned(own[i], p[i].A, p[i].B, p[i].K, p[i].out, out_f32, ws, ws_bytes, st);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -457,6 +475,10 @@ hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws,
         g.first[i] = i < n ? wgs : INT_MAX;
         if (i < n) wgs += g.g[i].tiles_m * g.g[i].tiles_n;
         ps = ps && q.K % 256 == 0;
+    }
+    for (int i = 0; i < n; ++i) {                          // one kernel reads them all
+        const Plan whole{plan.tile, 1, (int)(mnk[i][2] / 64), plan.kw, 0.0};
+        if (p[i].A.blocked != p[0].A.blocked || !layout_fits(whole, p[i].A, p[i].B, p[i].K)) return hipErrorInvalidValue;
     }
     return launch_tiles(plan.tile, outer, ps, out_f32 != 0, plan.kw, g, dim3((unsigned)wgs, 1, 1), st);
 }
@@ -473,9 +495,7 @@ void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int
 GemmNeeds gemm_needs(int64_t M, int64_t N, int64_t K, int outer)
 {
     const Plan p = make_plan(M, N, K, outer);
-    const bool narrow = M <= (1 << 24) && N <= (1 << 24);  // 32-bit offsets over the chunks of a stage
-    const bool takes = !p.kw && (outer ? K % 256 == 0 : p.split == 1 || p.chunks_per_split % 2 == 0);
-    return GemmNeeds{split_bytes(p, M, N), narrow && takes};
+    return GemmNeeds{split_bytes(p, M, N), takes_blocked(p, M, N, K, outer)};
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer)
