@@ -632,7 +632,7 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
         const int64_t mnk[3][3] = {{N, D_lo, C}, {C, D_lo, N}, {N, D_hp, C}};
         int bm, bn;
         gemm_group_plan(mnk, 3, outer, &bm, &bn);
-        hp_blocked = bm > 0 && D_hp <= (1 << 24);
+        hp_blocked = bm > 0 && D_hp <= kMaxBlockedRows;
     }
     const bool bx = room && need.lo.blocked && hp_blocked && (!outer || need.w.blocked), bw = room && need.w.blocked && (!outer || bx);
     if (!carve_tensor(cv, N, C, outer, &q3, bx) || !carve_tensor(cv, D_lo, C, outer, &q4, bx) || !carve_tensor(cv, D_hp, C, outer, &q4h, bx) ||

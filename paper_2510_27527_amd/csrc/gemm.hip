@@ -287,8 +287,7 @@ int tile_of_blocked(const Plan &p, int64_t M, int64_t N, int64_t K)
 // Whether the plan's launch can read operands that are blocked along K (the reasons are at gemm_needs).
 bool takes_blocked(const Plan &p, int64_t M, int64_t N, int64_t K, int outer)
 {
-    const bool narrow = M <= (1 << 24) && N <= (1 << 24);  // 32-bit offsets over the chunks of a stage
-    return narrow && !p.kw && (outer ? K % 256 == 0 : p.split == 1 || p.chunks_per_split % 2 == 0);
+    return M <= kMaxBlockedRows && N <= kMaxBlockedRows && !p.kw && (outer ? K % 256 == 0 : p.split == 1 || p.chunks_per_split % 2 == 0);
 }
 
 // Operands in a layout that the launch would read as another one are refused: the product would be wrong without an error.

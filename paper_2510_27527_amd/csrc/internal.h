@@ -16,6 +16,9 @@ struct QuantOut {
     int blocked;       // 1: codes, scale bytes and outer scales in the order described at GemmOperand
 };
 
+// most rows of an operand that is blocked along K: offsets over the chunks of a stage (64 bytes a row) are 32-bit numbers
+constexpr int64_t kMaxBlockedRows = 1 << 24;
+
 struct QuantParams {
     int rounding;      // 0 RTN, 1 SR
     int scale_up;      // 0 nearest-even, 1 upward

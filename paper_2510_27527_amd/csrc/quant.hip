@@ -1049,6 +1049,13 @@ void launch_colw(const ColArgs &a0, const ColArgs &a1, bool pair, const QuantPar
 
 }  // namespace
 
+// Whether an output [rows x K] is in a layout its kernel writes: an output blocked along K has whole 64s and 32-bit offsets over the rows of a
+// block, and the row-wise and the two-operand kernel have that form for the backward operands' rounding only.
+static bool layout_fits(const QuantOut &o, int64_t rows, int64_t K, const QuantParams &p, bool any_rounding)
+{
+    return !o.blocked || (K % 64 == 0 && rows <= kMaxBlockedRows && (any_rounding || (p.rounding == 1 && p.scale_up)));
+}
+
 static int amax_grid(int64_t nchunks)
 {
     const int64_t want = (nchunks + (int64_t)kThreads * 8 - 1) / ((int64_t)kThreads * 8);
@@ -1124,6 +1131,7 @@ hipError_t launch_quant_row_bf16(const void *src, int64_t rows, int64_t K, const
 {
     const int64_t nchunks = rows * K / 8;
     if (nchunks == 0) return hipSuccess;
+    if (!layout_fits(o, rows, K, p, false)) return hipErrorInvalidValue;
     RowJob j0{reinterpret_cast<const uint4 *>(src), nchunks, make_kargs(p, o), (uint32_t)(K / 128), rows, K}, j1{};
     const bool deq = o.amax_deq != nullptr && p.rounding == 0 && !p.rht;
     launch_row_sel(j0, j1, p, deq, st);
@@ -1137,6 +1145,7 @@ hipError_t launch_quant_row_bf16_pair(const void *src0, int64_t rows0, int64_t K
 {
     if (rows0 * K0 == 0) return launch_quant_row_bf16(src1, rows1, K1, p1, o1, st);
     if (rows1 * K1 == 0) return launch_quant_row_bf16(src0, rows0, K0, p0, o0, st);
+    if (o0.blocked || o1.blocked) return hipErrorInvalidValue;      // forward operands
     RowJob j0{reinterpret_cast<const uint4 *>(src0), rows0 * K0 / 8, make_kargs(p0, o0), (uint32_t)(K0 / 128), rows0, K0};
     RowJob j1{reinterpret_cast<const uint4 *>(src1), rows1 * K1 / 8, make_kargs(p1, o1), (uint32_t)(K1 / 128), rows1, K1};
     const bool deq = (o0.amax_deq != nullptr || o1.amax_deq != nullptr) && p0.rounding == 0;
@@ -1149,6 +1158,7 @@ hipError_t launch_quant_col_bf16(const void *src, int64_t R, int64_t C, const Qu
                                  hipStream_t st)
 {
     if (R == 0 || C == 0) return hipSuccess;
+    if (!layout_fits(o, C, R, p, true)) return hipErrorInvalidValue;
     ColArgs a{};
     a.src = reinterpret_cast<const uint4 *>(src);
     a.R = R;
@@ -1163,6 +1173,7 @@ hipError_t launch_quant_dual_bf16(const void *src, int64_t R, int64_t C, const Q
                                   const QuantParams &pcol, const QuantOut &ocol, hipStream_t st)
 {
     if (R == 0 || C == 0) return hipSuccess;
+    if (!layout_fits(orow, R, C, prow, false) || !layout_fits(ocol, C, R, pcol, false)) return hipErrorInvalidValue;
     ColArgs a{};
     a.src = reinterpret_cast<const uint4 *>(src);
     a.R = R;
@@ -1202,6 +1213,7 @@ hipError_t launch_requant_col(const PackedSrc &src, int64_t R, int64_t C, const 
                               hipStream_t st)
 {
     if (R == 0 || C == 0) return hipSuccess;
+    if (!layout_fits(o, C, R, p, true)) return hipErrorInvalidValue;
     ColArgs a = packed_args(src, R, C, p, o), none{};
     launch_colw<true>(a, none, false, p, st);
     return hipGetLastError();
@@ -1213,6 +1225,7 @@ hipError_t launch_requant_col_pair(const PackedSrc &src0, int64_t R0, int64_t C0
 {
     if (R0 == 0 || C0 == 0) return launch_requant_col(src1, R1, C1, p1, o1, st);
     if (R1 == 0 || C1 == 0) return launch_requant_col(src0, R0, C0, p0, o0, st);
+    if (!layout_fits(o0, C0, R0, p0, true) || !layout_fits(o1, C1, R1, p1, true)) return hipErrorInvalidValue;
     ColArgs a0 = packed_args(src0, R0, C0, p0, o0), a1 = packed_args(src1, R1, C1, p1, o1);
     launch_colw<true>(a0, a1, true, p0, st);
     return hipGetLastError();
@@ -1226,6 +1239,7 @@ hipError_t launch_requant_col_pair_amax(const PackedSrc &src0, int64_t R0, int64
         *npart = launch_amax_partials(bf16, n, partials, nullptr, st);
         return launch_requant_col_pair(src0, R0, C0, p0, o0, src1, R1, C1, p1, o1, st);
     }
+    if (!layout_fits(o0, C0, R0, p0, true) || !layout_fits(o1, C1, R1, p1, true)) return hipErrorInvalidValue;
     const ColArgs a0 = packed_args(src0, R0, C0, p0, o0), a1 = packed_args(src1, R1, C1, p1, o1);
     const AmaxJob am{reinterpret_cast<const uint4 *>(bf16), n / 8, partials, nullptr, (unsigned)amax_grid(n / 8)};
     auto launch = [&](auto slabs) {

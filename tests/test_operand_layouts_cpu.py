@@ -33,6 +33,29 @@ extern "C" int group(const int64_t *mnk, int n, int outer, const int *blocked)
         p[i] = GemmProduct{operand(mnk[3 * i], outer, blocked[i]), operand(mnk[3 * i + 1], outer, blocked[i]), mnk[3 * i + 2], kFar};
     return launch_gemm_group(p, n, 0, kFar, (size_t)1 << 40, nullptr);
 }
+
+// kind: 0 row-wise, 1 two row-wise ones, 2 column-wise, 3 both of one tensor, 4 column-wise from a packed one, 5 two of them, 6 and a maximum
+extern "C" int quantize(int kind, int64_t R, int64_t C, int rounding, int scale_up, int outer, int blocked0, int blocked1)
+{
+    float *const f = reinterpret_cast<float *>(kFar);
+    QuantParams p{};
+    p.rounding = rounding;
+    p.scale_up = scale_up;
+    p.outer = outer;
+    p.amax_scalar = f;
+    const QuantOut o0{kFar, kFar, f, nullptr, blocked0}, o1{kFar, kFar, f, nullptr, blocked1};
+    const PackedSrc s{kFar, kFar, f, outer};
+    int npart = 0;
+    switch (kind) {
+        case 0: return launch_quant_row_bf16(kFar, R, C, p, o0, nullptr);
+        case 1: return launch_quant_row_bf16_pair(kFar, R, C, p, o0, kFar, R, C, p, o1, nullptr);
+        case 2: return launch_quant_col_bf16(kFar, R, C, p, o0, nullptr);
+        case 3: return launch_quant_dual_bf16(kFar, R, C, p, o0, p, o1, nullptr);
+        case 4: return launch_requant_col(s, R, C, p, o0, nullptr);
+        case 5: return launch_requant_col_pair(s, R, C, p, o0, s, R, C, p, o1, nullptr);
+        default: return launch_requant_col_pair_amax(s, R, C, p, o0, s, R, C, p, o1, kFar, R * C, f, &npart, nullptr);
+    }
+}
 """
 
 
@@ -96,3 +119,26 @@ def test_launches_of_several_products_refuse_layouts_they_do_not_read(lib, outer
     products = [(N, D, Cc), (Cc, D, N)] + ([(N, H, Cc)] if H else [])
     for blocked in itertools.product((0, 1), repeat=len(products)):
         assert (_group(lib, products, outer, blocked) != INVALID) == (blocked in accepted), blocked
+
+
+@pytest.mark.parametrize("rounding,scale_up", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("kind", range(7))
+def test_quantizers_refuse_a_layout_they_do_not_write(lib, kind, rounding, scale_up):
+    def quantize(R, Cc, outer, b0, b1):
+        return lib.quantize(kind, C.c_int64(R), C.c_int64(Cc), rounding, scale_up, outer, b0, b1) != INVALID
+    backward = rounding == 1 and scale_up == 1
+    for outer in (0,) if kind == 3 else (0, 1):
+        assert quantize(256, 256, outer, 0, 0)
+        for b0, b1 in ((1, 1), (1, 0), (0, 1)):
+            second = kind in (1, 3, 5, 6)
+            if not second and not b0:
+                continue
+            # the row-wise pair is the forward call's; column-wise kernels write blocked operands of every rounding
+            assert quantize(256, 256, outer, b0, b1) == (kind != 1 and (kind not in (0, 3) or backward)), (outer, b0, b1)
+            # a row of the output is no whole number of 64s
+            if outer == 0:
+                axis_c = (b0 and kind in (0, 1, 3)), (b1 and kind == 1)
+                axis_r = (b0 and kind in (2, 4, 5, 6)), (b1 and kind in (3, 5, 6))
+                assert not quantize(256 + 32 * any(axis_r), 256 + 32 * any(axis_c), outer, b0, b1), (b0, b1)
+    rows, cols = ((1 << 24) + 64, 64) if kind < 2 else (128, (1 << 24) + 64)
+    assert not quantize(rows, cols, 0, *((0, 1) if kind == 3 else (1, 1)))
