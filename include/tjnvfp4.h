@@ -230,6 +230,18 @@ int nvfp4_outctl_dw_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int o
  * they are launched one after the other.  It follows from the sizes alone.  Host-only helper. */
 int nvfp4_backward_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *tile_m, int *tile_n);
 
+/* How one product of a backward call is computed, given a workspace of the size that the library reports. */
+typedef struct nvfp4_product_plan {
+    int32_t tile_m, tile_n;   /* workgroup tile: rows x columns of the output */
+    int32_t split;            /* pieces of the reduction (> 1: FP32 partial sums and a kernel that adds them) */
+    int32_t split_waves;      /* 1: a workgroup's waves split the reduction of its tile, 0: they split the tile */
+    int32_t blocked;          /* 1: the call's own copies of the operands are laid out in blocks along the reduction for this product */
+    int32_t together;         /* 1: in one launch with the call's other products */
+} nvfp4_product_plan;
+/* op: NVFP4_OP_LINEAR_BWD_DX, _DW (D_hp 0) or _BWD (with D_hp > 0 the call is nvfp4_outctl_bwd); product: 0 dX, 1 dW, 2 dX of the outlier
+ * channels, as far as the call has it (ENUM otherwise).  It follows from the sizes alone.  Host-only helper. */
+int nvfp4_backward_product_plan(int op, int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int product, nvfp4_product_plan *plan);
+
 /*
  * OsciReset (Sec. 3.2-3.3) for one weight matrix of binary32 master weights W [C x D], all arrays device memory of
  * C * D floats, 16-byte aligned, D % 128 == 0.  Q(W) below is the forward weight quantizer (groups of 16 along D,

@@ -24,7 +24,7 @@ SRC_BF16, SRC_NVFP4 = 0, 1
 OUT_BF16, OUT_F32 = 0, 1
 OP_QUANTIZE, OP_GEMM, OP_LINEAR_FWD, OP_LINEAR_BWD_DX, OP_LINEAR_BWD_DW, OP_LINEAR_BWD = 0, 1, 2, 3, 4, 5
 
-EXPORTS = ["nvfp4_quantize", "nvfp4_quantize_dual", "nvfp4_gemm_nt", "nvfp4_gemm_nt_static", "nvfp4_linear_fwd", "nvfp4_linear_bwd_dx", "nvfp4_linear_bwd_dw", "nvfp4_linear_bwd", "nvfp4_osci_update", "nvfp4_osci_suppress", "nvfp4_osci_select", "nvfp4_osci_update_sparse", "nvfp4_osci_suppress_sparse", "nvfp4_osci_select_workspace_bytes", "nvfp4_outctl_fwd", "nvfp4_outctl_bwd", "nvfp4_outctl_workspace_bytes", "nvfp4_outctl_dw_plan", "nvfp4_backward_plan",
+EXPORTS = ["nvfp4_quantize", "nvfp4_quantize_dual", "nvfp4_gemm_nt", "nvfp4_gemm_nt_static", "nvfp4_linear_fwd", "nvfp4_linear_bwd_dx", "nvfp4_linear_bwd_dw", "nvfp4_linear_bwd", "nvfp4_osci_update", "nvfp4_osci_suppress", "nvfp4_osci_select", "nvfp4_osci_update_sparse", "nvfp4_osci_suppress_sparse", "nvfp4_osci_select_workspace_bytes", "nvfp4_outctl_fwd", "nvfp4_outctl_bwd", "nvfp4_outctl_workspace_bytes", "nvfp4_outctl_dw_plan", "nvfp4_backward_plan", "nvfp4_backward_product_plan",
            "nvfp4_workspace_bytes", "nvfp4_gemm_plan", "nvfp4_gemm_plan_kernel", "nvfp4_amax_bf16", "nvfp4_stream_key", "nvfp4_strerror", "nvfp4_version"]
 
 
@@ -43,6 +43,21 @@ class CQcfg(C.Structure):
     _fields_ = [("rounding", C.c_int32), ("scale_round", C.c_int32), ("outer_mode", C.c_int32),
                 ("tensor_id", C.c_uint32), ("seed", C.c_uint64), ("amax_in", C.c_void_p), ("rht", C.c_int32),
                 ("rht_id", C.c_uint32)]
+
+
+class CProductPlan(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("tile_m", "tile_n", "split", "split_waves", "blocked", "together")]
+
+
+@dataclass(frozen=True)
+class ProductPlan:
+    """How one product of a backward call is computed: workgroup tile, pieces of the reduction, whether the waves split it, whether the operands
+    are blocked along it, whether the call's products share a launch."""
+    tile: tuple
+    split: int
+    split_waves: bool
+    blocked: bool
+    together: bool
 
 
 _lib = None
@@ -103,6 +118,8 @@ def lib():
         L.nvfp4_gemm_plan_kernel.argtypes = [i64, i64, i64, i32, C.POINTER(C.c_int)]
         L.nvfp4_backward_plan.restype = i32
         L.nvfp4_backward_plan.argtypes = [i64, i64, i64, i64, i32, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        L.nvfp4_backward_product_plan.restype = i32
+        L.nvfp4_backward_product_plan.argtypes = [i32, i64, i64, i64, i64, i32, i32, C.POINTER(CProductPlan)]
         L.nvfp4_outctl_dw_plan.restype = i32
         L.nvfp4_outctl_dw_plan.argtypes = [i64, i64, i64, i64, i32, C.POINTER(C.c_int), C.POINTER(C.c_int)]
         L.nvfp4_amax_bf16.restype = i32
@@ -194,6 +211,13 @@ def backward_plan(N: int, D_lo: int, D_hp: int, Cc: int, outer: int = OUTER_TENS
     a, b = C.c_int(0), C.c_int(0)
     _check(lib().nvfp4_backward_plan(N, D_lo, D_hp, Cc, outer, C.byref(a), C.byref(b)), "nvfp4_backward_plan")
     return a.value, b.value
+
+
+def backward_product_plan(op: int, N: int, D_lo: int, D_hp: int, Cc: int, outer: int, product: int) -> ProductPlan:
+    """Product 0 (dX), 1 (dW) or 2 (dX of the outlier channels) of a backward call: op OP_LINEAR_BWD_DX, _DW or _BWD."""
+    p = CProductPlan()
+    _check(lib().nvfp4_backward_product_plan(op, N, D_lo, D_hp, Cc, outer, product, C.byref(p)), "nvfp4_backward_product_plan")
+    return ProductPlan((p.tile_m, p.tile_n), p.split, bool(p.split_waves), bool(p.blocked), bool(p.together))
 
 
 def outctl_dw_plan(N: int, D_lo: int, D_hp: int, Cc: int, outer: int = OUTER_TENSOR):

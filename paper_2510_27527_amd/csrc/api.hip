@@ -286,26 +286,26 @@ int run_requant_pair(const nvfp4_tensor *s0, const QuantPlan &pl0, const nvfp4_q
 }
 
 int run_gemm(const nvfp4_tensor *A, const nvfp4_tensor *B, void *Out, int out_dtype, void *ws, size_t ws_bytes,
-             hipStream_t st, bool blocked = false)
+             hipStream_t st)
 {
     const int outer = A->outer_mode == NVFP4_OUTER_BLOCK128 ? 1 : 0;
-    GemmOperand a{A->codes, A->scales, A->gscale, A->rows, outer, blocked};
-    GemmOperand b{B->codes, B->scales, B->gscale, B->rows, outer, blocked};
+    GemmOperand a{A->codes, A->scales, A->gscale, A->rows, outer, 0};
+    GemmOperand b{B->codes, B->scales, B->gscale, B->rows, outer, 0};
     const hipError_t e = launch_gemm_nt(a, b, A->K, Out, out_dtype == NVFP4_OUT_F32, ws, ws_bytes, st);
     return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
 // products of one backward call, in one launch where that is faster
 struct Product { const nvfp4_tensor *A, *B; void *out; bool blocked; };
-int run_gemm_group(const Product *p, int n, int out_dtype, void *ws, size_t ws_bytes, hipStream_t st)
+int run_gemm_group(const GroupPlan &plan, const Product *p, int out_dtype, void *ws, size_t ws_bytes, hipStream_t st)
 {
     GemmProduct g[3];
-    for (int i = 0; i < n; ++i) {
+    for (int i = 0; i < plan.n; ++i) {
         const int outer = p[i].A->outer_mode == NVFP4_OUTER_BLOCK128 ? 1 : 0;
         g[i] = GemmProduct{GemmOperand{p[i].A->codes, p[i].A->scales, p[i].A->gscale, p[i].A->rows, outer, p[i].blocked},
                            GemmOperand{p[i].B->codes, p[i].B->scales, p[i].B->gscale, p[i].B->rows, outer, p[i].blocked}, p[i].A->K, p[i].out};
     }
-    return launch_gemm_group(g, n, out_dtype == NVFP4_OUT_F32, ws, ws_bytes, st) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
+    return launch_gemm_group(plan, g, out_dtype == NVFP4_OUT_F32, ws, ws_bytes, st) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
 int check_out(const void *p, int out_dtype)
@@ -384,6 +384,27 @@ static size_t backward_bytes(int op, int64_t N, int64_t D, int64_t C, int o, siz
     if (op != NVFP4_OP_LINEAR_BWD_DW) n += packed_bytes(N, C, o, blocked) + packed_bytes(D, C, o, blocked);
     if (op != NVFP4_OP_LINEAR_BWD_DX) n += packed_bytes(C, N, o, blocked) + packed_bytes(D, N, o, blocked);
     return n;
+}
+
+// The products of a backward call - dX, dW and the outlier channels' dX, as far as the call has them - and whether the operands of dX (x) and of
+// dW (w) are blocked along K.  Q3 serves both parts of dX, so that these are laid out alike.
+struct BackwardPlan { int n; int64_t mnk[3][3]; GroupPlan g; bool x, w; };
+static BackwardPlan plan_backward(int op, int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer)
+{
+    BackwardPlan b{};
+    auto add = [&](int64_t M, int64_t Nn, int64_t K) {
+        int64_t *s = b.mnk[b.n++];
+        s[0] = M; s[1] = Nn; s[2] = K;
+    };
+    const bool x = op != NVFP4_OP_LINEAR_BWD_DW, w = op != NVFP4_OP_LINEAR_BWD_DX;
+    if (x) add(N, D_lo, C);
+    if (w) add(C, D_lo, N);
+    if (D_hp > 0) add(N, D_hp, C);
+    b.g = plan_group(b.mnk, b.n, outer);
+    b.x = x && b.g.blocked[0] && (D_hp == 0 || b.g.blocked[2]);
+    b.w = w && b.g.blocked[b.n - 1 - (D_hp > 0)];
+    if (outer && x && w && !(b.x && b.w)) b.x = b.w = false;
+    return b;
 }
 
 size_t nvfp4_workspace_bytes(int op, int64_t N, int64_t D, int64_t C, int outer_mode)
@@ -542,20 +563,11 @@ static size_t outctl_bwd_bytes(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C,
            align_up((size_t)(N * D_hp) * 2) + align_up(gemm_ws);
 }
 
-// of its three products: dX_lo, dW_lo, dX_hp
-struct OutctlNeeds { GemmNeeds lo, w, hp; size_t ws; };
-static OutctlNeeds outctl_needs(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer)
-{
-    OutctlNeeds n{gemm_needs(N, D_lo, C, outer), gemm_needs(C, D_lo, N, outer), gemm_needs(N, D_hp, C, outer), 0};
-    n.ws = n.lo.ws > n.w.ws ? n.lo.ws : n.w.ws;
-    n.ws = n.ws > n.hp.ws ? n.ws : n.hp.ws;
-    return n;
-}
-
 size_t nvfp4_outctl_workspace_bytes(int backward, int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int out_dtype)
 {
     if (N < 0 || D_lo < 0 || D_hp < 0 || C < 0 || !valid_outer(outer_mode)) return 0;
-    return backward ? outctl_bwd_bytes(N, D_lo, D_hp, C, outer_mode, outctl_needs(N, D_lo, D_hp, C, outer_mode).ws, true) : outctl_fwd_bytes(N, D_lo, C, outer_mode, out_dtype);
+    if (!backward) return outctl_fwd_bytes(N, D_lo, C, outer_mode, out_dtype);
+    return outctl_bwd_bytes(N, D_lo, D_hp, C, outer_mode, plan_backward(NVFP4_OP_LINEAR_BWD, N, D_lo, D_hp, C, outer_mode).g.ws, true);
 }
 
 int nvfp4_outctl_dw_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int *split, int *stages)
@@ -572,8 +584,26 @@ int nvfp4_backward_plan(int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int ou
     if (!tile_m || !tile_n) return NVFP4_ERR_NULL;
     if (!valid_outer(outer_mode)) return NVFP4_ERR_ENUM;
     if (N < 0 || D_lo < 0 || D_hp < 0 || C < 0 || D_hp % 32 != 0 || check_reduction(N) || check_reduction(C)) return NVFP4_ERR_SHAPE;
-    const int64_t mnk[3][3] = {{N, D_lo, C}, {C, D_lo, N}, {N, D_hp, C}};
-    gemm_group_plan(mnk, D_hp > 0 ? 3 : 2, outer_mode == NVFP4_OUTER_BLOCK128 ? 1 : 0, tile_m, tile_n);
+    const BackwardPlan b = plan_backward(NVFP4_OP_LINEAR_BWD, N, D_lo, D_hp, C, outer_mode);
+    int split = 0, split_waves = 0;
+    *tile_m = *tile_n = 0;
+    if (b.g.tile >= 0) planned_launch(b.g, 0, b.mnk[0], b.x, outer_mode, tile_m, tile_n, &split, &split_waves);
+    return NVFP4_OK;
+}
+
+int nvfp4_backward_product_plan(int op, int64_t N, int64_t D_lo, int64_t D_hp, int64_t C, int outer_mode, int product, nvfp4_product_plan *plan)
+{
+    if (!plan) return NVFP4_ERR_NULL;
+    const bool x = op != NVFP4_OP_LINEAR_BWD_DW, w = op != NVFP4_OP_LINEAR_BWD_DX, both = x && w;
+    if (!valid_outer(outer_mode) || op < NVFP4_OP_LINEAR_BWD_DX || op > NVFP4_OP_LINEAR_BWD) return NVFP4_ERR_ENUM;
+    if (product < 0 || product > 2 || (product == 0 && !x) || (product == 1 && !w) || (product == 2 && (!both || D_hp <= 0))) return NVFP4_ERR_ENUM;
+    if (N < 0 || D_lo < 0 || D_hp < 0 || C < 0 || D_hp % 32 != 0 || (!both && D_hp != 0)) return NVFP4_ERR_SHAPE;
+    if ((x && check_reduction(C)) || (w && check_reduction(N))) return NVFP4_ERR_SHAPE;
+    const BackwardPlan b = plan_backward(op, N, D_lo, D_hp, C, outer_mode);
+    const int i = both ? product : 0;
+    plan->blocked = product == 1 ? b.w : b.x;
+    plan->together = b.g.tile >= 0;
+    planned_launch(b.g, i, b.mnk[i], plan->blocked, outer_mode, &plan->tile_m, &plan->tile_n, &plan->split, &plan->split_waves);
     return NVFP4_OK;
 }
 
@@ -618,28 +648,20 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     const int outer = Xq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
     if (!aligned16(dY) || !aligned16(X_hp) || !aligned16(W_hp)) return NVFP4_ERR_ALIGN;
-    const OutctlNeeds need = outctl_needs(N, D_lo, D_hp, C, outer);
-    if (!ws || ws_bytes < outctl_bwd_bytes(N, D_lo, D_hp, C, outer, need.ws, false)) return NVFP4_ERR_WORKSPACE;
+    const BackwardPlan plan = plan_backward(NVFP4_OP_LINEAR_BWD, N, D_lo, D_hp, C, outer);
+    if (!ws || ws_bytes < outctl_bwd_bytes(N, D_lo, D_hp, C, outer, plan.g.ws, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
     float *part = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     float *part2 = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     nvfp4_tensor q3{}, q4{}, q4h{}, q5{}, q6{};
-    const bool room = ws_bytes >= outctl_bwd_bytes(N, D_lo, D_hp, C, outer, need.ws, true);
-    // Q3 serves both column sets: the outlier channels' product, whatever kernel it would take alone, has to be launched together with the others
-    bool hp_blocked = need.hp.blocked || D_hp == 0;
-    if (!hp_blocked && need.lo.blocked && need.w.blocked) {
-        const int64_t mnk[3][3] = {{N, D_lo, C}, {C, D_lo, N}, {N, D_hp, C}};
-        int bm, bn;
-        gemm_group_plan(mnk, 3, outer, &bm, &bn);
-        hp_blocked = bm > 0 && D_hp <= kMaxBlockedRows;
-    }
-    const bool bx = room && need.lo.blocked && hp_blocked && (!outer || need.w.blocked), bw = room && need.w.blocked && (!outer || bx);
+    const bool room = ws_bytes >= outctl_bwd_bytes(N, D_lo, D_hp, C, outer, plan.g.ws, true);
+    const bool bx = room && plan.x, bw = room && plan.w;
     if (!carve_tensor(cv, N, C, outer, &q3, bx) || !carve_tensor(cv, D_lo, C, outer, &q4, bx) || !carve_tensor(cv, D_hp, C, outer, &q4h, bx) ||
         !carve_tensor(cv, C, N, outer, &q5, bw) || !carve_tensor(cv, D_lo, N, outer, &q6, bw))
         return NVFP4_ERR_WORKSPACE;
     void *dYT = cv.take((size_t)(N * C) * 2), *XhT = cv.take((size_t)(N * D_hp) * 2);
-    const size_t gbytes = need.ws;
+    const size_t gbytes = plan.g.ws;
     void *gws = gbytes ? cv.take(gbytes) : nullptr;
     if (!dYT || !XhT || (gbytes && !gws)) return NVFP4_ERR_WORKSPACE;
 
@@ -662,7 +684,7 @@ int nvfp4_outctl_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     if (rc) return rc;
     // dX over all input channels in FP4 (one Q3 operand serves both column sets); dW of the ordinary channels in FP4
     const Product products[] = {{&q3, &q4, dX_lo, bx}, {&q5, &q6, dW_lo, bw}, {&q3, &q4h, dX_hp, bx}};
-    rc = run_gemm_group(products, D_hp > 0 ? 3 : 2, out_dtype, gws, gbytes, st);
+    rc = run_gemm_group(plan.g, products, out_dtype, gws, gbytes, st);
     if (rc) return rc;
     // dW of the outlier channels in bf16: dY^T [C x N] times X_hp^T [D_hp x N]^T, the reduction running over tokens
     if (D_hp > 0 && C > 0) {
@@ -815,15 +837,15 @@ int nvfp4_linear_bwd_dx(const void *dY, const nvfp4_tensor *Wq_ctx, int64_t N, i
     if (Wq_ctx->rows != C || Wq_ctx->K != D) return NVFP4_ERR_MISMATCH;
     const int outer = Wq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
-    const GemmNeeds need = gemm_needs(N, D, C, outer);
-    if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD_DX, N, D, C, outer, need.ws, false)) return NVFP4_ERR_WORKSPACE;
+    const BackwardPlan plan = plan_backward(NVFP4_OP_LINEAR_BWD_DX, N, D, 0, C, outer);
+    if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD_DX, N, D, C, outer, plan.g.ws, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
     float *part = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     nvfp4_tensor dYq{}, Wq2{};
-    const bool blk = need.blocked && ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD_DX, N, D, C, outer, need.ws, true);
+    const bool blk = plan.x && ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD_DX, N, D, C, outer, plan.g.ws, true);
     if (!carve_tensor(cv, N, C, outer, &dYq, blk) || !carve_tensor(cv, D, C, outer, &Wq2, blk)) return NVFP4_ERR_WORKSPACE;
-    const size_t gbytes = need.ws;
+    const size_t gbytes = plan.g.ws;
     void *gws = gbytes ? cv.take(gbytes) : nullptr;
 
     nvfp4_qcfg c3 = bwd_cfg(seed, layer_id, 3, outer, rht), c4 = bwd_cfg(seed, layer_id, 4, outer, rht);
@@ -837,7 +859,8 @@ int nvfp4_linear_bwd_dx(const void *dY, const nvfp4_tensor *Wq_ctx, int64_t N, i
     if (rc) return rc;
     rc = run_quantize(Wq_ctx, p4, &c4, &Wq2, nullptr, st, blk);
     if (rc) return rc;
-    return run_gemm(&dYq, &Wq2, dX, out_dtype, gws, gbytes, st, blk);
+    const Product product{&dYq, &Wq2, dX, blk};
+    return run_gemm_group(plan.g, &product, out_dtype, gws, gbytes, st);
 }
 
 int nvfp4_linear_bwd_dw(const void *dY, const nvfp4_tensor *Xq_ctx, int64_t N, int64_t D, int64_t C, void *dW,
@@ -851,15 +874,15 @@ int nvfp4_linear_bwd_dw(const void *dY, const nvfp4_tensor *Xq_ctx, int64_t N, i
     if (Xq_ctx->rows != N || Xq_ctx->K != D) return NVFP4_ERR_MISMATCH;
     const int outer = Xq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
-    const GemmNeeds need = gemm_needs(C, D, N, outer);
-    if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD_DW, N, D, C, outer, need.ws, false)) return NVFP4_ERR_WORKSPACE;
+    const BackwardPlan plan = plan_backward(NVFP4_OP_LINEAR_BWD_DW, N, D, 0, C, outer);
+    if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD_DW, N, D, C, outer, plan.g.ws, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
     float *part = static_cast<float *>(cv.take(sizeof(float) * kMaxAmaxPartials));
     nvfp4_tensor dYq{}, Xq2{};
-    const bool blk = need.blocked && ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD_DW, N, D, C, outer, need.ws, true);
+    const bool blk = plan.w && ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD_DW, N, D, C, outer, plan.g.ws, true);
     if (!carve_tensor(cv, C, N, outer, &dYq, blk) || !carve_tensor(cv, D, N, outer, &Xq2, blk)) return NVFP4_ERR_WORKSPACE;
-    const size_t gbytes = need.ws;
+    const size_t gbytes = plan.g.ws;
     void *gws = gbytes ? cv.take(gbytes) : nullptr;
 
     nvfp4_qcfg c5 = bwd_cfg(seed, layer_id, 5, outer, rht), c6 = bwd_cfg(seed, layer_id, 6, outer, rht);
@@ -873,7 +896,8 @@ int nvfp4_linear_bwd_dw(const void *dY, const nvfp4_tensor *Xq_ctx, int64_t N, i
     if (rc) return rc;
     rc = run_quantize(Xq_ctx, p6, &c6, &Xq2, nullptr, st, blk);
     if (rc) return rc;
-    return run_gemm(&dYq, &Xq2, dW, out_dtype, gws, gbytes, st, blk);
+    const Product product{&dYq, &Xq2, dW, blk};
+    return run_gemm_group(plan.g, &product, out_dtype, gws, gbytes, st);
 }
 
 int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_tensor *Wq_ctx, int64_t N, int64_t D,
@@ -892,8 +916,8 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     const int outer = Xq_ctx->outer_mode;
     if (!valid_outer(outer)) return NVFP4_ERR_ENUM;
     if (!aligned16(dY)) return NVFP4_ERR_ALIGN;
-    const GemmNeeds nx = gemm_needs(N, D, C, outer), nw = gemm_needs(C, D, N, outer);
-    const size_t gbytes = nx.ws > nw.ws ? nx.ws : nw.ws;
+    const BackwardPlan plan = plan_backward(NVFP4_OP_LINEAR_BWD, N, D, 0, C, outer);
+    const size_t gbytes = plan.g.ws;
     if (!ws || ws_bytes < backward_bytes(NVFP4_OP_LINEAR_BWD, N, D, C, outer, gbytes, false)) return NVFP4_ERR_WORKSPACE;
     if (!aligned16(ws)) return NVFP4_ERR_ALIGN;
     Carver cv{static_cast<uint8_t *>(ws), ws_bytes, 0};
@@ -901,7 +925,7 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
     float *amax = static_cast<float *>(cv.take(sizeof(float)));
     nvfp4_tensor q3{}, q4{}, q5{}, q6{};
     const bool room = ws_bytes >= backward_bytes(NVFP4_OP_LINEAR_BWD, N, D, C, outer, gbytes, true);
-    const bool bx = room && nx.blocked && (!outer || nw.blocked), bw = room && nw.blocked && (!outer || nx.blocked);
+    const bool bx = room && plan.x, bw = room && plan.w;
     if (!carve_tensor(cv, N, C, outer, &q3, bx) || !carve_tensor(cv, D, C, outer, &q4, bx) || !carve_tensor(cv, C, N, outer, &q5, bw) ||
         !carve_tensor(cv, D, N, outer, &q6, bw))
         return NVFP4_ERR_WORKSPACE;
@@ -956,7 +980,7 @@ int nvfp4_linear_bwd(const void *dY, const nvfp4_tensor *Xq_ctx, const nvfp4_ten
         if (rc) return rc;
     }
     const Product products[] = {{&q3, &q4, dX, bx}, {&q5, &q6, dW, bw}};
-    return run_gemm_group(products, 2, out_dtype, gws, gbytes, st);
+    return run_gemm_group(plan.g, products, out_dtype, gws, gbytes, st);
 }
 
 }  // extern "C"

@@ -94,8 +94,6 @@ const TileCfg kTilesFit[2][kNumTiles] = {
 // that is the faster one for the tile and split that they give.
 const TileCfg kSmallRagged[2][2] = {{{1, 1, 0.6, 3.2, 3}, {1, 2, 0.85, 3.2, 2}}, {{1, 1, 0.81, 3.2, 3}, {1, 2, 1.2, 3.2, 2}}};
 
-struct Plan { int tile; int split; int chunks_per_split; bool kw; double time; };   // kw: by gemm_kw_kernel; time: the estimate
-
 // Whether the 64 x 64 (5) and 64 x 128 (6) tiles run on gemm_kw_kernel, for a reduction of `chunks` 64s per split: below these its four
 // waves have too little to share (device times of 700 random shapes, gemm_nt_kernel's over gemm_kw_kernel's: 64 x 64, 4 to 6 chunks
 // 1.00, 7 1.10, 12 1.1 to 1.25, 30 1.4; 64 x 128, 8 chunks 0.96, 12 0.99, 16 1.06; with outer blocks 64 x 64, 10 chunks 0.99, 12 1.06, 14 1.2,
@@ -284,7 +282,7 @@ int tile_of_blocked(const Plan &p, int64_t M, int64_t N, int64_t K)
     return time < p.time ? 3 : p.tile;
 }
 
-// Whether the plan's launch can read operands that are blocked along K (the reasons are at gemm_needs).
+// Whether the plan's launch can read operands that are blocked along K (the reasons are at GroupPlan).
 bool takes_blocked(const Plan &p, int64_t M, int64_t N, int64_t K, int outer)
 {
     return M <= kMaxBlockedRows && N <= kMaxBlockedRows && !p.kw && (outer ? K % 256 == 0 : p.split == 1 || p.chunks_per_split % 2 == 0);
@@ -380,26 +378,25 @@ double time_of_pool(const int64_t *count, const double *time, int n, int64_t pla
     return end;
 }
 
-struct GroupPlan { int tile; bool kw; int order[kMaxGroup]; int planned; Plan own[kMaxGroup]; };   // own: of the first `planned` products
+// product of K in the launch together, as a plan
+Plan joint_part(const GroupPlan &g, int64_t K) { return Plan{g.tile, 1, (int)(K / 64), g.kw, 0.0}; }
 
-GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
+// Fills in the launch together of g's products, if there is one.
+void plan_joint(GroupPlan &g, const int64_t (*mnk)[3], int outer)
 {
-    GroupPlan g{-1, false, {0, 1, 2}, 0, {}};
+    const int n = g.n;
     bool ps = true, whole = true;
-    for (int i = 0; i < n; ++i) {
-        const int64_t M = mnk[i][0], N = mnk[i][1], K = mnk[i][2];
-        if (M < (i < 2 ? 128 : 1) || N < (i < 2 ? 128 : 1) || K < 256) return g;
-        ps = ps && K % 256 == 0;
-        whole = whole && M % 64 == 0 && N % 64 == 0;
-    }
     double apart = 0.0;
     for (int i = 0; i < n; ++i) {
-        const Plan p = make_plan(mnk[i][0], mnk[i][1], mnk[i][2], outer);
-        g.own[g.planned++] = p;
-        if (i < 2 && (p.split > 1 || (i > 0 && p.kw != g.kw))) return g;
-        if (i < 2) g.kw = p.kw;
+        const int64_t M = mnk[i][0], N = mnk[i][1], K = mnk[i][2];
+        if (M < (i < 2 ? 128 : 1) || N < (i < 2 ? 128 : 1) || K < 256) return;
+        ps = ps && K % 256 == 0;
+        whole = whole && M % 64 == 0 && N % 64 == 0;
+        const Plan &p = g.own[i];
+        if (i < 2 && (p.split > 1 || p.kw != g.own[0].kw)) return;
         apart += p.time;
     }
+    g.kw = g.own[0].kw;
     const bool kw = g.kw;
     for (int i = 1; i < n; ++i)                            // the longest reduction first
         for (int j = i; j > 0 && mnk[g.order[j]][2] > mnk[g.order[j - 1]][2]; --j) std::swap(g.order[j], g.order[j - 1]);
@@ -435,32 +432,53 @@ GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
         best_t = rank;
         g.tile = t;
     }
-    return g;
 }
 
 }  // namespace
 
-void gemm_group_plan(const int64_t (*mnk)[3], int n, int outer, int *bm, int *bn)
+GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
 {
-    const int t = plan_group(mnk, n, outer).tile;
-    *bm = t < 0 ? 0 : 64 * kTiles[t].tm;
-    *bn = t < 0 ? 0 : 64 * kTiles[t].tn;
+    GroupPlan g{};
+    g.n = n;
+    g.tile = -1;
+    for (int i = 0; i < n; ++i) {
+        const int64_t M = mnk[i][0], N = mnk[i][1], K = mnk[i][2];
+        g.order[i] = i;
+        g.own[i] = make_plan(M, N, K, outer);
+        g.blocked[i] = takes_blocked(g.own[i], M, N, K, outer);
+        const size_t ws = split_bytes(g.own[i], M, N);
+        g.ws = g.ws > ws ? g.ws : ws;
+    }
+    if (n > 1) plan_joint(g, mnk, outer);
+    if (g.tile >= 0) {
+        bool all = true;
+        for (int i = 0; i < n; ++i) all = all && takes_blocked(joint_part(g, mnk[i][2]), mnk[i][0], mnk[i][1], mnk[i][2], outer);
+        for (int i = 0; i < n; ++i) g.blocked[i] = all;
+    }
+    return g;
 }
 
-hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws, size_t ws_bytes, hipStream_t st)
+void planned_launch(const GroupPlan &plan, int i, const int64_t *mnk, int blocked, int outer, int *bm, int *bn, int *split, int *split_waves)
 {
-    int64_t mnk[kMaxGroup][3];
-    for (int i = 0; i < n; ++i) { mnk[i][0] = p[i].A.rows; mnk[i][1] = p[i].B.rows; mnk[i][2] = p[i].K; }
-    const int outer = p[0].A.outer;
-    const GroupPlan plan = plan_group(mnk, n, outer);
+    const bool joint = plan.tile >= 0;
+    const int t = joint ? plan.tile : blocked && outer ? tile_of_blocked(plan.own[i], mnk[0], mnk[1], mnk[2]) : plan.own[i].tile;
+    *bm = 64 * kTiles[t].tm;
+    *bn = 64 * kTiles[t].tn;
+    *split = joint ? 1 : plan.own[i].split;
+    *split_waves = joint ? plan.kw : plan.own[i].kw;
+}
+
+hipError_t launch_gemm_group(const GroupPlan &plan, const GemmProduct *p, int out_f32, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    const int n = plan.n, outer = p[0].A.outer;
+    // all of them before the first launch; one kernel reads the operands of a launch together
+    for (int i = 0; i < n; ++i) {
+        const bool alike = plan.tile < 0 || p[i].A.blocked == p[0].A.blocked;
+        if (!alike || !layout_fits(plan.tile < 0 ? plan.own[i] : joint_part(plan, p[i].K), p[i].A, p[i].B, p[i].K)) return hipErrorInvalidValue;
+    }
     if (plan.tile < 0) {
-        Plan own[kMaxGroup];
-        for (int i = 0; i < n; ++i) {                      // all of them before the first launch
-            own[i] = i < plan.planned ? plan.own[i] : make_plan(mnk[i][0], mnk[i][1], mnk[i][2], outer);
-            if (!layout_fits(own[i], p[i].A, p[i].B, p[i].K)) return hipErrorInvalidValue;
-        }
         for (int i = 0; i < n; ++i) {
-            const hipError_t e = launch_planned(own[i], p[i].A, p[i].B, p[i].K, p[i].out, out_f32, ws, ws_bytes, st);
+            const hipError_t e = launch_planned(plan.own[i], p[i].A, p[i].B, p[i].K, p[i].out, out_f32, ws, ws_bytes, st);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -475,10 +493,6 @@ hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws,
         if (i < n) wgs += g.g[i].tiles_m * g.g[i].tiles_n;
         ps = ps && q.K % 256 == 0;
     }
-    for (int i = 0; i < n; ++i) {                          // one kernel reads them all
-        const Plan whole{plan.tile, 1, (int)(mnk[i][2] / 64), plan.kw, 0.0};
-        if (p[i].A.blocked != p[0].A.blocked || !layout_fits(whole, p[i].A, p[i].B, p[i].K)) return hipErrorInvalidValue;
-    }
     return launch_tiles(plan.tile, outer, ps, out_f32 != 0, plan.kw, g, dim3((unsigned)wgs, 1, 1), st);
 }
 
@@ -489,12 +503,6 @@ void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int
     *bn = 64 * kTiles[p.tile].tn;
     *split = p.split;
     *split_waves = p.kw ? 1 : 0;
-}
-
-GemmNeeds gemm_needs(int64_t M, int64_t N, int64_t K, int outer)
-{
-    const Plan p = make_plan(M, N, K, outer);
-    return GemmNeeds{split_bytes(p, M, N), takes_blocked(p, M, N, K, outer)};
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer)

@@ -98,13 +98,7 @@ inline size_t blocked_scale_bytes(int64_t rows, int64_t K) { return (size_t)rows
 
 // Out[M x N] = A[M x K] * B[N x K]^T; splitk_ws holds split * M * N floats when split > 1
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int outer);
-// the same, and whether the product takes blocked operands, from one plan (making one takes the host 0.4 to 1.1 us): not on the kernel whose waves
-// split the reduction (it gains 3 % on long ones - 3072 x 768 x 8192 52.1 -> 50.3 us - and small layers lose as much to the longer prologue);
-// with per-tensor scales where its splits start where the scale bytes' blocks, or halves of them, do; with 1 x 128 outer blocks where K is a multiple of 256,
-// and in one launch with others only if they do too
-struct GemmNeeds { size_t ws; bool blocked; };
-GemmNeeds gemm_needs(int64_t M, int64_t N, int64_t K, int outer);
-// workgroup tile and K split the launcher will use for this shape
+// workgroup tile and K split of a product of row-major operands
 void gemm_plan(int64_t M, int64_t N, int64_t K, int outer, int *bm, int *bn, int *split, int *split_waves);
 hipError_t launch_gemm_nt(const GemmOperand &A, const GemmOperand &B, int64_t K, void *out, int out_f32,
                           void *ws, size_t ws_bytes, hipStream_t st);
@@ -116,9 +110,24 @@ struct GemmProduct {
     int64_t K;
     void *out;
 };
-hipError_t launch_gemm_group(const GemmProduct *p, int n, int out_f32, void *ws, size_t ws_bytes, hipStream_t st);
-// the tile that a group of products (M, N, K each) is launched with, 0 x 0 where they run one after the other
-void gemm_group_plan(const int64_t (*mnk)[3], int n, int outer, int *bm, int *bn);
+struct Plan { int tile; int split; int chunks_per_split; bool kw; double time; };   // kw: by gemm_kw_kernel; time: the estimate
+// Products of M x N x K each: how they are launched and what they can read, from one plan per product (making one takes the host 0.4 to 1.1 us).
+struct GroupPlan {
+    int n;
+    Plan own[3];         // of a launch alone
+    int tile;            // of the launch together, -1 where they are launched one after the other
+    bool kw;             // the launch together is by gemm_kw_kernel
+    int order[3];        // and has them in this order
+    // The product takes blocked operands: not on the kernel whose waves split the reduction (it gains 3 % on long ones - 3072 x 768 x 8192 52.1 -> 50.3 us -
+    // and small layers lose as much to the longer prologue); with per-tensor scales where its splits start where the scale bytes' blocks, or
+    // halves of them, do; with 1 x 128 outer blocks where K is a multiple of 256.  In a launch together, all of them or none.
+    bool blocked[3];
+    size_t ws;           // bytes for the partial sums of the largest split
+};
+GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer);
+// tile, split and kernel of product i (of M x N x K), given operands of that layout
+void planned_launch(const GroupPlan &plan, int i, const int64_t *mnk, int blocked, int outer, int *bm, int *bn, int *split, int *split_waves);
+hipError_t launch_gemm_group(const GroupPlan &plan, const GemmProduct *p, int out_f32, void *ws, size_t ws_bytes, hipStream_t st);
 
 // bf16 side of the OutControl split linear: Out[M x N] = addend (optional, f32) + A[M x K] * B[N x K]^T with K % 32 == 0;
 // transpose of a bf16 [R x C] array

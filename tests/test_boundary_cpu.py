@@ -353,6 +353,20 @@ def test_split_of_the_outlier_weight_gradient(lib):
         assert B.outctl_dw_plan(*shape) == (1, shape[0] // 32)
 
 
+def test_backward_product_plan_checks_its_arguments(lib):
+    p = B.CProductPlan()
+    call = lambda op, N, D, H, Cc, outer, product: lib.nvfp4_backward_product_plan(op, N, D, H, Cc, outer, product, C.byref(p))  # noqa: E731
+    assert lib.nvfp4_backward_product_plan(5, 64, 64, 0, 64, 0, 0, None) == -1
+    for op, H, product in ((3, 0, 1), (4, 0, 0), (5, 0, 2), (5, 32, 3), (5, 0, -1), (3, 0, 2), (2, 0, 0), (6, 0, 0)):
+        assert call(op, 64, 64, H, 64, 0, product) == -3, (op, H, product)
+    assert call(5, 64, 64, 0, 64, 2, 0) == -3
+    for op, N, D, H, Cc, product in ((3, 64, 64, 32, 64, 0), (5, 64, 64, 48, 64, 2), (5, -64, 64, 0, 64, 0), (5, 96, 64, 0, 64, 0), (5, 64, 64, 0, 96, 0), (4, 96, 64, 0, 64, 1)):
+        assert call(op, N, D, H, Cc, 0, product) == -2, (op, N, D, H, Cc)
+    assert call(3, 96, 64, 0, 64, 0, 0) == 0 and call(4, 64, 64, 0, 96, 0, 1) == 0      # the reduction of that product alone
+    for N, D, Cc in ((0, 64, 64), (64, 0, 64), (64, 64, 0)):
+        assert call(5, N, D, 0, Cc, 0, 0) == 0 and call(5, N, D, 32, Cc, 0, 2) == 0
+
+
 def test_planner_keeps_products_within_the_static_scratch():
     """where a plan exists whose partial sums fit the static array of nvfp4_gemm_nt_static, a faster split that does not
     fit is not taken"""

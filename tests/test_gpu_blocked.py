@@ -1,12 +1,15 @@
 """The backward quantizers write their operands blocked along K for the products (codes [K/64][rows][32 bytes], scale bytes
 [ceil(K/256)][rows][16], outer scales [K/128][rows]).  The layout changes no value, so the gradients have to be, byte for byte, the products of
 the row-major operands that the public quantizer calls write, which are compared with the oracle elsewhere."""
+import math
+import random
+
 import pytest
 
 torch = pytest.importorskip("torch")
 
-# (outer mode, transform, N, D, C): every tile of the product kernel that reads blocked operands, with K = N or C of 0, 64, 128 and 192 mod 256, in
-# one piece and split (split on an odd number of 64s: row-major), outputs that end inside a tile, row-wise tiles of 256 and 512 columns
+# (outer mode, transform, N, D, C): reductions N and C of 0, 64, 128 and 192 mod 256, in one piece and split (split on an odd number of 64s: row-major),
+# outputs that end inside a tile, row-wise tiles of 256 and 512 columns
 CASES = [
     (0, 0, 64, 64, 64), (0, 0, 192, 128, 128), (0, 0, 128, 64, 192), (0, 0, 256, 64, 256), (0, 0, 1024, 64, 64), (0, 0, 64, 64, 1088),
     (0, 0, 1152, 64, 64), (0, 0, 64, 80, 1216), (0, 0, 640, 1664, 256), (0, 0, 512, 3520, 576), (0, 0, 2112, 3776, 64), (0, 0, 64, 2496, 3200),
@@ -14,10 +17,17 @@ CASES = [
     (1, 0, 256, 256, 256), (1, 1, 2048, 256, 256), (1, 0, 256, 4224, 256), (1, 1, 256, 128, 1024), (1, 0, 256, 1280, 3328), (1, 1, 3328, 1792, 256),
     (1, 0, 256, 4096, 1536), (1, 1, 384, 256, 512), (1, 0, 512, 256, 640),
 ]
-# long strips of the column-wise quantizers (four and eight slabs of 16 rows a wave), the last of them cut short
+# with the ones above: every instantiation of the product kernel that reads blocked operands, by tile, scale fetch, alone, split or together
+REACH = [
+    (0, 0, 256, 4560, 256), (0, 0, 256, 4320, 320), (0, 0, 2560, 144, 1152), (0, 0, 6656, 16, 4992), (0, 0, 7168, 16, 3136), (0, 0, 320, 6624, 256),
+    (0, 0, 256, 5632, 512), (0, 0, 512, 8128, 256), (0, 0, 320, 6928, 576), (0, 0, 64, 5424, 4672), (0, 0, 256, 5680, 1344), (0, 0, 5632, 8176, 64),
+    (0, 0, 7616, 1568, 256), (0, 0, 1280, 6640, 768), (0, 0, 8960, 464, 5696),
+    (1, 0, 256, 2176, 256), (1, 1, 256, 5504, 512), (1, 0, 256, 8192, 512), (1, 1, 2816, 384, 5888), (1, 0, 9472, 256, 2432),
+]
 # products with outer blocks planned with 256 x 128 or 128 x 256 tiles that 128 x 128 ones take once blocked (dX, then dW, some ending inside a planned tile)
 RETILED = [(1, 0, 5504, 1024, 256), (1, 1, 4224, 1408, 512), (1, 0, 256, 1024, 5504), (1, 1, 512, 1408, 4224),
            (1, 0, 640, 11264, 768)]
+# long strips of the column-wise quantizers (four and eight slabs of 16 rows a wave), the last of them cut short
 LONG = [(0, 0, 8256, 5120, 1088), (0, 0, 12352, 2048, 3456), (0, 0, 8256, 1024, 3584)]
 
 
@@ -54,7 +64,7 @@ def _least_workspace(N, D, C, outer):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("f32", [False, True])
-@pytest.mark.parametrize("outer,rht,N,D,C", CASES + RETILED + LONG)
+@pytest.mark.parametrize("outer,rht,N,D,C", CASES + REACH + RETILED + LONG)
 def test_gradients_of_blocked_operands(outer, rht, N, D, C, f32):
     import paper_2510_27527_amd as tj
     B = tj.binding
@@ -75,22 +85,41 @@ def test_gradients_of_blocked_operands(outer, rht, N, D, C, f32):
     assert torch.equal(dX, aX) and torch.equal(dW, aW)
 
 
-def test_cases_reach_both_kernels_and_every_fetch():
-    """what the table says of itself, by the planner (no GPU)"""
+def _plans(outer, N, D, C):
+    """dX and dW of the call for both and of the two separate calls"""
     import paper_2510_27527_amd.binding as B
-    seen = set()
-    for outer, _, N, D, C in CASES + LONG:
-        for M, Nn, K in ((N, D, C), (C, D, N)):
-            if not B.gemm_splits_waves(M, Nn, K, outer):
-                bm, bn, split = B.gemm_plan(M, Nn, K, outer)
-                seen.add((outer, bm, bn))
-                seen.add((outer, "split", split > 1))
-                seen.add((outer, "mod", K % 256))
-    for outer, tiles in ((0, [(64, 64), (64, 128), (128, 128), (128, 192), (128, 256), (256, 128), (256, 256)]),
-                         (1, [(64, 64), (64, 128), (128, 128), (128, 192), (256, 128)])):
-        assert {(outer, *t) for t in tiles} <= seen
-        assert {(outer, "split", False), (outer, "split", True)} <= seen
-    assert {(0, "mod", m) for m in (0, 64, 128, 192)} <= seen
+    plan = lambda op, product: B.backward_product_plan(op, N, D, 0, C, outer, product)  # noqa: E731
+    return [(plan(B.OP_LINEAR_BWD, 0), C), (plan(B.OP_LINEAR_BWD, 1), N), (plan(B.OP_LINEAR_BWD_DX, 0), C), (plan(B.OP_LINEAR_BWD_DW, 1), N)]
+
+
+def _blocked_launches(outer, N, D, C):
+    """the instantiations of the product kernel that a layer's backward calls run on blocked operands"""
+    out = set()
+    for p, K in _plans(outer, N, D, C):
+        if p.blocked:
+            assert not p.split_waves
+            out.add((outer, p.tile, "together" if p.together else "split" if p.split > 1 else "alone", N % 256 == C % 256 == 0 if p.together else K % 256 == 0))
+    return out
+
+
+def test_cases_reach_every_blocked_launch():
+    """The planner's own answers for the launches of the table: among 6000 random layers there is no launch on blocked operands whose kernel the table
+    does not run, every remainder of a reduction is there, and calls that block one product, both and none."""
+    import paper_2510_27527_amd.binding as B
+    table = CASES + REACH + RETILED + LONG
+    have = set().union(*(_blocked_launches(o, N, D, C) for o, _, N, D, C in table))
+    assert len(have) >= 43
+    rng = random.Random(17)
+    size = lambda lo, hi, step: step * max(1, round(math.exp(rng.uniform(math.log(lo), math.log(hi))) / step))  # noqa: E731
+    for _ in range(6000):
+        outer = rng.randint(0, 1)
+        u = 128 if outer else 64
+        N, D, C = size(u, 16384, u), size(128 if outer else 16, 8192, 128 if outer else 16), size(u, 8192, u)
+        assert _blocked_launches(outer, N, D, C) <= have, (outer, N, D, C)
+    for outer, remainders in ((0, {0, 64, 128, 192}), (1, {0})):
+        assert {K % 256 for o, _, N, D, C in table if o == outer for p, K in _plans(o, N, D, C)[:2] if p.blocked} == remainders
+        both = {tuple(p.blocked for p, _ in _plans(o, N, D, C)[:2]) for o, _, N, D, C in table if o == outer}
+        assert {(True, True), (False, False)} <= both and (outer or {(True, False), (False, True)} <= both)
 
 
 @pytest.mark.parametrize("outer,rht,N,D,C", RETILED)
