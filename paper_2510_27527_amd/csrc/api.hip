@@ -403,7 +403,6 @@ static BackwardPlan plan_backward(int op, int64_t N, int64_t D_lo, int64_t D_hp,
     b.g = plan_group(b.mnk, b.n, outer);
     b.x = x && b.g.blocked[0] && (D_hp == 0 || b.g.blocked[2]);
     b.w = w && b.g.blocked[b.n - 1 - (D_hp > 0)];
-    if (outer && x && w && !(b.x && b.w)) b.x = b.w = false;
     return b;
 }
 
