@@ -400,9 +400,10 @@ static BackwardPlan plan_backward(int op, int64_t N, int64_t D_lo, int64_t D_hp,
     if (x) add(N, D_lo, C);
     if (w) add(C, D_lo, N);
     if (D_hp > 0) add(N, D_hp, C);
-    b.g = plan_group(b.mnk, b.n, outer);
-    b.x = x && b.g.blocked[0] && (D_hp == 0 || b.g.blocked[2]);
-    b.w = w && b.g.blocked[b.n - 1 - (D_hp > 0)];
+    b.g = plan_group(b.mnk, b.n, outer, x && (outer || !w || D_hp > 0));
+    b.x = x && b.g.blocked[0] && b.g.pays[0] && (D_hp == 0 || b.g.blocked[2]);
+    const int iw = x ? 1 : 0;
+    b.w = w && b.g.blocked[iw] && b.g.pays[iw];
     return b;
 }
 

@@ -288,6 +288,21 @@ bool takes_blocked(const Plan &p, int64_t M, int64_t N, int64_t K, int outer)
     return M <= kMaxBlockedRows && N <= kMaxBlockedRows && !p.kw && (outer ? K % 256 == 0 : p.split == 1 || p.chunks_per_split % 2 == 0);
 }
 
+// Whether blocked operands pay for a product launched alone.  us of calls (quantizers and product), row-major -> blocked; runs of one side differ by up to 2 %:
+// - Outer blocks, dX (rowwise: A comes from the row-wise quantizer, which takes 0.5 us more until it fills the chip): not for short reductions
+//   (1792 x 256 x 256 13.4 -> 14.2, 512 x 6656 x 1280 33.2 -> 34.0, 7680 x 2304 x 256 37.0 -> 37.8), but from 2^21 elements of dY on (15616 x 128 -> 512 fused 59.7 -> 57.1), from
+//   2^33 multiplications on (2048 x 5632 x 1536 68.7 -> 67.3; 512 x 7040 x 1792 with 2^32.6 43.2 -> 44.5), for long reductions (256 x 128 x 2816 26.5 -> 25.7; x 1536 22.2 -> 22.4),
+//   and where the tile changes to 128 x 128.  dW: 0.2 us lost where the tile has 64 rows (256 x 2048 x 256 14.2 -> 14.5), else level or better (2048 x 1152 x 1024 30.0 -> 29.8).
+// - Per-tensor scales: a row of up to 128 k is one stage's copy in either layout (65536 x 256 x 64 fused 86.3 -> 87.9, x 128 dX alone 33.3 -> 36.5), and 192 gains nothing
+//   (4672 x 4736 x 192 38.6 -> 39.4).  Where the row-wise quantizer runs by itself (rowwise; the call for both gradients quantizes dY once for both), its tiles of 256 or 512
+//   columns are part empty for short reductions (32768 x 256 x 320 35.1 -> 36.7; 16384 x 512 x 576 38.2 -> 37.3), and slivers of an output lose to its longer start (1024 x 64 x 768
+//   23.5 -> 24.0).
+bool blocked_pays(const Plan &p, int64_t M, int64_t N, int64_t K, int outer, bool rowwise)
+{
+    if (!outer) return rowwise ? K >= 512 && M >= 128 && N >= 128 : K >= 256;
+    return K >= 2048 || (double)M * (double)N * (double)K >= 0x1p33 || tile_of_blocked(p, M, N, K) != p.tile || (rowwise ? M * K >= ((int64_t)1 << 21) : p.tile < 5);
+}
+
 // Operands in a layout that the launch would read as another one are refused: the product would be wrong without an error.
 bool layout_fits(const Plan &p, const GemmOperand &A, const GemmOperand &B, int64_t K)
 {
@@ -436,7 +451,7 @@ void plan_joint(GroupPlan &g, const int64_t (*mnk)[3], int outer)
 
 }  // namespace
 
-GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
+GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer, bool rowwise)
 {
     GroupPlan g{};
     g.n = n;
@@ -446,14 +461,23 @@ GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer)
         g.order[i] = i;
         g.own[i] = make_plan(M, N, K, outer);
         g.blocked[i] = takes_blocked(g.own[i], M, N, K, outer);
+        g.pays[i] = blocked_pays(g.own[i], M, N, K, outer, rowwise && i == 0);
         const size_t ws = split_bytes(g.own[i], M, N);
         g.ws = g.ws > ws ? g.ws : ws;
     }
     if (n > 1) plan_joint(g, mnk, outer);
     if (g.tile >= 0) {
+        // outer blocks: as for a product alone, but the gain begins earlier (together 256 x 2944 -> 512 26.0 -> 26.3 us, 256 x 7808 -> 512 32.9 -> 32.3, 1280 x 2688 -> 1280 49.0 -> 47.9)
         bool all = true;
-        for (int i = 0; i < n; ++i) all = all && takes_blocked(joint_part(g, mnk[i][2]), mnk[i][0], mnk[i][1], mnk[i][2], outer);
-        for (int i = 0; i < n; ++i) g.blocked[i] = all;
+        double work = 0.0;
+        for (int i = 0; i < n; ++i) {
+            all = all && takes_blocked(joint_part(g, mnk[i][2]), mnk[i][0], mnk[i][1], mnk[i][2], outer);
+            work += (double)mnk[i][0] * (double)mnk[i][1] * (double)mnk[i][2];
+        }
+        for (int i = 0; i < n; ++i) {
+            g.blocked[i] = all;
+            g.pays[i] = !outer || work >= 1.5e9;
+        }
     }
     return g;
 }

@@ -122,9 +122,11 @@ struct GroupPlan {
     // and small layers lose as much to the longer prologue); with per-tensor scales where its splits start where the scale bytes' blocks, or
     // halves of them, do; with 1 x 128 outer blocks where K is a multiple of 256.  In a launch together, all of them or none.
     bool blocked[3];
+    bool pays[3];        // and the call is the faster with them
     size_t ws;           // bytes for the partial sums of the largest split
 };
-GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer);
+// rowwise: the first product's A operand comes from a row-wise quantizer of its own (not together with a column-wise one)
+GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer, bool rowwise);
 // tile, split and kernel of product i (of M x N x K), given operands of that layout
 void planned_launch(const GroupPlan &plan, int i, const int64_t *mnk, int blocked, int outer, int *bm, int *bn, int *split, int *split_waves);
 hipError_t launch_gemm_group(const GroupPlan &plan, const GemmProduct *p, int out_f32, void *ws, size_t ws_bytes, hipStream_t st);

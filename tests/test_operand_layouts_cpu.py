@@ -31,7 +31,7 @@ extern "C" int group(const int64_t *mnk, int n, int outer, const int *blocked)
     GemmProduct p[3];
     for (int i = 0; i < n; ++i)
         p[i] = GemmProduct{operand(mnk[3 * i], outer, blocked[i]), operand(mnk[3 * i + 1], outer, blocked[i]), mnk[3 * i + 2], kFar};
-    return launch_gemm_group(plan_group(reinterpret_cast<const int64_t (*)[3]>(mnk), n, outer), p, 0, kFar, (size_t)1 << 40, nullptr);
+    return launch_gemm_group(plan_group(reinterpret_cast<const int64_t (*)[3]>(mnk), n, outer, false), p, 0, kFar, (size_t)1 << 40, nullptr);
 }
 
 // kind: 0 row-wise, 1 two row-wise ones, 2 column-wise, 3 both of one tensor, 4 column-wise from a packed one, 5 two of them, 6 and a maximum
