@@ -25,7 +25,7 @@ REACH = [
     (1, 0, 256, 2176, 256), (1, 1, 256, 5504, 512), (1, 0, 256, 8192, 512), (1, 1, 2816, 384, 5888), (1, 0, 9472, 256, 2432),
     (0, 0, 320, 3696, 2176), (1, 0, 4096, 256, 512), (1, 1, 4480, 256, 512), (1, 0, 1024, 128, 128), (1, 0, 512, 3200, 512), (1, 1, 512, 5760, 256),
 ]
-# products with outer blocks planned with 256 x 128 or 128 x 256 tiles that 128 x 128 ones take once blocked (dX, then dW, some ending inside a planned tile)
+# products in one piece with outer blocks, planned with 256 x 128 or 128 x 256 tiles that 128 x 128 ones take once blocked (dX, then dW, some ending inside a planned tile)
 RETILED = [(1, 0, 5504, 1024, 256), (1, 1, 4224, 1408, 512), (1, 0, 256, 1024, 5504), (1, 1, 512, 1408, 4224),
            (1, 0, 640, 11264, 768)]
 # long strips of the column-wise quantizers (four and eight slabs of 16 rows a wave), the last of them cut short
@@ -54,13 +54,17 @@ def _row_major(dY, Xq, Wq, seed, layer, outer, rht):
     return q(dY, 0, 3), q(Wq, 1, 4), q(dY, 1, 5), q(Xq, 1, 6)
 
 
-def _least_workspace(N, D, C, outer):
-    """bytes of a call's workspace without the scale bytes that only whole 256 k need"""
+def _without_padding(nbytes, operands):
+    """bytes of a call's workspace without the scale bytes that only whole 256 k need; rows and reduction of each operand"""
+    up = lambda v: (v + 255) // 256 * 256  # noqa: E731
+    return nbytes - sum(up(r * ((k + 255) // 256) * 16) - up(r * k // 16) for r, k in operands)
+
+
+def _least_workspace(op, N, D, C, outer):
     import paper_2510_27527_amd as tj
     B = tj.binding
-    up = lambda v: (v + 255) // 256 * 256  # noqa: E731
-    more = sum(up(r * ((k + 255) // 256) * 16) - up(r * k // 16) for r, k in ((N, C), (D, C), (C, N), (D, N)))
-    return B.workspace_bytes(B.OP_LINEAR_BWD, N, D, C, outer) - more
+    x, w = [(N, C), (D, C)], [(C, N), (D, N)]
+    return _without_padding(B.workspace_bytes(op, N, D, C, outer), {B.OP_LINEAR_BWD_DX: x, B.OP_LINEAR_BWD_DW: w}.get(op, x + w))
 
 
 @pytest.mark.gpu
@@ -80,10 +84,66 @@ def test_gradients_of_blocked_operands(outer, rht, N, D, C, f32):
     assert torch.equal(dX, tj.linear_bwd_dx(dY, Wq, 11, 5, dt, rht=bool(rht)))
     assert torch.equal(dW, tj.linear_bwd_dw(dY, Xq, 11, 5, dt, rht=bool(rht)))
     # a workspace without room for the blocked scale bytes
-    least = _least_workspace(N, D, C, outer)
-    assert least <= B.workspace_bytes(B.OP_LINEAR_BWD, N, D, C, outer)
-    aX, aW = tj.linear_bwd(dY, Xq, Wq, 11, 5, dt, rht=bool(rht), ws=tj.alloc_workspace(least))
+    ws = {op: tj.alloc_workspace(_least_workspace(op, N, D, C, outer)) for op in (B.OP_LINEAR_BWD, B.OP_LINEAR_BWD_DX, B.OP_LINEAR_BWD_DW)}
+    assert all(w.numel() <= max(16, B.workspace_bytes(op, N, D, C, outer)) for op, w in ws.items())
+    aX, aW = tj.linear_bwd(dY, Xq, Wq, 11, 5, dt, rht=bool(rht), ws=ws[B.OP_LINEAR_BWD])
     assert torch.equal(dX, aX) and torch.equal(dW, aW)
+    assert torch.equal(dX, tj.linear_bwd_dx(dY, Wq, 11, 5, dt, rht=bool(rht), ws=ws[B.OP_LINEAR_BWD_DX]))
+    assert torch.equal(dW, tj.linear_bwd_dw(dY, Xq, 11, 5, dt, rht=bool(rht), ws=ws[B.OP_LINEAR_BWD_DW]))
+
+
+# The split layer: outer mode, transform, N, D_lo, D_hp, C; whether dX_lo and dX_hp, and dW_lo, run on blocked operands; the tile of their launch together; whether
+# the outlier channels' product would take another kernel or splits if launched alone
+SPLIT = [
+    (0, 0, 64, 64, 320, 64, False, False, None, False), (0, 0, 256, 64, 160, 64, False, True, None, False), (0, 0, 2944, 384, 416, 512, True, False, None, False),
+    (0, 0, 1600, 6208, 96, 1280, True, True, None, True), (0, 0, 256, 4736, 64, 512, True, True, (128, 128), False), (0, 0, 256, 4352, 704, 256, True, True, (128, 128), True),
+    (0, 0, 256, 7232, 64, 512, True, True, (128, 192), False), (0, 0, 384, 6912, 96, 640, True, True, (128, 256), False), (0, 0, 384, 8000, 576, 320, True, True, (128, 256), True),
+    (0, 0, 448, 6336, 64, 320, True, True, (256, 128), False), (0, 0, 320, 5760, 192, 320, True, True, (256, 128), True), (0, 0, 448, 7488, 192, 640, True, True, (256, 256), True),
+    (1, 0, 128, 128, 64, 128, False, False, None, False), (1, 0, 256, 128, 736, 128, False, True, None, False), (1, 1, 128, 128, 256, 2304, True, False, None, True),
+    (1, 0, 256, 128, 448, 2048, True, True, None, True), (1, 0, 256, 1792, 640, 256, False, False, (64, 128), False), (1, 0, 512, 3072, 640, 512, True, True, (128, 128), False),
+    (1, 1, 1280, 2304, 864, 1024, True, True, (128, 128), True), (1, 1, 512, 5760, 384, 256, True, True, (128, 192), False), (1, 0, 768, 3328, 832, 768, True, True, (128, 192), True),
+    (1, 0, 512, 6016, 416, 512, True, True, (256, 128), False), (1, 1, 1024, 3072, 800, 768, True, True, (256, 128), True),
+]
+
+
+@pytest.mark.parametrize("outer,rht,N,D,H,C,x,w,tile,other", SPLIT)
+def test_split_layers_run_on_the_stated_operands(outer, rht, N, D, H, C, x, w, tile, other):
+    import paper_2510_27527_amd.binding as B
+    lo, dw, hp = (B.backward_product_plan(B.OP_LINEAR_BWD, N, D, H, C, outer, k) for k in range(3))
+    assert (lo.blocked, dw.blocked, hp.blocked) == (x, w, x)
+    assert {lo.together, dw.together, hp.together} == {tile is not None} and (tile is None or lo.tile == tile)
+    assert (B.gemm_splits_waves(N, H, C, outer) or B.gemm_plan(N, H, C, outer)[2] > 1) == other
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("outer,rht,N,D,H,C,x,w,tile,other", SPLIT)
+def test_gradients_of_the_split_layer(outer, rht, N, D, H, C, x, w, tile, other, f32):
+    """Byte for byte the gradients of a workspace that keeps the operands row-major, and the products of the quantizers' own row-major operands; where the
+    launch together changes the outlier channels' kernel, and with it the order of summation, those within the products' tolerance."""
+    import paper_2510_27527_amd as tj
+    B = tj.binding
+    dt = B.OUT_F32 if f32 else B.OUT_BF16
+    dY, Xq, Wq = _tensors(N, D, C, outer, 9)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(10)
+    Xh, Wh = ((torch.randn((r, H), generator=g, device="cuda") * s).bfloat16() for r, s in ((N, 30.0), (C, 0.02)))
+    got = tj.outctl_bwd(dY, Xq, Wq, Xh, Wh, 11, 5, dt, rht=bool(rht))
+    size = B.lib().nvfp4_outctl_workspace_bytes(1, N, D, H, C, outer, dt)
+    least = _without_padding(size, [(N, C), (D, C), (H, C), (C, N), (D, N)])
+    assert (least < size) == (N % 256 != 0 or C % 256 != 0)
+    for name, a, b in zip(("dX_lo", "dX_hp", "dW_lo", "dW_hp"), got, tj.outctl_bwd(dY, Xq, Wq, Xh, Wh, 11, 5, dt, rht=bool(rht), ws=tj.alloc_workspace(least))):
+        assert torch.equal(a, b), name
+    q3, q4, q5, q6 = _row_major(dY, Xq, Wq, 11, 5, outer, rht)
+    q9 = tj.quantize(Wh, 1, B.ROUND_SR, outer=outer, seed=11, tensor_id=5 * 16 + 9, rht_id=5 * 16 + 7 if rht else None)
+    assert torch.equal(got[0], tj.gemm_nt(q3, q4, dt)) and torch.equal(got[2], tj.gemm_nt(q5, q6, dt))
+    if tile is None or not other:
+        assert torch.equal(got[1], tj.gemm_nt(q3, q9, dt))
+    else:
+        ref = tj.gemm_nt(q3, q9, B.OUT_F32).double()
+        near = 1e-3 if f32 else 2.0 ** -8
+        # sums of C terms in another order, of operands whose products add up to some 1 / sqrt(C) of the sum of their sizes
+        assert torch.all((got[1].double() - ref).abs() <= near * ref.abs() + 1e-6 * C ** 0.5 * ref.square().mean().sqrt())
 
 
 def _plans(outer, N, D, C):
@@ -161,9 +221,10 @@ def test_calls_that_lose_by_blocked_operands_keep_them_row_major(op):
 
 @pytest.mark.parametrize("outer,rht,N,D,C", RETILED)
 def test_retiled_cases_are_planned_otherwise(outer, rht, N, D, C):
-    import paper_2510_27527_amd as tj
-    M, K = (N, C) if C % 256 == 0 else (C, N)
-    if K % 256 or (M // 128) * (D // 128) <= 256:
-        M, K = C, N
-    assert K % 256 == 0 and (M // 128) * (D // 128) > 256
-    assert tj.binding.gemm_plan(M, D, K, outer) in ((256, 128, 1), (128, 256, 1))
+    import paper_2510_27527_amd.binding as B
+    seen = 0
+    for (p, K), (M, Nn) in zip(_plans(outer, N, D, C), ((N, D), (C, D)) * 2):
+        if p.blocked and not p.together and B.gemm_plan(M, Nn, K, outer) in ((256, 128, 1), (128, 256, 1)):
+            assert p.tile == (128, 128) and p.split == 1
+            seen += 1
+    assert seen
