@@ -265,22 +265,13 @@ hipError_t launch_tiles(int tile, int outer, bool ps, bool out_f32, bool kw, con
     return (kw ? kws[outer ? 1 : 0][out_f32] : inst[outer ? 1 : 0][ps][out_f32])(tile, g, grid, st);
 }
 
-// The tile of a product in one piece whose operands are blocked along K and carry 1 x 128 outer blocks.  The planned costs are those of row-major
-// operands; with blocked ones two 128 x 128 workgroups on a CU overtake many of the 256 x 128 and 128 x 256 tiles those costs choose.  Device times,
-// M x N x K, the planned 256 x 128 tile -> 128 x 128 in us: 8192 x 3072 x 768 63.4 -> 57.6, 16384 x 8192 x 1024 399 -> 354, 6144 x 6144 x 1024
-// 116.8 -> 92.7, 4096 x 2048 x 2048 44.8 -> 42.5, 9984 x 7936 x 256 87.4 -> 68.4, 9088 x 2944 x 768 74.3 -> 56.1, 1664 x 9344 x 1280 57.9 -> 50.5; a planned 128 x 256 one:
-// 3456 x 12032 x 1024 125.4 -> 111.8, 4480 x 11008 x 256 53.7 -> 46.1, 640 x 11264 x 768 22.7 -> 21.9.
-// The estimate only ranks against plan.time, in whose scale its constants are chosen: against the times of 19 products that change tile it lies
-// between 21 % below (one round of 512, part full) and 24 % above (a last round that is part full).  Up to 256 tiles the planned one stays.  All these
-// tiles add in the same order.
-int tile_of_blocked(const Plan &p, int64_t M, int64_t N, int64_t K)
-{
-    if (p.split > 1 || p.kw || (p.tile != 1 && p.tile != 2)) return p.tile;
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles <= kNumCU) return p.tile;
-    const double time = (double)((tiles + 2 * kNumCU - 1) / (2 * kNumCU)) * ((double)(K / 128) * 2.31 + 3.5);
-    return time < p.time ? 3 : p.tile;
-}
+// The tile of a product launched alone whose operands are blocked along K and carry 1 x 128 outer blocks.  The planned costs are those of row-major
+// operands; with blocked ones two 128 x 128 workgroups on a CU are faster than every 256 x 128 and 128 x 256 tile that those costs choose for a product in one piece (they are
+// chosen only where there are more 128 x 128 tiles than CUs).  Partial sums of a split keep the planned tile.  All these tiles add in the same order.
+// us of the product, M x N x K, row-major on the planned 256 x 128 tile -> blocked on 128 x 128: 8192 x 3072 x 768 56.3 -> 53.1, 16384 x 8192 x 1024 354.6 -> 332.6,
+// 6144 x 6144 x 1024 110.6 -> 93.3, 4096 x 2048 x 2048 44.6 -> 42.7, 9984 x 7936 x 256 82.5 -> 70.7, 9088 x 2944 x 768 72.2 -> 55.9, 5504 x 1024 x 256 11.6 -> 10.6; on a planned
+// 128 x 256 one: 3456 x 12032 x 1024 115.4 -> 103.0, 640 x 11264 x 768 20.8 -> 20.0.  Where the tile stays 128 x 128, the layout alone gives 1.07 (8192 x 4096 x 4096 337 -> 315).
+int tile_of_blocked(const Plan &p) { return p.split == 1 && !p.kw && (p.tile == 1 || p.tile == 2) ? 3 : p.tile; }
 
 // Whether the plan's launch can read operands that are blocked along K (the reasons are at GroupPlan).
 bool takes_blocked(const Plan &p, int64_t M, int64_t N, int64_t K, int outer)
@@ -300,7 +291,7 @@ bool takes_blocked(const Plan &p, int64_t M, int64_t N, int64_t K, int outer)
 bool blocked_pays(const Plan &p, int64_t M, int64_t N, int64_t K, int outer, bool rowwise)
 {
     if (!outer) return rowwise ? K >= 512 && M >= 128 && N >= 128 : K >= 256;
-    return K >= 2048 || (double)M * (double)N * (double)K >= 0x1p33 || tile_of_blocked(p, M, N, K) != p.tile || (rowwise ? M * K >= ((int64_t)1 << 21) : p.tile < 5);
+    return K >= 2048 || (double)M * (double)N * (double)K >= 0x1p33 || tile_of_blocked(p) != p.tile || (rowwise ? M * K >= ((int64_t)1 << 21) : p.tile < 5);
 }
 
 // Operands in a layout that the launch would read as another one are refused: the product would be wrong without an error.
@@ -315,7 +306,7 @@ hipError_t launch_planned(const Plan &plan, const GemmOperand &A, const GemmOper
     const int64_t M = A.rows, N = B.rows;
     if (!layout_fits(plan, A, B, K)) return hipErrorInvalidValue;
     Plan p = plan;
-    if (A.blocked && A.outer) p.tile = tile_of_blocked(plan, M, N, K);
+    if (A.blocked && A.outer) p.tile = tile_of_blocked(plan);
     if (M == 0 || N == 0) return hipSuccess;
     if (K == 0) {
         const int64_t n16 = M * N * (out_f32 ? 2 : 1);
@@ -485,7 +476,7 @@ GroupPlan plan_group(const int64_t (*mnk)[3], int n, int outer, bool rowwise)
 void planned_launch(const GroupPlan &plan, int i, const int64_t *mnk, int blocked, int outer, int *bm, int *bn, int *split, int *split_waves)
 {
     const bool joint = plan.tile >= 0;
-    const int t = joint ? plan.tile : blocked && outer ? tile_of_blocked(plan.own[i], mnk[0], mnk[1], mnk[2]) : plan.own[i].tile;
+    const int t = joint ? plan.tile : blocked && outer ? tile_of_blocked(plan.own[i]) : plan.own[i].tile;
     *bm = 64 * kTiles[t].tm;
     *bn = 64 * kTiles[t].tn;
     *split = joint ? 1 : plan.own[i].split;

@@ -413,7 +413,6 @@ __global__ __launch_bounds__(kThreads, PACK || TM * TN * (OUTER + 1) < 8 ? 2 : 1
         // bytes: missing rows are never stored, late chunks get zero scales when they are read).
         const uint8_t *ac_next = a_cbase, *bc_next = b_cbase, *as_next = a_sbase, *bs_next = b_sbase;
         auto issue_loads = [&](int kt, int buf) {
-
             const int64_t c0 = (int64_t)kt * NC;                  // first chunk of the stage, relative to cbeg
             const uint32_t dst = lds_base + buf * CODE_BYTES;
             const uint32_t sdst = lds_base + SC_BASE + buf * SC_BYTES;
@@ -631,11 +630,11 @@ hipError_t launch_layout(const Args &g, dim3 grid, hipStream_t st)
 __host__ inline bool is_blocked(const GemmArgs &g) { return g.blocked != 0; }
 __host__ inline bool is_blocked(const GemmGroup &p) { return p.g[0].blocked != 0; }
 
-template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK = false, class Args>
+// (with outer blocks, blocked operands come with the paired scale fetch)
+template <int TM, int TN, int OUT, bool PS, int OUTER, bool PACK = false, bool BLOCKED = (PS || OUTER == 0), class Args>
 hipError_t launch_cfg(const Args &g, dim3 grid, hipStream_t st)
 {
-    // (with outer blocks, blocked operands come with the paired scale fetch)
-    if constexpr (PS || OUTER == 0) {
+    if constexpr (BLOCKED) {
         if (is_blocked(g)) return launch_layout<TM, TN, OUT, PS, OUTER, PACK, true>(g, grid, st);
     } else if (is_blocked(g)) {
         return hipErrorInvalidValue;
@@ -648,12 +647,14 @@ hipError_t launch_cfg(const Args &g, dim3 grid, hipStream_t st)
 template <int OUT, bool PS, int OUTER, class Args>
 hipError_t launch_tile(int tile, const Args &g, dim3 grid, hipStream_t st)
 {
+    // with outer blocks, a product in one piece and alone has blocked operands on 128 x 128 tiles only (tile_of_blocked)
+    constexpr bool kBlocked = OUTER == 0 || (PS && (OUT == 2 || std::is_same<Args, GemmGroup>::value));
     switch (tile) {
         case 0:
             if constexpr (OUTER == 0) return launch_cfg<4, 4, OUT, PS, 0>(g, grid, st);
             else return hipErrorInvalidValue;
-        case 1: return launch_cfg<4, 2, OUT, PS, OUTER>(g, grid, st);
-        case 2: return launch_cfg<2, 4, OUT, PS, OUTER>(g, grid, st);
+        case 1: return launch_cfg<4, 2, OUT, PS, OUTER, false, kBlocked>(g, grid, st);
+        case 2: return launch_cfg<2, 4, OUT, PS, OUTER, false, kBlocked>(g, grid, st);
         case 4:
             if constexpr (PS) return launch_cfg<2, 3, OUT, true, OUTER>(g, grid, st);
             else return hipErrorInvalidValue;

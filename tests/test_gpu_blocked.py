@@ -170,6 +170,7 @@ def test_cases_reach_every_blocked_launch():
     table = CASES + REACH + RETILED + LONG
     have = set().union(*(_blocked_launches(o, N, D, C) for o, _, N, D, C in table))
     assert len(have) >= 41
+    assert not {k for k in have if k[0] == 1 and k[1] in ((256, 128), (128, 256)) and k[2] == "alone"}    # 128 x 128 takes their place
     rng = random.Random(17)
     size = lambda lo, hi, step: step * max(1, round(math.exp(rng.uniform(math.log(lo), math.log(hi))) / step))  # noqa: E731
     for _ in range(6000):
