@@ -25,7 +25,8 @@
  *     the call only.
  *   - Return value: 0 on success, a negative NVFP4_ERR_* otherwise; on error
  *     nothing has been enqueued unless the code is NVFP4_ERR_HIP.
- *   - `ws` is a scratch buffer of at least nvfp4_workspace_bytes(...) bytes that
+ *   - `ws` is a scratch buffer of at least nvfp4_workspace_bytes(...) bytes (the
+ *     backward calls accept somewhat less, see there) that
  *     must stay untouched until the enqueued work has finished.  Two calls that
  *     overlap in time need different workspaces.
  *
@@ -58,7 +59,7 @@ enum {
                                  elements; C % 8 != 0 for a column-wise bf16 source; for the products: reduction
                                  length not a multiple of 64 or above 2^22 */
     NVFP4_ERR_ENUM = -3,      /* unknown enum value, or a combination this build does not provide */
-    NVFP4_ERR_WORKSPACE = -4, /* ws is NULL or smaller than nvfp4_workspace_bytes() */
+    NVFP4_ERR_WORKSPACE = -4, /* ws is NULL or smaller than the call needs (nvfp4_workspace_bytes()) */
     NVFP4_ERR_ALIGN = -5,     /* a device pointer is not 16-byte aligned */
     NVFP4_ERR_MISMATCH = -6,  /* operand descriptors disagree with each other or with N, D, C */
     NVFP4_ERR_HIP = -7,       /* a HIP launch failed; see hipGetLastError() */
@@ -291,6 +292,11 @@ int nvfp4_osci_suppress_sparse(float *W, int64_t C, int64_t D, const uint32_t *i
 /*
  * Scratch bytes an operation needs.  op = NVFP4_OP_*.  QUANTIZE: (N, D) = (R, C) of the source, C ignored.
  * GEMM: Out is [N x C] with reduction length D.  LINEAR_*: as in the calls above.  Returns 0 for a bad op.
+ *
+ * For the backward calls (and nvfp4_outctl_workspace_bytes with backward != 0) the size has room to lay the call's own operands out in blocks along the
+ * reduction, which pads the E4M3 scales of an operand [rows x K] to rows * ceil(K / 256) * 16 bytes.  A call accepts what suffices without the
+ * padding - for each of its operands those bytes and rows * K / 16, both rounded up to 256, less - and then keeps all of them row-major: the same bytes in
+ * the gradients, in more time where nvfp4_backward_product_plan says `blocked` (1 to 10 % in most layers).
  */
 size_t nvfp4_workspace_bytes(int op, int64_t N, int64_t D, int64_t C, int outer_mode);
 

@@ -83,9 +83,9 @@ hipError_t launch_requant_col_pair_amax(const PackedSrc &src0, int64_t R0, int64
 
 // Operands that only products read (the backward quantizers') can be blocked along K, so that what a workgroup copies for a pipeline
 // stage is whole cache lines one after the other: codes [K/64][rows][32 bytes], scale bytes [ceil(K/256)][rows][16], outer scales [K/128][rows].
-// Row-major, a stage takes 64 bytes of codes and 16 (or 4) scale bytes of every row.  Measured row-major -> blocked, us:
-// 8192 x 3072 x 768 45.5 -> 42.8, 16384 x 1024 x 8192 225 -> 217, 8192 cubed 802 -> 773, 4096 x 4096 x 3712 119 -> 110; with 1 x 128 outer blocks
-// 8192 x 4096 x 4096 352 -> 325, 8192 cubed 1282 -> 1158, 4096 x 4096 x 3712 197 -> 183.
+// Row-major, a stage takes 64 bytes of codes and 16 (or 4) scale bytes of every row.  us of the product M x N x K, row-major -> blocked on the same tile, each pair
+// from one run (between runs a large product differs by up to 8 % with the card and with what ran before): 8192 x 3072 x 768 42.5 -> 41.4, 16384 x 1024 x 8192 215 -> 210,
+// 8192 cubed 766 -> 748, 4096 x 4096 x 3712 101 -> 94; with 1 x 128 outer blocks 8192 x 4096 x 4096 337 -> 315, 8192 cubed 1231 -> 1145.
 struct GemmOperand {
     const uint8_t *codes;
     const uint8_t *scales;

@@ -172,8 +172,9 @@ struct RowJob {
 //
 // BLK (0, 256 or 512): the output is blocked along K.  A workgroup then takes BLK columns of 8192 / BLK rows instead of 8192 consecutive elements, 16 rows x
 // 128 at a time, so that it writes runs of 512 bytes (16 rows of 32), in bands of tiles per XCD as in the column kernel: 512 where that covers no more
-// columns past K than 256 does.  Bound by the vector ALU like the row-major form (8192 x 4096 with the transform, 1 x 128 outer blocks: 25.9 -> 25.8 us; 27.0 with
-// 64-bit addresses per lane).
+// columns past K than 256 does.  Bound by the vector ALU like the row-major form once it fills the chip (1 x 128 outer blocks, row-major -> blocked: 8192 x 4096 with the
+// transform 24.0 -> 25.3 us, 4096 x 4096 12.9 -> 12.5); its start is longer (256 x 256 3.8 -> 4.4, hence blocked_pays in gemm.hip).  Tiles as blocks of a grid, 32-bit bounds and
+// unconditional loads halved the start's instructions, and won 0.2 us there with the transform, nothing without, and lost up to 1.6 on tall inputs (65536 x 256).
 template <int ROUND, bool SUP, int OUTER, bool DEQ, bool RHT = false, int BLK = 0>
 __global__ __launch_bounds__(kThreads) void quant_row_kernel(RowJob j0, RowJob j1, unsigned first_second)
 {
@@ -452,8 +453,8 @@ __device__ __forceinline__ int tile_pos(int row, int dwcol) { return row * 32 + 
 // while a row passes through registers, it is quantized row-wise (groups along C); after the transpose a lane owns
 // two columns x 16 rows = two groups of the column-wise operand.
 // BROW, BCOL: the row-wise / column-wise operand is blocked along K (the source's columns / rows are then a multiple of 64): the four passes
-// over a tile's rows write 4 KB of codes in one run, where row-major rows get 32 bytes each (16384 x 8192: 127 -> 105 us;
-// 102.6 with uniform addresses and 32-bit offsets, which took a tenth of the vector instructions: the vector ALU bounds it).
+// over a tile's rows write 4 KB of codes in one run, where row-major rows get 32 bytes each (16384 x 8192: 129.6 -> 101.6 us;
+// the waves wait a third less, and 3 % of the vector instructions are gone; row-wise operand alone, 8192 x 3072: 30.5 -> 27.4).
 template <int ROUND, bool SUP, bool BROW = false, bool BCOL = false>
 __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
 {
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(kThreads) void quant_dual_kernel(ColArgs a)
     const int rb = tid & 7, cp = tid >> 3;
     const int64_t c_first = C0 + 2 * cp;
     const int64_t out_lane = c_first * R + 16 * rb;        // + R0 (+ R for the second column): output element index
-    // Blocked outputs: a uniform address per tile plus a 32-bit offset per lane.  (R and C are at most 2^24 there.)
+    // Blocked outputs: a uniform address per tile plus a 32-bit offset per lane.  (The blocked operand's rows are at most 2^24.)
     const uint32_t ccode = (uint32_t)(rb >> 2) * (uint32_t)(C * 32) + (uint32_t)cp * 64u + (uint32_t)(rb & 3) * 8u;
     // numbers of the first quads (four elements): the lane's part, modulo 2^32; R, C and the tile's rows are multiples of 4 there
     const uint32_t rquad = (uint32_t)(ld_lane >> 2), cquad = (uint32_t)(out_lane >> 2);
@@ -870,7 +871,7 @@ __global__ __launch_bounds__(kThreads) void quant_colw_kernel(ColArgs a0, ColArg
     }
     __syncthreads();
     if (a.k.blocked) {
-        // (against runs of 64 bytes per output row: 8192 x 4096 with outer blocks and transform 22.7 -> 20.8 us, the pair X, W of that layer 31.6 -> 30.4)
+        // (against runs of 64 bytes per output row: 8192 x 4096 with outer blocks and transform 22.4 -> 20.6 us, the pair X, W of that layer 29.0 -> 29.1)
         // codes: 4 KB per 64 k, 128 output rows of 32 bytes; scale bytes: min(16, 4 SLABS) per output row and 256 k (or part of them)
         const int64_t Rg = (int64_t)trg * kWaves * kStripR;
         uint8_t *out_codes = reinterpret_cast<uint8_t *>(a.k.codes);
